@@ -1,19 +1,27 @@
-"""ctypes binding of libqbert.so: argument marshalling only.
+"""Binding of libqbert.so: argument marshalling only.
 
 Every function has the name and meaning of the C entry point declared in include/qbert.h and
 takes torch tensors that live on the GPU.  Outputs may be passed in (they are then written in
 place) or are allocated here with torch; every step of the computation runs in the library's
 HIP kernels on torch's current stream.  There is no fallback of any kind: if the shared
 library has not been built, loading raises.
+
+The calls that take GPU tensors do their marshalling in _calls.so (csrc/host_calls.cpp): for small inputs the host's
+share of a call is what it costs.  The rest (sizes, the power iteration with its callback, host functions) goes
+through ctypes.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libqbert.so")
+CALLS_PATH = os.path.join(_HERE, "_calls.so")
 _lib = None
+_calls = None
 
 QB_K_ALIGN = 64
 QB_N_BLOCK = 32
@@ -135,6 +143,23 @@ def load_library():
     return lib
 
 
+def _native():
+    """The module with the native halves of the calls below (loaded once; raises if it is not built)."""
+    global _calls
+    if _calls is None:
+        load_library()
+        if not os.path.exists(CALLS_PATH):
+            raise RuntimeError("_calls.so is not built: run `python -m paper_1909_05840_amd.build` "
+                               "(or __graft_entry__.build()) first")
+        name = __package__ + "._calls"
+        loader = importlib.machinery.ExtensionFileLoader(name, CALLS_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location(name, CALLS_PATH, loader=loader))
+        loader.exec_module(module)
+        module.set_error(QBError)
+        _calls = module
+    return _calls
+
+
 def _check(status):
     if status != 0:
         raise QBError(status, load_library().qb_status_string(status).decode())
@@ -175,282 +200,87 @@ def qb_bwd_workspace_nbytes(T, N, K):
 
 def qb_quantize_groupwise(W, bits, groups, packed=None, h=None, m=None, rs_w=None):
     """W[N,K] fp32 -> (packed uint8 buffer, h[G], m[G], rs_w[N])."""
-    lib = load_library()
-    _dev(W, torch.float32, "W")
-    N, K = W.shape
-    dev = W.device
-    if packed is None:
-        packed = torch.empty(max(qb_packed_nbytes(N, K, bits), 1), dtype=torch.uint8, device=dev)
-    if h is None:
-        h = torch.empty(max(groups, 1), dtype=torch.float32, device=dev)
-    if m is None:
-        m = torch.empty(max(groups, 1), dtype=torch.float32, device=dev)
-    if rs_w is None:
-        rs_w = torch.empty(N, dtype=torch.int32, device=dev)
-    _check(lib.qb_quantize_groupwise(_p(W), N, K, bits, groups, _p(packed), _p(h), _p(m), _p(rs_w), _stream()))
-    return packed, h, m, rs_w
+    return _native().quantize_groupwise(W, bits, groups, packed, h, m, rs_w)
 
 
 def qb_quantize_groupwise_batched(jobs):
     """jobs: list of dicts with W, bits, groups and optionally packed, h, m, rs_w (allocated here if absent).
     Returns the list of (packed, h, m, rs_w) tuples."""
-    lib = load_library()
-    arr = (_QuantJob * max(len(jobs), 1))()
-    outs = []
-    for i, j in enumerate(jobs):
-        W = _dev(j["W"], torch.float32, "W")
-        N, K = W.shape
-        bits, groups = int(j["bits"]), int(j["groups"])
-        dev = W.device
-        packed = j.get("packed")
-        if packed is None:
-            packed = torch.empty(max(qb_packed_nbytes(N, K, bits), 1), dtype=torch.uint8, device=dev)
-        h = j.get("h") if j.get("h") is not None else torch.empty(max(groups, 1), dtype=torch.float32, device=dev)
-        m = j.get("m") if j.get("m") is not None else torch.empty(max(groups, 1), dtype=torch.float32, device=dev)
-        rs = j.get("rs_w") if j.get("rs_w") is not None else torch.empty(N, dtype=torch.int32, device=dev)
-        arr[i] = _QuantJob(W.data_ptr(), N, K, bits, groups, packed.data_ptr(), h.data_ptr(), m.data_ptr(), rs.data_ptr())
-        outs.append((packed, h, m, rs))
-    _check(lib.qb_quantize_groupwise_batched(arr, len(jobs), _stream()))
-    return outs
+    return _native().quantize_groupwise_batched(jobs)
 
 
 def qb_quantize_act(X, clip, Xq=None, rs_x=None):
     """X[T,K] fp32 -> (Xq[T,K] int8, rs_x[T] int32)."""
-    lib = load_library()
-    _dev(X, torch.float32, "X")
-    T, K = X.shape
-    if Xq is None:
-        Xq = torch.empty((T, K), dtype=torch.int8, device=X.device)
-    if rs_x is None:
-        rs_x = torch.empty(T, dtype=torch.int32, device=X.device)
-    _check(lib.qb_quantize_act(_p(X), T, K, float(clip), _p(Xq), _p(rs_x), _stream()))
-    return Xq, rs_x
+    return _native().quantize_act(X, clip, Xq, rs_x)
 
 
 def qb_quantize_act_batched(jobs):
     """jobs: list of dicts with X, clip and optionally Xq, rs_x (allocated here if absent): several tensors, one launch.
     Returns the list of (Xq, rs_x) tuples."""
-    lib = load_library()
-    arr = (_ActJob * max(len(jobs), 1))()
-    outs = []
-    for i, j in enumerate(jobs):
-        X = _dev(j["X"], torch.float32, "X")
-        T, K = X.shape
-        Xq = j.get("Xq") if j.get("Xq") is not None else torch.empty((T, K), dtype=torch.int8, device=X.device)
-        rs = j.get("rs_x") if j.get("rs_x") is not None else torch.empty(T, dtype=torch.int32, device=X.device)
-        arr[i] = _ActJob(X.data_ptr(), T, K, float(j["clip"]), _dev(Xq, torch.int8, "Xq").data_ptr(),
-                         _dev(rs, torch.int32, "rs_x").data_ptr())
-        outs.append((Xq, rs))
-    _check(lib.qb_quantize_act_batched(arr, len(jobs), _stream()))
-    return outs
+    return _native().quantize_act_batched(jobs)
 
 
 def qb_qlinear_fwd(Xq, rs_x, clip, packed, h, rs_w, bits, groups, N, bias=None, Y=None, A4_debug=None,
                    want_a4=False):
     """Integer product + de-quantization. Returns Y[T,N] fp32 (and A4[T,N] int32 if asked)."""
-    lib = load_library()
-    _dev(Xq, torch.int8, "Xq")
-    T, K = Xq.shape
-    if Y is None:
-        Y = torch.empty((T, N), dtype=torch.float32, device=Xq.device)
-    if want_a4 and A4_debug is None:
-        A4_debug = torch.empty((T, N), dtype=torch.int32, device=Xq.device)
-    _check(lib.qb_qlinear_fwd(_p(Xq), _p(rs_x), float(clip), _p(packed), _p(h), _p(rs_w), bits, groups,
-                              T, N, K, _p(bias), _p(Y), _p(A4_debug), _stream()))
-    return (Y, A4_debug) if A4_debug is not None else Y
+    return _native().qlinear_fwd(Xq, rs_x, clip, packed, h, rs_w, bits, groups, N, bias, Y, A4_debug, want_a4)
 
 
 def qb_qlinear_fwd_batched(jobs):
     """jobs: list of dicts with Xq, rs_x, clip, packed, h, rs_w, bits, groups, N and optionally bias, Y (allocated
     here if absent).  Independent linear layers, as few launches as possible.  Returns the list of Y tensors."""
-    lib = load_library()
-    arr = (_FwdJob * max(len(jobs), 1))()
-    outs = []
-    for i, j in enumerate(jobs):
-        Xq = _dev(j["Xq"], torch.int8, "Xq")
-        T, K = Xq.shape
-        N = int(j["N"])
-        Y = j.get("Y")
-        if Y is None:
-            Y = torch.empty((T, N), dtype=torch.float32, device=Xq.device)
-        bias = j.get("bias")
-        arr[i] = _FwdJob(Xq.data_ptr(), _dev(j["rs_x"], torch.int32, "rs_x").data_ptr(), float(j["clip"]),
-                         _dev(j["packed"], torch.uint8, "packed").data_ptr(), _dev(j["h"], torch.float32, "h").data_ptr(),
-                         _dev(j["rs_w"], torch.int32, "rs_w").data_ptr(), int(j["bits"]), int(j["groups"]), T, N, K,
-                         _p(_dev(bias, torch.float32, "bias")) if bias is not None else None,
-                         _dev(Y, torch.float32, "Y").data_ptr())
-        outs.append(Y)
-    _check(lib.qb_qlinear_fwd_batched(arr, len(jobs), _stream()))
-    return outs
+    return _native().qlinear_fwd_batched(jobs)
 
 
 def qb_qlinear_fwd_q8(Xq, rs_x, clip, packed, h, rs_w, bits, groups, N, clip_out, bias=None, act=0, Yq=None,
                       rs_y=None):
     """Forward with the output quantized to 8 bits at once. Returns Yq[T,N] int8 (= u - 128), rs_y[T] int32."""
-    lib = load_library()
-    _dev(Xq, torch.int8, "Xq")
-    T, K = Xq.shape
-    if Yq is None:
-        Yq = torch.empty((T, N), dtype=torch.int8, device=Xq.device)
-    if rs_y is None:
-        rs_y = torch.empty(T, dtype=torch.int32, device=Xq.device)
-    _check(lib.qb_qlinear_fwd_q8(_p(Xq), _p(rs_x), float(clip), _p(packed), _p(h), _p(rs_w), bits, groups,
-                                 T, N, K, _p(bias), int(act), float(clip_out), _p(Yq), _p(rs_y), _stream()))
-    return Yq, rs_y
+    return _native().qlinear_fwd_q8(Xq, rs_x, clip, packed, h, rs_w, bits, groups, N, clip_out, bias, act, Yq, rs_y)
 
 
 def qb_qlinear_bwd_ste(dY, Xq, clip, packed, h, bits, groups, want_dx=True, want_dw=True, dX=None, dW=None,
                        workspace=None):
     """dY[T,N] bf16 -> (dX[T,K] bf16 or None, dW[N,K] fp32 or None)."""
-    lib = load_library()
-    _dev(dY, torch.bfloat16, "dY")
-    _dev(Xq, torch.int8, "Xq")
-    T, N = dY.shape
-    K = Xq.shape[1]
-    dev = dY.device
-    if want_dx and dX is None:
-        dX = torch.empty((T, K), dtype=torch.bfloat16, device=dev)
-    if want_dw and dW is None:
-        dW = torch.empty((N, K), dtype=torch.float32, device=dev)
-    if workspace is None:
-        workspace = torch.empty(max(qb_bwd_workspace_nbytes(T, N, K), 256), dtype=torch.uint8, device=dev)
-    _check(lib.qb_qlinear_bwd_ste(_p(dY), _p(Xq), float(clip), _p(packed), _p(h), bits, groups, T, N, K,
-                                  _p(dX), _p(dW), _p(workspace), _stream()))
-    return dX, dW
+    return _native().qlinear_bwd_ste(dY, Xq, clip, packed, h, bits, groups, want_dx, want_dw, dX, dW, workspace)
 
 
 def qb_qlinear_bwd_ste_static(dY, Xq, clip, packed, h, bits, groups, dX=None, dW=None):
     """qb_qlinear_bwd_ste without a workspace (the library's fixed staging area); dX and dW are the caller's, or null
     to skip one of them.  The call itself allocates nothing."""
-    lib = load_library()
-    _dev(dY, torch.bfloat16, "dY")
-    _dev(Xq, torch.int8, "Xq")
-    T, N = dY.shape
-    K = Xq.shape[1]
-    _check(lib.qb_qlinear_bwd_ste_static(_p(dY), _p(Xq), float(clip), _p(packed), _p(h), bits, groups, T, N, K,
-                                         _p(dX), _p(dW), _stream()))
-    return dX, dW
+    return _native().qlinear_bwd_ste_static(dY, Xq, clip, packed, h, bits, groups, dX, dW)
 
 
 def qb_qlinear_bwd_ste_masked(dY, Xq, clip, packed, h, bits, groups, X=None, W=None, m=None, want_dx=True,
                               want_dw=True, dX=None, dW=None, workspace=None):
     """The backward with the clamp's derivative: dX zero where |X| > clip (X given), dW zero where |W| > m of
     its group (W and m given)."""
-    lib = load_library()
-    _dev(dY, torch.bfloat16, "dY")
-    _dev(Xq, torch.int8, "Xq")
-    T, N = dY.shape
-    K = Xq.shape[1]
-    dev = dY.device
-    if X is not None:
-        _dev(X, torch.float32, "X")
-        if tuple(X.shape) != (T, K):
-            raise ValueError("X must be [T, K]")
-    if W is not None:
-        _dev(W, torch.float32, "W")
-        if tuple(W.shape) != (N, K):
-            raise ValueError("W must be [N, K]")
-    if m is not None:
-        _dev(m, torch.float32, "m")
-        if m.numel() != groups:
-            raise ValueError("m must hold one range per group")
-    if want_dx and dX is None:
-        dX = torch.empty((T, K), dtype=torch.bfloat16, device=dev)
-    if want_dw and dW is None:
-        dW = torch.empty((N, K), dtype=torch.float32, device=dev)
-    if workspace is None:
-        workspace = torch.empty(max(qb_bwd_workspace_nbytes(T, N, K), 256), dtype=torch.uint8, device=dev)
-    _check(lib.qb_qlinear_bwd_ste_masked(_p(dY), _p(Xq), float(clip), _p(packed), _p(h), bits, groups, T, N, K,
-                                         _p(X), _p(W), _p(m), _p(dX), _p(dW), _p(workspace), _stream()))
-    return dX, dW
+    return _native().qlinear_bwd_ste_masked(dY, Xq, clip, packed, h, bits, groups, X, W, m, want_dx, want_dw, dX, dW, workspace)
 
 
 def qb_quantize_groupwise_asym(W, bits, groups, packed=None, delta=None, q0=None, rs_w=None):
     """Group ranges [min, max]: W[N,K] fp32 -> (packed, delta[G], q0[G], rs_w[N])."""
-    lib = load_library()
-    _dev(W, torch.float32, "W")
-    N, K = W.shape
-    dev = W.device
-    if packed is None:
-        packed = torch.empty(max(qb_packed_nbytes(N, K, bits), 1), dtype=torch.uint8, device=dev)
-    if delta is None:
-        delta = torch.empty(groups, dtype=torch.float32, device=dev)
-    if q0 is None:
-        q0 = torch.empty(groups, dtype=torch.float32, device=dev)
-    if rs_w is None:
-        rs_w = torch.empty(N, dtype=torch.int32, device=dev)
-    _check(lib.qb_quantize_groupwise_asym(_p(W), N, K, bits, groups, _p(packed), _p(delta), _p(q0), _p(rs_w), _stream()))
-    return packed, delta, q0, rs_w
+    return _native().quantize_groupwise_asym(W, bits, groups, packed, delta, q0, rs_w)
 
 
 def qb_quantize_groupwise_asym_range(W, bits, lo, hi, packed=None, delta=None, q0=None, rs_w=None):
     """Asymmetric group ranges [lo[g], hi[g]] given by the caller. Returns (packed, delta[G], q0[G], rs_w[N])."""
-    lib = load_library()
-    _dev(W, torch.float32, "W")
-    _dev(lo, torch.float32, "lo")
-    _dev(hi, torch.float32, "hi")
-    N, K = W.shape
-    groups = lo.numel()
-    dev = W.device
-    if packed is None:
-        packed = torch.empty(max(qb_packed_nbytes(N, K, bits), 1), dtype=torch.uint8, device=dev)
-    delta = delta if delta is not None else torch.empty(groups, dtype=torch.float32, device=dev)
-    q0 = q0 if q0 is not None else torch.empty(groups, dtype=torch.float32, device=dev)
-    rs_w = rs_w if rs_w is not None else torch.empty(N, dtype=torch.int32, device=dev)
-    _check(lib.qb_quantize_groupwise_asym_range(_p(W), N, K, bits, groups, _p(lo), _p(hi), _p(packed), _p(delta), _p(q0),
-                                                _p(rs_w), _stream()))
-    return packed, delta, q0, rs_w
+    return _native().quantize_groupwise_asym_range(W, bits, lo, hi, packed, delta, q0, rs_w)
 
 
 def qb_qlinear_fwd_asym(Xq, rs_x, clip, packed, delta, q0, rs_w, bits, groups, N, bias=None, Y=None, want_a4=False):
     """Forward with asymmetric group ranges. Returns Y[T,N] fp32 (and A4[T,N] int32 if asked)."""
-    lib = load_library()
-    _dev(Xq, torch.int8, "Xq")
-    _dev(delta, torch.float32, "delta")
-    _dev(q0, torch.float32, "q0")
-    T, K = Xq.shape
-    if Y is None:
-        Y = torch.empty((T, N), dtype=torch.float32, device=Xq.device)
-    A4 = torch.empty((T, N), dtype=torch.int32, device=Xq.device) if want_a4 else None
-    _check(lib.qb_qlinear_fwd_asym(_p(Xq), _p(rs_x), float(clip), _p(packed), _p(delta), _p(q0), _p(rs_w), bits, groups,
-                                   T, N, K, _p(bias), _p(Y), _p(A4), _stream()))
-    return (Y, A4) if want_a4 else Y
+    return _native().qlinear_fwd_asym(Xq, rs_x, clip, packed, delta, q0, rs_w, bits, groups, N, bias, Y, want_a4)
 
 
 def qb_qlinear_fwd_asym_dyn(Xq, rs_x, hx_rows, packed, delta, q0, rs_w, bits, groups, N, bias=None, Y=None, want_a4=False):
     """Forward with asymmetric group ranges and one activation scale per token. Returns Y (and A4 if asked)."""
-    lib = load_library()
-    _dev(Xq, torch.int8, "Xq")
-    _dev(hx_rows, torch.float32, "hx_rows")
-    _dev(delta, torch.float32, "delta")
-    _dev(q0, torch.float32, "q0")
-    T, K = Xq.shape
-    if Y is None:
-        Y = torch.empty((T, N), dtype=torch.float32, device=Xq.device)
-    A4 = torch.empty((T, N), dtype=torch.int32, device=Xq.device) if want_a4 else None
-    _check(lib.qb_qlinear_fwd_asym_dyn(_p(Xq), _p(rs_x), _p(hx_rows), _p(packed), _p(delta), _p(q0), _p(rs_w), bits, groups,
-                                       T, N, K, _p(bias), _p(Y), _p(A4), _stream()))
-    return (Y, A4) if want_a4 else Y
+    return _native().qlinear_fwd_asym_dyn(Xq, rs_x, hx_rows, packed, delta, q0, rs_w, bits, groups, N, bias, Y, want_a4)
 
 
 def qb_qlinear_bwd_ste_asym(dY, Xq, clip, packed, delta, q0, bits, groups, want_dx=True, want_dw=True, dX=None, dW=None,
                             workspace=None):
     """STE backward with asymmetric group ranges: dY[T,N] bf16 -> (dX[T,K] bf16 or None, dW[N,K] fp32 or None)."""
-    lib = load_library()
-    _dev(dY, torch.bfloat16, "dY")
-    _dev(Xq, torch.int8, "Xq")
-    T, N = dY.shape
-    K = Xq.shape[1]
-    dev = dY.device
-    if want_dx and dX is None:
-        dX = torch.empty((T, K), dtype=torch.bfloat16, device=dev)
-    if want_dw and dW is None:
-        dW = torch.empty((N, K), dtype=torch.float32, device=dev)
-    if workspace is None:
-        workspace = torch.empty(max(qb_bwd_workspace_nbytes(T, N, K), 256), dtype=torch.uint8, device=dev)
-    _check(lib.qb_qlinear_bwd_ste_asym(_p(dY), _p(Xq), float(clip), _p(packed), _p(delta), _p(q0), bits, groups, T, N, K,
-                                       _p(dX), _p(dW), _p(workspace), _stream()))
-    return dX, dW
+    return _native().qlinear_bwd_ste_asym(dY, Xq, clip, packed, delta, q0, bits, groups, want_dx, want_dw, dX, dW, workspace)
 
 
 def qb_power_iteration(hv, v, iters, hv_buf=None, scratch=None, estimates=None):
@@ -522,118 +352,38 @@ def qb_unpack_codes(packed, N, K, bits, codes=None):
 
 
 def qb_embedding_quantize(E, groups, codes=None, h=None, m=None):
-    lib = load_library()
-    _dev(E, torch.float32, "E")
-    V, d = E.shape
-    if codes is None:
-        codes = torch.empty((V, d), dtype=torch.uint8, device=E.device)
-    if h is None:
-        h = torch.empty(max(groups, 1), dtype=torch.float32, device=E.device)
-    if m is None:
-        m = torch.empty(max(groups, 1), dtype=torch.float32, device=E.device)
-    _check(lib.qb_embedding_quantize(_p(E), V, d, groups, _p(codes), _p(h), _p(m), _stream()))
-    return codes, h, m
+    return qb_embedding_quantize_bits(E, 8, groups, codes, h, m)
 
 
 def qb_embedding_gather(codes, h, groups, ids, out=None):
-    lib = load_library()
-    _dev(codes, torch.uint8, "codes")
-    _dev(ids, torch.int64, "ids")
-    V, d = codes.shape
-    n = ids.shape[0]
-    if out is None:
-        out = torch.empty((n, d), dtype=torch.float32, device=codes.device)
-    _check(lib.qb_embedding_gather(_p(codes), _p(h), V, d, groups, _p(ids), n, _p(out), _stream()))
-    return out
+    return qb_embedding_gather_bits(codes, h, 8, groups, ids, out)
 
 
 def qb_embedding_quantize_bits(E, bits, groups, codes=None, h=None, m=None):
     """bits = 8: codes [V,d] uint8; bits = 4: codes [V,d/2], two codes per byte (even column in the low nibble)."""
-    lib = load_library()
-    _dev(E, torch.float32, "E")
-    V, d = E.shape
-    if codes is None:
-        codes = torch.empty((V, d * bits // 8), dtype=torch.uint8, device=E.device)
-    if h is None:
-        h = torch.empty(max(groups, 1), dtype=torch.float32, device=E.device)
-    if m is None:
-        m = torch.empty(max(groups, 1), dtype=torch.float32, device=E.device)
-    _check(lib.qb_embedding_quantize_bits(_p(E), V, d, bits, groups, _p(codes), _p(h), _p(m), _stream()))
-    return codes, h, m
+    return _native().embedding_quantize_bits(E, bits, groups, codes, h, m)
 
 
 def qb_embedding_gather_bits(codes, h, bits, groups, ids, out=None):
-    lib = load_library()
-    _dev(codes, torch.uint8, "codes")
-    _dev(ids, torch.int64, "ids")
-    V = codes.shape[0]
-    d = codes.shape[1] * 8 // bits
-    n = ids.shape[0]
-    if out is None:
-        out = torch.empty((n, d), dtype=torch.float32, device=codes.device)
-    _check(lib.qb_embedding_gather_bits(_p(codes), _p(h), V, d, bits, groups, _p(ids), n, _p(out), _stream()))
-    return out
+    return _native().embedding_gather_bits(codes, h, bits, groups, ids, out)
 
 
 def qb_quantize_act_dyn(X, Xq=None, rs_x=None, hx_rows=None):
     """Per-token max-abs range: X[T,K] fp32 -> (Xq[T,K] int8, rs_x[T] int32, hx_rows[T] fp32)."""
-    lib = load_library()
-    _dev(X, torch.float32, "X")
-    T, K = X.shape
-    if Xq is None:
-        Xq = torch.empty((T, K), dtype=torch.int8, device=X.device)
-    if rs_x is None:
-        rs_x = torch.empty(T, dtype=torch.int32, device=X.device)
-    if hx_rows is None:
-        hx_rows = torch.empty(T, dtype=torch.float32, device=X.device)
-    _check(lib.qb_quantize_act_dyn(_p(X), T, K, _p(Xq), _p(rs_x), _p(hx_rows), _stream()))
-    return Xq, rs_x, hx_rows
+    return _native().quantize_act_dyn(X, Xq, rs_x, hx_rows)
 
 
 def qb_quantize_act_dyn_tensor(X, Xq=None, rs_x=None, hx_rows=None, c=None):
     """One max-abs range for the whole tensor: X[T,K] fp32 -> (Xq[T,K] int8, rs_x[T] int32, hx_rows[T] fp32 (all
     equal c/255), c[1] fp32 = max|X|)."""
-    lib = load_library()
-    _dev(X, torch.float32, "X")
-    T, K = X.shape
-    if Xq is None:
-        Xq = torch.empty((T, K), dtype=torch.int8, device=X.device)
-    if rs_x is None:
-        rs_x = torch.empty(T, dtype=torch.int32, device=X.device)
-    if hx_rows is None:
-        hx_rows = torch.empty(T, dtype=torch.float32, device=X.device)
-    if c is None:
-        c = torch.empty(1, dtype=torch.float32, device=X.device)
-    _check(lib.qb_quantize_act_dyn_tensor(_p(X), T, K, _p(Xq), _p(rs_x), _p(hx_rows), _p(c), _stream()))
-    return Xq, rs_x, hx_rows, c
+    return _native().quantize_act_dyn_tensor(X, Xq, rs_x, hx_rows, c)
 
 
 def qb_qlinear_fwd_dyn(Xq, rs_x, hx_rows, packed, h, rs_w, bits, groups, N, bias=None, Y=None, want_a4=False):
     """Forward with one activation scale per token. Returns Y[T,N] fp32 (and A4[T,N] int32 if asked)."""
-    lib = load_library()
-    _dev(Xq, torch.int8, "Xq")
-    _dev(hx_rows, torch.float32, "hx_rows")
-    T, K = Xq.shape
-    if Y is None:
-        Y = torch.empty((T, N), dtype=torch.float32, device=Xq.device)
-    A4 = torch.empty((T, N), dtype=torch.int32, device=Xq.device) if want_a4 else None
-    _check(lib.qb_qlinear_fwd_dyn(_p(Xq), _p(rs_x), _p(hx_rows), _p(packed), _p(h), _p(rs_w), bits, groups,
-                                  T, N, K, _p(bias), _p(Y), _p(A4), _stream()))
-    return (Y, A4) if want_a4 else Y
+    return _native().qlinear_fwd_dyn(Xq, rs_x, hx_rows, packed, h, rs_w, bits, groups, N, bias, Y, want_a4)
 
 
 def qb_quantize_groupwise_clip(W, bits, m_in, packed=None, h=None, rs_w=None):
     """Group ranges [-m_in[g], +m_in[g]] given by the caller (device fp32 [G]). Returns (packed, h, rs_w)."""
-    lib = load_library()
-    _dev(W, torch.float32, "W")
-    _dev(m_in, torch.float32, "m_in")
-    N, K = W.shape
-    G = m_in.shape[0]
-    if packed is None:
-        packed = torch.empty(max(qb_packed_nbytes(N, K, bits), 1), dtype=torch.uint8, device=W.device)
-    if h is None:
-        h = torch.empty(G, dtype=torch.float32, device=W.device)
-    if rs_w is None:
-        rs_w = torch.empty(N, dtype=torch.int32, device=W.device)
-    _check(lib.qb_quantize_groupwise_clip(_p(W), N, K, bits, G, _p(m_in), _p(packed), _p(h), _p(rs_w), _stream()))
-    return packed, h, rs_w
+    return _native().quantize_groupwise_clip(W, bits, m_in, packed, h, rs_w)

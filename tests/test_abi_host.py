@@ -222,3 +222,19 @@ def test_sensitivity_host_functions_against_eq2():
     assert lib.qb_probe_mfma_i8(0, 100, P, NULL) == 3
     assert lib.qb_probe_mfma_i8(512, 0, P, NULL) == 3
 
+
+
+@pytest.mark.parametrize("call, error", [
+    (lambda t: qb.qb_quantize_act(t["f32"], 6.0), TypeError),                                       # not on the GPU
+    (lambda t: qb.qb_qlinear_fwd(t["i8"], None, 6.0, None, None, None, 4, 1, 64), TypeError),
+    (lambda t: qb.qb_qlinear_bwd_ste(t["f32"], t["i8"], 6.0, None, None, 4, 1), TypeError),
+    (lambda t: qb.qb_quantize_groupwise_batched([{}]), KeyError),                                   # a job without its matrix
+    (lambda t: qb.qb_quantize_act_batched([3]), TypeError),                                         # a job that is no dict
+    (lambda t: qb.qb_qlinear_fwd_batched(7), TypeError),                                            # no sequence of jobs
+])
+def test_python_calls_refuse_wrong_objects(lib, call, error):
+    """The binding's native half refuses, before anything is launched, what the library could not check behind a pointer."""
+    import torch
+    t = {"f32": torch.zeros(4, 64), "i8": torch.zeros(4, 64, dtype=torch.int8)}
+    with pytest.raises(error):
+        call(t)
