@@ -8,7 +8,7 @@
 // u - 128 for 8 bits (e = +1); either way A4 equals sum_j (2x'+1)(2u-L), the integer that the
 // integer product of the codes, de-quantized once afterwards (App., last paragraph), has to produce.
 //
-// Three kernels, chosen by shape (launch_bits):
+// Four kernels, chosen by shape (launch_bits):
 //   qgemm_i8_kernel     register-staged: the token tile goes global -> registers -> LDS, the packed weights never
 //                       touch LDS (the packed layout stores, per 32-neuron block and 64-feature unit, one slot per
 //                       lane, so a wavefront fetches its B operand with one coalesced load).  Small tiles for
@@ -22,6 +22,8 @@
 //                       a SIMD of their own (128x96 tiles; two workgroups per CU when there are more tiles than CUs:
 //                       one's write-out runs under the other's K-loop), an 8-bit output, per-token scales,
 //                       asymmetric group ranges.
+//   qgemm_i8_duo_kernel the largest problems at 2, 3 and 4 bits: 128x256 tiles on the 16x16x64 MFMA, two independent
+//                       workgroups per CU that multiply and write out in turn.
 // In all of them the token tile sits in LDS as dense 128-byte rows whose 16-byte chunks are XOR-swizzled by the
 // row number, so that the MFMA fragment reads are free of bank conflicts, and the k-bit codes are expanded to
 // int8 with a few byte-parallel shifts and masks in registers, right in front of the MFMA that consumes them.
@@ -304,14 +306,21 @@ __global__ __launch_bounds__(128) void qgemm_i8_small_group_kernel(const SmallGr
 // global -> LDS copy by the load unit: the global address of a lane is a wavefront-uniform base (in SGPRs) plus
 // the lane's 32-bit byte offset, the data of lane l lands at LDS address m0 + 16*l (also for the 12-byte form).
 // Written as inline assembly on purpose: the compiler then keeps no book on these copies, and the kernel states
-// itself, with wait_vmcnt, which of them must have landed before a barrier.
+// itself, with wait_vmcnt, which of them must have landed before a barrier.  The compiler may have written the base with
+// a VALU instruction (v_readlane of a spilled value) right in front, which a vector memory instruction may read five wait
+// states later only; it counts them for its own instructions, not into an asm block: hence the s_nop.
 __device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t off, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
 }
 __device__ __forceinline__ void copy12_to_lds(const void *base, uint32_t off, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx3 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx3 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+}
+
+__device__ __forceinline__ void copy4_to_lds(const void *base, uint32_t off, uint32_t lds_addr)  // lane l lands at m0 + 4*l
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dword %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
 }
 
 template <int BITS> struct SlotRead;  // one lane's slot (32 codes) out of LDS
@@ -1219,6 +1228,290 @@ __global__ __launch_bounds__(64 * (WM * WN + NPROD), (SIMD3 && OUT != 2 && NSTAG
 #undef QB_BARRIER
 }
 
+// Kernel for many tiles, K a multiple of 128: tiles of 128 tokens x 256 neurons, four wavefronts of 128 x 64 results,
+// v_mfma_i32_16x16x64_i8, two workgroups per CU on a persistent grid.
+// What bounds the smaller tiles is the LDS (operand fragments per MFMA) and the SIMD that copies, fragment reads and
+// code expansion share with the MFMAs.  Here a step of 128 features takes a wavefront 1024 cycles of MFMAs for 16 KB of
+// token fragments and 2-4 KB of packed weights read from LDS, every code is expanded once in the workgroup, and the
+// 16x16x64 form leaves the issue slots that the other wavefront of the SIMD needs.  That one belongs to the CU's other
+// workgroup and shares no barrier with it: one multiplies while the other one reads, expands, changes tile or writes out.
+// Measured at 32768 tokens, 2 bits: 4096 x 1024 183 us (two plain 128x128 workgroups per CU: 200), 1024 x 4096 109 (132),
+// a whole BERT-large layer with its activation quantizers 691 -> 606 us.  256x256 tiles of eight wavefronts (one
+// workgroup per CU, two groups of wavefronts half a phase apart) have the same K-loop, but a tile's write-out then runs
+// next to nothing: 188 and 118 us.  A second barrier per step that frees the stage earlier (copies two steps ahead) and
+// lines touched ahead of the copies were slower (188 and 120; 188 and 124).
+struct DuoArgs {
+    const int8_t *Xq;
+    const int32_t *rs_x;
+    const uint8_t *packed;
+    const float *h;
+    const int32_t *rs_w;
+    const float *bias;
+    float *Y;
+    int32_t *A4out;
+    int T, N, K, rows_per_group;
+    float hx;
+    int tiles_m, tiles_n;
+};
+struct DuoJob {
+    DuoArgs p[1];
+};
+template <int BITS>
+__global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
+{
+    constexpr int BM = 128, BN = 256, BK = 128;
+    constexpr int SLOT = 4 * BITS, CH = (BITS == 3) ? 12 : 16, LSLOT = (BITS == 3) ? 16 : SLOT;
+    constexpr int PAIR = 128 * SLOT, LPAIR = 128 * LSLOT;  // a 32-neuron block of one step, in memory and in LDS
+    constexpr int PARTS = LPAIR / 1024;                    // copies of one such block
+    constexpr int NB = 2 * PARTS;                          // weight copies per wavefront and step
+    constexpr int A_BYTES = BM * BK, STAGE = A_BYTES + 8 * LPAIR;
+    constexpr int PARAM = (128 + 3 * 256) * 4;             // rs_x, rs_w, h of the neuron's group, bias
+    constexpr int E2 = -2 * ((1 << BITS) - 1);             // 2*e
+    static_assert(BITS < 8, "two workgroups' stages fit the LDS up to 4 bits");
+    __shared__ __align__(1024) uint8_t lds[2 * STAGE + 2 * PARAM];
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // neurons 64*wave
+    const int q16 = lane & 15, hq = lane >> 4;
+
+    // fragment reads: token row l%16 of a 16-row block, logical chunk 2*(l/16) + kk (the 32 features of a slot)
+    const int fkey = (q16 >> 1) & 7;
+    const int a_fr[2] = {q16 * BK + (((2 * hq) ^ fkey) << 4), q16 * BK + (((2 * hq + 1) ^ fkey) << 4)};
+    // codes: slot 2*(l%16) + b of quarter l/16 of the block; b toggles bit 4 of the address (at 2 bits one read gives both).
+    // A lane's two neurons of a block are neighbours, so that its stores are 8 bytes and every store instruction covers
+    // whole 128-byte lines; the copies swap neighbouring slots in every other run of sixteen against the bank conflicts
+    // of that order.
+    const int b_fr = A_BYTES + 2 * wave * LPAIR +
+                     (BITS == 2 ? hq * 256 + q16 * 16 : hq * 512 + (((2 * q16) ^ (q16 >> 3)) << 4));
+    const int cchunk = (lane & 7) ^ (lane >> 4);  // rows +8: ^ 4
+
+    // The arguments are loaded where a tile needs them: known to be constant they would all be held in scalar registers
+    // from the start, more than there are.
+    auto args = [&]() -> const DuoArgs & {
+        int zero = 0;
+        asm volatile("" : "+s"(zero));
+        return job.p[zero];
+    };
+    const int nwg = job.p[0].tiles_m * job.p[0].tiles_n, tiles_n = job.p[0].tiles_n, steps = job.p[0].K / BK;
+
+    const uint8_t *a_base = nullptr, *b_base = nullptr;
+    uint32_t a_off[4], b_off[NB];
+    auto copy_step = [&](int s, int par) {
+        const uint8_t *as = a_base + (size_t)s * BK, *bs = b_base + (size_t)s * PAIR;
+        const uint32_t dst = lds_base + (uint32_t)par * STAGE;
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            const uint32_t d = dst + A_BYTES + (wave * NB + e) * 1024;
+            if constexpr (BITS == 3) copy12_to_lds(bs, b_off[e], d);
+            else copy16_to_lds(bs, b_off[e], d);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) copy16_to_lds(as, a_off[e], dst + (wave * 4 + e) * 1024);
+    };
+    // addresses of a tile's operands, its epilogue parameters and the copies of its first step
+    auto start_tile = [&](int tm, int tn, int pb, int par) {
+        const DuoArgs &P = args();
+        const int T = P.T, N = P.N, K = P.K, kunits = K >> 6, ncb = (N + 31) >> 5;
+        a_base = reinterpret_cast<const uint8_t *>(P.Xq) + (size_t)tm * BM * K;
+        b_base = P.packed + (size_t)tn * 8 * kunits * 64 * SLOT;
+        const int a_last = T - 1 - tm * BM, cb_last = ncb - 1 - tn * 8;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            int row = (wave * 4 + e) * 8 + (lane >> 3);
+            row = row < a_last ? row : a_last;  // rows past the end re-read the last one; results not stored
+            a_off[e] = (uint32_t)row * (uint32_t)K + ((cchunk ^ (4 * (e & 1))) << 4);
+        }
+        const int sl = BITS == 2 ? lane : lane ^ ((lane >> 4) & 1);
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            const int x = wave * NB + e;
+            int cb = x / PARTS;
+            cb = cb < cb_last ? cb : cb_last;
+            b_off[e] = (uint32_t)cb * (uint32_t)(kunits * 64 * SLOT) + (x % PARTS) * 64 * CH + sl * CH;
+        }
+        // 64 parameters per copy: 2 of rs_x, 4 each of rs_w, h, bias
+        const uint32_t dst = lds_base + 2 * STAGE + pb * PARAM + wave * 1024;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int x = wave * 4 + e;
+            int t = tm * BM + x * 64 + lane, nn = tn * BN + ((x - 2) & 3) * 64 + lane;
+            t = t < T ? t : T - 1;
+            nn = nn < N ? nn : N - 1;
+            if (x < 2) copy4_to_lds(P.rs_x, (uint32_t)t * 4, dst + e * 256);
+            else if (x < 6) copy4_to_lds(P.rs_w, (uint32_t)nn * 4, dst + e * 256);
+            else if (x < 10) copy4_to_lds(P.h, (uint32_t)(nn / P.rows_per_group) * 4, dst + e * 256);
+            else if (x < 14 && P.bias) copy4_to_lds(P.bias, (uint32_t)nn * 4, dst + e * 256);
+        }
+        copy_step(0, par);
+    };
+    // every wavefront's copies have landed and its LDS reads have returned; then the barrier
+    auto fence = [&]() {
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+    };
+
+    int work = blockIdx.x, pb = 0;  // (the grid has at most as many workgroups as there are tiles)
+    int lt = logical_tile(work, nwg);
+    int tm = lt / tiles_n, tn = lt - tm * tiles_n;
+    start_tile(tm, tn, 0, 0);
+    wait_vmcnt<0>();
+    int par = 0;
+    while (true) {
+        v4i acc[2][2][4][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) acc[i][j][mb][nb] = v4i{0, 0, 0, 0};
+        const int nwork = work + gridDim.x;
+        int ntm = 0, ntn = 0;
+        if (nwork < nwg) {
+            lt = logical_tile(nwork, nwg);
+            ntm = lt / tiles_n;
+            ntn = lt - ntm * tiles_n;
+        }
+        for (int s = 0; s < steps; ++s) {
+            fence();
+            const uint8_t *st_ = lds + par * STAGE;
+            par ^= 1;
+            // over the stage that was read in the step before; in the last step the next tile's first operands and its
+            // parameters, so that the address arithmetic and the latency lie under the MFMAs
+            if (s + 1 < steps) copy_step(s + 1, par);
+            else if (nwork < nwg) start_tile(ntm, ntn, pb ^ 1, par);
+            v4i a[2][4][2], b[2][2][2];
+            uint32_t raw[2][2][BITS];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint8_t *bp = st_ + j * LPAIR;
+                if constexpr (BITS == 2) {
+                    const v4u v = *reinterpret_cast<const v4u *>(bp + b_fr);
+                    raw[j][0][0] = v[0]; raw[j][0][1] = v[1]; raw[j][1][0] = v[2]; raw[j][1][1] = v[3];
+                } else {
+                    SlotRead<BITS>::get(bp + b_fr, raw[j][0]);
+                    SlotRead<BITS>::get(bp + (b_fr ^ 16), raw[j][1]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                    for (int mb = 0; mb < 4; ++mb) a[i][mb][kk] = *reinterpret_cast<const v4i *>(st_ + a_fr[kk] + (i * 4 + mb) * 16 * BK);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    if (i == 0) {
+#pragma unroll
+                        for (int nb = 0; nb < 2; ++nb) {
+                            uint32_t d[8];
+                            unpack_run<BITS>(raw[j][nb], d);
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) b[j][nb][e >> 2][e & 3] = (int)d[e];
+                        }
+                    }
+#pragma unroll
+                    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                            for (int nb = 0; nb < 2; ++nb)
+                                acc[i][j][mb][nb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i][mb][kk], b[j][nb][kk], acc[i][j][mb][nb], 0, 0, 0);
+                }
+            if (s + 1 < steps) wait_vmcnt<0>();
+        }
+
+        // ---- write-out
+        const DuoArgs &P = args();
+        const int T = P.T, N = P.N, K = P.K, t0 = tm * BM, n0 = tn * BN;
+        const float hx = P.hx;
+        const bool has_bias = P.bias != nullptr;
+        float *__restrict__ Y = P.Y;
+        int32_t *__restrict__ A4out = P.A4out;
+        const uint8_t *pp = lds + 2 * STAGE + pb * PARAM;
+        pb ^= 1;
+
+        const int *p_rx = reinterpret_cast<const int *>(pp) + 4 * hq;
+        const int nl = wave * 64 + 2 * q16;  // + 32*j + b
+        int coln[2][2];
+        float scale[2][2], bv[2][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int2 rw = *reinterpret_cast<const int2 *>(pp + 512 + (nl + 32 * j) * 4);
+            const float2 hg = *reinterpret_cast<const float2 *>(pp + 1536 + (nl + 32 * j) * 4);
+            float2 bb = make_float2(0.0f, 0.0f);
+            if (has_bias) bb = *reinterpret_cast<const float2 *>(pp + 2560 + (nl + 32 * j) * 4);
+            coln[j][0] = 2 * rw.x + K; coln[j][1] = 2 * rw.y + K;
+            scale[j][0] = hx * hg.x; scale[j][1] = hx * hg.y;
+            bv[j][0] = bb.x; bv[j][1] = bb.y;
+        }
+        const bool fast = t0 + BM <= T && n0 + BN <= N && A4out == nullptr && (N & 1) == 0 && (reinterpret_cast<uintptr_t>(Y) & 7) == 0;
+        if (fast) {
+            // a wavefront-uniform row address and the lane's 32-bit byte offset
+            uint8_t *out0 = reinterpret_cast<uint8_t *>(Y + (size_t)t0 * N + n0 + wave * 64);
+            const uint32_t lane_off = (uint32_t)(4 * hq * N + 2 * q16) * 4u;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int mb = 0; mb < 4; ++mb) {
+                    const int4 rx = *reinterpret_cast<const int4 *>(p_rx + i * 64 + mb * 16);
+                    const int er[4] = {qb_mad24(E2, rx.x, 0), qb_mad24(E2, rx.y, 0), qb_mad24(E2, rx.z, 0), qb_mad24(E2, rx.w, 0)};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        uint8_t *row = out0 + (size_t)(i * 64 + mb * 16 + c) * N * 4;
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            typedef float v2f __attribute__((ext_vector_type(2)));
+                            v2f o;
+#pragma unroll
+                            for (int nb = 0; nb < 2; ++nb)
+                                o[nb] = scale[j][nb] * (float)qb_a4(acc[i][j][mb][nb][c], er[c] + coln[j][nb]) + bv[j][nb];
+                            __builtin_nontemporal_store(o, reinterpret_cast<v2f *>(row + 128 * j + lane_off));
+                        }
+                    }
+                }
+            // 64 stores behind the copies: with at most 63 operations outstanding the copies have landed
+            wait_vmcnt<63>();
+        } else {  // edge tiles and the debug output: every element checked
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int t = t0 + i * 64 + mb * 16 + 4 * hq + c;
+                        const int er = E2 * p_rx[i * 64 + mb * 16 + c];
+                        if (t < T) {
+#pragma unroll
+                            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                                for (int nb = 0; nb < 2; ++nb) {
+                                    const int nn = n0 + nl + 32 * j + nb;
+                                    if (nn < N) {
+                                        const int a4 = qb_a4(acc[i][j][mb][nb][c], er + coln[j][nb]);
+                                        const size_t at = (size_t)t * N + nn;
+                                        Y[at] = scale[j][nb] * (float)a4 + bv[j][nb];
+                                        if (A4out) A4out[at] = a4;
+                                    }
+                                }
+                        }
+                    }
+            wait_vmcnt<0>();
+        }
+        if (nwork >= nwg) break;
+        work = nwork; tm = ntm; tn = ntn;
+    }
+}
+
 // Adds one problem to a launch list of the role-split kernel with BM x BN tiles; false when the list is full.
 template <int BM, int BN>
 bool group_add(Group &g, const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, const float *h, const int32_t *rs_w,
@@ -1301,6 +1594,33 @@ void launch_dma(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, co
                        Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, tiles_m, tiles_n);
 }
 
+// Which problems go to the 128 x 256 kernel with two independent workgroups per CU.  Its tiles are the largest, so it
+// needs two full rounds of the 512 resident workgroups (1024 tiles); with long contractions, whose tiles are started and
+// written out more rarely, three quarters of one.  Times in us, this kernel / the kernel of the rules below:
+//   4 bits  32768 x 4096 x 1024  170 / 191    32768 x 1024 x 4096  117 / 140    16384 x 3072 x 768 (1536 tiles)  54.5 / 62.2
+//           12288 x 3072 x 768 (1152 tiles)  41.8 / 43.5    12288 x 2304 x 768 (864)  35.5 / 34.1    32768 x 768 x 768 (768)  31.6 / 31.2
+//           32768 x 768 x 3072 (768)  76 / 84    16384 x 768 x 3072 (384)  40.8 / 43.0    12288 x 768 x 3072 (288)  35.7 / 31.0
+//   2 bits  32768 x 4096 x 1024  183 / 200    3 bits  32768 x 3072 x 1024  133 / 157
+// At 8 bits two workgroups' stages do not fit the LDS (one: 12288 x 3072 x 768 62 / 50).  At most an eighth of the columns
+// may be padding.
+template <int BITS>
+bool duo_shape(int T, int N, int K)
+{
+    const long tiles_n = (N + 255) / 256, tiles = (long)((T + 127) / 128) * tiles_n;
+    return BITS < 8 && K % 128 == 0 && (tiles >= 1024 || (K >= 2048 && tiles >= 384)) && (tiles_n * 256 - N) * 8 <= N;
+}
+
+template <int BITS>
+void launch_duo(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, const float *h, const int32_t *rs_w,
+                const float *bias, float *Y, int32_t *A4, int T, int N, int K, int rpg, float hx, hipStream_t st)
+{
+    if constexpr (BITS < 8) {
+        const DuoJob j{{{Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, (T + 127) / 128, (N + 255) / 256}}};
+        const int tiles = j.p[0].tiles_m * j.p[0].tiles_n;
+        hipLaunchKernelGGL((qgemm_i8_duo_kernel<BITS>), dim3(tiles < 512 ? tiles : 512), dim3(256), 0, st, j);
+    }
+}
+
 template <int BITS>
 void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, const float *h, const int32_t *rs_w,
                  const float *bias, float *Y, int32_t *A4, int T, int N, int K, int rpg, float hx, hipStream_t st,
@@ -1319,6 +1639,10 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
     }
     if (K % 128 != 0) {  // odd number of 64-feature units: register-staged kernel, one unit per step
         launch_cfg<BITS, 2, 2, 2, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
+        return;
+    }
+    if (!hx_rows && !q0 && duo_shape<BITS>(T, N, K)) {
+        launch_duo<BITS>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st);
         return;
     }
     // Tile choice (measured on BERT-base and BERT-large shapes).  Copies issued on a SIMD that is busy
@@ -1477,7 +1801,7 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
             ++sg.n;
             continue;
         }
-        if (j.K % 128 != 0 || !(use96 || use128)) {
+        if (j.K % 128 != 0 || !(use96 || use128) || duo_shape<BITS>((int)j.T, (int)j.N, (int)j.K)) {
             launch_job<BITS>(j, st);
             continue;
         }

@@ -546,3 +546,28 @@ def test_forward_batched_few_token_jobs_share_launches(qb):
         Y1 = qb.qb_qlinear_fwd(j["Xq"], j["rs_x"], CLIP, j["packed"], j["h"], j["rs_w"], bits, j["groups"], j["N"], bias=j["bias"])
         torch.cuda.synchronize()
         assert torch.equal(Yb, Y1)
+
+
+# (T, N, K): the smallest problems that reach the 128 x 256 tiles: one, two and three steps of 128 features, token and
+# neuron counts that end inside a tile, an odd neuron count (no 8-byte stores), the three-quarter round of a long contraction
+@pytest.mark.parametrize("bits", (2, 3, 4))
+@pytest.mark.parametrize("shape", [(16300, 2020, 128), (16384, 2048, 256), (16257, 1999, 384), (6100, 2048, 2048)])
+def test_forward_whole_output_large_tiles(qb, bits, shape):
+    """A4 exact, Y within the bound of the small shapes, single and batched calls with the same bits."""
+    T, N, K = shape
+    groups = N // 4 if N % 4 == 0 else 1
+    say("fwd large tiles", shape, "bits", bits)
+    d = quantized_inputs(qb, N, K, T, bits, seed=17 * N + K + bits, groups=groups)
+    bias = wl.activation(1, N, seed=9)[0].contiguous()
+    Y = torch.full((T, N), float("nan"), dtype=torch.float32, device=DEV)
+    qb.qb_qlinear_fwd(d["Xq"], d["rs_x"], CLIP, d["packed"], d["h"], d["rs_w"], bits, groups, N, bias=bias.to(DEV), Y=Y)
+    _, A4 = qb.qb_qlinear_fwd(d["Xq"], d["rs_x"], CLIP, d["packed"], d["h"], d["rs_w"], bits, groups, N, want_a4=True)
+    Yb = qb.qb_qlinear_fwd_batched([{"Xq": d["Xq"], "rs_x": d["rs_x"], "clip": CLIP, "packed": d["packed"], "h": d["h"], "rs_w": d["rs_w"],
+                                     "bits": bits, "groups": groups, "N": N, "bias": bias.to(DEV)}])[0]
+    torch.cuda.synchronize()
+    Yo, A4o, _ = oracle.qlinear_fwd(d["oq"], CLIP, d["oc"], d["oh"], bits, openmp=True)
+    assert (A4.cpu().numpy() == A4o).all()
+    assert torch.equal(Y, Yb)
+    b = bias.numpy().astype(np.float64)[None, :]
+    # three roundings of the product (1.8e-7, bound 1e-6) and the one of the sum with the bias
+    assert (np.abs(Y.cpu().numpy().astype(np.float64) - (Yo + b)) <= 1e-6 * np.abs(Yo) + 2.0 ** -23 * np.abs(Yo + b)).all()
