@@ -792,37 +792,56 @@ __global__ __launch_bounds__(256) void embedding_quantize_kernel(const float *__
     }
 }
 
+// A thread keeps four columns and their scales and takes EMB_IDS rows of ids, all their code loads in flight, so that a
+// result costs one load, four conversions and products and a streaming 16-byte store.  (One thread per four results,
+// each with its own divisions by d and by the group width and its own loads of the scales: 47-48 us for 32768 ids of
+// 1024 columns; so 32 us = 5.0 TB/s, the card's copy rate being 5.2.)  min(d/4, 256) threads cover a row or 1024 columns of it, the
+// workgroup as many rows at once as it has threads for.
+constexpr int EMB_IDS = 8;
 template <int BITS>
 __global__ __launch_bounds__(256) void embedding_gather_kernel(const uint8_t *__restrict__ codes,
                                                                const float *__restrict__ h, int64_t V, int d,
                                                                int cols_per_group, const int64_t *__restrict__ ids,
-                                                               int64_t n_ids, float *__restrict__ out)
+                                                               int n_ids, float *__restrict__ out)
 {
+    typedef float v4f __attribute__((ext_vector_type(4)));
     constexpr int L = (1 << BITS) - 1;
-    const int d4 = d >> 2;
-    const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (id >= n_ids * d4) return;
-    const int64_t i = id / d4;
-    const int c = (int)(id % d4) << 2;
-    const int64_t tok = ids[i];
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (tok >= 0 && tok < V) {
-        int u0, u1, u2, u3;
-        if constexpr (BITS == 8) {
-            const uint32_t q = *reinterpret_cast<const uint32_t *>(codes + tok * d + c);
-            u0 = q & 255u; u1 = (q >> 8) & 255u; u2 = (q >> 16) & 255u; u3 = q >> 24;
-        } else {
-            const uint32_t q = *reinterpret_cast<const uint16_t *>(codes + ((tok * d + c) >> 1));
-            u0 = q & 15u; u1 = (q >> 4) & 15u; u2 = (q >> 8) & 15u; u3 = (q >> 12) & 15u;
-        }
-        o.x = h[(c + 0) / cols_per_group] * (float)(2 * u0 - L);
-        o.y = h[(c + 1) / cols_per_group] * (float)(2 * u1 - L);
-        o.z = h[(c + 2) / cols_per_group] * (float)(2 * u2 - L);
-        o.w = h[(c + 3) / cols_per_group] * (float)(2 * u3 - L);
+    const int d4 = d >> 2, cw = d4 < 256 ? d4 : 256;
+    const int nsub = 256 / cw, sub = threadIdx.x / cw;
+    const int c4 = blockIdx.y * 256 + threadIdx.x - sub * cw;
+    if (sub >= nsub || c4 >= d4) return;
+    const int c = c4 << 2;
+    float hs[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) hs[e] = h[(c + e) / cols_per_group];
+    const int64_t i0 = (int64_t)blockIdx.x * (EMB_IDS * nsub) + sub;
+    int64_t tok[EMB_IDS];
+#pragma unroll
+    for (int r = 0; r < EMB_IDS; ++r) {
+        const int64_t i = i0 + r * nsub;
+        tok[r] = i < n_ids ? ids[i] : -1;
     }
-    reinterpret_cast<float4 *>(out)[id] = o;
+    uint32_t q[EMB_IDS];
+#pragma unroll
+    for (int r = 0; r < EMB_IDS; ++r) {
+        q[r] = 0;
+        if (tok[r] >= 0 && tok[r] < V) {
+            if constexpr (BITS == 8) q[r] = *reinterpret_cast<const uint32_t *>(codes + tok[r] * d + c);
+            else q[r] = *reinterpret_cast<const uint16_t *>(codes + ((tok[r] * d + c) >> 1));
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < EMB_IDS; ++r) {
+        const int64_t i = i0 + r * nsub;
+        if (i >= n_ids) continue;
+        v4f o = {0.f, 0.f, 0.f, 0.f};
+        if (tok[r] >= 0 && tok[r] < V) {  // (an id outside the table gives a row of zeros)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = hs[e] * (float)(2 * (int)((q[r] >> (BITS * e)) & (uint32_t)L) - L);
+        }
+        __builtin_nontemporal_store(o, reinterpret_cast<v4f *>(out) + i * d4 + c4);
+    }
 }
-
 
 template <int BITS, int THREADS, bool ASYM = false>
 void launch_panel(const float *W, int K, int rows_per_group, int prow, int panels, uint8_t *packed, float *h, float *m,
@@ -1219,14 +1238,13 @@ extern "C" qb_status qb_embedding_gather_bits(const uint8_t *codes, const float 
     if (bits != 4 && bits != 8) return QB_ERR_BITS;
     if (V <= 0 || !k_ok(d) || groups <= 0 || d % groups != 0 || n_ids < 0 || n_ids > (1 << 30)) return QB_ERR_SHAPE;
     if (n_ids == 0) return QB_OK;
-    const int64_t n4 = n_ids * (d / 4);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const int64_t d4 = d / 4, rows = EMB_IDS * (256 / (d4 < 256 ? d4 : 256));
+    const dim3 grid((unsigned)((n_ids + rows - 1) / rows), (unsigned)((d4 + 255) / 256));
     if (bits == 8)
-        hipLaunchKernelGGL(embedding_gather_kernel<8>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, codes, h, V,
-                           (int)d, (int)(d / groups), ids, n_ids, out);
+        hipLaunchKernelGGL(embedding_gather_kernel<8>, grid, dim3(256), 0, st, codes, h, V, (int)d, (int)(d / groups), ids, (int)n_ids, out);
     else
-        hipLaunchKernelGGL(embedding_gather_kernel<4>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, codes, h, V,
-                           (int)d, (int)(d / groups), ids, n_ids, out);
+        hipLaunchKernelGGL(embedding_gather_kernel<4>, grid, dim3(256), 0, st, codes, h, V, (int)d, (int)(d / groups), ids, (int)n_ids, out);
     return launch_status();
 }
 
