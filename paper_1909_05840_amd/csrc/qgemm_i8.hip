@@ -8,7 +8,7 @@
 // u - 128 for 8 bits (e = +1); either way A4 equals sum_j (2x'+1)(2u-L), the integer that the
 // integer product of the codes, de-quantized once afterwards (App., last paragraph), has to produce.
 //
-// Four kernels, chosen by shape (launch_bits):
+// Five kernels, chosen by shape (launch_bits):
 //   qgemm_i8_kernel     register-staged: the token tile goes global -> registers -> LDS, the packed weights never
 //                       touch LDS (the packed layout stores, per 32-neuron block and 64-feature unit, one slot per
 //                       lane, so a wavefront fetches its B operand with one coalesced load).  Small tiles for
@@ -22,6 +22,7 @@
 //                       a SIMD of their own (128x96 tiles; two workgroups per CU when there are more tiles than CUs:
 //                       one's write-out runs under the other's K-loop), an 8-bit output, per-token scales,
 //                       asymmetric group ranges.
+//   qgemm_i8_split_kernel the smallest problems: the contraction sliced inside the workgroup, no LDS in the loop.
 //   qgemm_i8_duo_kernel the largest problems at 2, 3 and 4 bits: 128x256 tiles on the 16x16x64 MFMA, two independent
 //                       workgroups per CU that multiply and write out in turn.
 // In all of them the token tile sits in LDS as dense 128-byte rows whose 16-byte chunks are XOR-swizzled by the
@@ -271,9 +272,13 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_i8_kernel(
                                             tiles_n, hx_rows, q0, blockIdx.x);
 }
 
-// Several few-tile problems (small token counts: the inference regime, where a launch costs more than its work) in one
-// launch of the 32x64-tile form: workgroup w serves tile w - first_wg[j] of problem j; a problem's workgroups start at
-// a multiple of 8, so that its tiles keep their XCD (the fill-up workgroups leave at once).
+// The few tiles of a small token count: 32 x 64 tiles, the contraction cut into eight slices inside the workgroup.
+// What bounds these calls is latency: a K-loop that walks the features step by step pays a memory latency per step,
+// while the operands' bytes take a fraction of one.  So each of the eight wavefronts takes one slice of the features, loads
+// its operands straight into registers in the layout of the MFMA (no LDS and no barrier in the loop), and the slices' integer
+// sums meet in LDS; the write-out is split over the wavefronts as well.  Integer sums: the order does not matter, the
+// results are the ones of the other kernels bit for bit.  The direct loads touch 32 rows per instruction, so that with
+// more workgroups than CUs the kernel above is ahead again (see launch_bits).
 struct SmallProblem {
     const int8_t *Xq;
     const int32_t *rs_x;
@@ -282,10 +287,150 @@ struct SmallProblem {
     const int32_t *rs_w;
     const float *bias;
     float *Y;
+    int32_t *A4out;
+    const float *hx_rows;  // one activation scale per token (dynamic range) instead of hx, or null
+    const float *q0;       // asymmetric group ranges: h holds Delta and q0 the lower end of every group, or null
     int T, N, K, rows_per_group;
     float hx;
     int tiles_m, tiles_n;
 };
+
+template <int BITS>
+__device__ __forceinline__ void qgemm_i8_split_body(const SmallProblem &p, const int bid)
+{
+    constexpr int KS = 8, SLOT = 4 * BITS, U = 2;  // units in flight, besides as many being multiplied
+    __shared__ __align__(16) int4 red[KS * 2 * 4 * 64];
+    const int T = p.T, N = p.N, K = p.K;
+    const int nwg = p.tiles_m * p.tiles_n;
+    int logical;  // each XCD a contiguous range of tiles, n fastest
+    {
+        const int xcd = bid & 7, idx = bid >> 3;
+        const int q = nwg >> 3, r = nwg & 7;
+        logical = xcd * q + (xcd < r ? xcd : r) + idx;
+    }
+    const int tile_m = logical / p.tiles_n, tile_n = logical - tile_m * p.tiles_n;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // slice of the contraction
+    const int l32 = lane & 31, hf = lane >> 5;
+
+    const int units = K >> 6, ncb = (N + 31) >> 5;
+    const int u0 = units * wave / KS, u1 = units * (wave + 1) / KS;
+    int t = tile_m * 32 + l32;
+    t = t < T ? t : T - 1;  // rows past the end re-read the last one; their outputs are masked
+    const int8_t *a_src = p.Xq + (size_t)t * K + hf * 32;
+    const uint8_t *b_src[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        int cb = tile_n * 2 + j;
+        cb = cb < ncb ? cb : ncb - 1;
+        b_src[j] = p.packed + ((size_t)cb * units * 64 + lane) * SLOT;
+    }
+
+    v16i acc[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[j][i] = 0;
+    v4i a[2][U][2];
+    uint32_t b[2][U][2][BITS];
+    auto load = [&](int u, int set) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            int v = u + i;
+            v = v < units ? v : units - 1;  // (a unit behind the slice is loaded and not used)
+            const v4i *as = reinterpret_cast<const v4i *>(a_src + (size_t)v * 64);
+            a[set][i][0] = as[0];
+            a[set][i][1] = as[1];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t *bs = reinterpret_cast<const uint32_t *>(b_src[j] + (size_t)v * 64 * SLOT);
+#pragma unroll
+                for (int e = 0; e < BITS; ++e) b[set][i][j][e] = bs[e];
+            }
+        }
+    };
+    auto mma = [&](int u, int set) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            if (u + i >= u1) break;  // (uniform)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                uint32_t d[8];
+                unpack_run<BITS>(b[set][i][j], d);
+                if constexpr (BITS == 8) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) d[e] ^= 0x80808080u;
+                }
+#pragma unroll
+                for (int sub = 0; sub < 2; ++sub) {
+                    const v4i bb = {(int)d[4 * sub], (int)d[4 * sub + 1], (int)d[4 * sub + 2], (int)d[4 * sub + 3]};
+                    acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[set][i][sub], bb, acc[j], 0, 0, 0);
+                }
+            }
+        }
+    };
+    load(u0, 0);
+
+    // the epilogue's parameters, on their way during the loop.  The wavefront writes quad wave/2 of every lane's sixteen
+    // results of block wave%2 (result i is token 8*(i/4) + 4*hf + i%4 of the tile)
+    constexpr int L = (1 << BITS) - 1;
+    constexpr int E2 = (BITS == 8) ? 2 : -2 * L;  // 2*e
+    const int wn = wave & 1, quad = wave >> 1, tl = tile_m * 32 + 8 * quad + 4 * hf;
+    const int n = tile_n * 64 + wn * 32 + l32, nn = n < N ? n : N - 1;
+    const int coln = 2 * p.rs_w[nn] + K;
+    const float hg = p.h[nn / p.rows_per_group];
+    const float zn = p.q0 ? p.q0[nn / p.rows_per_group] : 0.0f;
+    const float bv = p.bias ? p.bias[nn] : 0.0f;
+    int rx[4];
+    float hr[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int tt = tl + r < T ? tl + r : T - 1;
+        rx[r] = p.rs_x[tt];
+        hr[r] = p.hx_rows ? p.hx_rows[tt] : p.hx;
+    }
+
+    for (int u = u0; u < u1; u += 2 * U) {
+        if (u + U < u1) load(u + U, 1);
+        mma(u, 0);
+        if (u + 2 * U < u1) load(u + 2 * U, 0);
+        mma(u + U, 1);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            red[((wave * 2 + j) * 4 + q) * 64 + lane] = make_int4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
+    __syncthreads();
+    int4 sum = make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int4 v = red[((s * 2 + wn) * 4 + quad) * 64 + lane];
+        sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+    }
+    if (n >= N) return;
+    const int sums[4] = {sum.x, sum.y, sum.z, sum.w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int tt = tl + r;
+        if (tt >= T) break;
+        const int a4 = qb_a4(sums[r], E2 * rx[r] + coln);
+        const size_t at = (size_t)tt * N + n;
+        if (p.q0) p.Y[at] = asym_value(a4, rx[r] + (K >> 1), L, hr[r], hg, zn) + bv;
+        else p.Y[at] = (hr[r] * hg) * (float)a4 + bv;
+        if (p.A4out) p.A4out[at] = a4;
+    }
+}
+
+template <int BITS>
+__global__ __launch_bounds__(512) void qgemm_i8_split_kernel(const SmallProblem p)
+{
+    qgemm_i8_split_body<BITS>(p, blockIdx.x);
+}
+
+// Several few-tile problems (small token counts: the inference regime, where a launch costs more than its work) in one
+// launch: workgroup w serves tile w - first_wg[j] of problem j; a problem's workgroups start at
+// a multiple of 8, so that its tiles keep their XCD (the fill-up workgroups leave at once).
 struct SmallGroup {
     int n;
     int first_wg[QB_MAX_BATCH + 1];
@@ -301,6 +446,16 @@ __global__ __launch_bounds__(128) void qgemm_i8_small_group_kernel(const SmallGr
     if (local >= p.tiles_m * p.tiles_n) return;  // (uniform over the workgroup)
     qgemm_i8_body<BITS, 1, 1, 1, 2, KU>(p.Xq, p.rs_x, p.packed, p.h, p.rs_w, p.bias, p.Y, nullptr, p.T, p.N, p.K,
                                         p.rows_per_group, p.hx, p.tiles_m, p.tiles_n, nullptr, nullptr, local);
+}
+
+template <int BITS>
+__global__ __launch_bounds__(512) void qgemm_i8_split_group_kernel(const SmallGroup g)
+{
+    int j = 0;
+    while (j + 1 < g.n && (int)blockIdx.x >= g.first_wg[j + 1]) ++j;
+    const int local = blockIdx.x - g.first_wg[j];
+    if (local >= g.p[j].tiles_m * g.p[j].tiles_n) return;  // (uniform over the workgroup)
+    qgemm_i8_split_body<BITS>(g.p[j], local);
 }
 
 // global -> LDS copy by the load unit: the global address of a lane is a wavefront-uniform base (in SGPRs) plus
@@ -1594,6 +1749,12 @@ void launch_dma(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, co
                        Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, tiles_m, tiles_n);
 }
 
+// Which few-tile problems have their contraction sliced (tiles of 32 x 64): up to one workgroup per CU.  Kernel times in
+// us, sliced / stepped: 12 tiles, K = 768 3.7 / 4.3, K = 3072 4.8 / 7.5; 156 tiles, K = 3072 6.7 / 7.7 (4 bits), 7.4 / 8.1
+// (8 bits); 240 tiles, K = 3072 6.1 / 8.0; 224 tiles, K = 1792 5.7 / 6.4, K = 448 4.2 / 4.3; but 468 tiles of 8 bits, K = 768
+// 7.5 / 5.6 and 564 tiles, K = 3072 13.9 / 11.0 (the direct loads then wait for the L1s).
+inline bool split_shape(long tiles) { return tiles <= 256; }
+
 // Which problems go to the 128 x 256 kernel with two independent workgroups per CU.  Its tiles are the largest, so it
 // needs two full rounds of the 512 resident workgroups (1024 tiles); with long contractions, whose tiles are started and
 // written out more rarely, three quarters of one.  Times in us, this kernel / the kernel of the rules below:
@@ -1632,7 +1793,10 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
         // and pay ~6.5 us at least; 32x64 tiles of the register-staged kernel spread the work over the chip
         // (measured 4.4-5 us against 8 at T <= 1024, N = 768; 6.8 against 8.4 at 1024 x 2304 x 768; equal
         // at about 190 tiles).  Long contractions take 256 features per step.
-        if (K % 256 == 0 && K >= 2048) launch_cfg<BITS, 1, 1, 1, 2, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
+        const SmallProblem sp{Xq, rs_x, packed, h, rs_w, bias, Y, A4, hx_rows, q0, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64};
+        const int tiles = sp.tiles_m * sp.tiles_n;
+        if (split_shape(tiles)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sp);
+        else if (K % 256 == 0 && K >= 2048) launch_cfg<BITS, 1, 1, 1, 2, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         else if (K % 128 == 0) launch_cfg<BITS, 1, 1, 1, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         else launch_cfg<BITS, 1, 1, 1, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         return;
@@ -1759,13 +1923,14 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
 {
     Group g96, g128;
     g96.n = g128.n = 0;
-    SmallGroup small[3];  // few-tile problems, by features per step (64, 128, 256)
-    small[0].n = small[1].n = small[2].n = 0;
+    SmallGroup small[4];  // few-tile problems, by features per step (64, 128, 256), and those with a sliced contraction
+    small[0].n = small[1].n = small[2].n = small[3].n = 0;
     auto flush_small = [&](int c) {
         SmallGroup &sg = small[c];
         if (sg.n == 0) return;
         const dim3 grid(sg.first_wg[sg.n]);
-        if (c == 0) hipLaunchKernelGGL((qgemm_i8_small_group_kernel<BITS, 1>), grid, dim3(128), 0, st, sg);
+        if (c == 3) hipLaunchKernelGGL((qgemm_i8_split_group_kernel<BITS>), grid, dim3(512), 0, st, sg);
+        else if (c == 0) hipLaunchKernelGGL((qgemm_i8_small_group_kernel<BITS, 1>), grid, dim3(128), 0, st, sg);
         else if (c == 1) hipLaunchKernelGGL((qgemm_i8_small_group_kernel<BITS, 2>), grid, dim3(128), 0, st, sg);
         else hipLaunchKernelGGL((qgemm_i8_small_group_kernel<BITS, 4>), grid, dim3(128), 0, st, sg);
         sg.n = 0;
@@ -1787,14 +1952,14 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
         // workgroups per CU stay 3-5 % ahead)
         const bool use96 = 86 * rounds96 < 100 * rounds128 || (!few128 && j.N % 96 == 0 && tiles96 <= 1280);
         const bool use128 = !use96 && few128;
-        if (tiles128 <= 160) {  // few tiles: the 32x64-tile form, the step width of the single call, one launch per width
-            const int c = (j.K % 256 == 0 && j.K >= 2048) ? 2 : (j.K % 128 == 0) ? 1 : 0;
+        if (tiles128 <= 160) {  // few tiles: the kernel of the single call, one launch per kernel
+            const int c = split_shape((long)((j.T + 31) / 32 * ((j.N + 63) / 64))) ? 3 : (j.K % 256 == 0 && j.K >= 2048) ? 2 : (j.K % 128 == 0) ? 1 : 0;
             SmallGroup &sg = small[c];
             if (sg.n == QB_MAX_BATCH) flush_small(c);
             if (sg.n == 0) sg.first_wg[0] = 0;
             SmallProblem &sp = sg.p[sg.n];
             sp.Xq = j.Xq; sp.rs_x = j.rs_x; sp.packed = static_cast<const uint8_t *>(j.packed); sp.h = j.h; sp.rs_w = j.rs_w;
-            sp.bias = j.bias; sp.Y = j.Y; sp.T = (int)j.T; sp.N = (int)j.N; sp.K = (int)j.K;
+            sp.bias = j.bias; sp.Y = j.Y; sp.A4out = nullptr; sp.hx_rows = nullptr; sp.q0 = nullptr; sp.T = (int)j.T; sp.N = (int)j.N; sp.K = (int)j.K;
             sp.rows_per_group = (int)(j.N / j.groups); sp.hx = j.clip / 255.0f;
             sp.tiles_m = (int)((j.T + 31) / 32); sp.tiles_n = (int)((j.N + 63) / 64);
             sg.first_wg[sg.n + 1] = sg.first_wg[sg.n] + ((sp.tiles_m * sp.tiles_n + 7) & ~7);
@@ -1824,7 +1989,7 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
     }
     if (g96.n) launch_g96<BITS>(g96, st);
     if (g128.n) launch_group<BITS, 2, 2, 2, 2, 3, 4, false, 0>(g128, st, 256);
-    for (int c = 0; c < 3; ++c) flush_small(c);
+    for (int c = 0; c < 4; ++c) flush_small(c);
 }
 }  // namespace
 

@@ -571,3 +571,36 @@ def test_forward_whole_output_large_tiles(qb, bits, shape):
     b = bias.numpy().astype(np.float64)[None, :]
     # three roundings of the product (1.8e-7, bound 1e-6) and the one of the sum with the bias
     assert (np.abs(Y.cpu().numpy().astype(np.float64) - (Yo + b)) <= 1e-6 * np.abs(Yo) + 2.0 ** -23 * np.abs(Yo + b)).all()
+
+
+# K of one unit of 64 features (three of the four slices empty) up to uneven eighths; one token, one more than a tile of
+# 32; neuron counts around the tile of 64
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("shape", [(1, 1, 64), (33, 65, 128), (31, 63, 192), (32, 64, 320), (70, 130, 832), (33, 96, 1984), (33, 66, 2048), (5, 33, 2112)])
+def test_forward_few_tokens_slices_of_the_contraction(qb, bits, shape):
+    """A4 exact, Y within the bound; static and per-token scales, symmetric and asymmetric ranges, single and batched."""
+    T, N, K = shape
+    say("fwd slices", shape, "bits", bits)
+    d = quantized_inputs(qb, N, K, T, bits, seed=7 * N + K + bits, groups=1)
+    bias = wl.activation(1, N, seed=9)[0].contiguous().to(DEV)
+    args = (d["packed"], d["h"], d["rs_w"], bits, 1, N)
+    Y, A4 = qb.qb_qlinear_fwd(d["Xq"], d["rs_x"], CLIP, *args, bias=bias, want_a4=True)
+    Yb = qb.qb_qlinear_fwd_batched([{"Xq": d["Xq"], "rs_x": d["rs_x"], "clip": CLIP, "packed": d["packed"], "h": d["h"], "rs_w": d["rs_w"],
+                                     "bits": bits, "groups": 1, "N": N, "bias": bias}] * 3)
+    hx = torch.full((T,), float(np.float32(CLIP) / np.float32(255)), device=DEV)  # (one rounded division, as the static call)
+    Yd = qb.qb_qlinear_fwd_dyn(d["Xq"], d["rs_x"], hx, *args, bias=bias)
+    pa, da, qa, ra = qb.qb_quantize_groupwise_asym(d["W"].to(DEV), bits, 1)
+    Ya = qb.qb_qlinear_fwd_asym(d["Xq"], d["rs_x"], CLIP, pa, da, qa, ra, bits, 1, N)
+    ua = qb.qb_unpack_codes(pa, N, K, bits).cpu().double()
+    torch.cuda.synchronize()
+    Yo, A4o, _ = oracle.qlinear_fwd(d["oq"], CLIP, d["oc"], d["oh"], bits, openmp=True)
+    assert (A4.cpu().numpy() == A4o).all()
+    b = bias.cpu().numpy().astype(np.float64)[None, :]
+    assert (np.abs(Y.cpu().numpy().astype(np.float64) - (Yo + b)) <= 1e-6 * np.abs(Yo) + 2.0 ** -23 * np.abs(Yo + b)).all()
+    assert all(torch.equal(Y, y) for y in Yb) and torch.equal(Y, Yd)
+    x2 = 2 * torch.from_numpy(d["oq"]).double() + 1
+    S, R = x2 @ ua.T, x2.sum(1, keepdim=True)
+    hx64, dl, z = CLIP / 255.0, da.cpu().double()[0], qa.cpu().double()[0]
+    ref = hx64 * (dl * S + z * R)
+    # four roundings, relative to the two terms that may cancel (2.4e-7; bound 1e-6)
+    assert ((Ya.cpu().double() - ref).abs() <= 1e-6 * hx64 * (dl * S.abs() + z.abs() * R.abs())).all()
