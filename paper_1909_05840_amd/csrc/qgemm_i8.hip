@@ -464,13 +464,23 @@ __global__ __launch_bounds__(512) void qgemm_i8_split_group_kernel(const SmallGr
 // itself, with wait_vmcnt, which of them must have landed before a barrier.  The compiler may have written the base with
 // a VALU instruction (v_readlane of a spilled value) right in front, which a vector memory instruction may read five wait
 // states later only; it counts them for its own instructions, not into an asm block: hence the s_nop.
+// NOP = 0: kernels whose copies take their base from scalar arithmetic (no spilled scalar registers), which needs no such
+// distance (the 8-bit feed-forward pair at 4096 tokens: 55.5 us, with the longer wait in every copy 56.2).
+template <int NOP = 0>
 __device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t off, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+    if constexpr (NOP == 0)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
 }
+template <int NOP = 0>
 __device__ __forceinline__ void copy12_to_lds(const void *base, uint32_t off, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx3 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+    if constexpr (NOP == 0)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx3 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx3 %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
 }
 
 __device__ __forceinline__ void copy4_to_lds(const void *base, uint32_t off, uint32_t lds_addr)  // lane l lands at m0 + 4*l
@@ -1458,11 +1468,11 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
 #pragma unroll
         for (int e = 0; e < NB; ++e) {
             const uint32_t d = dst + A_BYTES + (wave * NB + e) * 1024;
-            if constexpr (BITS == 3) copy12_to_lds(bs, b_off[e], d);
-            else copy16_to_lds(bs, b_off[e], d);
+            if constexpr (BITS == 3) copy12_to_lds<3>(bs, b_off[e], d);
+            else copy16_to_lds<3>(bs, b_off[e], d);
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) copy16_to_lds(as, a_off[e], dst + (wave * 4 + e) * 1024);
+        for (int e = 0; e < 4; ++e) copy16_to_lds<3>(as, a_off[e], dst + (wave * 4 + e) * 1024);
     };
     // addresses of a tile's operands, its epilogue parameters and the copies of its first step
     auto start_tile = [&](int tm, int tn, int pb, int par) {
