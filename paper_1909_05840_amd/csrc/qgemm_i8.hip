@@ -1762,7 +1762,8 @@ void launch_dma(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, co
 // Which few-tile problems have their contraction sliced (tiles of 32 x 64): up to one workgroup per CU.  Kernel times in
 // us, sliced / stepped: 12 tiles, K = 768 3.7 / 4.3, K = 3072 4.8 / 7.5; 156 tiles, K = 3072 6.7 / 7.7 (4 bits), 7.4 / 8.1
 // (8 bits); 240 tiles, K = 3072 6.1 / 8.0; 224 tiles, K = 1792 5.7 / 6.4, K = 448 4.2 / 4.3; but 468 tiles of 8 bits, K = 768
-// 7.5 / 5.6 and 564 tiles, K = 3072 13.9 / 11.0 (the direct loads then wait for the L1s).
+// 7.5 / 5.6 and 564 tiles, K = 3072 13.9 / 11.0 (the direct loads then wait for the L1s).  The same call repeated, all operands
+// in the L2: 48 tiles, K = 768 4.6 / 4.4; between other kernels, as a layer's calls come, 4.0 / 5.1.
 inline bool split_shape(long tiles) { return tiles <= 256; }
 
 // Which problems go to the 128 x 256 kernel with two independent workgroups per CU.  Its tiles are the largest, so it
@@ -1946,6 +1947,10 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
         sg.n = 0;
     };
     const OutQ none{nullptr, nullptr, 1.0f, 0, nullptr, nullptr};
+    auto few_tiles = [](const qb_fwd_job &j) { return (long)((j.T + 127) / 128) * ((j.N + 127) / 128) <= 160; };
+    long small_tiles = 0;  // of all few-tile jobs of the width together: they run side by side
+    for (int i = 0; i < n_jobs; ++i)
+        if (jobs[i].bits == BITS && few_tiles(jobs[i])) small_tiles += (long)((jobs[i].T + 31) / 32) * ((jobs[i].N + 63) / 64);
     for (int i = 0; i < n_jobs; ++i) {
         const qb_fwd_job &j = jobs[i];
         if (j.bits != BITS) continue;
@@ -1962,8 +1967,8 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
         // workgroups per CU stay 3-5 % ahead)
         const bool use96 = 86 * rounds96 < 100 * rounds128 || (!few128 && j.N % 96 == 0 && tiles96 <= 1280);
         const bool use128 = !use96 && few128;
-        if (tiles128 <= 160) {  // few tiles: the kernel of the single call, one launch per kernel
-            const int c = split_shape((long)((j.T + 31) / 32 * ((j.N + 63) / 64))) ? 3 : (j.K % 256 == 0 && j.K >= 2048) ? 2 : (j.K % 128 == 0) ? 1 : 0;
+        if (few_tiles(j)) {  // few tiles: one launch per kernel (the sliced one by the rule of the single call, for the sum)
+            const int c = split_shape(small_tiles) ? 3 : (j.K % 256 == 0 && j.K >= 2048) ? 2 : (j.K % 128 == 0) ? 1 : 0;
             SmallGroup &sg = small[c];
             if (sg.n == QB_MAX_BATCH) flush_small(c);
             if (sg.n == 0) sg.first_wg[0] = 0;
