@@ -3,6 +3,8 @@ host functions are right, and invalid arguments are refused before anything is l
 import ctypes
 import os
 import re
+import struct
+import subprocess
 
 import pytest
 
@@ -238,3 +240,51 @@ def test_python_calls_refuse_wrong_objects(lib, call, error):
     t = {"f32": torch.zeros(4, 64), "i8": torch.zeros(4, 64, dtype=torch.int8)}
     with pytest.raises(error):
         call(t)
+
+
+def gfx950_code_objects(path):
+    """The device code objects of a library built here: the entries of the offload bundles in its .hip_fatbin section."""
+    blob = open(path, "rb").read()
+    magic, out, at = b"__CLANG_OFFLOAD_BUNDLE__", [], 0
+    while (at := blob.find(magic, at)) >= 0:
+        p = at + len(magic)
+        (count,) = struct.unpack_from("<Q", blob, p)
+        p += 8
+        for _ in range(count if count < 16 else 0):    # (the name alone also stands among the runtime's strings)
+            offset, size, name = struct.unpack_from("<QQQ", blob, p)
+            triple = blob[p + 24:p + 24 + name].decode()
+            p += 24 + name
+            if "gfx950" in triple and size:
+                out.append(blob[at + offset:at + offset + size])
+        at += len(magic)
+    return out
+
+
+def test_copies_keep_their_distance_to_the_scalar_base(lib, tmp_path):
+    """A vector memory instruction may read a scalar register five wait states after a VALU instruction wrote it at the
+    earliest.  The compiler does not see into the asm blocks of the global -> LDS copies, and it may write a block's base with
+    v_readlane or v_readfirstlane right in front: the wait states have to lie inside the block, in front of its first copy."""
+    copies = 0
+    for i, code in enumerate(gfx950_code_objects(qb.LIB_PATH)):
+        f = tmp_path / ("%d.o" % i)
+        f.write_bytes(code)
+        listing = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", "--no-show-raw-insn", "--no-leading-addr", str(f)], check=True,
+                                 capture_output=True, text=True).stdout
+        states = 0    # wait states since the last instruction that is not part of a run of copies
+        for line in listing.splitlines():
+            text = line.split("//")[0].strip()
+            if not text:
+                continue
+            op = text.split()[0]
+            if op.startswith("global_load_lds"):
+                if "s[" in text:
+                    copies += 1
+                    assert states >= 5, text
+                states += 1
+            elif op == "s_nop":
+                states += int(text.split()[1]) + 1
+            elif text.startswith("s_mov_b32 m0,"):
+                states += 1
+            else:
+                states = 0
+    assert copies > 100
