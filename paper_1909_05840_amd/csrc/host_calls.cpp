@@ -39,6 +39,17 @@ typedef PyObject *const *Args;
     throw_python_error();
 }
 
+// The interpreter lock is given up while this lives.  The runtime blocks in allocations (until memory is given back) and in
+// launches (while the stream's queue is full); other threads go on meanwhile, among them a host callback that the stream may
+// be waiting for.  (torch's own calls do the same.)
+struct Unlocked {
+    PyThreadState *const state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked &) = delete;
+    Unlocked &operator=(const Unlocked &) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 const Tensor &tensor(PyObject *o, const char *name)
 {
     if (!THPVariable_Check(o)) raise(PyExc_TypeError, "%s must be a tensor", name);
@@ -88,6 +99,7 @@ uint16_t *bits16(const Tensor &t) { return t.defined() ? static_cast<uint16_t *>
 
 Tensor fresh(at::IntArrayRef size, at::ScalarType t, const at::Device &dev)
 {
+    const Unlocked unlocked;
     return Tensor(at::detail::empty_cuda(size, t, dev, std::nullopt));
 }
 
@@ -123,8 +135,19 @@ int small(PyObject *o)  // an argument the C side takes as int
 
 void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-void check(qb_status s)
+// Calls a C entry point without the interpreter lock and raises if it fails.  The arguments are converted before, with the
+// lock; what they point into belongs to objects that are held until it has returned (the call's arguments, Jobs, Tensor).
+template <typename T>
+struct Same {
+    using type = T;
+};
+template <typename... P>
+void call(qb_status (*entry)(P...), typename Same<P>::type... args)
 {
+    const qb_status s = [&] {
+        const Unlocked unlocked;
+        return entry(args...);
+    }();
     if (s == QB_OK) return;
     PyObject *e = PyObject_CallFunction(g_error, "is", static_cast<int>(s), qb_status_string(s));
     if (e) {
@@ -179,8 +202,8 @@ QB_CALL(quantize_groupwise, 7)  // W, bits, groups, packed, h, m, rs_w
     const Tensor h = out(a[4], {groups > 0 ? groups : 1}, at::kFloat, dev, "h");
     const Tensor m = out(a[5], {groups > 0 ? groups : 1}, at::kFloat, dev, "m");
     const Tensor rs = out(a[6], {N}, at::kInt, dev, "rs_w");
-    check(qb_quantize_groupwise(ptr<float>(W), N, K, bits, groups, p.data_ptr(), ptr<float>(h), ptr<float>(m),
-                                ptr<int32_t>(rs), stream()));
+    call(qb_quantize_groupwise, ptr<float>(W), N, K, bits, groups, p.data_ptr(), ptr<float>(h), ptr<float>(m),
+                                ptr<int32_t>(rs), stream());
     return tuple({p, h, m, rs});
 }
 
@@ -192,8 +215,8 @@ QB_CALL(quantize_groupwise_clip, 6)  // W, bits, m_in, packed, h, rs_w
     const at::Device dev = W.device();
     const Tensor p = packed_buffer(a[3], N, K, bits, dev);
     const Tensor h = out(a[4], {G}, at::kFloat, dev, "h"), rs = out(a[5], {N}, at::kInt, dev, "rs_w");
-    check(qb_quantize_groupwise_clip(ptr<float>(W), N, K, bits, static_cast<int>(G), ptr<float>(m), p.data_ptr(), ptr<float>(h),
-                                     ptr<int32_t>(rs), stream()));
+    call(qb_quantize_groupwise_clip, ptr<float>(W), N, K, bits, static_cast<int>(G), ptr<float>(m), p.data_ptr(), ptr<float>(h),
+                                     ptr<int32_t>(rs), stream());
     return tuple({p, h, rs});
 }
 
@@ -206,8 +229,8 @@ QB_CALL(quantize_groupwise_asym, 7)  // W, bits, groups, packed, delta, q0, rs_w
     const Tensor p = packed_buffer(a[3], N, K, bits, dev);
     const Tensor d = out(a[4], {groups}, at::kFloat, dev, "delta"), q0 = out(a[5], {groups}, at::kFloat, dev, "q0");
     const Tensor rs = out(a[6], {N}, at::kInt, dev, "rs_w");
-    check(qb_quantize_groupwise_asym(ptr<float>(W), N, K, bits, groups, p.data_ptr(), ptr<float>(d), ptr<float>(q0),
-                                     ptr<int32_t>(rs), stream()));
+    call(qb_quantize_groupwise_asym, ptr<float>(W), N, K, bits, groups, p.data_ptr(), ptr<float>(d), ptr<float>(q0),
+                                     ptr<int32_t>(rs), stream());
     return tuple({p, d, q0, rs});
 }
 
@@ -220,8 +243,8 @@ QB_CALL(quantize_groupwise_asym_range, 8)  // W, bits, lo, hi, packed, delta, q0
     const Tensor p = packed_buffer(a[4], N, K, bits, dev);
     const Tensor d = out(a[5], {G}, at::kFloat, dev, "delta"), q0 = out(a[6], {G}, at::kFloat, dev, "q0");
     const Tensor rs = out(a[7], {N}, at::kInt, dev, "rs_w");
-    check(qb_quantize_groupwise_asym_range(ptr<float>(W), N, K, bits, static_cast<int>(G), ptr<float>(lo), ptr<float>(hi),
-                                           p.data_ptr(), ptr<float>(d), ptr<float>(q0), ptr<int32_t>(rs), stream()));
+    call(qb_quantize_groupwise_asym_range, ptr<float>(W), N, K, bits, static_cast<int>(G), ptr<float>(lo), ptr<float>(hi),
+                                           p.data_ptr(), ptr<float>(d), ptr<float>(q0), ptr<int32_t>(rs), stream());
     return tuple({p, d, q0, rs});
 }
 
@@ -236,21 +259,29 @@ PyObject *key(const char *name)  // interned once per name: `name` is a literal 
 
 struct Jobs {
     PyObject *seq;
-    explicit Jobs(PyObject *o) : seq(PySequence_Fast(o, "jobs must be a sequence"))
+    std::vector<PyObject *> held;  // the entries read, until the call has returned: it runs without the interpreter lock
+    explicit Jobs(PyObject *o) : seq(PySequence_Tuple(o))
     {
         if (!seq) throw_python_error();
     }
-    ~Jobs() { Py_DECREF(seq); }
+    ~Jobs()
+    {
+        for (PyObject *v : held) Py_DECREF(v);
+        Py_DECREF(seq);
+    }
     Jobs(const Jobs &) = delete;
     Jobs &operator=(const Jobs &) = delete;
-    Py_ssize_t size() const { return PySequence_Fast_GET_SIZE(seq); }
-    // borrowed; None where an optional entry is absent
-    PyObject *get(Py_ssize_t i, PyObject *k, bool required) const
+    Py_ssize_t size() const { return PyTuple_GET_SIZE(seq); }
+    // held by this object; None where an optional entry is absent
+    PyObject *get(Py_ssize_t i, PyObject *k, bool required)
     {
-        PyObject *d = PySequence_Fast_GET_ITEM(seq, i);
+        PyObject *d = PyTuple_GET_ITEM(seq, i);
         if (!PyDict_Check(d)) raise(PyExc_TypeError, "a job must be a dict");
         PyObject *v = PyDict_GetItemWithError(d, k);
-        if (v) return v;
+        if (v) {
+            held.push_back(Py_NewRef(v));
+            return v;
+        }
         if (!PyErr_Occurred() && required) PyErr_SetObject(PyExc_KeyError, k);
         if (PyErr_Occurred()) throw_python_error();
         return Py_None;
@@ -268,7 +299,7 @@ QB_CALL(quantize_groupwise_batched, 1)
 {
     static PyObject *const kW = key("W"), *const kBits = key("bits"), *const kGroups = key("groups"), *const kPacked = key("packed"),
                     *const kH = key("h"), *const kM = key("m"), *const kRs = key("rs_w");
-    const Jobs jobs(a[0]);
+    Jobs jobs(a[0]);
     const Py_ssize_t n = jobs.size();
     std::vector<qb_quant_job> arr(n);
     THPObjectPtr outs(new_list(n));
@@ -284,14 +315,14 @@ QB_CALL(quantize_groupwise_batched, 1)
         arr[i] = qb_quant_job{ptr<float>(W), N, K, bits, groups, p.data_ptr(), ptr<float>(h), ptr<float>(m), ptr<int32_t>(rs)};
         PyList_SET_ITEM(outs.get(), i, tuple({p, h, m, rs}));
     }
-    check(qb_quantize_groupwise_batched(arr.data(), static_cast<int>(n), stream()));
+    call(qb_quantize_groupwise_batched, arr.data(), static_cast<int>(n), stream());
     return outs.release();
 }
 
 QB_CALL(quantize_act_batched, 1)
 {
     static PyObject *const kX = key("X"), *const kClip = key("clip"), *const kXq = key("Xq"), *const kRs = key("rs_x");
-    const Jobs jobs(a[0]);
+    Jobs jobs(a[0]);
     const Py_ssize_t n = jobs.size();
     std::vector<qb_act_job> arr(n);
     THPObjectPtr outs(new_list(n));
@@ -304,7 +335,7 @@ QB_CALL(quantize_act_batched, 1)
         arr[i] = qb_act_job{ptr<float>(X), T, K, static_cast<float>(real(jobs.get(i, kClip, true))), ptr<int8_t>(Xq), ptr<int32_t>(rs)};
         PyList_SET_ITEM(outs.get(), i, tuple({Xq, rs}));
     }
-    check(qb_quantize_act_batched(arr.data(), static_cast<int>(n), stream()));
+    call(qb_quantize_act_batched, arr.data(), static_cast<int>(n), stream());
     return outs.release();
 }
 
@@ -313,7 +344,7 @@ QB_CALL(qlinear_fwd_batched, 1)
     static PyObject *const kXq = key("Xq"), *const kRs = key("rs_x"), *const kClip = key("clip"), *const kPacked = key("packed"),
                     *const kH = key("h"), *const kRw = key("rs_w"), *const kBits = key("bits"), *const kGroups = key("groups"),
                     *const kN = key("N"), *const kBias = key("bias"), *const kY = key("Y");
-    const Jobs jobs(a[0]);
+    Jobs jobs(a[0]);
     const Py_ssize_t n = jobs.size();
     std::vector<qb_fwd_job> arr(n);
     THPObjectPtr outs(new_list(n));
@@ -331,7 +362,7 @@ QB_CALL(qlinear_fwd_batched, 1)
         if (!v) throw_python_error();
         PyList_SET_ITEM(outs.get(), i, v);
     }
-    check(qb_qlinear_fwd_batched(arr.data(), static_cast<int>(n), stream()));
+    call(qb_qlinear_fwd_batched, arr.data(), static_cast<int>(n), stream());
     return outs.release();
 }
 
@@ -342,7 +373,7 @@ QB_CALL(quantize_act, 4)  // X, clip, Xq, rs_x
     const Tensor &X = matrix(a[0], at::kFloat, "X");
     const int64_t T = X.size(0), K = X.size(1);
     const Tensor Xq = out(a[2], {T, K}, at::kChar, X.device(), "Xq"), rs = out(a[3], {T}, at::kInt, X.device(), "rs_x");
-    check(qb_quantize_act(ptr<float>(X), T, K, static_cast<float>(real(a[1])), ptr<int8_t>(Xq), ptr<int32_t>(rs), stream()));
+    call(qb_quantize_act, ptr<float>(X), T, K, static_cast<float>(real(a[1])), ptr<int8_t>(Xq), ptr<int32_t>(rs), stream());
     return tuple({Xq, rs});
 }
 
@@ -353,7 +384,7 @@ QB_CALL(quantize_act_dyn, 4)  // X, Xq, rs_x, hx_rows
     const at::Device dev = X.device();
     const Tensor Xq = out(a[1], {T, K}, at::kChar, dev, "Xq"), rs = out(a[2], {T}, at::kInt, dev, "rs_x");
     const Tensor hx = out(a[3], {T}, at::kFloat, dev, "hx_rows");
-    check(qb_quantize_act_dyn(ptr<float>(X), T, K, ptr<int8_t>(Xq), ptr<int32_t>(rs), ptr<float>(hx), stream()));
+    call(qb_quantize_act_dyn, ptr<float>(X), T, K, ptr<int8_t>(Xq), ptr<int32_t>(rs), ptr<float>(hx), stream());
     return tuple({Xq, rs, hx});
 }
 
@@ -364,7 +395,7 @@ QB_CALL(quantize_act_dyn_tensor, 5)  // X, Xq, rs_x, hx_rows, c
     const at::Device dev = X.device();
     const Tensor Xq = out(a[1], {T, K}, at::kChar, dev, "Xq"), rs = out(a[2], {T}, at::kInt, dev, "rs_x");
     const Tensor hx = out(a[3], {T}, at::kFloat, dev, "hx_rows"), c = out(a[4], {1}, at::kFloat, dev, "c");
-    check(qb_quantize_act_dyn_tensor(ptr<float>(X), T, K, ptr<int8_t>(Xq), ptr<int32_t>(rs), ptr<float>(hx), ptr<float>(c), stream()));
+    call(qb_quantize_act_dyn_tensor, ptr<float>(X), T, K, ptr<int8_t>(Xq), ptr<int32_t>(rs), ptr<float>(hx), ptr<float>(c), stream());
     return tuple({Xq, rs, hx, c});
 }
 
@@ -395,9 +426,9 @@ QB_CALL(qlinear_fwd, 13)  // Xq, rs_x, clip, packed, h, rs_w, bits, groups, N, b
     const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[8]);
     const Tensor Y = out(a[10], {T, N}, at::kFloat, Xq.device(), "Y");
     const Tensor A4 = debug_output(a[11], a[12], T, N, Xq.device());
-    check(qb_qlinear_fwd(ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
+    call(qb_qlinear_fwd, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
                          ptr<float>(a[4], "h"), ptr<int32_t>(a[5], "rs_w"), small(a[6]), small(a[7]), T, N, K,
-                         ptr<float>(a[9], "bias"), ptr<float>(Y), debug_ptr(A4), stream()));
+                         ptr<float>(a[9], "bias"), ptr<float>(Y), debug_ptr(A4), stream());
     return forward_result(Y, A4);
 }
 
@@ -407,9 +438,9 @@ QB_CALL(qlinear_fwd_dyn, 12)  // Xq, rs_x, hx_rows, packed, h, rs_w, bits, group
     const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[8]);
     const Tensor Y = out(a[10], {T, N}, at::kFloat, Xq.device(), "Y");
     const Tensor A4 = debug_output(Py_None, a[11], T, N, Xq.device());
-    check(qb_qlinear_fwd_dyn(ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), ptr<float>(hx), ptr<void>(a[3], "packed"),
+    call(qb_qlinear_fwd_dyn, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), ptr<float>(hx), ptr<void>(a[3], "packed"),
                              ptr<float>(a[4], "h"), ptr<int32_t>(a[5], "rs_w"), small(a[6]), small(a[7]), T, N, K,
-                             ptr<float>(a[9], "bias"), ptr<float>(Y), debug_ptr(A4), stream()));
+                             ptr<float>(a[9], "bias"), ptr<float>(Y), debug_ptr(A4), stream());
     return forward_result(Y, A4);
 }
 
@@ -419,9 +450,9 @@ QB_CALL(qlinear_fwd_asym, 13)  // Xq, rs_x, clip, packed, delta, q0, rs_w, bits,
     const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[9]);
     const Tensor Y = out(a[11], {T, N}, at::kFloat, Xq.device(), "Y");
     const Tensor A4 = debug_output(Py_None, a[12], T, N, Xq.device());
-    check(qb_qlinear_fwd_asym(ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
+    call(qb_qlinear_fwd_asym, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
                               ptr<float>(d), ptr<float>(q0), ptr<int32_t>(a[6], "rs_w"), small(a[7]), small(a[8]), T, N, K,
-                              ptr<float>(a[10], "bias"), ptr<float>(Y), debug_ptr(A4), stream()));
+                              ptr<float>(a[10], "bias"), ptr<float>(Y), debug_ptr(A4), stream());
     return forward_result(Y, A4);
 }
 
@@ -432,9 +463,9 @@ QB_CALL(qlinear_fwd_asym_dyn, 13)  // Xq, rs_x, hx_rows, packed, delta, q0, rs_w
     const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[9]);
     const Tensor Y = out(a[11], {T, N}, at::kFloat, Xq.device(), "Y");
     const Tensor A4 = debug_output(Py_None, a[12], T, N, Xq.device());
-    check(qb_qlinear_fwd_asym_dyn(ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), ptr<float>(hx), ptr<void>(a[3], "packed"),
+    call(qb_qlinear_fwd_asym_dyn, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), ptr<float>(hx), ptr<void>(a[3], "packed"),
                                   ptr<float>(d), ptr<float>(q0), ptr<int32_t>(a[6], "rs_w"), small(a[7]), small(a[8]), T, N, K,
-                                  ptr<float>(a[10], "bias"), ptr<float>(Y), debug_ptr(A4), stream()));
+                                  ptr<float>(a[10], "bias"), ptr<float>(Y), debug_ptr(A4), stream());
     return forward_result(Y, A4);
 }
 
@@ -443,10 +474,10 @@ QB_CALL(qlinear_fwd_q8, 14)  // Xq, rs_x, clip, packed, h, rs_w, bits, groups, N
     const Tensor &Xq = matrix(a[0], at::kChar, "Xq");
     const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[8]);
     const Tensor Yq = out(a[12], {T, N}, at::kChar, Xq.device(), "Yq"), rs = out(a[13], {T}, at::kInt, Xq.device(), "rs_y");
-    check(qb_qlinear_fwd_q8(ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
+    call(qb_qlinear_fwd_q8, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
                             ptr<float>(a[4], "h"), ptr<int32_t>(a[5], "rs_w"), small(a[6]), small(a[7]), T, N, K,
                             ptr<float>(a[10], "bias"), small(a[11]), static_cast<float>(real(a[9])), ptr<int8_t>(Yq), ptr<int32_t>(rs),
-                            stream()));
+                            stream());
     return tuple({Yq, rs});
 }
 
@@ -485,18 +516,18 @@ QB_CALL(qlinear_bwd_ste, 12)  // dY, Xq, clip, packed, h, bits, groups, want_dx,
 {
     Bwd b(a[0], a[1]);
     b.outputs(a[7], a[8], a[9], a[10], a[11]);
-    check(qb_qlinear_bwd_ste(bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
+    call(qb_qlinear_bwd_ste, bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
                              ptr<float>(a[4], "h"), small(a[5]), small(a[6]), b.T, b.N, b.K, bits16(b.dX), b.dw_ptr(),
-                             b.workspace.data_ptr(), stream()));
+                             b.workspace.data_ptr(), stream());
     return tuple({b.dX, b.dW});
 }
 
 QB_CALL(qlinear_bwd_ste_static, 9)  // dY, Xq, clip, packed, h, bits, groups, dX, dW
 {
     const Bwd b(a[0], a[1]);
-    check(qb_qlinear_bwd_ste_static(bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
+    call(qb_qlinear_bwd_ste_static, bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
                                     ptr<float>(a[4], "h"), small(a[5]), small(a[6]), b.T, b.N, b.K, ptr<uint16_t>(a[7], "dX"),
-                                    ptr<float>(a[8], "dW"), stream()));
+                                    ptr<float>(a[8], "dW"), stream());
     return PyTuple_Pack(2, a[7], a[8]);
 }
 
@@ -515,10 +546,10 @@ QB_CALL(qlinear_bwd_ste_masked, 15)  // dY, Xq, clip, packed, h, bits, groups, X
     if (a[9] != Py_None && typed(a[9], at::kFloat, "m").numel() != groups)
         raise(PyExc_ValueError, "m must hold one range per group");
     b.outputs(a[10], a[11], a[12], a[13], a[14]);
-    check(qb_qlinear_bwd_ste_masked(bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
+    call(qb_qlinear_bwd_ste_masked, bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
                                     ptr<float>(a[4], "h"), small(a[5]), groups, b.T, b.N, b.K, ptr<float>(a[7], "X"),
                                     ptr<float>(a[8], "W"), ptr<float>(a[9], "m"), bits16(b.dX), b.dw_ptr(), b.workspace.data_ptr(),
-                                    stream()));
+                                    stream());
     return tuple({b.dX, b.dW});
 }
 
@@ -526,9 +557,9 @@ QB_CALL(qlinear_bwd_ste_asym, 13)  // dY, Xq, clip, packed, delta, q0, bits, gro
 {
     Bwd b(a[0], a[1]);
     b.outputs(a[8], a[9], a[10], a[11], a[12]);
-    check(qb_qlinear_bwd_ste_asym(bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
+    call(qb_qlinear_bwd_ste_asym, bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
                                   ptr<float>(a[4], "delta"), ptr<float>(a[5], "q0"), small(a[6]), small(a[7]), b.T, b.N, b.K,
-                                  bits16(b.dX), b.dw_ptr(), b.workspace.data_ptr(), stream()));
+                                  bits16(b.dX), b.dw_ptr(), b.workspace.data_ptr(), stream());
     return tuple({b.dX, b.dW});
 }
 
@@ -542,7 +573,7 @@ QB_CALL(embedding_quantize_bits, 6)  // E, bits, groups, codes, h, m
     const at::Device dev = E.device();
     const Tensor codes = out(a[3], {V, d * bits / 8}, at::kByte, dev, "codes");
     const Tensor h = out(a[4], {groups > 0 ? groups : 1}, at::kFloat, dev, "h"), m = out(a[5], {groups > 0 ? groups : 1}, at::kFloat, dev, "m");
-    check(qb_embedding_quantize_bits(ptr<float>(E), V, d, bits, groups, ptr<uint8_t>(codes), ptr<float>(h), ptr<float>(m), stream()));
+    call(qb_embedding_quantize_bits, ptr<float>(E), V, d, bits, groups, ptr<uint8_t>(codes), ptr<float>(h), ptr<float>(m), stream());
     return tuple({codes, h, m});
 }
 
@@ -552,8 +583,8 @@ QB_CALL(embedding_gather_bits, 6)  // codes, h, bits, groups, ids, out
     const int bits = small(a[2]), groups = small(a[3]);
     const int64_t V = codes.size(0), d = bits > 0 ? codes.size(1) * 8 / bits : 0, n = ids.dim() ? ids.size(0) : 0;
     const Tensor o = out(a[5], {n, d}, at::kFloat, codes.device(), "out");
-    check(qb_embedding_gather_bits(ptr<uint8_t>(codes), ptr<float>(a[1], "h"), V, d, bits, groups, ptr<int64_t>(ids), n, ptr<float>(o),
-                                   stream()));
+    call(qb_embedding_gather_bits, ptr<uint8_t>(codes), ptr<float>(a[1], "h"), V, d, bits, groups, ptr<int64_t>(ids), n, ptr<float>(o),
+                                   stream());
     PyObject *v = THPVariable_Wrap(o);
     if (!v) throw_python_error();
     return v;

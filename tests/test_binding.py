@@ -1,0 +1,64 @@
+"""The binding's native half: what it does with the interpreter lock, with numbers and with lists of jobs."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+import paper_1909_05840_amd.binding
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+UNLOCKED_CALLS = r'''
+import importlib.machinery, importlib.util, sys, ctypes
+import torch
+from paper_1909_05840_amd import binding as qb
+stub, native = sys.argv[1:]
+marks = ctypes.CDLL(stub)
+loader = importlib.machinery.ExtensionFileLoader("_calls", native)
+qb._calls = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_calls", native, loader=loader))
+loader.exec_module(qb._calls)
+qb._calls.set_error(qb.QBError)
+def t(*shape, dtype=torch.float32):
+    return torch.zeros(*shape, dtype=dtype, device="cuda")
+x, g, i32 = t(64, 64), t(1), t(64, dtype=torch.int32)
+q, p, dy, ids = t(64, 64, dtype=torch.int8), t(64, 64, dtype=torch.uint8), t(64, 64, dtype=torch.bfloat16), t(4, dtype=torch.int64)
+f = (q, i32, 6.0, p, g, i32, 8, 1, 64)
+calls = [
+    lambda: qb.qb_quantize_groupwise(x, 8, 1), lambda: qb.qb_quantize_groupwise_clip(x, 8, g),
+    lambda: qb.qb_quantize_groupwise_asym(x, 8, 1), lambda: qb.qb_quantize_groupwise_asym_range(x, 8, g, g),
+    lambda: qb.qb_quantize_groupwise_batched([{"W": x, "bits": 8, "groups": 1}]), lambda: qb.qb_quantize_act(x, 6.0),
+    lambda: qb.qb_quantize_act_batched([{"X": x, "clip": 6.0}]), lambda: qb.qb_quantize_act_dyn(x), lambda: qb.qb_quantize_act_dyn_tensor(x),
+    lambda: qb.qb_qlinear_fwd(*f), lambda: qb.qb_qlinear_fwd_dyn(q, i32, g, p, g, i32, 8, 1, 64),
+    lambda: qb.qb_qlinear_fwd_asym(q, i32, 6.0, p, g, g, i32, 8, 1, 64), lambda: qb.qb_qlinear_fwd_asym_dyn(q, i32, g, p, g, g, i32, 8, 1, 64),
+    lambda: qb.qb_qlinear_fwd_batched([dict(zip(("Xq", "rs_x", "clip", "packed", "h", "rs_w", "bits", "groups", "N"), f))]),
+    lambda: qb.qb_qlinear_fwd_q8(*f, 6.0), lambda: qb.qb_qlinear_bwd_ste(dy, q, 6.0, p, g, 8, 1),
+    lambda: qb.qb_qlinear_bwd_ste_static(dy, q, 6.0, p, g, 8, 1), lambda: qb.qb_qlinear_bwd_ste_masked(dy, q, 6.0, p, g, 8, 1),
+    lambda: qb.qb_qlinear_bwd_ste_asym(dy, q, 6.0, p, g, g, 8, 1), lambda: qb.qb_embedding_quantize_bits(x, 8, 1),
+    lambda: qb.qb_embedding_gather_bits(p, g, 8, 1, ids)]
+for c in calls: c()
+print(len(calls), marks.qb_test_calls(), marks.qb_test_locked())
+'''
+
+
+@pytest.mark.gpu
+def test_library_is_called_without_the_interpreter_lock(qb, tmp_path):
+    """Every call of the binding gives up the interpreter lock around the C entry point, as a call through ctypes does.  The
+    binding's native half runs in a process of its own against a stand-in of the library that launches nothing and counts the
+    calls that come with the lock."""
+    names = [n for n in qb.EXPORTS if n not in ("qb_status_string", "qb_packed_nbytes", "qb_bwd_workspace_nbytes")]
+    source = tmp_path / "stub.c"
+    source.write_text("extern int PyGILState_Check(void);\nstatic int calls, locked;\nint qb_test_calls(void) { return calls; }\n"
+                      "int qb_test_locked(void) { return locked; }\nconst char *qb_status_string(int s) { return \"\"; }\n"
+                      "unsigned long qb_packed_nbytes() { return 4096; }\nunsigned long qb_bwd_workspace_nbytes() { return 4096; }\n"
+                      + "".join("int %s() { ++calls; locked += PyGILState_Check(); return 0; }\n" % n for n in names))
+    stub, native = str(tmp_path / "libqbert.so"), str(tmp_path / "_calls.so")   # (the native half looks for the library beside itself)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-w", str(source), "-o", stub], check=True)
+    shutil.copy(paper_1909_05840_amd.binding.CALLS_PATH, native)
+    print("calls without the interpreter lock", flush=True)
+    r = subprocess.run([sys.executable, "-c", UNLOCKED_CALLS, stub, native], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    made, seen, locked = map(int, r.stdout.split()[-3:])
+    assert made == seen > 0 and locked == 0
