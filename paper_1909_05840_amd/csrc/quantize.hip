@@ -794,13 +794,46 @@ __global__ __launch_bounds__(256) void embedding_quantize_kernel(const float *__
     }
 }
 
-// A thread keeps four columns and their scales and takes EMB_IDS rows of ids, all their code loads in flight, so that a
-// result costs one load, four conversions and products and a streaming 16-byte store.  (One thread per four results,
-// each with its own divisions by d and by the group width and its own loads of the scales: 47-48 us for 32768 ids of
-// 1024 columns; so 32 us = 5.0 TB/s, the card's copy rate being 5.2.)  min(d/4, 256) threads cover a row or 1024 columns of it, the
+// Gather, two forms.  Few results (latency: the id, the code, the store, one after the other): one thread per four results.
+// Many (memory): a thread keeps four columns and their scales and takes IDS rows of ids, all their code loads in flight, so
+// that a result costs one load, four conversions and products and a streaming 16-byte store, and the divisions by d and by
+// the group width and the loads of the scales come once.  min(d/4, 256) threads cover a row or 1024 columns of it, the
 // workgroup as many rows at once as it has threads for.
-constexpr int EMB_IDS = 8;
+// The second form starts at EMB_MANY results, 6144 wavefronts of the first, with four rows, and takes eight from EMB_MOST on.
+// Times in us, 8 bits, first form / four rows / eight rows:
+//   128 ids x 1024   2.7 / 3.4 / 4.3      1000 x 768   3.2 / 3.7 / 4.5      1000 x 1024   3.5 / 3.9 / 4.8     6000 x 256   4.1 / 4.2 / 5.0
+//   2000 x 1024   4.7 / 4.5 / 5.2      8000 x 256   4.7 / 4.5 / 5.2      24000 x 64   4.3 / 4.2 / 5.0      8000 x 1024   10.9 / 7.4 / 8.0
+//   32768 x 320   13.2 / 8.7 / 9.9     32768 x 1024   32.6 / 25.0 / 25.8; behind the kernels that write the table 47 / 33.3 / 32.0
+//   (5.0 TB/s, the card's copy rate being 5.2)
+constexpr int64_t EMB_MANY = 3 << 19, EMB_MOST = 1 << 24;
 template <int BITS>
+__global__ __launch_bounds__(256) void embedding_gather_few_kernel(const uint8_t *__restrict__ codes,
+                                                                   const float *__restrict__ h, int64_t V, int d,
+                                                                   int cols_per_group, const int64_t *__restrict__ ids,
+                                                                   int n_ids, float *__restrict__ out)
+{
+    constexpr int L = (1 << BITS) - 1;
+    const int d4 = d >> 2;
+    const int id = blockIdx.x * 256 + threadIdx.x;
+    const int i = id / d4;
+    if (i >= n_ids) return;
+    const int c = (id - i * d4) << 2;
+    const int64_t tok = ids[i];
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (tok >= 0 && tok < V) {  // (an id outside the table gives a row of zeros)
+        uint32_t q;
+        if constexpr (BITS == 8) q = *reinterpret_cast<const uint32_t *>(codes + tok * d + c);
+        else q = *reinterpret_cast<const uint16_t *>(codes + ((tok * d + c) >> 1));
+        auto value = [&](int e) { return h[(c + e) / cols_per_group] * (float)(2 * (int)((q >> (BITS * e)) & (uint32_t)L) - L); };
+        o.x = value(0);
+        o.y = value(1);
+        o.z = value(2);
+        o.w = value(3);
+    }
+    reinterpret_cast<float4 *>(out)[id] = o;
+}
+
+template <int BITS, int IDS>
 __global__ __launch_bounds__(256) void embedding_gather_kernel(const uint8_t *__restrict__ codes,
                                                                const float *__restrict__ h, int64_t V, int d,
                                                                int cols_per_group, const int64_t *__restrict__ ids,
@@ -816,16 +849,16 @@ __global__ __launch_bounds__(256) void embedding_gather_kernel(const uint8_t *__
     float hs[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) hs[e] = h[(c + e) / cols_per_group];
-    const int64_t i0 = (int64_t)blockIdx.x * (EMB_IDS * nsub) + sub;
-    int64_t tok[EMB_IDS];
+    const int64_t i0 = (int64_t)blockIdx.x * (IDS * nsub) + sub;
+    int64_t tok[IDS];
 #pragma unroll
-    for (int r = 0; r < EMB_IDS; ++r) {
+    for (int r = 0; r < IDS; ++r) {
         const int64_t i = i0 + r * nsub;
         tok[r] = i < n_ids ? ids[i] : -1;
     }
-    uint32_t q[EMB_IDS];
+    uint32_t q[IDS];
 #pragma unroll
-    for (int r = 0; r < EMB_IDS; ++r) {
+    for (int r = 0; r < IDS; ++r) {
         q[r] = 0;
         if (tok[r] >= 0 && tok[r] < V) {
             if constexpr (BITS == 8) q[r] = *reinterpret_cast<const uint32_t *>(codes + tok[r] * d + c);
@@ -833,7 +866,7 @@ __global__ __launch_bounds__(256) void embedding_gather_kernel(const uint8_t *__
         }
     }
 #pragma unroll
-    for (int r = 0; r < EMB_IDS; ++r) {
+    for (int r = 0; r < IDS; ++r) {
         const int64_t i = i0 + r * nsub;
         if (i >= n_ids) continue;
         v4f o = {0.f, 0.f, 0.f, 0.f};
@@ -843,6 +876,24 @@ __global__ __launch_bounds__(256) void embedding_gather_kernel(const uint8_t *__
         }
         __builtin_nontemporal_store(o, reinterpret_cast<v4f *>(out) + i * d4 + c4);
     }
+}
+
+template <int BITS>
+void launch_gather(const uint8_t *codes, const float *h, int64_t V, int d, int cols_per_group, const int64_t *ids, int n_ids, float *out,
+                   hipStream_t st)
+{
+    const int64_t d4 = d / 4, results = n_ids * (int64_t)d;
+    if (results < EMB_MANY) {
+        hipLaunchKernelGGL(embedding_gather_few_kernel<BITS>, dim3((unsigned)((n_ids * d4 + 255) / 256)), dim3(256), 0, st, codes, h, V, d,
+                           cols_per_group, ids, n_ids, out);
+        return;
+    }
+    const int64_t rows = (results < EMB_MOST ? 4 : 8) * (256 / (d4 < 256 ? d4 : 256));
+    const dim3 grid((unsigned)((n_ids + rows - 1) / rows), (unsigned)((d4 + 255) / 256));
+    if (results < EMB_MOST)
+        hipLaunchKernelGGL((embedding_gather_kernel<BITS, 4>), grid, dim3(256), 0, st, codes, h, V, d, cols_per_group, ids, n_ids, out);
+    else
+        hipLaunchKernelGGL((embedding_gather_kernel<BITS, 8>), grid, dim3(256), 0, st, codes, h, V, d, cols_per_group, ids, n_ids, out);
 }
 
 template <int BITS, int THREADS, bool ASYM = false>
@@ -1242,12 +1293,8 @@ extern "C" qb_status qb_embedding_gather_bits(const uint8_t *codes, const float 
     if (V <= 0 || !k_ok(d) || groups <= 0 || d % groups != 0 || n_ids < 0 || n_ids > (1 << 30)) return QB_ERR_SHAPE;
     if (n_ids == 0) return QB_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int64_t d4 = d / 4, rows = EMB_IDS * (256 / (d4 < 256 ? d4 : 256));
-    const dim3 grid((unsigned)((n_ids + rows - 1) / rows), (unsigned)((d4 + 255) / 256));
-    if (bits == 8)
-        hipLaunchKernelGGL(embedding_gather_kernel<8>, grid, dim3(256), 0, st, codes, h, V, (int)d, (int)(d / groups), ids, (int)n_ids, out);
-    else
-        hipLaunchKernelGGL(embedding_gather_kernel<4>, grid, dim3(256), 0, st, codes, h, V, (int)d, (int)(d / groups), ids, (int)n_ids, out);
+    if (bits == 8) launch_gather<8>(codes, h, V, (int)d, (int)(d / groups), ids, (int)n_ids, out, st);
+    else launch_gather<4>(codes, h, V, (int)d, (int)(d / groups), ids, (int)n_ids, out, st);
     return launch_status();
 }
 

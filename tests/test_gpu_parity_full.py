@@ -604,3 +604,25 @@ def test_forward_few_tokens_slices_of_the_contraction(qb, bits, shape):
     ref = hx64 * (dl * S + z * R)
     # four roundings, relative to the two terms that may cancel (2.4e-7; bound 1e-6)
     assert ((Ya.cpu().double() - ref).abs() <= 1e-6 * hx64 * (dl * S.abs() + z.abs() * R.abs())).all()
+
+
+# (d, ids): on both sides of the lines between the gather's forms (1572864 and 16777216 results), rows that end inside a workgroup's
+# share, columns that fill a workgroup's threads only in part (d / 4 = 80) and that take a second workgroup (d = 1088)
+@pytest.mark.parametrize("bits", (4, 8))
+@pytest.mark.parametrize("shape", [(64, 24575), (64, 24577), (320, 4915), (320, 4919), (768, 2047), (768, 2049), (1088, 1445), (1088, 1447), (1088, 15419), (1088, 15421)])
+def test_embedding_gather_around_its_dispatch(qb, bits, shape):
+    """Every value one rounded product of the scale and the code, bit for bit; ids outside the table give zeros."""
+    d, n = shape
+    V, groups = 1001, d // 16
+    say("embedding gather", shape, "bits", bits)
+    E = wl.embedding_table(V, d, seed=d + bits)
+    ids = wl.token_ids(n, V, seed=n)
+    ids[::97], ids[-1] = -1, V
+    codes, h, _ = qb.qb_embedding_quantize_bits(E.to(DEV), bits, groups)
+    out = torch.full((n, d), float("nan"), device=DEV)
+    qb.qb_embedding_gather_bits(codes, h, bits, groups, ids.to(DEV), out=out)
+    torch.cuda.synchronize()
+    oc, oh, _ = oracle.embedding_quantize(E.numpy(), groups, bits=bits)
+    inside = (ids >= 0) & (ids < V)
+    want = oracle.embedding_gather(oc, oh, torch.where(inside, ids, 0).numpy(), bits=bits).astype(np.float32) * inside.numpy()[:, None]
+    assert (out.cpu().numpy() == want).all()
