@@ -1769,12 +1769,20 @@ void launch_dma(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, co
                        Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, tiles_m, tiles_n);
 }
 
-// Which few-tile problems have their contraction sliced (tiles of 32 x 64): up to one workgroup per CU.  Kernel times in
-// us, sliced / stepped: 12 tiles, K = 768 3.7 / 4.3, K = 3072 4.8 / 7.5; 156 tiles, K = 3072 6.7 / 7.7 (4 bits), 7.4 / 8.1
-// (8 bits); 240 tiles, K = 3072 6.1 / 8.0; 224 tiles, K = 1792 5.7 / 6.4, K = 448 4.2 / 4.3; but 468 tiles of 8 bits, K = 768
-// 7.5 / 5.6 and 564 tiles, K = 3072 13.9 / 11.0 (the direct loads then wait for the L1s).  The same call repeated, all operands
-// in the L2: 48 tiles, K = 768 4.6 / 4.4; between other kernels, as a layer's calls come, 4.0 / 5.1.
-inline bool split_shape(long tiles) { return tiles <= 256; }
+// The stepped kernel's units of 64 features per step, and its steps.
+inline int stepped_units(int K) { return (K % 256 == 0 && K >= 2048) ? 4 : (K % 128 == 0) ? 2 : 1; }
+inline int stepped_steps(int K) { return K / (64 * stepped_units(K)); }
+
+// Which few-tile problems have their contraction sliced (tiles of 32 x 64): up to one workgroup per CU, and a contraction of
+// more than three steps of the other kernel (with fewer there is no latency to save, but the sum of the slices to pay), or
+// less than one tile of tokens, where the other kernel checks every element it writes.  Times in us behind the activation
+// quantizer that wrote the tokens, both kernels together, sliced / stepped, 4 bits:
+//   256 x 768, K = 128 6.2 / 5.4, 256 6.3 / 5.9, 384 6.5 / 6.4, 448 6.1 / 7.4, 512 6.5 / 6.8, 768 6.7 / 7.7, 1024 6.8 / 8.5
+//   16 x 1536, K = 256 5.8 / 6.2, 384 6.0 / 6.8;     24 x 768, K = 192 5.7 / 6.7
+// Alone, 156 tiles, K = 3072 6.7 / 7.7 (4 bits), 7.4 / 8.1 (8 bits); but 468 tiles of 8 bits, K = 768 7.5 / 5.6 and 564 tiles,
+// K = 3072 13.9 / 11.0 (the direct loads then wait for the L1s).
+inline bool sliced_pays(int T, int K) { return stepped_steps(K) > 3 || (T < 32 && K >= 192); }
+inline bool split_shape(long tiles, int T, int K) { return tiles <= 256 && sliced_pays(T, K); }
 
 // Which problems go to the 128 x 256 kernel with two independent workgroups per CU.  Its tiles are the largest, so it
 // needs two full rounds of the 512 resident workgroups (1024 tiles); with long contractions, whose tiles are started and
@@ -1816,9 +1824,9 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
         // at about 190 tiles).  Long contractions take 256 features per step.
         const SmallProblem sp{Xq, rs_x, packed, h, rs_w, bias, Y, A4, hx_rows, q0, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64};
         const int tiles = sp.tiles_m * sp.tiles_n;
-        if (split_shape(tiles)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sp);
-        else if (K % 256 == 0 && K >= 2048) launch_cfg<BITS, 1, 1, 1, 2, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
-        else if (K % 128 == 0) launch_cfg<BITS, 1, 1, 1, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
+        if (split_shape(tiles, T, K)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sp);
+        else if (stepped_units(K) == 4) launch_cfg<BITS, 1, 1, 1, 2, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
+        else if (stepped_units(K) == 2) launch_cfg<BITS, 1, 1, 1, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         else launch_cfg<BITS, 1, 1, 1, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         return;
     }
@@ -1958,9 +1966,23 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
     };
     const OutQ none{nullptr, nullptr, 1.0f, 0, nullptr, nullptr};
     auto few_tiles = [](const qb_fwd_job &j) { return (long)((j.T + 127) / 128) * ((j.N + 127) / 128) <= 160; };
-    long small_tiles = 0;  // of all few-tile jobs of the width together: they run side by side
+    // The few-tile jobs of the width run side by side: the sliced kernel by the rule of the single call for their sum, one
+    // of them being enough (the longest decides how long the launch takes).  A few workgroups more than CUs (every job's start
+    // at a multiple of 8) cost a second round, which only long contractions are worth: 16 jobs of four widths, sliced / stepped,
+    // 252 tiles in 264 workgroups, K up to 1024 (8 steps) 24.2 / 19.5 us, K up to 1792 (28 steps) 29.5 / 54.4.
+    long small_tiles = 0, small_wgs = 0;
+    int longest = 0;
+    bool sliced = false;
     for (int i = 0; i < n_jobs; ++i)
-        if (jobs[i].bits == BITS && few_tiles(jobs[i])) small_tiles += (long)((jobs[i].T + 31) / 32) * ((jobs[i].N + 63) / 64);
+        if (jobs[i].bits == BITS && few_tiles(jobs[i])) {
+            const long tiles = (long)((jobs[i].T + 31) / 32) * ((jobs[i].N + 63) / 64);
+            const int K = (int)jobs[i].K;
+            small_tiles += tiles;
+            small_wgs += (tiles + 7) & ~7l;
+            longest = stepped_steps(K) > longest ? stepped_steps(K) : longest;
+            sliced = sliced || sliced_pays((int)jobs[i].T, K);
+        }
+    sliced = sliced && small_tiles <= 256 && (small_wgs <= 256 || longest > 12);
     for (int i = 0; i < n_jobs; ++i) {
         const qb_fwd_job &j = jobs[i];
         if (j.bits != BITS) continue;
@@ -1977,8 +1999,8 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
         // workgroups per CU stay 3-5 % ahead)
         const bool use96 = 86 * rounds96 < 100 * rounds128 || (!few128 && j.N % 96 == 0 && tiles96 <= 1280);
         const bool use128 = !use96 && few128;
-        if (few_tiles(j)) {  // few tiles: one launch per kernel (the sliced one by the rule of the single call, for the sum)
-            const int c = split_shape(small_tiles) ? 3 : (j.K % 256 == 0 && j.K >= 2048) ? 2 : (j.K % 128 == 0) ? 1 : 0;
+        if (few_tiles(j)) {  // few tiles: one launch per kernel
+            const int units = stepped_units((int)j.K), c = sliced ? 3 : units == 4 ? 2 : units == 2 ? 1 : 0;
             SmallGroup &sg = small[c];
             if (sg.n == QB_MAX_BATCH) flush_small(c);
             if (sg.n == 0) sg.first_wg[0] = 0;

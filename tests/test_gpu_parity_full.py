@@ -626,3 +626,67 @@ def test_embedding_gather_around_its_dispatch(qb, bits, shape):
     inside = (ids >= 0) & (ids < V)
     want = oracle.embedding_gather(oc, oh, torch.where(inside, ids, 0).numpy(), bits=bits).astype(np.float32) * inside.numpy()[:, None]
     assert (out.cpu().numpy() == want).all()
+
+
+def within_roundings(Y, Yo, bias=None):
+    """Y against A4 times the scale in 64 bits: three roundings of the product (1.8e-7, bound 1e-6) and the one of the sum with
+    the bias."""
+    b = 0.0 if bias is None else bias.cpu().numpy().astype(np.float64)[None, :]
+    extra = 0.0 if bias is None else 2.0 ** -23 * np.abs(Yo + b)
+    return (np.abs(Y.cpu().numpy().astype(np.float64) - (Yo + b)) <= 1e-6 * np.abs(Yo) + extra).all()
+
+
+# (T, N, K): on both sides of the rule between the sliced and the stepped kernel (three steps of the latter: K = 192, 256 and
+# 384 against 320 and 512; less than a tile of tokens), and more tiles than CUs for each of the stepped kernel's widths (64, 128
+# and 256 features per step), token and neuron counts that end inside a tile
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("shape", [(31, 66, 192), (32, 66, 192), (31, 130, 256), (33, 130, 256), (40, 70, 384), (40, 70, 320), (65, 100, 512),
+                                   (1001, 770, 192), (1001, 770, 768), (1001, 770, 3072)])
+def test_forward_few_tile_kernels(qb, bits, shape):
+    """A4 exact, Y within the bound; static and per-token scales, symmetric and asymmetric ranges."""
+    T, N, K = shape
+    groups = N // 2
+    say("fwd few tiles", shape, "bits", bits)
+    d = quantized_inputs(qb, N, K, T, bits, seed=5 * N + K + bits, groups=groups)
+    bias = wl.activation(1, N, seed=3)[0].contiguous().to(DEV)
+    args = (d["packed"], d["h"], d["rs_w"], bits, groups, N)
+    Y, A4 = qb.qb_qlinear_fwd(d["Xq"], d["rs_x"], CLIP, *args, bias=bias, want_a4=True)
+    hx = torch.full((T,), float(np.float32(CLIP) / np.float32(255)), device=DEV)  # (one rounded division, as the static call)
+    Yd = qb.qb_qlinear_fwd_dyn(d["Xq"], d["rs_x"], hx, *args, bias=bias)
+    asym = qb.qb_quantize_groupwise_asym(d["W"].to(DEV), bits, groups)
+    Ya = qb.qb_qlinear_fwd_asym(d["Xq"], d["rs_x"], CLIP, *asym, bits, groups, N)
+    Yad = qb.qb_qlinear_fwd_asym_dyn(d["Xq"], d["rs_x"], hx, *asym, bits, groups, N)
+    ua = qb.qb_unpack_codes(asym[0], N, K, bits).cpu().double()
+    torch.cuda.synchronize()
+    Yo, A4o, _ = oracle.qlinear_fwd(d["oq"], CLIP, d["oc"], d["oh"], bits, openmp=True)
+    assert (A4.cpu().numpy() == A4o).all()
+    assert within_roundings(Y, Yo, bias) and torch.equal(Y, Yd) and torch.equal(Ya, Yad)
+    x2 = 2 * torch.from_numpy(d["oq"]).double() + 1
+    S, R = x2 @ ua.T, x2.sum(1, keepdim=True)
+    dl, z = (t.cpu().double().repeat_interleave(2) for t in asym[1:3])
+    # four roundings, relative to the two terms that may cancel (2.4e-7; bound 1e-6)
+    assert ((Ya.cpu().double() - CLIP / 255.0 * (dl * S + z * R)).abs() <= 1e-6 * CLIP / 255.0 * (dl * S.abs() + z.abs() * R.abs())).all()
+
+
+# lists of few-tile jobs of one width.  short: three steps of the stepped kernel at most, 18 jobs each of 64 and of 128 features per
+# step (a launch takes 16); many: more tiles than CUs, all three step widths; sliced: 18 jobs; second round: 252 tiles in 264
+# workgroups with a contraction of 28 steps
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("shapes", [[(33, 130, 192), (64, 96, 256), (40, 66, 64), (100, 70, 384)] * 9,
+                                    [(333, 514, 192), (333, 514, 768), (333, 514, 3072)],
+                                    [(7, 70, 192), (33, 66, 320), (33, 64, 1024)] * 6,
+                                    [(128, 1344, 448), (100, 448, 448), (128, 1790, 448), (128, 448, 1792)]], ids=("short", "many", "sliced", "second_round"))
+def test_forward_batched_few_tile_kernels(qb, bits, shapes):
+    say("fwd batched, few tiles:", shapes[:4], len(shapes), "bits", bits)
+    jobs, refs = [], []
+    for i, (T, N, K) in enumerate(shapes):
+        d = quantized_inputs(qb, N, K, T, bits, seed=11 * N + K + T + 7 * i, groups=N // 2)
+        bias = wl.activation(1, N, seed=i)[0].contiguous().to(DEV) if i % 2 else None
+        jobs.append(dict(Xq=d["Xq"], rs_x=d["rs_x"], clip=CLIP, packed=d["packed"], h=d["h"], rs_w=d["rs_w"], bits=bits, groups=N // 2, N=N,
+                         bias=bias, Y=torch.full((T, N), float("nan"), device=DEV)))
+        refs.append((d, bias))
+    Ys = qb.qb_qlinear_fwd_batched(jobs)
+    torch.cuda.synchronize()
+    for Y, (d, bias) in zip(Ys, refs):
+        Yo, _, _ = oracle.qlinear_fwd(d["oq"], CLIP, d["oc"], d["oh"], bits, openmp=True)
+        assert within_roundings(Y, Yo, bias)
