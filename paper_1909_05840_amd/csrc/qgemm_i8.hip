@@ -287,16 +287,16 @@ struct SmallProblem {
     const int32_t *rs_w;
     const float *bias;
     float *Y;
-    int32_t *A4out;
-    const float *hx_rows;  // one activation scale per token (dynamic range) instead of hx, or null
-    const float *q0;       // asymmetric group ranges: h holds Delta and q0 the lower end of every group, or null
     int T, N, K, rows_per_group;
     float hx;
     int tiles_m, tiles_n;
 };
 
+// A4out: the debug output, or null; hx_rows: one activation scale per token (dynamic range) instead of hx, or null; q0: asymmetric
+// group ranges (h holds Delta and q0 the lower end of every group), or null
 template <int BITS>
-__device__ __forceinline__ void qgemm_i8_split_body(const SmallProblem &p, const int bid)
+__device__ __forceinline__ void qgemm_i8_split_body(const SmallProblem &p, int32_t *__restrict__ A4out, const float *__restrict__ hx_rows,
+                                                    const float *__restrict__ q0, const int bid)
 {
     constexpr int KS = 8, SLOT = 4 * BITS, U = 2;  // units in flight, besides as many being multiplied
     __shared__ __align__(16) int4 red[KS * 2 * 4 * 64];
@@ -379,7 +379,7 @@ __device__ __forceinline__ void qgemm_i8_split_body(const SmallProblem &p, const
     const int n = tile_n * 64 + wn * 32 + l32, nn = n < N ? n : N - 1;
     const int coln = 2 * p.rs_w[nn] + K;
     const float hg = p.h[nn / p.rows_per_group];
-    const float zn = p.q0 ? p.q0[nn / p.rows_per_group] : 0.0f;
+    const float zn = q0 ? q0[nn / p.rows_per_group] : 0.0f;
     const float bv = p.bias ? p.bias[nn] : 0.0f;
     int rx[4];
     float hr[4];
@@ -387,7 +387,7 @@ __device__ __forceinline__ void qgemm_i8_split_body(const SmallProblem &p, const
     for (int r = 0; r < 4; ++r) {
         const int tt = tl + r < T ? tl + r : T - 1;
         rx[r] = p.rs_x[tt];
-        hr[r] = p.hx_rows ? p.hx_rows[tt] : p.hx;
+        hr[r] = hx_rows ? hx_rows[tt] : p.hx;
     }
 
     for (int u = u0; u < u1; u += 2 * U) {
@@ -416,21 +416,23 @@ __device__ __forceinline__ void qgemm_i8_split_body(const SmallProblem &p, const
         if (tt >= T) break;
         const int a4 = qb_a4(sums[r], E2 * rx[r] + coln);
         const size_t at = (size_t)tt * N + n;
-        if (p.q0) p.Y[at] = asym_value(a4, rx[r] + (K >> 1), L, hr[r], hg, zn) + bv;
+        if (q0) p.Y[at] = asym_value(a4, rx[r] + (K >> 1), L, hr[r], hg, zn) + bv;
         else p.Y[at] = (hr[r] * hg) * (float)a4 + bv;
-        if (p.A4out) p.A4out[at] = a4;
+        if (A4out) A4out[at] = a4;
     }
 }
 
 template <int BITS>
-__global__ __launch_bounds__(512) void qgemm_i8_split_kernel(const SmallProblem p)
+__global__ __launch_bounds__(512) void qgemm_i8_split_kernel(const SmallProblem p, int32_t *__restrict__ A4out,
+                                                             const float *__restrict__ hx_rows, const float *__restrict__ q0)
 {
-    qgemm_i8_split_body<BITS>(p, blockIdx.x);
+    qgemm_i8_split_body<BITS>(p, A4out, hx_rows, q0, blockIdx.x);
 }
 
 // Several few-tile problems (small token counts: the inference regime, where a launch costs more than its work) in one
 // launch: workgroup w serves tile w - first_wg[j] of problem j; a problem's workgroups start at
-// a multiple of 8, so that its tiles keep their XCD (the fill-up workgroups leave at once).
+// a multiple of 8, so that its tiles keep their XCD (the fill-up workgroups leave at once).  (The list is a kernel argument
+// of 1.5 KB; 24 bytes more per problem cost 0.2 us a launch.)
 struct SmallGroup {
     int n;
     int first_wg[QB_MAX_BATCH + 1];
@@ -455,7 +457,7 @@ __global__ __launch_bounds__(512) void qgemm_i8_split_group_kernel(const SmallGr
     while (j + 1 < g.n && (int)blockIdx.x >= g.first_wg[j + 1]) ++j;
     const int local = blockIdx.x - g.first_wg[j];
     if (local >= g.p[j].tiles_m * g.p[j].tiles_n) return;  // (uniform over the workgroup)
-    qgemm_i8_split_body<BITS>(g.p[j], local);
+    qgemm_i8_split_body<BITS>(g.p[j], nullptr, nullptr, nullptr, local);
 }
 
 // global -> LDS copies by the load unit: the global address of a lane is a wavefront-uniform base (in SGPRs) plus
@@ -1822,9 +1824,9 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
         // and pay ~6.5 us at least; 32x64 tiles of the register-staged kernel spread the work over the chip
         // (measured 4.4-5 us against 8 at T <= 1024, N = 768; 6.8 against 8.4 at 1024 x 2304 x 768; equal
         // at about 190 tiles).  Long contractions take 256 features per step.
-        const SmallProblem sp{Xq, rs_x, packed, h, rs_w, bias, Y, A4, hx_rows, q0, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64};
+        const SmallProblem sp{Xq, rs_x, packed, h, rs_w, bias, Y, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64};
         const int tiles = sp.tiles_m * sp.tiles_n;
-        if (split_shape(tiles, T, K)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sp);
+        if (split_shape(tiles, T, K)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sp, A4, hx_rows, q0);
         else if (stepped_units(K) == 4) launch_cfg<BITS, 1, 1, 1, 2, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         else if (stepped_units(K) == 2) launch_cfg<BITS, 1, 1, 1, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         else launch_cfg<BITS, 1, 1, 1, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
@@ -2006,7 +2008,7 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
             if (sg.n == 0) sg.first_wg[0] = 0;
             SmallProblem &sp = sg.p[sg.n];
             sp.Xq = j.Xq; sp.rs_x = j.rs_x; sp.packed = static_cast<const uint8_t *>(j.packed); sp.h = j.h; sp.rs_w = j.rs_w;
-            sp.bias = j.bias; sp.Y = j.Y; sp.A4out = nullptr; sp.hx_rows = nullptr; sp.q0 = nullptr; sp.T = (int)j.T; sp.N = (int)j.N; sp.K = (int)j.K;
+            sp.bias = j.bias; sp.Y = j.Y; sp.T = (int)j.T; sp.N = (int)j.N; sp.K = (int)j.K;
             sp.rows_per_group = (int)(j.N / j.groups); sp.hx = j.clip / 255.0f;
             sp.tiles_m = (int)((j.T + 31) / 32); sp.tiles_n = (int)((j.N + 63) / 64);
             sg.first_wg[sg.n + 1] = sg.first_wg[sg.n] + ((sp.tiles_m * sp.tiles_n + 7) & ~7);
