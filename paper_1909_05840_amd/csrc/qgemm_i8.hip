@@ -460,46 +460,26 @@ __global__ __launch_bounds__(512) void qgemm_i8_split_group_kernel(const SmallGr
     qgemm_i8_split_body<BITS>(g.p[j], nullptr, nullptr, nullptr, local);
 }
 
-// global -> LDS copies by the load unit: the global address of a lane is a wavefront-uniform base (in SGPRs) plus
-// the lane's 32-bit byte offset, the data of lane l lands at LDS address m0 + 16*l (also for the 12-byte form).
+// global -> LDS copy by the load unit: the global address of a lane is a wavefront-uniform base (in SGPRs) plus
+// the lane's 32-bit byte offset, the data of lane l lands at LDS address m0 + BYTES*l (16*l also for the 12-byte form).
 // Written as inline assembly on purpose: the compiler then keeps no book on these copies, and the kernel states
 // itself, with wait_vmcnt, which of them must have landed before a barrier.  The compiler may have written the base with
 // a VALU instruction (v_readlane of a spilled value, v_readfirstlane) right in front, which a vector memory instruction may
-// read five wait states later only; it counts them for its own instructions, not into an asm block.  Hence the s_nop 3 (with
-// the s_mov five states) in front of a block's first copy; the others of the block come later still, and nothing that the
-// compiler emits can get between them.  (The 8-bit feed-forward pair at 4096 tokens: 55.7 us, with the longer
-// wait in front of every copy 56.2, in front of none 55.6; the four widths of a layer in batched calls 226.1 and 225.5.)
-#define QB_COPY_FIRST(W, o, d) "s_mov_b32 m0, %" d "\n\ts_nop 3\n\tglobal_load_lds_dword" W " %" o ", %0"
-#define QB_COPY_NEXT(W, o, d) "\n\ts_mov_b32 m0, %" d "\n\ts_nop 0\n\tglobal_load_lds_dword" W " %" o ", %0"
-#define QB_COPY_BLOCK(W)                                                                                                        \
-    if constexpr (LEFT >= 4)                                                                                                    \
-        asm volatile(QB_COPY_FIRST(W, "1", "2") QB_COPY_NEXT(W, "3", "4") QB_COPY_NEXT(W, "5", "6") QB_COPY_NEXT(W, "7", "8")   \
-                     ::"s"(base), "v"(off[I]), "s"(dst[I]), "v"(off[I + 1]), "s"(dst[I + 1]), "v"(off[I + 2]), "s"(dst[I + 2]), \
-                     "v"(off[I + 3]), "s"(dst[I + 3]) : "memory", "m0");                                                        \
-    else if constexpr (LEFT == 3)                                                                                               \
-        asm volatile(QB_COPY_FIRST(W, "1", "2") QB_COPY_NEXT(W, "3", "4") QB_COPY_NEXT(W, "5", "6")                             \
-                     ::"s"(base), "v"(off[I]), "s"(dst[I]), "v"(off[I + 1]), "s"(dst[I + 1]), "v"(off[I + 2]), "s"(dst[I + 2])  \
-                     : "memory", "m0");                                                                                         \
-    else if constexpr (LEFT == 2)                                                                                               \
-        asm volatile(QB_COPY_FIRST(W, "1", "2") QB_COPY_NEXT(W, "3", "4")                                                       \
-                     ::"s"(base), "v"(off[I]), "s"(dst[I]), "v"(off[I + 1]), "s"(dst[I + 1]) : "memory", "m0");                 \
-    else                                                                                                                        \
-        asm volatile(QB_COPY_FIRST(W, "1", "2") ::"s"(base), "v"(off[I]), "s"(dst[I]) : "memory", "m0");
-// N copies of BYTES (12 or 16) bytes a lane from one base, four to a block: copy i from base + off[i] to LDS address dst[i]
-template <int BYTES, int N, int I = 0>
-__device__ __forceinline__ void copies_to_lds(const void *base, const uint32_t (&off)[N], const uint32_t (&dst)[N])
+// read five wait states later only; it counts them for its own instructions, not into an asm block.  So the block moves the
+// base into registers of its own: a scalar instruction may read what a VALU instruction wrote at any time, the copy what a
+// scalar one wrote; and the move is the wait state that m0 asks for in front of the copy.  (The
+// kernel below at 2 bits, 16384 x 2304 x 768: 41.2 us, with five wait states in front of every copy 41.8, with one 40.6.)
+template <int BYTES>
+__device__ __forceinline__ void copy_to_lds(const void *base, uint32_t off, uint32_t lds_addr)
 {
-    constexpr int LEFT = N - I;
-    if constexpr (BYTES == 12) { QB_COPY_BLOCK("x3") } else { QB_COPY_BLOCK("x4") }
-    if constexpr (LEFT > 4) copies_to_lds<BYTES, N, I + 4>(base, off, dst);
-}
-#undef QB_COPY_BLOCK
-#undef QB_COPY_NEXT
-#undef QB_COPY_FIRST
-
-__device__ __forceinline__ void copy4_to_lds(const void *base, uint32_t off, uint32_t lds_addr)  // lane l lands at m0 + 4*l
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dword %1, %0" ::"s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+    static_assert(BYTES == 4 || BYTES == 12 || BYTES == 16, "");
+    const void *own;
+    if constexpr (BYTES == 16)
+        asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %1\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(own) : "s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+    else if constexpr (BYTES == 12)
+        asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %1\n\tglobal_load_lds_dwordx3 %2, %0" : "=&s"(own) : "s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %1\n\tglobal_load_lds_dword %2, %0" : "=&s"(own) : "s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
 }
 
 template <int BITS> struct SlotRead;  // one lane's slot (32 codes) out of LDS
@@ -646,11 +626,10 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_i8_dma_kernel(
 #define QB_FETCH(step, stage)                                                                             \
     {                                                                                                     \
         const uint32_t st_ = lds_base + (stage) * STAGE_BYTES;                                            \
-        uint32_t bd_[B_DMA], ad_[A_DMA];                                                                  \
-        _Pragma("unroll") for (int i = 0; i < B_DMA; ++i) bd_[i] = st_ + A_BYTES + b_ldst[i];             \
-        _Pragma("unroll") for (int i = 0; i < A_DMA; ++i) ad_[i] = st_ + (i * NW + wave) * 1024;          \
-        copies_to_lds<CH>(b_base + (size_t)(step) * PAIR, b_off, bd_);                                    \
-        copies_to_lds<16>(a_base + (size_t)(step) * BK, a_off, ad_);                                      \
+        _Pragma("unroll") for (int i = 0; i < B_DMA; ++i)                                                 \
+            copy_to_lds<CH>(b_base + (size_t)(step) * PAIR, b_off[i], st_ + A_BYTES + b_ldst[i]);         \
+        _Pragma("unroll") for (int i = 0; i < A_DMA; ++i)                                                 \
+            copy_to_lds<16>(a_base + (size_t)(step) * BK, a_off[i], st_ + (i * NW + wave) * 1024);        \
     }
 #define QB_MMA(stage)                                                                                     \
     {                                                                                                     \
@@ -1141,13 +1120,10 @@ __global__ __launch_bounds__(64 * (WM * WN + NPROD), (SIMD3 && OUT != 2 && NSTAG
                 const uint32_t st_ = lds_base + stage * STAGE_BYTES;
                 const uint8_t *bs = b_base + (size_t)step * PAIR;
                 const int8_t *as = a_base + (size_t)step * BK;
-                uint32_t bd[B_PER], ad[A_PER];
 #pragma unroll
-                for (int i = 0; i < B_PER; ++i) bd[i] = st_ + b_dst[i];
+                for (int i = 0; i < B_PER; ++i) copy_to_lds<CH>(bs, b_off[i], st_ + b_dst[i]);
 #pragma unroll
-                for (int i = 0; i < A_PER; ++i) ad[i] = st_ + a_dst[i];
-                copies_to_lds<CH>(bs, b_off, bd);
-                copies_to_lds<16>(as, a_off, ad);
+                for (int i = 0; i < A_PER; ++i) copy_to_lds<16>(as, a_off[i], st_ + a_dst[i]);
             };
             if (0 < nsteps) fetch(0, 0);  // the first step's copies go first: the K-loop waits for nothing else
             if (p == 0) {  // the tile's epilogue parameters: needed after the K-loop only
@@ -1478,13 +1454,10 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
     auto copy_step = [&](int s, int par) {
         const uint8_t *as = a_base + (size_t)s * BK, *bs = b_base + (size_t)s * PAIR;
         const uint32_t dst = lds_base + (uint32_t)par * STAGE;
-        uint32_t bd[NB], ad[4];
 #pragma unroll
-        for (int e = 0; e < NB; ++e) bd[e] = dst + A_BYTES + (wave * NB + e) * 1024;
+        for (int e = 0; e < NB; ++e) copy_to_lds<CH>(bs, b_off[e], dst + A_BYTES + (wave * NB + e) * 1024);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ad[e] = dst + (wave * 4 + e) * 1024;
-        copies_to_lds<CH>(bs, b_off, bd);
-        copies_to_lds<16>(as, a_off, ad);
+        for (int e = 0; e < 4; ++e) copy_to_lds<16>(as, a_off[e], dst + (wave * 4 + e) * 1024);
     };
     // addresses of a tile's operands, its epilogue parameters and the copies of its first step
     auto start_tile = [&](int tm, int tn, int pb, int par) {
@@ -1515,10 +1488,10 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
             int t = tm * BM + x * 64 + lane, nn = tn * BN + ((x - 2) & 3) * 64 + lane;
             t = t < T ? t : T - 1;
             nn = nn < N ? nn : N - 1;
-            if (x < 2) copy4_to_lds(P.rs_x, (uint32_t)t * 4, dst + e * 256);
-            else if (x < 6) copy4_to_lds(P.rs_w, (uint32_t)nn * 4, dst + e * 256);
-            else if (x < 10) copy4_to_lds(P.h, (uint32_t)(nn / P.rows_per_group) * 4, dst + e * 256);
-            else if (x < 14 && P.bias) copy4_to_lds(P.bias, (uint32_t)nn * 4, dst + e * 256);
+            if (x < 2) copy_to_lds<4>(P.rs_x, (uint32_t)t * 4, dst + e * 256);
+            else if (x < 6) copy_to_lds<4>(P.rs_w, (uint32_t)nn * 4, dst + e * 256);
+            else if (x < 10) copy_to_lds<4>(P.h, (uint32_t)(nn / P.rows_per_group) * 4, dst + e * 256);
+            else if (x < 14 && P.bias) copy_to_lds<4>(P.bias, (uint32_t)nn * 4, dst + e * 256);
         }
         copy_step(0, par);
     };

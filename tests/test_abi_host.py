@@ -260,31 +260,23 @@ def gfx950_code_objects(path):
     return out
 
 
-def test_copies_keep_their_distance_to_the_scalar_base(lib, tmp_path):
+def test_copies_take_their_base_from_a_scalar_instruction(lib, tmp_path):
     """A vector memory instruction may read a scalar register five wait states after a VALU instruction wrote it at the
     earliest.  The compiler does not see into the asm blocks of the global -> LDS copies, and it may write a block's base with
-    v_readlane or v_readfirstlane right in front: the wait states have to lie inside the block, in front of its first copy."""
+    v_readlane or v_readfirstlane right in front: so every copy reads a base that the instruction before it, a scalar one,
+    has written."""
     copies = 0
     for i, code in enumerate(gfx950_code_objects(qb.LIB_PATH)):
         f = tmp_path / ("%d.o" % i)
         f.write_bytes(code)
         listing = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", "--no-show-raw-insn", "--no-leading-addr", str(f)], check=True,
                                  capture_output=True, text=True).stdout
-        states = 0    # wait states since the last instruction that is not part of a run of copies
+        before = ""
         for line in listing.splitlines():
             text = line.split("//")[0].strip()
-            if not text:
-                continue
-            op = text.split()[0]
-            if op.startswith("global_load_lds"):
-                if "s[" in text:
-                    copies += 1
-                    assert states >= 5, text
-                states += 1
-            elif op == "s_nop":
-                states += int(text.split()[1]) + 1
-            elif text.startswith("s_mov_b32 m0,"):
-                states += 1
-            else:
-                states = 0
+            base = re.match(r"global_load_lds\w+ v\d+, (s\[\d+:\d+\])", text)
+            if base:
+                copies += 1
+                assert before.startswith("s_mov_b64 %s," % base[1]), (before, text)
+            before = text or before
     assert copies > 100
