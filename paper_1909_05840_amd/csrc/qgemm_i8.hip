@@ -1761,18 +1761,27 @@ inline bool split_shape(long tiles, int T, int K) { return tiles <= 256 && slice
 
 // Which problems go to the 128 x 256 kernel with two independent workgroups per CU.  Its tiles are the largest, so it
 // needs two full rounds of the 512 resident workgroups (1024 tiles); with long contractions, whose tiles are started and
-// written out more rarely, three quarters of one.  Times in us, this kernel / the kernel of the rules below:
-//   4 bits  32768 x 4096 x 1024  170 / 191    32768 x 1024 x 4096  117 / 140    16384 x 3072 x 768 (1536 tiles)  54.5 / 62.2
-//           12288 x 3072 x 768 (1152 tiles)  41.8 / 43.5    12288 x 2304 x 768 (864)  35.5 / 34.1    32768 x 768 x 768 (768)  31.6 / 31.2
-//           32768 x 768 x 3072 (768)  76 / 84    16384 x 768 x 3072 (384)  40.8 / 43.0    12288 x 768 x 3072 (288)  35.7 / 31.0
-//   2 bits  32768 x 4096 x 1024  183 / 200    3 bits  32768 x 3072 x 1024  133 / 157
-// At 8 bits two workgroups' stages do not fit the LDS (one: 12288 x 3072 x 768 62 / 50).  At most an eighth of the columns
-// may be padding.
+// written out more rarely, three quarters of one.  At most an eighth of the columns may be padding.  At 8 bits two workgroups'
+// stages do not fit the LDS (one: 12288 x 3072 x 768 62 / 50 us).  Time / time with the kernels of the rules below, behind the
+// activation quantizer, lowest to highest of 2 to 4 bits; n2 and n1: the most tiles of 128 x 256 and of 128 x 128 on a CU:
+//   K = 512 to 1024   (n1, n2) = (8,4) .86-.95, (9,5) .81-1.08, (10,5) .81-.97, (11,6) .85-1.06, (12,6) .87-.97, (15,8) .95-1.05, above .78-1.04
+//   K < 512           (8,4) .96-.99, (9,5) .92-1.08, (10,5) .95-.97, (11,6) 1.04-1.09, (12,6) .95-1.0: with so short a contraction
+//                     tiles are mostly start and write-out, and the odd one of a CU has nothing beside it
+//   K >= 2048         (3,2) .92-1.09, (4,2) .73-.98, (5,3) 1.04-1.29, (6,3) .72-1.07, (7,4) .69-1.05, (8,4) .68-.93, (9,5) .99-1.08,
+//                     above .79-.99: the third tile of a CU runs alone for 0.7 of a pair's time
+//   N = 1152, 1920, 2688 (the last column of tiles half empty and written element by element; the 128 x 128 tiles fill theirs)
+//                     1.03-1.05, 1.14-1.34, .89-1.16
+//   N = 998 to 3520, no multiple of 128, K <= 1024 .35-1.04;  no multiple of 4 (no 16-byte rows), K >= 2048 .63-1.0
 template <int BITS>
 bool duo_shape(int T, int N, int K)
 {
-    const long tiles_n = (N + 255) / 256, tiles = (long)((T + 127) / 128) * tiles_n;
-    return BITS < 8 && K % 128 == 0 && (tiles >= 1024 || (K >= 2048 && tiles >= 384)) && (tiles_n * 256 - N) * 8 <= N;
+    const long tiles_m = (T + 127) / 128, tiles_n = (N + 255) / 256, tiles = tiles_m * tiles_n;
+    const bool long_k = K >= 2048;
+    if (BITS == 8 || K % 128 != 0 || tiles < (long_k ? 384 : 1024) || (tiles_n * 256 - N) * 8 > N) return false;
+    if (N % 4 != 0 || (N % 128 != 0 && !long_k)) return true;
+    const long n1 = (tiles_m * ((N + 127) / 128) + 255) / 256, n2 = (tiles + 255) / 256;
+    if (long_k) return 100 * n2 + 40 * (n2 & 1) < 67 * n1;
+    return N % 256 == 0 && (K >= 512 || n1 >= 2 * n2);
 }
 
 template <int BITS>

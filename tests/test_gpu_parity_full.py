@@ -549,9 +549,10 @@ def test_forward_batched_few_token_jobs_share_launches(qb):
 
 
 # (T, N, K): the smallest problems that reach the 128 x 256 tiles: one, two and three steps of 128 features, token and
-# neuron counts that end inside a tile, an odd neuron count (no 8-byte stores), the three-quarter round of a long contraction
+# neuron counts that end inside a tile, an odd neuron count (no 8-byte stores), long contractions in three quarters of a round and a
+# little more, and shapes beside them that the rule leaves to the 128 x 128 tiles (1920 neurons, K = 384 with an odd tile, 576 tiles)
 @pytest.mark.parametrize("bits", (2, 3, 4))
-@pytest.mark.parametrize("shape", [(16300, 2020, 128), (16384, 2048, 256), (16257, 1999, 384), (6100, 2048, 2048)])
+@pytest.mark.parametrize("shape", [(16300, 2020, 128), (16384, 2048, 256), (16257, 1999, 384), (6100, 2048, 2048), (6200, 2048, 2048), (6100, 2046, 2048), (16384, 1920, 256), (22222, 1536, 384), (9216, 2048, 2048)])
 def test_forward_whole_output_large_tiles(qb, bits, shape):
     """A4 exact, Y within the bound of the small shapes, single and batched calls with the same bits."""
     T, N, K = shape
