@@ -109,28 +109,33 @@ Tensor out(PyObject *o, at::IntArrayRef size, at::ScalarType t, const at::Device
     return o == Py_None ? fresh(size, t, dev) : tensor(o, name);
 }
 
-int64_t integer(PyObject *o)
+// Numbers.  The single calls take integers and what stands for one (a numpy integer, a tensor of one), no floats or strings;
+// a job's entries may be anything that int() takes.  A value that does not fit is an OverflowError.
+int64_t integer(PyObject *o, PyObject *(*convert)(PyObject *) = PyNumber_Index)
 {
-    if (PyLong_CheckExact(o)) return PyLong_AsLongLong(o);
-    PyObject *n = PyNumber_Long(o);
+    PyObject *const n = PyLong_CheckExact(o) ? Py_NewRef(o) : convert(o);
     if (!n) throw_python_error();
     const int64_t v = PyLong_AsLongLong(n);
     Py_DECREF(n);
-    return v;
-}
-
-double real(PyObject *o)
-{
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw_python_error();
-    return v;
-}
-
-int small(PyObject *o)  // an argument the C side takes as int
-{
-    const int64_t v = integer(o);
     if (v == -1 && PyErr_Occurred()) throw_python_error();
-    return v > INT32_MAX || v < INT32_MIN ? -1 : static_cast<int>(v);
+    return v;
+}
+
+int small(PyObject *o, PyObject *(*convert)(PyObject *) = PyNumber_Index)  // an argument the C side takes as int
+{
+    const int64_t v = integer(o, convert);
+    if (v > INT32_MAX || v < INT32_MIN) raise(PyExc_OverflowError, "integer does not fit a C int");
+    return static_cast<int>(v);
+}
+
+float real(PyObject *o)  // what float() takes
+{
+    if (PyFloat_CheckExact(o)) return static_cast<float>(PyFloat_AS_DOUBLE(o));
+    PyObject *const f = PyNumber_Float(o);
+    if (!f) throw_python_error();
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
+    return static_cast<float>(v);
 }
 
 void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
@@ -194,9 +199,9 @@ Tensor packed_buffer(PyObject *o, int64_t N, int64_t K, int bits, const at::Devi
 
 QB_CALL(quantize_groupwise, 7)  // W, bits, groups, packed, h, m, rs_w
 {
+    const int bits = small(a[1]), groups = small(a[2]);
     const Tensor &W = matrix(a[0], at::kFloat, "W");
     const int64_t N = W.size(0), K = W.size(1);
-    const int bits = small(a[1]), groups = small(a[2]);
     const at::Device dev = W.device();
     const Tensor p = packed_buffer(a[3], N, K, bits, dev);
     const Tensor h = out(a[4], {groups > 0 ? groups : 1}, at::kFloat, dev, "h");
@@ -209,9 +214,9 @@ QB_CALL(quantize_groupwise, 7)  // W, bits, groups, packed, h, m, rs_w
 
 QB_CALL(quantize_groupwise_clip, 6)  // W, bits, m_in, packed, h, rs_w
 {
+    const int bits = small(a[1]);
     const Tensor &W = matrix(a[0], at::kFloat, "W"), &m = typed(a[2], at::kFloat, "m_in");
     const int64_t N = W.size(0), K = W.size(1), G = m.dim() ? m.size(0) : 0;
-    const int bits = small(a[1]);
     const at::Device dev = W.device();
     const Tensor p = packed_buffer(a[3], N, K, bits, dev);
     const Tensor h = out(a[4], {G}, at::kFloat, dev, "h"), rs = out(a[5], {N}, at::kInt, dev, "rs_w");
@@ -222,9 +227,9 @@ QB_CALL(quantize_groupwise_clip, 6)  // W, bits, m_in, packed, h, rs_w
 
 QB_CALL(quantize_groupwise_asym, 7)  // W, bits, groups, packed, delta, q0, rs_w
 {
+    const int bits = small(a[1]), groups = small(a[2]);
     const Tensor &W = matrix(a[0], at::kFloat, "W");
     const int64_t N = W.size(0), K = W.size(1);
-    const int bits = small(a[1]), groups = small(a[2]);
     const at::Device dev = W.device();
     const Tensor p = packed_buffer(a[3], N, K, bits, dev);
     const Tensor d = out(a[4], {groups}, at::kFloat, dev, "delta"), q0 = out(a[5], {groups}, at::kFloat, dev, "q0");
@@ -236,9 +241,9 @@ QB_CALL(quantize_groupwise_asym, 7)  // W, bits, groups, packed, delta, q0, rs_w
 
 QB_CALL(quantize_groupwise_asym_range, 8)  // W, bits, lo, hi, packed, delta, q0, rs_w
 {
+    const int bits = small(a[1]);
     const Tensor &W = matrix(a[0], at::kFloat, "W"), &lo = typed(a[2], at::kFloat, "lo"), &hi = typed(a[3], at::kFloat, "hi");
     const int64_t N = W.size(0), K = W.size(1), G = lo.numel();
-    const int bits = small(a[1]);
     const at::Device dev = W.device();
     const Tensor p = packed_buffer(a[4], N, K, bits, dev);
     const Tensor d = out(a[5], {G}, at::kFloat, dev, "delta"), q0 = out(a[6], {G}, at::kFloat, dev, "q0");
@@ -306,7 +311,7 @@ QB_CALL(quantize_groupwise_batched, 1)
     for (Py_ssize_t i = 0; i < n; ++i) {
         const Tensor &W = matrix(jobs.get(i, kW, true), at::kFloat, "W");
         const int64_t N = W.size(0), K = W.size(1);
-        const int bits = small(jobs.get(i, kBits, true)), groups = small(jobs.get(i, kGroups, true));
+        const int bits = small(jobs.get(i, kBits, true), PyNumber_Long), groups = small(jobs.get(i, kGroups, true), PyNumber_Long);
         const at::Device dev = W.device();
         const Tensor p = packed_buffer(jobs.get(i, kPacked, false), N, K, bits, dev);
         const Tensor h = out(jobs.get(i, kH, false), {groups > 0 ? groups : 1}, at::kFloat, dev, "h");
@@ -332,7 +337,7 @@ QB_CALL(quantize_act_batched, 1)
         PyObject *oq = jobs.get(i, kXq, false), *ors = jobs.get(i, kRs, false);
         const Tensor Xq = oq == Py_None ? fresh({T, K}, at::kChar, X.device()) : typed(oq, at::kChar, "Xq");
         const Tensor rs = ors == Py_None ? fresh({T}, at::kInt, X.device()) : typed(ors, at::kInt, "rs_x");
-        arr[i] = qb_act_job{ptr<float>(X), T, K, static_cast<float>(real(jobs.get(i, kClip, true))), ptr<int8_t>(Xq), ptr<int32_t>(rs)};
+        arr[i] = qb_act_job{ptr<float>(X), T, K, real(jobs.get(i, kClip, true)), ptr<int8_t>(Xq), ptr<int32_t>(rs)};
         PyList_SET_ITEM(outs.get(), i, tuple({Xq, rs}));
     }
     call(qb_quantize_act_batched, arr.data(), static_cast<int>(n), stream());
@@ -350,13 +355,13 @@ QB_CALL(qlinear_fwd_batched, 1)
     THPObjectPtr outs(new_list(n));
     for (Py_ssize_t i = 0; i < n; ++i) {
         const Tensor &Xq = matrix(jobs.get(i, kXq, true), at::kChar, "Xq");
-        const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(jobs.get(i, kN, true));
+        const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(jobs.get(i, kN, true), PyNumber_Long);
         PyObject *oy = jobs.get(i, kY, false), *ob = jobs.get(i, kBias, false);
         const Tensor Y = oy == Py_None ? fresh({T, N}, at::kFloat, Xq.device()) : typed(oy, at::kFloat, "Y");
         arr[i] = qb_fwd_job{ptr<int8_t>(Xq), ptr<int32_t>(typed(jobs.get(i, kRs, true), at::kInt, "rs_x")),
-                            static_cast<float>(real(jobs.get(i, kClip, true))), typed(jobs.get(i, kPacked, true), at::kByte, "packed").data_ptr(),
+                            real(jobs.get(i, kClip, true)), typed(jobs.get(i, kPacked, true), at::kByte, "packed").data_ptr(),
                             ptr<float>(typed(jobs.get(i, kH, true), at::kFloat, "h")), ptr<int32_t>(typed(jobs.get(i, kRw, true), at::kInt, "rs_w")),
-                            small(jobs.get(i, kBits, true)), small(jobs.get(i, kGroups, true)), T, N, K,
+                            small(jobs.get(i, kBits, true), PyNumber_Long), small(jobs.get(i, kGroups, true), PyNumber_Long), T, N, K,
                             ob == Py_None ? nullptr : ptr<float>(typed(ob, at::kFloat, "bias")), ptr<float>(Y)};
         PyObject *v = THPVariable_Wrap(Y);
         if (!v) throw_python_error();
@@ -370,10 +375,11 @@ QB_CALL(qlinear_fwd_batched, 1)
 
 QB_CALL(quantize_act, 4)  // X, clip, Xq, rs_x
 {
+    const float clip = real(a[1]);
     const Tensor &X = matrix(a[0], at::kFloat, "X");
     const int64_t T = X.size(0), K = X.size(1);
     const Tensor Xq = out(a[2], {T, K}, at::kChar, X.device(), "Xq"), rs = out(a[3], {T}, at::kInt, X.device(), "rs_x");
-    call(qb_quantize_act, ptr<float>(X), T, K, static_cast<float>(real(a[1])), ptr<int8_t>(Xq), ptr<int32_t>(rs), stream());
+    call(qb_quantize_act, ptr<float>(X), T, K, clip, ptr<int8_t>(Xq), ptr<int32_t>(rs), stream());
     return tuple({Xq, rs});
 }
 
@@ -422,61 +428,76 @@ int32_t *debug_ptr(const Tensor &t) { return t.defined() ? ptr<int32_t>(t) : nul
 
 QB_CALL(qlinear_fwd, 13)  // Xq, rs_x, clip, packed, h, rs_w, bits, groups, N, bias, Y, A4_debug, want_a4
 {
+    const float clip = real(a[2]);
+    const int bits = small(a[6]), groups = small(a[7]);
+    const int64_t N = integer(a[8]);
     const Tensor &Xq = matrix(a[0], at::kChar, "Xq");
-    const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[8]);
+    const int64_t T = Xq.size(0), K = Xq.size(1);
     const Tensor Y = out(a[10], {T, N}, at::kFloat, Xq.device(), "Y");
     const Tensor A4 = debug_output(a[11], a[12], T, N, Xq.device());
-    call(qb_qlinear_fwd, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
-                         ptr<float>(a[4], "h"), ptr<int32_t>(a[5], "rs_w"), small(a[6]), small(a[7]), T, N, K,
+    call(qb_qlinear_fwd, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), clip, ptr<void>(a[3], "packed"),
+                         ptr<float>(a[4], "h"), ptr<int32_t>(a[5], "rs_w"), bits, groups, T, N, K,
                          ptr<float>(a[9], "bias"), ptr<float>(Y), debug_ptr(A4), stream());
     return forward_result(Y, A4);
 }
 
 QB_CALL(qlinear_fwd_dyn, 12)  // Xq, rs_x, hx_rows, packed, h, rs_w, bits, groups, N, bias, Y, want_a4
 {
+    const int bits = small(a[6]), groups = small(a[7]);
+    const int64_t N = integer(a[8]);
     const Tensor &Xq = matrix(a[0], at::kChar, "Xq"), &hx = typed(a[2], at::kFloat, "hx_rows");
-    const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[8]);
+    const int64_t T = Xq.size(0), K = Xq.size(1);
     const Tensor Y = out(a[10], {T, N}, at::kFloat, Xq.device(), "Y");
     const Tensor A4 = debug_output(Py_None, a[11], T, N, Xq.device());
     call(qb_qlinear_fwd_dyn, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), ptr<float>(hx), ptr<void>(a[3], "packed"),
-                             ptr<float>(a[4], "h"), ptr<int32_t>(a[5], "rs_w"), small(a[6]), small(a[7]), T, N, K,
+                             ptr<float>(a[4], "h"), ptr<int32_t>(a[5], "rs_w"), bits, groups, T, N, K,
                              ptr<float>(a[9], "bias"), ptr<float>(Y), debug_ptr(A4), stream());
     return forward_result(Y, A4);
 }
 
 QB_CALL(qlinear_fwd_asym, 13)  // Xq, rs_x, clip, packed, delta, q0, rs_w, bits, groups, N, bias, Y, want_a4
 {
+    const float clip = real(a[2]);
+    const int bits = small(a[7]), groups = small(a[8]);
+    const int64_t N = integer(a[9]);
     const Tensor &Xq = matrix(a[0], at::kChar, "Xq"), &d = typed(a[4], at::kFloat, "delta"), &q0 = typed(a[5], at::kFloat, "q0");
-    const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[9]);
+    const int64_t T = Xq.size(0), K = Xq.size(1);
     const Tensor Y = out(a[11], {T, N}, at::kFloat, Xq.device(), "Y");
     const Tensor A4 = debug_output(Py_None, a[12], T, N, Xq.device());
-    call(qb_qlinear_fwd_asym, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
-                              ptr<float>(d), ptr<float>(q0), ptr<int32_t>(a[6], "rs_w"), small(a[7]), small(a[8]), T, N, K,
+    call(qb_qlinear_fwd_asym, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), clip, ptr<void>(a[3], "packed"),
+                              ptr<float>(d), ptr<float>(q0), ptr<int32_t>(a[6], "rs_w"), bits, groups, T, N, K,
                               ptr<float>(a[10], "bias"), ptr<float>(Y), debug_ptr(A4), stream());
     return forward_result(Y, A4);
 }
 
 QB_CALL(qlinear_fwd_asym_dyn, 13)  // Xq, rs_x, hx_rows, packed, delta, q0, rs_w, bits, groups, N, bias, Y, want_a4
 {
+    const int bits = small(a[7]), groups = small(a[8]);
+    const int64_t N = integer(a[9]);
     const Tensor &Xq = matrix(a[0], at::kChar, "Xq"), &hx = typed(a[2], at::kFloat, "hx_rows");
     const Tensor &d = typed(a[4], at::kFloat, "delta"), &q0 = typed(a[5], at::kFloat, "q0");
-    const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[9]);
+    const int64_t T = Xq.size(0), K = Xq.size(1);
     const Tensor Y = out(a[11], {T, N}, at::kFloat, Xq.device(), "Y");
     const Tensor A4 = debug_output(Py_None, a[12], T, N, Xq.device());
     call(qb_qlinear_fwd_asym_dyn, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), ptr<float>(hx), ptr<void>(a[3], "packed"),
-                                  ptr<float>(d), ptr<float>(q0), ptr<int32_t>(a[6], "rs_w"), small(a[7]), small(a[8]), T, N, K,
+                                  ptr<float>(d), ptr<float>(q0), ptr<int32_t>(a[6], "rs_w"), bits, groups, T, N, K,
                                   ptr<float>(a[10], "bias"), ptr<float>(Y), debug_ptr(A4), stream());
     return forward_result(Y, A4);
 }
 
 QB_CALL(qlinear_fwd_q8, 14)  // Xq, rs_x, clip, packed, h, rs_w, bits, groups, N, clip_out, bias, act, Yq, rs_y
 {
+    const float clip = real(a[2]);
+    const float clip_out = real(a[9]);
+    const int act = small(a[11], PyNumber_Long);
+    const int bits = small(a[6]), groups = small(a[7]);
+    const int64_t N = integer(a[8]);
     const Tensor &Xq = matrix(a[0], at::kChar, "Xq");
-    const int64_t T = Xq.size(0), K = Xq.size(1), N = integer(a[8]);
+    const int64_t T = Xq.size(0), K = Xq.size(1);
     const Tensor Yq = out(a[12], {T, N}, at::kChar, Xq.device(), "Yq"), rs = out(a[13], {T}, at::kInt, Xq.device(), "rs_y");
-    call(qb_qlinear_fwd_q8, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
-                            ptr<float>(a[4], "h"), ptr<int32_t>(a[5], "rs_w"), small(a[6]), small(a[7]), T, N, K,
-                            ptr<float>(a[10], "bias"), small(a[11]), static_cast<float>(real(a[9])), ptr<int8_t>(Yq), ptr<int32_t>(rs),
+    call(qb_qlinear_fwd_q8, ptr<int8_t>(Xq), ptr<int32_t>(a[1], "rs_x"), clip, ptr<void>(a[3], "packed"),
+                            ptr<float>(a[4], "h"), ptr<int32_t>(a[5], "rs_w"), bits, groups, T, N, K,
+                            ptr<float>(a[10], "bias"), act, clip_out, ptr<int8_t>(Yq), ptr<int32_t>(rs),
                             stream());
     return tuple({Yq, rs});
 }
@@ -514,27 +535,32 @@ struct Bwd {
 
 QB_CALL(qlinear_bwd_ste, 12)  // dY, Xq, clip, packed, h, bits, groups, want_dx, want_dw, dX, dW, workspace
 {
+    const float clip = real(a[2]);
+    const int bits = small(a[5]), groups = small(a[6]);
     Bwd b(a[0], a[1]);
     b.outputs(a[7], a[8], a[9], a[10], a[11]);
-    call(qb_qlinear_bwd_ste, bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
-                             ptr<float>(a[4], "h"), small(a[5]), small(a[6]), b.T, b.N, b.K, bits16(b.dX), b.dw_ptr(),
+    call(qb_qlinear_bwd_ste, bits16(b.dY), ptr<int8_t>(b.Xq), clip, ptr<void>(a[3], "packed"),
+                             ptr<float>(a[4], "h"), bits, groups, b.T, b.N, b.K, bits16(b.dX), b.dw_ptr(),
                              b.workspace.data_ptr(), stream());
     return tuple({b.dX, b.dW});
 }
 
 QB_CALL(qlinear_bwd_ste_static, 9)  // dY, Xq, clip, packed, h, bits, groups, dX, dW
 {
+    const float clip = real(a[2]);
+    const int bits = small(a[5]), groups = small(a[6]);
     const Bwd b(a[0], a[1]);
-    call(qb_qlinear_bwd_ste_static, bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
-                                    ptr<float>(a[4], "h"), small(a[5]), small(a[6]), b.T, b.N, b.K, ptr<uint16_t>(a[7], "dX"),
+    call(qb_qlinear_bwd_ste_static, bits16(b.dY), ptr<int8_t>(b.Xq), clip, ptr<void>(a[3], "packed"),
+                                    ptr<float>(a[4], "h"), bits, groups, b.T, b.N, b.K, ptr<uint16_t>(a[7], "dX"),
                                     ptr<float>(a[8], "dW"), stream());
     return PyTuple_Pack(2, a[7], a[8]);
 }
 
 QB_CALL(qlinear_bwd_ste_masked, 15)  // dY, Xq, clip, packed, h, bits, groups, X, W, m, want_dx, want_dw, dX, dW, workspace
 {
+    const float clip = real(a[2]);
+    const int bits = small(a[5]), groups = small(a[6]);
     Bwd b(a[0], a[1]);
-    const int groups = small(a[6]);
     if (a[7] != Py_None) {
         const Tensor &X = typed(a[7], at::kFloat, "X");
         if (X.dim() != 2 || X.size(0) != b.T || X.size(1) != b.K) raise(PyExc_ValueError, "X must be [T, K]");
@@ -546,8 +572,8 @@ QB_CALL(qlinear_bwd_ste_masked, 15)  // dY, Xq, clip, packed, h, bits, groups, X
     if (a[9] != Py_None && typed(a[9], at::kFloat, "m").numel() != groups)
         raise(PyExc_ValueError, "m must hold one range per group");
     b.outputs(a[10], a[11], a[12], a[13], a[14]);
-    call(qb_qlinear_bwd_ste_masked, bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
-                                    ptr<float>(a[4], "h"), small(a[5]), groups, b.T, b.N, b.K, ptr<float>(a[7], "X"),
+    call(qb_qlinear_bwd_ste_masked, bits16(b.dY), ptr<int8_t>(b.Xq), clip, ptr<void>(a[3], "packed"),
+                                    ptr<float>(a[4], "h"), bits, groups, b.T, b.N, b.K, ptr<float>(a[7], "X"),
                                     ptr<float>(a[8], "W"), ptr<float>(a[9], "m"), bits16(b.dX), b.dw_ptr(), b.workspace.data_ptr(),
                                     stream());
     return tuple({b.dX, b.dW});
@@ -555,10 +581,12 @@ QB_CALL(qlinear_bwd_ste_masked, 15)  // dY, Xq, clip, packed, h, bits, groups, X
 
 QB_CALL(qlinear_bwd_ste_asym, 13)  // dY, Xq, clip, packed, delta, q0, bits, groups, want_dx, want_dw, dX, dW, workspace
 {
+    const float clip = real(a[2]);
+    const int bits = small(a[6]), groups = small(a[7]);
     Bwd b(a[0], a[1]);
     b.outputs(a[8], a[9], a[10], a[11], a[12]);
-    call(qb_qlinear_bwd_ste_asym, bits16(b.dY), ptr<int8_t>(b.Xq), static_cast<float>(real(a[2])), ptr<void>(a[3], "packed"),
-                                  ptr<float>(a[4], "delta"), ptr<float>(a[5], "q0"), small(a[6]), small(a[7]), b.T, b.N, b.K,
+    call(qb_qlinear_bwd_ste_asym, bits16(b.dY), ptr<int8_t>(b.Xq), clip, ptr<void>(a[3], "packed"),
+                                  ptr<float>(a[4], "delta"), ptr<float>(a[5], "q0"), bits, groups, b.T, b.N, b.K,
                                   bits16(b.dX), b.dw_ptr(), b.workspace.data_ptr(), stream());
     return tuple({b.dX, b.dW});
 }
@@ -567,9 +595,9 @@ QB_CALL(qlinear_bwd_ste_asym, 13)  // dY, Xq, clip, packed, delta, q0, bits, gro
 
 QB_CALL(embedding_quantize_bits, 6)  // E, bits, groups, codes, h, m
 {
+    const int bits = small(a[1]), groups = small(a[2]);
     const Tensor &E = matrix(a[0], at::kFloat, "E");
     const int64_t V = E.size(0), d = E.size(1);
-    const int bits = small(a[1]), groups = small(a[2]);
     const at::Device dev = E.device();
     const Tensor codes = out(a[3], {V, d * bits / 8}, at::kByte, dev, "codes");
     const Tensor h = out(a[4], {groups > 0 ? groups : 1}, at::kFloat, dev, "h"), m = out(a[5], {groups > 0 ? groups : 1}, at::kFloat, dev, "m");
@@ -579,8 +607,8 @@ QB_CALL(embedding_quantize_bits, 6)  // E, bits, groups, codes, h, m
 
 QB_CALL(embedding_gather_bits, 6)  // codes, h, bits, groups, ids, out
 {
-    const Tensor &codes = matrix(a[0], at::kByte, "codes"), &ids = typed(a[4], at::kLong, "ids");
     const int bits = small(a[2]), groups = small(a[3]);
+    const Tensor &codes = matrix(a[0], at::kByte, "codes"), &ids = typed(a[4], at::kLong, "ids");
     const int64_t V = codes.size(0), d = bits > 0 ? codes.size(1) * 8 / bits : 0, n = ids.dim() ? ids.size(0) : 0;
     const Tensor o = out(a[5], {n, d}, at::kFloat, codes.device(), "out");
     call(qb_embedding_gather_bits, ptr<uint8_t>(codes), ptr<float>(a[1], "h"), V, d, bits, groups, ptr<int64_t>(ids), n, ptr<float>(o),

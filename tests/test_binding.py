@@ -4,7 +4,9 @@ import shutil
 import subprocess
 import sys
 
+import numpy as np
 import pytest
+import torch
 
 import paper_1909_05840_amd.binding
 
@@ -62,3 +64,51 @@ def test_library_is_called_without_the_interpreter_lock(qb, tmp_path):
     assert r.returncode == 0, r.stderr[-2000:]
     made, seen, locked = map(int, r.stdout.split()[-3:])
     assert made == seen > 0 and locked == 0
+
+
+# every single call with a number in each place that takes a whole one; the tensors are looked at after the numbers
+WHOLE_NUMBERS = [
+    ("quantize_groupwise", lambda qb, t, n: qb.qb_quantize_groupwise(t, n, 1)),
+    ("quantize_groupwise groups", lambda qb, t, n: qb.qb_quantize_groupwise(t, 4, n)),
+    ("quantize_groupwise_clip", lambda qb, t, n: qb.qb_quantize_groupwise_clip(t, n, t)),
+    ("quantize_groupwise_asym", lambda qb, t, n: qb.qb_quantize_groupwise_asym(t, 4, n)),
+    ("quantize_groupwise_asym_range", lambda qb, t, n: qb.qb_quantize_groupwise_asym_range(t, n, t, t)),
+    ("qlinear_fwd bits", lambda qb, t, n: qb.qb_qlinear_fwd(t, t, 6.0, t, t, t, n, 1, 64)),
+    ("qlinear_fwd N", lambda qb, t, n: qb.qb_qlinear_fwd(t, t, 6.0, t, t, t, 4, 1, n)),
+    ("qlinear_fwd_dyn", lambda qb, t, n: qb.qb_qlinear_fwd_dyn(t, t, t, t, t, t, 4, n, 64)),
+    ("qlinear_fwd_asym", lambda qb, t, n: qb.qb_qlinear_fwd_asym(t, t, 6.0, t, t, t, t, n, 1, 64)),
+    ("qlinear_fwd_asym_dyn", lambda qb, t, n: qb.qb_qlinear_fwd_asym_dyn(t, t, t, t, t, t, t, 4, 1, n)),
+    ("qlinear_fwd_q8", lambda qb, t, n: qb.qb_qlinear_fwd_q8(t, t, 6.0, t, t, t, 4, 1, n, 6.0)),
+    ("qlinear_bwd_ste", lambda qb, t, n: qb.qb_qlinear_bwd_ste(t, t, 6.0, t, t, n, 1)),
+    ("qlinear_bwd_ste_static", lambda qb, t, n: qb.qb_qlinear_bwd_ste_static(t, t, 6.0, t, t, 4, n)),
+    ("qlinear_bwd_ste_masked", lambda qb, t, n: qb.qb_qlinear_bwd_ste_masked(t, t, 6.0, t, t, n, 1)),
+    ("qlinear_bwd_ste_asym", lambda qb, t, n: qb.qb_qlinear_bwd_ste_asym(t, t, 6.0, t, t, t, 4, n)),
+    ("embedding_quantize_bits", lambda qb, t, n: qb.qb_embedding_quantize_bits(t, n, 1)),
+    ("embedding_gather_bits", lambda qb, t, n: qb.qb_embedding_gather_bits(t, t, 8, n, t)),
+]
+
+
+@pytest.mark.parametrize("call", [c for _, c in WHOLE_NUMBERS], ids=[n for n, _ in WHOLE_NUMBERS])
+def test_whole_numbers(call):
+    """Floats and strings are refused, not cut; what does not fit is an overflow, not another number; numpy's and torch's
+    integers pass (the call then refuses the tensor, which is not on the GPU)."""
+    qb, t = paper_1909_05840_amd, torch.zeros(4, 64)
+    for n in (3.9, 4.0, "4", None):
+        with pytest.raises(TypeError, match="integer"):
+            call(qb, t, n)
+    for n in (2 ** 70, -2 ** 63 - 1):
+        with pytest.raises(OverflowError):
+            call(qb, t, n)
+    for n in (4, np.int64(4), torch.tensor(4)):
+        with pytest.raises(TypeError, match="contiguous"):
+            call(qb, t, n)
+
+
+@pytest.mark.gpu
+def test_numbers_of_jobs(qb):
+    """Entries of a job are what int() and float() make of them."""
+    W, X = torch.randn(64, 64, device="cuda"), torch.randn(8, 64, device="cuda")
+    for W4, want in zip(qb.qb_quantize_groupwise_batched([{"W": W, "bits": "4", "groups": 2.0}])[0], qb.qb_quantize_groupwise(W, 4, 2)):
+        assert torch.equal(W4, want)
+    for a, b in zip(qb.qb_quantize_act_batched([{"X": X, "clip": "3"}])[0], qb.qb_quantize_act(X, np.float32(3.0))):
+        assert torch.equal(a, b)
