@@ -253,7 +253,7 @@ QB_CALL(quantize_groupwise_asym_range, 8)  // W, bits, lo, hi, packed, delta, q0
     return tuple({p, d, q0, rs});
 }
 
-// ---- lists of jobs: dicts with the names of the single calls' arguments
+// ---- lists of jobs: mappings with the names of the single calls' arguments
 
 PyObject *key(const char *name)  // interned once per name: `name` is a literal at a fixed call site
 {
@@ -263,10 +263,11 @@ PyObject *key(const char *name)  // interned once per name: `name` is a literal 
 }
 
 struct Jobs {
-    PyObject *seq;
+    PyObject *seq = nullptr;
     std::vector<PyObject *> held;  // the entries read, until the call has returned: it runs without the interpreter lock
-    explicit Jobs(PyObject *o) : seq(PySequence_Tuple(o))
+    explicit Jobs(PyObject *o)
     {
+        if (PyObject_Size(o) >= 0) seq = PySequence_Tuple(o);  // (what has no length, a generator, is refused)
         if (!seq) throw_python_error();
     }
     ~Jobs()
@@ -277,19 +278,26 @@ struct Jobs {
     Jobs(const Jobs &) = delete;
     Jobs &operator=(const Jobs &) = delete;
     Py_ssize_t size() const { return PyTuple_GET_SIZE(seq); }
-    // held by this object; None where an optional entry is absent
+    // held by this object; None where an optional entry is absent.  A job is whatever has [] and, for the optional entries,
+    // get(); a plain dict is read directly.
     PyObject *get(Py_ssize_t i, PyObject *k, bool required)
     {
-        PyObject *d = PyTuple_GET_ITEM(seq, i);
-        if (!PyDict_Check(d)) raise(PyExc_TypeError, "a job must be a dict");
-        PyObject *v = PyDict_GetItemWithError(d, k);
-        if (v) {
-            held.push_back(Py_NewRef(v));
-            return v;
+        static PyObject *const kGet = key("get");
+        PyObject *const d = PyTuple_GET_ITEM(seq, i);
+        PyObject *v;
+        if (PyDict_CheckExact(d)) {
+            v = PyDict_GetItemWithError(d, k);
+            if (!v && !PyErr_Occurred()) {
+                if (!required) return Py_None;
+                PyErr_SetObject(PyExc_KeyError, k);
+            }
+            Py_XINCREF(v);
+        } else {
+            v = required ? PyObject_GetItem(d, k) : PyObject_CallMethodOneArg(d, kGet, k);
         }
-        if (!PyErr_Occurred() && required) PyErr_SetObject(PyExc_KeyError, k);
-        if (PyErr_Occurred()) throw_python_error();
-        return Py_None;
+        if (!v) throw_python_error();
+        held.push_back(v);
+        return v;
     }
 };
 

@@ -1,8 +1,10 @@
 """The binding's native half: what it does with the interpreter lock, with numbers and with lists of jobs."""
+import collections
 import os
 import shutil
 import subprocess
 import sys
+import types
 
 import numpy as np
 import pytest
@@ -112,3 +114,66 @@ def test_numbers_of_jobs(qb):
         assert torch.equal(W4, want)
     for a, b in zip(qb.qb_quantize_act_batched([{"X": X, "clip": "3"}])[0], qb.qb_quantize_act(X, np.float32(3.0))):
         assert torch.equal(a, b)
+
+
+class Defaults(dict):
+    """a dict that knows its optional entries and computes a missing one"""
+
+    def __missing__(self, k):
+        return self["matrix"] if k in ("W", "X") else {"bits": 4, "groups": 2, "clip": 3.0}[k]
+
+
+class Record:
+    """no dict at all: [] and get()"""
+
+    def __init__(self, **entries):
+        self.entries = entries
+
+    def __getitem__(self, k):
+        return self.entries[k]
+
+    def get(self, k):
+        return self.entries.get(k)
+
+
+JOB_FORMS = [lambda **e: e, lambda **e: collections.ChainMap(e), lambda **e: types.MappingProxyType(e), lambda **e: Record(**e)]
+
+
+@pytest.mark.parametrize("form", JOB_FORMS, ids=("dict", "chain", "proxy", "record"))
+def test_jobs_of_any_mapping_are_read(form):
+    """The tensor is refused (it is not on the GPU), not the job; entries that are not there are a KeyError."""
+    qb, t = paper_1909_05840_amd, torch.zeros(4, 64)
+    with pytest.raises(TypeError, match="contiguous"):
+        qb.qb_quantize_groupwise_batched([form(W=t, bits=4, groups=1)])
+    with pytest.raises(TypeError, match="contiguous"):
+        qb.qb_quantize_act_batched((form(X=t, clip=6.0),))
+    with pytest.raises(TypeError, match="contiguous"):
+        qb.qb_qlinear_fwd_batched({0: form(Xq=t, clip=6.0)}.values())
+    with pytest.raises(KeyError):
+        qb.qb_quantize_act_batched([form(clip=6.0)])
+
+
+def test_lists_of_jobs_that_are_refused():
+    qb, t = paper_1909_05840_amd, torch.zeros(4, 64)
+    for jobs in (7, None, ({"X": t, "clip": 6.0} for _ in range(1)), [3], [None], "X"):
+        with pytest.raises((TypeError, AttributeError)):
+            qb.qb_quantize_act_batched(jobs)
+    with pytest.raises(TypeError, match="contiguous"):
+        qb.qb_quantize_act_batched([Defaults(matrix=t)])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", JOB_FORMS + [Defaults], ids=("dict", "chain", "proxy", "record", "missing"))
+def test_jobs_of_any_mapping(qb, form):
+    """The results of the single calls, for every kind of mapping; outputs that are passed in are written in place."""
+    W, X = torch.randn(64, 64, device="cuda"), torch.randn(8, 64, device="cuda")
+    weights, act = qb.qb_quantize_groupwise(W, 4, 2), qb.qb_quantize_act(X, 3.0)
+    named = form is Defaults
+    h = torch.empty(2, device="cuda")
+    got = qb.qb_quantize_groupwise_batched([form(matrix=W, h=h) if named else form(W=W, bits=4, groups=2, h=h)])[0]
+    assert all(torch.equal(a, b) for a, b in zip(got, weights)) and got[1] is h
+    got = qb.qb_quantize_act_batched([form(matrix=X) if named else form(X=X, clip=3.0)])[0]
+    assert all(torch.equal(a, b) for a, b in zip(got, act))
+    if not named:
+        Y = qb.qb_qlinear_fwd_batched([form(Xq=act[0], rs_x=act[1], clip=3.0, packed=weights[0], h=h, rs_w=weights[3], bits=4, groups=2, N=64)])[0]
+        assert torch.equal(Y, qb.qb_qlinear_fwd(*act, 3.0, weights[0], h, weights[3], 4, 2, 64))
