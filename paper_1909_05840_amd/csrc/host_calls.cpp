@@ -84,6 +84,14 @@ const Tensor &matrix(PyObject *o, at::ScalarType t, const char *name)
     return x;
 }
 
+// a tensor of which the first dimensions are read, any more being the caller's affair
+const Tensor &leading(PyObject *o, at::ScalarType t, const char *name, int dims)
+{
+    const Tensor &x = typed(o, t, name);
+    if (x.dim() < dims) raise(PyExc_IndexError, "%s must have %d dimensions or more", name, dims);
+    return x;
+}
+
 // a tensor or None, as a pointer
 template <typename T>
 T *ptr(PyObject *o, const char *name)
@@ -215,8 +223,8 @@ QB_CALL(quantize_groupwise, 7)  // W, bits, groups, packed, h, m, rs_w
 QB_CALL(quantize_groupwise_clip, 6)  // W, bits, m_in, packed, h, rs_w
 {
     const int bits = small(a[1]);
-    const Tensor &W = matrix(a[0], at::kFloat, "W"), &m = typed(a[2], at::kFloat, "m_in");
-    const int64_t N = W.size(0), K = W.size(1), G = m.dim() ? m.size(0) : 0;
+    const Tensor &W = matrix(a[0], at::kFloat, "W"), &m = leading(a[2], at::kFloat, "m_in", 1);
+    const int64_t N = W.size(0), K = W.size(1), G = m.size(0);
     const at::Device dev = W.device();
     const Tensor p = packed_buffer(a[3], N, K, bits, dev);
     const Tensor h = out(a[4], {G}, at::kFloat, dev, "h"), rs = out(a[5], {N}, at::kInt, dev, "rs_w");
@@ -517,7 +525,7 @@ struct Bwd {
     int64_t T, N, K;
     Tensor dX, dW, workspace;
     // the outputs wanted and the workspace; each the caller's or new
-    Bwd(PyObject *dy, PyObject *xq) : dY(matrix(dy, at::kBFloat16, "dY")), Xq(matrix(xq, at::kChar, "Xq"))
+    Bwd(PyObject *dy, PyObject *xq) : dY(matrix(dy, at::kBFloat16, "dY")), Xq(leading(xq, at::kChar, "Xq", 2))
     {
         T = dY.size(0);
         N = dY.size(1);
@@ -616,8 +624,8 @@ QB_CALL(embedding_quantize_bits, 6)  // E, bits, groups, codes, h, m
 QB_CALL(embedding_gather_bits, 6)  // codes, h, bits, groups, ids, out
 {
     const int bits = small(a[2]), groups = small(a[3]);
-    const Tensor &codes = matrix(a[0], at::kByte, "codes"), &ids = typed(a[4], at::kLong, "ids");
-    const int64_t V = codes.size(0), d = bits > 0 ? codes.size(1) * 8 / bits : 0, n = ids.dim() ? ids.size(0) : 0;
+    const Tensor &codes = leading(a[0], at::kByte, "codes", 2), &ids = leading(a[4], at::kLong, "ids", 1);
+    const int64_t V = codes.size(0), d = bits > 0 ? codes.size(1) * 8 / bits : 0, n = ids.size(0);
     const Tensor o = out(a[5], {n, d}, at::kFloat, codes.device(), "out");
     call(qb_embedding_gather_bits, ptr<uint8_t>(codes), ptr<float>(a[1], "h"), V, d, bits, groups, ptr<int64_t>(ids), n, ptr<float>(o),
                                    stream());

@@ -177,3 +177,23 @@ def test_jobs_of_any_mapping(qb, form):
     if not named:
         Y = qb.qb_qlinear_fwd_batched([form(Xq=act[0], rs_x=act[1], clip=3.0, packed=weights[0], h=h, rs_w=weights[3], bits=4, groups=2, N=64)])[0]
         assert torch.equal(Y, qb.qb_qlinear_fwd(*act, 3.0, weights[0], h, weights[3], 4, 2, 64))
+
+
+@pytest.mark.gpu
+def test_dimensions_that_are_read(qb):
+    """Only the first dimensions of the backward's codes and of an embedding table are read; ids and ranges need one."""
+    W, X = torch.randn(64, 128, device="cuda"), torch.randn(8, 128, device="cuda")
+    packed, h, m, _ = qb.qb_quantize_groupwise(W, 4, 2)
+    Xq, _ = qb.qb_quantize_act(X, 3.0)
+    dY = torch.randn(8, 64, device="cuda").to(torch.bfloat16)
+    for a, b in zip(qb.qb_qlinear_bwd_ste(dY, Xq[:, :, None], 3.0, packed, h, 4, 2), qb.qb_qlinear_bwd_ste(dY, Xq, 3.0, packed, h, 4, 2)):
+        assert torch.equal(a, b)
+    codes, eh, _ = qb.qb_embedding_quantize_bits(W, 8, 2)
+    ids = torch.tensor([5, 0], device="cuda")
+    assert torch.equal(qb.qb_embedding_gather_bits(codes[:, :, None], eh, 8, 2, ids), qb.qb_embedding_gather_bits(codes, eh, 8, 2, ids))
+    with pytest.raises(IndexError):
+        qb.qb_embedding_gather_bits(codes, eh, 8, 2, ids[0])
+    with pytest.raises(IndexError):
+        qb.qb_quantize_groupwise_clip(W, 4, m[0])
+    with pytest.raises(IndexError):
+        qb.qb_qlinear_bwd_ste(dY, Xq[0], 3.0, packed, h, 4, 2)
