@@ -352,11 +352,11 @@ def qb_unpack_codes(packed, N, K, bits, codes=None):
 
 
 def qb_embedding_quantize(E, groups, codes=None, h=None, m=None):
-    return qb_embedding_quantize_bits(E, 8, groups, codes, h, m)
+    return _native().embedding_quantize(E, groups, codes, h, m)
 
 
 def qb_embedding_gather(codes, h, groups, ids, out=None):
-    return qb_embedding_gather_bits(codes, h, 8, groups, ids, out)
+    return _native().embedding_gather(codes, h, groups, ids, out)
 
 
 def qb_embedding_quantize_bits(E, bits, groups, codes=None, h=None, m=None):

@@ -609,29 +609,63 @@ QB_CALL(qlinear_bwd_ste_asym, 13)  // dY, Xq, clip, packed, delta, q0, bits, gro
 
 // ---- embedding
 
+// the 8-bit table's entry points, or with bits those for either width
+template <typename F>
+PyObject *embedding_quantize_with(const F &entry, int64_t bits, int groups, PyObject *e, PyObject *given_codes, PyObject *given_h, PyObject *given_m)
+{
+    const Tensor &E = matrix(e, at::kFloat, "E");
+    const int64_t V = E.size(0), d = E.size(1);
+    const at::Device dev = E.device();
+    const Tensor codes = out(given_codes, {V, d * bits / 8}, at::kByte, dev, "codes");
+    const Tensor h = out(given_h, {groups > 0 ? groups : 1}, at::kFloat, dev, "h"), m = out(given_m, {groups > 0 ? groups : 1}, at::kFloat, dev, "m");
+    entry(ptr<float>(E), V, d, ptr<uint8_t>(codes), ptr<float>(h), ptr<float>(m));
+    return tuple({codes, h, m});
+}
+
+template <typename F>
+PyObject *embedding_gather_with(const F &entry, int bits, const Tensor &codes, PyObject *given_ids, PyObject *given_out)
+{
+    const Tensor &ids = leading(given_ids, at::kLong, "ids", 1);
+    const int64_t V = codes.size(0), d = bits > 0 ? codes.size(1) * 8 / bits : 0, n = ids.size(0);
+    const Tensor o = out(given_out, {n, d}, at::kFloat, codes.device(), "out");
+    entry(V, d, ptr<int64_t>(ids), n, ptr<float>(o));
+    PyObject *v = THPVariable_Wrap(o);
+    if (!v) throw_python_error();
+    return v;
+}
+
+QB_CALL(embedding_quantize, 5)  // E, groups, codes, h, m
+{
+    const int groups = small(a[1]);
+    return embedding_quantize_with([&](const float *E, int64_t V, int64_t d, uint8_t *codes, float *h, float *m) {
+        call(qb_embedding_quantize, E, V, d, groups, codes, h, m, stream());
+    }, 8, groups, a[0], a[2], a[3], a[4]);
+}
+
 QB_CALL(embedding_quantize_bits, 6)  // E, bits, groups, codes, h, m
 {
     const int bits = small(a[1]), groups = small(a[2]);
-    const Tensor &E = matrix(a[0], at::kFloat, "E");
-    const int64_t V = E.size(0), d = E.size(1);
-    const at::Device dev = E.device();
-    const Tensor codes = out(a[3], {V, d * bits / 8}, at::kByte, dev, "codes");
-    const Tensor h = out(a[4], {groups > 0 ? groups : 1}, at::kFloat, dev, "h"), m = out(a[5], {groups > 0 ? groups : 1}, at::kFloat, dev, "m");
-    call(qb_embedding_quantize_bits, ptr<float>(E), V, d, bits, groups, ptr<uint8_t>(codes), ptr<float>(h), ptr<float>(m), stream());
-    return tuple({codes, h, m});
+    return embedding_quantize_with([&](const float *E, int64_t V, int64_t d, uint8_t *codes, float *h, float *m) {
+        call(qb_embedding_quantize_bits, E, V, d, bits, groups, codes, h, m, stream());
+    }, bits, groups, a[0], a[3], a[4], a[5]);
+}
+
+QB_CALL(embedding_gather, 5)  // codes, h, groups, ids, out
+{
+    const int groups = small(a[2]);
+    const Tensor &codes = matrix(a[0], at::kByte, "codes");
+    return embedding_gather_with([&](int64_t V, int64_t d, const int64_t *ids, int64_t n, float *o) {
+        call(qb_embedding_gather, ptr<uint8_t>(codes), ptr<float>(a[1], "h"), V, d, groups, ids, n, o, stream());
+    }, 8, codes, a[3], a[4]);
 }
 
 QB_CALL(embedding_gather_bits, 6)  // codes, h, bits, groups, ids, out
 {
     const int bits = small(a[2]), groups = small(a[3]);
-    const Tensor &codes = leading(a[0], at::kByte, "codes", 2), &ids = leading(a[4], at::kLong, "ids", 1);
-    const int64_t V = codes.size(0), d = bits > 0 ? codes.size(1) * 8 / bits : 0, n = ids.size(0);
-    const Tensor o = out(a[5], {n, d}, at::kFloat, codes.device(), "out");
-    call(qb_embedding_gather_bits, ptr<uint8_t>(codes), ptr<float>(a[1], "h"), V, d, bits, groups, ptr<int64_t>(ids), n, ptr<float>(o),
-                                   stream());
-    PyObject *v = THPVariable_Wrap(o);
-    if (!v) throw_python_error();
-    return v;
+    const Tensor &codes = leading(a[0], at::kByte, "codes", 2);
+    return embedding_gather_with([&](int64_t V, int64_t d, const int64_t *ids, int64_t n, float *o) {
+        call(qb_embedding_gather_bits, ptr<uint8_t>(codes), ptr<float>(a[1], "h"), V, d, bits, groups, ids, n, o, stream());
+    }, bits, codes, a[4], a[5]);
 }
 
 PyObject *set_error(PyObject *, PyObject *cls)
@@ -648,7 +682,8 @@ PyMethodDef g_methods[] = {
     QB_ENTRY(qlinear_fwd_batched), QB_ENTRY(quantize_act), QB_ENTRY(quantize_act_dyn), QB_ENTRY(quantize_act_dyn_tensor),
     QB_ENTRY(qlinear_fwd), QB_ENTRY(qlinear_fwd_dyn), QB_ENTRY(qlinear_fwd_asym), QB_ENTRY(qlinear_fwd_asym_dyn),
     QB_ENTRY(qlinear_fwd_q8), QB_ENTRY(qlinear_bwd_ste), QB_ENTRY(qlinear_bwd_ste_static), QB_ENTRY(qlinear_bwd_ste_masked),
-    QB_ENTRY(qlinear_bwd_ste_asym), QB_ENTRY(embedding_quantize_bits), QB_ENTRY(embedding_gather_bits),
+    QB_ENTRY(qlinear_bwd_ste_asym), QB_ENTRY(embedding_quantize), QB_ENTRY(embedding_quantize_bits), QB_ENTRY(embedding_gather),
+    QB_ENTRY(embedding_gather_bits),
     {"set_error", set_error, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};

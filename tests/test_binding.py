@@ -41,31 +41,33 @@ calls = [
     lambda: qb.qb_qlinear_fwd_q8(*f, 6.0), lambda: qb.qb_qlinear_bwd_ste(dy, q, 6.0, p, g, 8, 1),
     lambda: qb.qb_qlinear_bwd_ste_static(dy, q, 6.0, p, g, 8, 1), lambda: qb.qb_qlinear_bwd_ste_masked(dy, q, 6.0, p, g, 8, 1),
     lambda: qb.qb_qlinear_bwd_ste_asym(dy, q, 6.0, p, g, g, 8, 1), lambda: qb.qb_embedding_quantize_bits(x, 8, 1),
-    lambda: qb.qb_embedding_gather_bits(p, g, 8, 1, ids)]
+    lambda: qb.qb_embedding_gather_bits(p, g, 8, 1, ids), lambda: qb.qb_embedding_quantize(x, 1), lambda: qb.qb_embedding_gather(p, g, 1, ids)]
 for c in calls: c()
-print(len(calls), marks.qb_test_calls(), marks.qb_test_locked())
+names = [n for n in qb.EXPORTS if hasattr(marks, "qb_test_made_" + n) and getattr(marks, "qb_test_made_" + n)()]
+print(len(calls), marks.qb_test_calls(), len(names), marks.qb_test_locked())
 '''
 
 
 @pytest.mark.gpu
 def test_library_is_called_without_the_interpreter_lock(qb, tmp_path):
-    """Every call of the binding gives up the interpreter lock around the C entry point, as a call through ctypes does.  The
-    binding's native half runs in a process of its own against a stand-in of the library that launches nothing and counts the
-    calls that come with the lock."""
+    """Every call of the binding gives up the interpreter lock around the C entry point, as a call through ctypes does, and calls
+    the entry point of its own name.  The binding's native half runs in a process of its own against a stand-in of the library
+    that launches nothing, notes which entry points were called and counts the calls that come with the lock."""
     names = [n for n in qb.EXPORTS if n not in ("qb_status_string", "qb_packed_nbytes", "qb_bwd_workspace_nbytes")]
     source = tmp_path / "stub.c"
     source.write_text("extern int PyGILState_Check(void);\nstatic int calls, locked;\nint qb_test_calls(void) { return calls; }\n"
                       "int qb_test_locked(void) { return locked; }\nconst char *qb_status_string(int s) { return \"\"; }\n"
                       "unsigned long qb_packed_nbytes() { return 4096; }\nunsigned long qb_bwd_workspace_nbytes() { return 4096; }\n"
-                      + "".join("int %s() { ++calls; locked += PyGILState_Check(); return 0; }\n" % n for n in names))
+                      + "".join("static int made_%s;\nint qb_test_made_%s(void) { return made_%s; }\n"
+                                "int %s() { ++calls; ++made_%s; locked += PyGILState_Check(); return 0; }\n" % ((n,) * 5) for n in names))
     stub, native = str(tmp_path / "libqbert.so"), str(tmp_path / "_calls.so")   # (the native half looks for the library beside itself)
     subprocess.run(["gcc", "-shared", "-fPIC", "-w", str(source), "-o", stub], check=True)
     shutil.copy(paper_1909_05840_amd.binding.CALLS_PATH, native)
     print("calls without the interpreter lock", flush=True)
     r = subprocess.run([sys.executable, "-c", UNLOCKED_CALLS, stub, native], cwd=ROOT, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stderr[-2000:]
-    made, seen, locked = map(int, r.stdout.split()[-3:])
-    assert made == seen > 0 and locked == 0
+    made, seen, entries, locked = map(int, r.stdout.split()[-4:])
+    assert made == seen == entries > 0 and locked == 0
 
 
 # every single call with a number in each place that takes a whole one; the tensors are looked at after the numbers
@@ -87,6 +89,8 @@ WHOLE_NUMBERS = [
     ("qlinear_bwd_ste_asym", lambda qb, t, n: qb.qb_qlinear_bwd_ste_asym(t, t, 6.0, t, t, t, 4, n)),
     ("embedding_quantize_bits", lambda qb, t, n: qb.qb_embedding_quantize_bits(t, n, 1)),
     ("embedding_gather_bits", lambda qb, t, n: qb.qb_embedding_gather_bits(t, t, 8, n, t)),
+    ("embedding_quantize", lambda qb, t, n: qb.qb_embedding_quantize(t, n)),
+    ("embedding_gather", lambda qb, t, n: qb.qb_embedding_gather(t, t, n, t)),
 ]
 
 
