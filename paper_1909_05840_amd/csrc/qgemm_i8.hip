@@ -25,9 +25,10 @@
 //   qgemm_i8_split_kernel the smallest problems: the contraction sliced inside the workgroup, no LDS in the loop.
 //   qgemm_i8_duo_kernel the largest problems at 2, 3 and 4 bits: 128x256 tiles on the 16x16x64 MFMA, two independent
 //                       workgroups per CU that multiply and write out in turn.
-// In all of them the token tile sits in LDS as dense 128-byte rows whose 16-byte chunks are XOR-swizzled by the
-// row number, so that the MFMA fragment reads are free of bank conflicts, and the k-bit codes are expanded to
-// int8 with a few byte-parallel shifts and masks in registers, right in front of the MFMA that consumes them.
+// In all of them but the split kernel, whose operands go straight to registers, the token tile sits in LDS as dense
+// 128-byte rows whose 16-byte chunks are XOR-swizzled by the row number, so that the MFMA fragment reads are free of bank
+// conflicts; and in all of them the k-bit codes are expanded to int8 with a few byte-parallel shifts and masks in registers,
+// right in front of the MFMA that consumes them.
 // Workgroups are renumbered so that the ones sharing a token panel run on the same XCD (same L2).
 #include "qb_common.hpp"
 
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_i8_kernel(
 // its operands straight into registers in the layout of the MFMA (no LDS and no barrier in the loop), and the slices' integer
 // sums meet in LDS; the write-out is split over the wavefronts as well.  Integer sums: the order does not matter, the
 // results are the ones of the other kernels bit for bit.  The direct loads touch 32 rows per instruction, so that with
-// more workgroups than CUs the kernel above is ahead again (see launch_bits).
+// more workgroups than CUs the kernel above is ahead again, as it is with contractions of a few steps (see split_shape).
 struct SmallProblem {
     const int8_t *Xq;
     const int32_t *rs_x;
@@ -1394,6 +1395,9 @@ __global__ __launch_bounds__(64 * (WM * WN + NPROD), (SIMD3 && OUT != 2 && NSTAG
 // workgroup per CU, two groups of wavefronts half a phase apart) have the same K-loop, but a tile's write-out then runs
 // next to nothing: 188 and 118 us.  A second barrier per step that frees the stage earlier (copies two steps ahead) and
 // lines touched ahead of the copies were slower (188 and 120; 188 and 124).
+// That is the 2-bit build.  At 3 and 4 bits one vector register does not fit, and its reload in front of the write-out waits
+// for the next tile's copies before the first store goes out: 4096 x 1024 165 and 155 us, 1024 x 4096 129 and 116, to 148 and 110 at
+// 2 bits (with the tokens in the last-level cache).
 struct DuoArgs {
     const int8_t *Xq;
     const int32_t *rs_x;
@@ -1803,7 +1807,7 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
     const long tiles128 = (long)((T + 127) / 128) * ((N + 127) / 128);
     if (tiles128 <= 160) {
         // Few tiles (small token counts, the inference regime): the persistent kernels below leave most CUs idle
-        // and pay ~6.5 us at least; 32x64 tiles of the register-staged kernel spread the work over the chip
+        // and pay ~6.5 us at least; 32x64 tiles, sliced (split_shape) or of the register-staged kernel, spread the work over the chip
         // (measured 4.4-5 us against 8 at T <= 1024, N = 768; 6.8 against 8.4 at 1024 x 2304 x 768; equal
         // at about 190 tiles).  Long contractions take 256 features per step.
         const SmallProblem sp{Xq, rs_x, packed, h, rs_w, bias, Y, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64};

@@ -376,8 +376,8 @@ def test_forward_plain_call_matches_checked_call(qb, bits, shape):
     path) must give bit for bit the Y of the call with the debug output (every element checked), which the
     other tests compare with the oracle.  The shapes walk through every branch of the tile dispatch: 128x96
     tiles on three SIMDs, role-split 128x128, two plain workgroups per CU, the register-staged kernel with
-    128x128 tiles for K not a multiple of 128 and with 32x64 tiles (64, 128 and 256 features per step) for
-    problems of few tiles, ragged T and N, N not a multiple of 4; with and without bias."""
+    128x128 tiles for K not a multiple of 128 and with 32x64 tiles (64 and 128 features per step; 256:
+    test_forward_few_tile_kernels) for problems of few tiles, the sliced one for those with long contractions, ragged T and N, N not a multiple of 4; with and without bias."""
     T, N, K = shape
     G = 128 if N % 128 == 0 else (N // 2 if N % 2 == 0 else 1)
     say("fwd plain vs checked", shape, "bits", bits)
@@ -489,8 +489,8 @@ def test_quantize_act_dynamic(qb, shape):
                                    (2048, 1024, 128, 128), (2304, 1536, 128, 128), (4096, 768, 128, 128),
                                    (4096, 768, 192, 128)])
 def test_forward_dynamic_scales(qb, bits, shape):
-    """Per-token scales through every kernel that takes them (32x64 register-staged tiles, the 128x128 one for K not a
-    multiple of 128, both role-split layouts), ragged T and N, with and without bias."""
+    """Per-token scales through every kernel that takes them (32x64 register-staged tiles, sliced contractions, the 128x128
+    one for K not a multiple of 128, both role-split layouts), ragged T and N, with and without bias."""
     T, N, K, G = shape
     say("fwd dynamic", shape, "bits", bits)
     W = wl.weight_uniform(N, K, seed=17 * N + K + bits, lo=-0.1, hi=0.1)
@@ -810,7 +810,7 @@ def test_quantize_asymmetric_ranges(qb, bits, shape):
                                    (2048, 1024, 128, 128), (2304, 1536, 128, 128), (4096, 768, 256, 128), (100, 96, 2048, 96)])
 def test_forward_asymmetric_ranges(qb, bits, shape):
     """Y against the oracle within 1e-6 of h_x*(Delta*|S| + |q0|*|R|) (the two products that are added), A4 bit for
-    bit; through the register-staged kernel (few tiles, K not a multiple of 128) and both role-split layouts; ragged
+    bit; through the register-staged kernel (few tiles, K not a multiple of 128), the sliced one and both role-split layouts; ragged
     T and N; with bias."""
     T, N, K, G = shape
     say("fwd asym", shape, "bits", bits)

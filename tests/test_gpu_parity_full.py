@@ -467,8 +467,8 @@ def _shifted_weight(N, K, G, seed):
 @pytest.mark.parametrize("shape", [(300, 160, 192, 8), (1, 32, 64, 1), (129, 130, 320, 10), (513, 768, 768, 128),
                                    (2048, 1024, 128, 128), (2304, 1536, 128, 128), (4096, 768, 256, 128)])
 def test_forward_asymmetric_ranges_with_per_token_scales(qb, bits, shape):
-    """qb_qlinear_fwd_asym_dyn: asymmetric group ranges and one activation scale per token, through the register-staged
-    kernel and both role-split layouts, ragged T and N, with and without bias; rows of very different magnitude and an
+    """qb_qlinear_fwd_asym_dyn: asymmetric group ranges and one activation scale per token, through the few-tile kernels (the
+    stepped and the sliced one) and both role-split layouts, ragged T and N, with and without bias; rows of very different magnitude and an
     all-zero row.  Y against the oracle within 1e-6 of h_x[t]*(Delta*|S| + |q0|*|R|), A4 bit for bit; a constant scale
     vector gives the fixed-clip call's bits."""
     T, N, K, G = shape
@@ -513,15 +513,16 @@ def test_forward_asymmetric_ranges_with_per_token_scales(qb, bits, shape):
 
 
 def test_forward_batched_few_token_jobs_share_launches(qb):
-    """The inference regime: few-token problems of a batched call go through shared launches of the 32x64-tile kernel
-    (one per bit-width and step width).  More jobs of one kind than a launch takes, all three step widths (K = 192,
-    768, 3072), ragged T and N, with and without bias: every Y element by element against the oracle, pre-filled
-    outputs fully written."""
+    """The inference regime: few-token problems of a batched call go through shared launches (one per bit-width and
+    kernel).  At 4 bits 21 jobs with more tiles than CUs: the stepped kernel in its three step widths (K = 192, 768, 3072);
+    at the other widths the seven jobs take the sliced kernel.  Ragged T and N, with and without bias: every Y element by
+    element against the oracle, pre-filled outputs fully written.  (More jobs than a launch takes:
+    test_forward_batched_few_tile_kernels.)"""
     jobs, refs = [], []
     shapes = [(1, 768, 768), (8, 2304, 768), (64, 3072, 768), (128, 768, 3072), (33, 130, 192), (100, 96, 3072), (5, 64, 64)]
     case = 0
     for bits in BITS:
-        for rep in range(3 if bits == 4 else 1):        # 21 jobs at 4 bits: more than one launch holds
+        for rep in range(3 if bits == 4 else 1):        # 21 jobs and 621 tiles at 4 bits, 7 and 207 at the others
             for (T, N, K) in shapes:
                 groups = G if N % G == 0 else (N // 2 if N % 2 == 0 else 1)
                 d = quantized_inputs(qb, N, K, T, bits, seed=31 * N + K + T + bits + 7 * rep, groups=groups)
@@ -574,8 +575,8 @@ def test_forward_whole_output_large_tiles(qb, bits, shape):
     assert (np.abs(Y.cpu().numpy().astype(np.float64) - (Yo + b)) <= 1e-6 * np.abs(Yo) + 2.0 ** -23 * np.abs(Yo + b)).all()
 
 
-# K of one unit of 64 features (three of the four slices empty) up to uneven eighths; one token, one more than a tile of
-# 32; neuron counts around the tile of 64
+# K of three units of 64 features (five of the eight slices empty) up to uneven eighths; one token, one more than a tile of
+# 32; neuron counts around the tile of 64; beside them the shortest contractions, which the stepped kernel takes
 @pytest.mark.parametrize("bits", BITS)
 @pytest.mark.parametrize("shape", [(1, 1, 64), (33, 65, 128), (31, 63, 192), (32, 64, 320), (70, 130, 832), (33, 96, 1984), (33, 66, 2048), (5, 33, 2112)])
 def test_forward_few_tokens_slices_of_the_contraction(qb, bits, shape):
