@@ -423,11 +423,15 @@ __device__ __forceinline__ void qgemm_i8_split_body(const SmallProblem &p, int32
     }
 }
 
+struct SplitCall {  // one kernel argument: as four they cost 0.3 us of host time a call
+    SmallProblem p;
+    int32_t *A4out;
+    const float *hx_rows, *q0;
+};
 template <int BITS>
-__global__ __launch_bounds__(512) void qgemm_i8_split_kernel(const SmallProblem p, int32_t *__restrict__ A4out,
-                                                             const float *__restrict__ hx_rows, const float *__restrict__ q0)
+__global__ __launch_bounds__(512) void qgemm_i8_split_kernel(const SplitCall c)
 {
-    qgemm_i8_split_body<BITS>(p, A4out, hx_rows, q0, blockIdx.x);
+    qgemm_i8_split_body<BITS>(c.p, c.A4out, c.hx_rows, c.q0, blockIdx.x);
 }
 
 // Several few-tile problems (small token counts: the inference regime, where a launch costs more than its work) in one
@@ -1810,9 +1814,9 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
         // and pay ~6.5 us at least; 32x64 tiles, sliced (split_shape) or of the register-staged kernel, spread the work over the chip
         // (measured 4.4-5 us against 8 at T <= 1024, N = 768; 6.8 against 8.4 at 1024 x 2304 x 768; equal
         // at about 190 tiles).  Long contractions take 256 features per step.
-        const SmallProblem sp{Xq, rs_x, packed, h, rs_w, bias, Y, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64};
-        const int tiles = sp.tiles_m * sp.tiles_n;
-        if (split_shape(tiles, T, K)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sp, A4, hx_rows, q0);
+        const SplitCall sc{{Xq, rs_x, packed, h, rs_w, bias, Y, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64}, A4, hx_rows, q0};
+        const int tiles = sc.p.tiles_m * sc.p.tiles_n;
+        if (split_shape(tiles, T, K)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sc);
         else if (stepped_units(K) == 4) launch_cfg<BITS, 1, 1, 1, 2, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         else if (stepped_units(K) == 2) launch_cfg<BITS, 1, 1, 1, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         else launch_cfg<BITS, 1, 1, 1, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
