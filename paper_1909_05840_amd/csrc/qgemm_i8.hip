@@ -1826,7 +1826,7 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
         launch_cfg<BITS, 2, 2, 2, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
         return;
     }
-    if (!hx_rows && !q0 && duo_shape<BITS>(T, N, K)) {
+    if (!hx_rows && !q0 && duo_shape<BITS>(T, N, K)) {  // (its epilogue has neither per-token scales nor asymmetric ranges)
         launch_duo<BITS>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st);
         return;
     }
