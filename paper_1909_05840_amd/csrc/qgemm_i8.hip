@@ -423,10 +423,12 @@ __device__ __forceinline__ void qgemm_i8_split_body(const SmallProblem &p, int32
     }
 }
 
-struct SplitCall {  // one kernel argument: as four they cost 0.3 us of host time a call
-    SmallProblem p;
+// One kernel argument: as four they cost 0.3 us of host time a call.  In this order the compiler loads all of it at the start; with
+// the problem first it fetched the pointers behind it when they were needed, in front of the contraction.
+struct SplitCall {
     int32_t *A4out;
     const float *hx_rows, *q0;
+    SmallProblem p;
 };
 template <int BITS>
 __global__ __launch_bounds__(512) void qgemm_i8_split_kernel(const SplitCall c)
@@ -1814,7 +1816,7 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
         // and pay ~6.5 us at least; 32x64 tiles, sliced (split_shape) or of the register-staged kernel, spread the work over the chip
         // (measured 4.4-5 us against 8 at T <= 1024, N = 768; 6.8 against 8.4 at 1024 x 2304 x 768; equal
         // at about 190 tiles).  Long contractions take 256 features per step.
-        const SplitCall sc{{Xq, rs_x, packed, h, rs_w, bias, Y, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64}, A4, hx_rows, q0};
+        const SplitCall sc{A4, hx_rows, q0, {Xq, rs_x, packed, h, rs_w, bias, Y, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64}};
         const int tiles = sc.p.tiles_m * sc.p.tiles_n;
         if (split_shape(tiles, T, K)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sc);
         else if (stepped_units(K) == 4) launch_cfg<BITS, 1, 1, 1, 2, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
