@@ -14,6 +14,7 @@
 // or more workgroups worked on has its partial sums added in a fixed order, so results do not change from run
 // to run.
 #include "qb_common.hpp"
+#include "bwd_direct.hpp"
 #include <mutex>
 
 namespace qb {
@@ -872,9 +873,17 @@ static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const
     if (!dX && !dW) return QB_OK;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return QB_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const int rpg = (int)(N / groups);
+    const int teams = bwd_direct_teams(T, N, K, dX != nullptr, dW != nullptr);
+    if (teams && ((reinterpret_cast<uintptr_t>(dY) | reinterpret_cast<uintptr_t>(packed)) & 15) == 0 && (reinterpret_cast<uintptr_t>(Xq) & 1) == 0) {
+        DirectArgs d = {};
+        d.dY = dY; d.Xq = Xq; d.packed = static_cast<const uint8_t *>(packed); d.h = h; d.q0 = q0; d.X = X; d.W = W; d.m = m;
+        d.dX = dX; d.dW = dW; d.T = (int)T; d.N = (int)N; d.K = (int)K; d.rows_per_group = rpg; d.clip = clip; d.scale = clip / 255.0f;
+        bwd_direct_run(d, teams, bits, st);
+        return launch_status();
+    }
     const BwdPlan p = make_plan(T, N, K);
     uint8_t *ws = static_cast<uint8_t *>(workspace);
-    const int rpg = (int)(N / groups);
     const int Np = (int)p.Np, Tp = (int)p.Tp;
 
     uint16_t *WT = reinterpret_cast<uint16_t *>(ws + p.off_wt);

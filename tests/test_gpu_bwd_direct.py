@@ -1,0 +1,86 @@
+"""The backward's one-launch kernel for small calls (N a multiple of 64) at the edges of its tiles and steps, for one, two
+and four teams per workgroup, against the oracle and against the staged kernels."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1909_05840_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+CLIP = 6.0
+
+
+def bounds(dY, W_hat, x_hat):
+    """per element: bf16 rounding of the de-quantized weights and of the result; fp32 sums of exact products"""
+    a = np.abs(dY.float().numpy().astype(np.float64))
+    return 2.0 ** -8 * (a @ np.abs(W_hat)), 2.0 ** -12 * (a.T @ np.abs(x_hat))
+
+
+def behind(t, elements):
+    """the same values in memory that starts `elements` elements behind an allocation's start"""
+    buf = torch.empty(t.numel() + elements, dtype=t.dtype, device=DEV)
+    view = buf[elements:].view(t.shape)
+    view.copy_(t)
+    return view
+
+
+# (T, N, K, groups): one step and one tile; one row beyond a step or tile, one short of it; contractions of 1..9 steps in
+# one direction and up to 36 in the other, so that teams end with and without a last step; rows per group 1, 3, 6, N
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("shape", [(64, 64, 64, 64), (65, 128, 64, 1), (127, 192, 128, 64), (193, 64, 320, 8), (130, 2304, 64, 384),
+                                   (577, 448, 192, 64), (1001, 448, 448, 64), (600, 768, 768, 128), (2111, 64, 128, 1)])
+def test_one_launch_backward(qb, bits, shape):
+    T, N, K, G = shape
+    print("bwd direct", shape, bits, flush=True)
+    W = wl.weight(N, K, seed=N + K + bits)
+    X = wl.activation(T, K, seed=T + bits)
+    X[0, 0], X[T - 1, K - 1] = CLIP, -100.0
+    dY = wl.grad_output_bf16(T, N, seed=T + N)
+    Wd, Xd, dYd = W.to(DEV), X.to(DEV), dY.to(DEV)
+    packed, h, m, _ = qb.qb_quantize_groupwise(Wd, bits, G)
+    Xq, _ = qb.qb_quantize_act(Xd, CLIP)
+    dX, dW = qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G)
+    sX, sW = qb.qb_qlinear_bwd_ste(behind(dYd, 4), Xq, CLIP, packed, h, bits, G)  # (8-byte aligned: staged)
+    mX, mW = qb.qb_qlinear_bwd_ste_masked(dYd, Xq, CLIP, packed, h, bits, G, X=Xd, W=Wd, m=0.5 * m)
+    oX = behind(torch.empty(T, K, dtype=torch.bfloat16, device=DEV), 1)
+    oW = behind(torch.empty(N, K, device=DEV), 1)
+    qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, dX=oX, dW=oW)
+    torch.cuda.synchronize()
+    oc, oh, om, _ = oracle.quantize_groupwise(W.numpy(), bits, G)
+    oq, _ = oracle.quantize_act(X.numpy(), CLIP)
+    rX, rW = oracle.qlinear_bwd_ste(wl.bf16_bits(dY), oq, CLIP, oc, oh, bits, openmp=True)
+    tX, tW = bounds(dY, oracle.dequantize_groupwise(oc, oh, bits), oracle.dequantize_act(oq, CLIP))
+    for a, b in ((dX, dW), (sX, sW)):
+        a, b = a.float().cpu().numpy().astype(np.float64), b.cpu().numpy().astype(np.float64)
+        assert (np.abs(a - rX) <= 2.0 ** -8 * np.abs(rX) + tX).all() and (np.abs(b - rW) <= tW).all()
+    assert torch.equal(oX, dX) and torch.equal(oW, dW)
+    out_x, out_w = Xd.abs() > CLIP, Wd.abs() > (0.5 * m).repeat_interleave(N // G)[:, None]
+    assert bool(out_x[T - 1, K - 1]) and not bool(out_x[0, 0]) and bool(out_w.any())
+    assert torch.equal(mX, torch.where(out_x, torch.zeros_like(dX), dX)) and torch.equal(mW, torch.where(out_w, torch.zeros_like(dW), dW))
+    # one output only: another number of teams may be chosen, so only the bounds hold
+    a, none = qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, want_dw=False)
+    none2, b = qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, want_dx=False)
+    assert none is None and none2 is None
+    assert (np.abs(a.float().cpu().numpy() - rX) <= 2.0 ** -8 * np.abs(rX) + tX).all() and (np.abs(b.cpu().numpy() - rW) <= tW).all()
+
+
+@pytest.mark.parametrize("shape", [(65, 128, 64, 2), (577, 448, 192, 64)])
+def test_one_launch_backward_asymmetric(qb, shape):
+    T, N, K, G = shape
+    bits = 4
+    W = wl.weight(N, K, seed=N + K) + 0.05
+    X = wl.activation(T, K, seed=T)
+    dY = wl.grad_output_bf16(T, N, seed=T + N)
+    packed, delta, q0, _ = qb.qb_quantize_groupwise_asym(W.to(DEV), bits, G)
+    Xq, _ = qb.qb_quantize_act(X.to(DEV), CLIP)
+    dX, dW = qb.qb_qlinear_bwd_ste_asym(dY.to(DEV), Xq, CLIP, packed, delta, q0, bits, G)
+    torch.cuda.synchronize()
+    oc, od, oq0, _ = oracle.quantize_groupwise_asym(W.numpy(), bits, G)
+    oq, _ = oracle.quantize_act(X.numpy(), CLIP)
+    rX = oracle.qlinear_bwd_dx_asym(wl.bf16_bits(dY), oc, od, oq0, openmp=True)
+    _, rW = oracle.qlinear_bwd_ste(wl.bf16_bits(dY), oq, CLIP, oc, np.ones(G, np.float32), bits, want_dx=False, openmp=True)
+    tX, tW = bounds(dY, oracle.dequantize_groupwise_asym(oc, od, oq0), oracle.dequantize_act(oq, CLIP))
+    assert (np.abs(dX.float().cpu().numpy() - rX) <= 2.0 ** -8 * np.abs(rX) + tX).all()
+    assert (np.abs(dW.cpu().numpy() - rW) <= tW).all()
