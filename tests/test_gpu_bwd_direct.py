@@ -66,6 +66,21 @@ def test_one_launch_backward(qb, bits, shape):
     assert (np.abs(a.float().cpu().numpy() - rX) <= 2.0 ** -8 * np.abs(rX) + tX).all() and (np.abs(b.cpu().numpy() - rW) <= tW).all()
 
 
+# (T, N, K): N a multiple of 8 only, T with and without rows beyond a multiple of 64, tiles of 128 x 96 and 128 x 192, columns
+# past the end of a tile
+@pytest.mark.parametrize("shape", [(65, 72, 64), (300, 136, 192), (640, 8, 128), (4099, 520, 1088), (4160, 520, 1088)])
+def test_turned_operand_gives_the_staged_operands_sums(qb, shape):
+    T, N, K = shape
+    dY = wl.grad_output_bf16(T, N, seed=T + N).to(DEV)
+    packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N, K, seed=N + K).to(DEV), 4, 8)
+    Xq, _ = qb.qb_quantize_act(wl.activation(T, K, seed=T).to(DEV), CLIP)
+    dX, dW = qb.qb_qlinear_bwd_ste(dY, Xq, CLIP, packed, h, 4, 8)
+    sX, sW = qb.qb_qlinear_bwd_ste(behind(dY, 4), Xq, CLIP, packed, h, 4, 8)
+    assert torch.equal(dX, sX) and torch.equal(dW, sW)
+    ref = dY.double().T @ ((2.0 * Xq.double() + 1.0) * (CLIP / 255.0))
+    assert (dW.double() - ref).norm() <= 1e-5 * ref.norm()  # fp32 sums of exact products
+
+
 @pytest.mark.parametrize("shape", [(65, 128, 64, 2), (577, 448, 192, 64)])
 def test_one_launch_backward_asymmetric(qb, shape):
     T, N, K, G = shape
