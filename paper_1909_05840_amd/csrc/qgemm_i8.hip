@@ -31,6 +31,7 @@
 // right in front of the MFMA that consumes them.
 // Workgroups are renumbered so that the ones sharing a token panel run on the same XCD (same L2).
 #include "qb_common.hpp"
+#include <type_traits>
 
 namespace qb {
 namespace {
@@ -961,14 +962,28 @@ __device__ __forceinline__ int logical_tile(int local, int nwg)
     return xcd * q + (xcd < r ? xcd : r) + idx;
 }
 
+// GELU(y) = y/2 * (1 + erf(y/sqrt(2))) = max(y, 0) - w/2 * E, w = |y|, E = erfc(w/sqrt(2)) = 2^(w*R(w)), to within 8e-7: R
+// is a polynomial of degree 4, fitted on [0, 5.5] for the smallest largest error of w/2 * E (5.4e-7; Lawson's reweighted
+// least squares), beyond which w/2 * E is less than 1.1e-7.  (y + |y|)/2 keeps infinities and NaN as the product has them.
+__device__ __forceinline__ float gelu_near(float y)
+{
+    const float w = fminf(fabsf(y), 5.5f);
+    float r = __builtin_fmaf(-0.0004881021741311997f, w, 0.0071987188421189785f);
+    r = __builtin_fmaf(r, w, -0.052146632224321365f);
+    r = __builtin_fmaf(r, w, -0.45959582924842834f);
+    r = __builtin_fmaf(r, w, -1.1510004997253418f);
+    const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(r, w, -1.0f));
+    return __builtin_fmaf(0.5f, y + fabsf(y), -(w * e));
+}
+
 // One 32x32 block of the 8-bit output: the value that decides the code is formed in binary32 with one
 // rounding per step, scale = h_x*h_g, y = scale*float(A4), y = y + bias; then the optional GELU, the clamp to
 // the output range and the activation quantizer.  The bytes go to the workgroup's staging tile in LDS
 // (BM rows of BN bytes), from where whole rows are written out.  Lane/register roles as in store_block_lds.
-template <int BM, int BN, int BNT>
+template <int BM, int BN, int BNT, int GELU>  // GELU: 0 none, 1 exact, 2 quick
 __device__ __forceinline__ void quant_block_lds(const v16i &acc, const uint8_t *pp, int e2, int tl, int nl, int K,
-                                                float hx, bool has_bias, const Quantizer &qo, int act,
-                                                uint8_t *stg)
+                                                float hx, bool has_bias, const Quantizer &qo,
+                                                uint8_t *stg, uint2 *list, int lane)
 {
     // (this file is compiled with -ffp-contract=off: y = scale*float(A4) and y + bias are two roundings)
     asm volatile("" : "+v"(tl));
@@ -987,29 +1002,88 @@ __device__ __forceinline__ void quant_block_lds(const v16i &acc, const uint8_t *
 #pragma unroll
         for (int i = 0; i < 4; ++i) y[4 * q + i] = scale * (float)qb_a4(acc[4 * q + i], qb_mad24(e2, rx[i], coln)) + bv;  // |rs_x| < 2^23
     }
-    if (act == 1) {
+    uint8_t *const dst = stg + tl * BNT + nl;
+    auto at = [&](int r) { return (8 * (r >> 2) + (r & 3)) * BNT; };
+    if constexpr (GELU == 0) {
+        // The quantizer (same steps as Quantizer::code_f) without a branch per element: the reciprocal route for
+        // all sixteen, and the true division for all sixteen if any lane's product came too close to a rounding
+        // boundary (about one block in five) or the range is too extreme for the reciprocal.
+        float s[16], rr[16];
+        bool redo = !qo.fast;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) y[r] = 0.5f * y[r] * (1.0f + erff(y[r] * 0.70710678118654752f));
+        for (int r = 0; r < 16; ++r) {
+            s[r] = __builtin_amdgcn_fmed3f(y[r], -c, c) + c;
+            const float tp = s[r] * qo.rinv;
+            rr[r] = rintf(tp);
+            redo |= !(fabsf(tp - rr[r]) <= 0.4999f);
+        }
+        if (__any(redo)) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) rr[r] = rintf(__fdiv_rn(s[r], qo.delta));
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dst[at(r)] = (uint8_t)(uint32_t)rr[r];  // the code u; u - 128 is formed on the way out
+        return;
     }
-    // The quantizer (same steps as Quantizer::code_f) without a branch per element: the reciprocal route for
-    // all sixteen, and the true division for all sixteen if any lane's product came too close to a rounding
-    // boundary (about one block in five) or the range is too extreme for the reciprocal.
-    float s[16], rr[16];
-    bool redo = !qo.fast;
+    // With GELU.  The exact steps are erff, the true division and a rounding; the quick ones gelu_near and the reciprocal,
+    // for all sixteen values without a branch.  They give the same code unless the quick product lies closer to a rounding
+    // boundary than the two routes can differ: 4.6e-5 for the division (derived at Quantizer), 1.6e-5 for the rounding of
+    // v + c, and 2e-6 in v for GELU (8e-7 of gelu_near, 7e-7 of the binary32 steps around erff).  The few such values
+    // (GELU's flat tail below -4.7 among them, where the code hangs on the last bits of erff) are gathered over the block
+    // and done exactly, 64 at a time.  A block with many of them, as a look at a quarter of its values tells before the
+    // quick steps, or a range too extreme for the reciprocal, goes through the exact steps.
+    // Feed-forward up (N 3072, K 768), where erff for every value bound the epilogue (some forty operations, both sides of
+    // its branch): 4096 tokens, 4 bits 38.8 -> 30.9 us; 12000 tokens, 8 bits 97 -> 74; 100 tokens 13.7 -> 12.4.  At 2 and 3
+    // bits the exact steps alone: the few levels have to reach the outliers of a group, so the pre-activations are wide
+    // and most blocks full of tails (with the quick steps 37.1 and, at 3584 x 896, 62.6 us, without 34.4 and 58.3; the
+    // exact steps one register at a time are also faster than a reciprocal pass with the division behind it: 37.3, 60.8).
+    auto exact = [&](float v) {
+        v = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
+        return (uint8_t)(uint32_t)rintf(__fdiv_rn(__builtin_amdgcn_fmed3f(v, -c, c) + c, qo.delta));
+    };
+    if constexpr (GELU == 2) {
+        int total = 0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        s[r] = __builtin_amdgcn_fmed3f(y[r], -c, c) + c;
-        const float tp = s[r] * qo.rinv;
-        rr[r] = rintf(tp);
-        redo |= !(fabsf(tp - rr[r]) <= 0.4999f);
+        for (int r = 0; r < 16; r += 4) total += 4 * __popcll(__ballot(y[r] < -4.7f));
+        if (qo.fast && total <= 64) {
+            uint64_t near[16];
+            const float lim = 0.49993f - 2.0e-6f * qo.rinv;
+            total = 0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float tp = (__builtin_amdgcn_fmed3f(gelu_near(y[r]), -c, c) + c) * qo.rinv, rr = rintf(tp);
+                near[r] = __ballot(!(fabsf(tp - rr) <= lim));
+                total += __popcll(near[r]);
+                dst[at(r)] = (uint8_t)(uint32_t)rr;
+            }
+            if (total == 0) return;
+            if (total <= 128) {
+                asm volatile("" ::: "memory");  // (a wavefront's LDS operations keep their order)
+                int n = 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (near[r]) {
+                        if ((near[r] >> lane) & 1) {
+                            const int k = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(near[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)near[r], 0));
+                            list[k] = make_uint2(__float_as_uint(y[r]), (uint32_t)(tl * BNT + nl + at(r)));
+                        }
+                        n += __popcll(near[r]);
+                    }
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_wave_barrier();
+#pragma clang loop unroll(disable)
+                for (int k = lane; k < total; k += 64) {
+                    const uint2 e = list[k];
+                    stg[e.y] = exact(__uint_as_float(e.x));
+                }
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_wave_barrier();
+                return;
+            }
+        }
     }
-    if (__any(redo)) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) rr[r] = rintf(__fdiv_rn(s[r], qo.delta));
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-        stg[(tl + 8 * (r >> 2) + (r & 3)) * BNT + nl] = (uint8_t)(uint32_t)rr[r];  // the code u; u - 128 is formed on the way out
+    for (int r = 0; r < 16; ++r) dst[at(r)] = exact(y[r]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1029,12 +1103,12 @@ __device__ __forceinline__ void quant_block_lds(const v16i &acc, const uint8_t *
 // OUTQ: instead of Y the tile is quantized to 8 bits (quant_block_lds) into an LDS staging tile and, after one
 // more barrier per tile (E, executed by the producers once the next tile's first copies are on their way), written
 // out in whole rows; the rows' sums are collected in LDS and added to rs_y one tile later.
-// OUT: 0 fp32 Y, 1 the 8-bit output (OUTQ), 2 fp32 Y from asymmetric group ranges (ASYM; a variant of its own so
+// OUT: 0 fp32 Y, 1 the 8-bit output (OUTQ), 3 the same with GELU, 2 fp32 Y from asymmetric group ranges (ASYM; a variant of its own so
 // that the others carry none of its code)
 template <int BITS, int TM, int TN, int WM, int WN, int NSTAGE, int NPROD, bool SIMD3, int OUT>
 __global__ __launch_bounds__(64 * (WM * WN + NPROD), (SIMD3 && OUT != 2 && NSTAGE == 2) ? 4 : 2) void qgemm_i8_ws_kernel(const Group g)
 {
-    constexpr bool OUTQ = OUT == 1, ASYM = OUT == 2;
+    constexpr bool OUTQ = OUT == 1 || OUT == 3, ASYM = OUT == 2;
     static_assert(NSTAGE >= 2 && NSTAGE <= 4, "ring of 2..4 stages");
     constexpr int NC = WM * WN;
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32, BK = 128;
@@ -1061,7 +1135,8 @@ __global__ __launch_bounds__(64 * (WM * WN + NPROD), (SIMD3 && OUT != 2 && NSTAG
     constexpr int NPARAM = 2;
 
     constexpr int STG_OFF = NSTAGE * STAGE_BYTES + NPARAM * PARAM_BYTES;  // staging tile, then BM row sums
-    constexpr int STG_BYTES = OUTQ ? BM * BN + BM * 4 : 0;
+    constexpr int LIST_OFF = STG_OFF + (OUTQ ? BM * BN + BM * 4 : 0);  // then up to 128 gathered values per MFMA wavefront
+    constexpr int STG_BYTES = OUTQ ? BM * BN + BM * 4 + (OUT == 3 && BITS >= 4 ? NC * 128 * 8 : 0) : 0;
     static_assert(STG_OFF % 16 == 0 && BN % 16 == 0 && BM <= NC * 64, "staging tile: 16-byte pieces, one thread per row sum");
     __shared__ __align__(1024) uint8_t lds[STG_OFF + STG_BYTES];
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
@@ -1210,6 +1285,7 @@ __global__ __launch_bounds__(64 * (WM * WN + NPROD), (SIMD3 && OUT != 2 && NSTAG
     const int ctid = cidx * 64 + lane;
     uint8_t *stg = lds + STG_OFF;
     int *rowsum = reinterpret_cast<int *>(lds + STG_OFF + BM * BN);
+    uint2 *near_list = reinterpret_cast<uint2 *>(lds + LIST_OFF) + cidx * 128;
     Quantizer qo;
     int prev_t0 = -1, prev_T = 0;  // the tile whose row sums still sit in LDS, and its problem's token count and rs_y
     int32_t *prev_rs_y = nullptr;
@@ -1325,9 +1401,9 @@ __global__ __launch_bounds__(64 * (WM * WN + NPROD), (SIMD3 && OUT != 2 && NSTAG
             for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
                 for (int tn = 0; tn < TN; ++tn)
-                    quant_block_lds<BM, BNP, BN>(acc[tm][tn], lds + NSTAGE * STAGE_BYTES + pb * PARAM_BYTES, E2,
+                    quant_block_lds<BM, BNP, BN, OUT != 3 ? 0 : BITS >= 4 ? 2 : 1>(acc[tm][tn], lds + NSTAGE * STAGE_BYTES + pb * PARAM_BYTES, E2,
                                                  (wm * TM + tm) * 32 + 4 * hf, (wn * TN + tn) * 32 + l32, K, hx,
-                                                 bias != nullptr, qo, oq.act, stg);
+                                                 bias != nullptr, qo, stg, near_list, lane);
             __builtin_amdgcn_s_waitcnt(0xC07F);  // the staging bytes are written
             QB_BARRIER()                         // barrier E
             // whole rows out: 16-byte pieces, BN/16 per row
@@ -1726,7 +1802,8 @@ void launch_ws_q8(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, 
     Group g;
     g.n = 0;
     group_add<BM, BN>(g, Xq, rs_x, packed, h, rs_w, bias, nullptr, nullptr, T, N, K, rpg, hx, oq);
-    launch_group<BITS, TM, TN, WM, WN, NSTAGE, NPROD, SIMD3, 1>(g, st, grid_cap);
+    if (oq.act == 1) launch_group<BITS, TM, TN, WM, WN, NSTAGE, NPROD, SIMD3, 3>(g, st, grid_cap);
+    else launch_group<BITS, TM, TN, WM, WN, NSTAGE, NPROD, SIMD3, 1>(g, st, grid_cap);
 }
 
 template <int BITS, int TM, int TN, int WM, int WN, int KU>
