@@ -218,7 +218,7 @@ __device__ __forceinline__ void wait_vmcnt()
 //   MFMA wavefronts: BARRIER; for s: multiply stage s % NSTAGE; wait until the stage's LDS reads have returned; BARRIER
 //
 // Division of the work.  The products of a call (dX, dW or both) form one sequence of units, a unit being one
-// 64-wide contraction step of one tile: problem after problem, tile after tile (the tiles of one row of tiles
+// 64-wide contraction step of one tile: problem after problem, tile after tile (the tiles of one row of a strip
 // next to each other), step after step.  The G workgroups of the launch (at most one per CU) cut the sequence
 // into G equal runs, so that every CU does the same number of steps whatever the tile counts and contraction
 // lengths are; workgroup b takes run v(b) = (b%8)*(G/8) + b/8, which gives each XCD (workgroups are dealt to
@@ -250,7 +250,8 @@ struct SkProblem {
     int out;       // 0: bf16 C, 1: fp32 C * scale
     float scale;
     void *C;
-    int tiles_n;   // tiles along Nc
+    int tiles_m, tiles_n;  // tiles along M and Nc
+    int strip;     // tiles of a strip (sk_place)
     int t_rows;    // 0, or A is dY as it lies in memory (rows along the contraction, t_rows of them)
     ClampMask mask;
 };
@@ -283,6 +284,19 @@ __device__ __forceinline__ SkPiece sk_piece_at(const SkGroup &g, long long u, lo
     q.s1 = (q.nsteps - q.s0 <= room) ? q.nsteps : q.s0 + (int)room;
     q.tile_first_unit = u - q.s0;
     return q;
+}
+
+// Where tile number t of a problem lies: strips of P.strip tiles' width, row after row.  Rows of sixteen tiles (768 x 3072)
+// made the CUs of an XCD share A panels only; in strips of four they share panels in both directions, which L2 has to fetch
+// once: 12288 tokens, 768 x 3072 163.8 -> 148.9 us a call, 960 x 3840 at 6000 tokens 144 -> 134.5, 1024 x 4096 at 8000
+// 198 -> 188.5.  Rows of fewer than twelve tiles stay whole: cut into four and a narrow rest they lose (six, 1024 x 1024 at
+// 8000 tokens: 62.5 -> 68.0; eleven, 2048 x 2048 at 3000 tokens: 68.9 -> 70.2) or gain nothing (eight: 44.7, 45.0).
+__device__ __forceinline__ void sk_place(const SkProblem &P, int t, int &tile_m, int &tile_n)
+{
+    const int per_strip = P.strip * P.tiles_m, col = t / per_strip, left = t - col * per_strip;
+    const int rest = P.tiles_n - P.strip * col, width = rest < P.strip ? rest : P.strip;
+    tile_m = left / width;
+    tile_n = P.strip * col + left - tile_m * width;
 }
 
 // Partial sums and flags travel between workgroups on different XCDs, whose L2 caches are not coherent with each
@@ -354,7 +368,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
         const int p = wave >> 2;
         auto copy_piece = [&](const SkPiece &q) {
             const SkProblem &P = g.p[q.pi];
-            const int tile_m = q.tile / P.tiles_n, tile_n = q.tile - tile_m * P.tiles_n;
+            int tile_m, tile_n;
+            sk_place(P, q.tile, tile_m, tile_n);
             const int M = P.M, Nc = P.Nc, lda = P.lda, ldb = P.ldb;
             const int nsteps = q.s1 - q.s0;
             // addresses: a wavefront-uniform base per piece and step, a 32-bit byte offset per lane and copy
@@ -465,7 +480,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
 
     auto mma_piece = [&](const SkPiece &q) {
         const SkProblem &P = g.p[q.pi];
-        const int tile_m = q.tile / P.tiles_n, tile_n = q.tile - tile_m * P.tiles_n;
+        int tile_m, tile_n;
+        sk_place(P, q.tile, tile_m, tile_n);
         const int M = P.M, Nc = P.Nc;
         const int nsteps = q.s1 - q.s0;
         const bool writes_tile = q.s1 == q.nsteps;  // uniform over the workgroup
@@ -821,9 +837,11 @@ void sk_add(SkGroup &g, const uint16_t *A, const uint16_t *B, int M, int Nc, int
     SkProblem &P = g.p[g.n];
     P.A = A; P.B = B; P.M = M; P.Nc = Nc; P.lda = lda; P.ldb = ldb; P.nsteps = Kc / 64; P.out = out; P.scale = scale; P.C = C;
     P.tiles_n = (Nc + 96 * TN - 1) / (96 * TN);
+    P.tiles_m = (M + 64 * TM - 1) / (64 * TM);
+    P.strip = P.tiles_n >= 12 ? 4 : P.tiles_n;
     P.t_rows = t_rows;
     P.mask = mask ? *mask : ClampMask{nullptr, nullptr, 0.0f, 1};
-    const long long tiles = (long long)((M + 64 * TM - 1) / (64 * TM)) * P.tiles_n;
+    const long long tiles = (long long)P.tiles_m * P.tiles_n;
     g.ustart[g.n + 1] = g.ustart[g.n] + tiles * P.nsteps;
     ++g.n;
 }
