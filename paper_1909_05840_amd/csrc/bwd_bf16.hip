@@ -147,6 +147,7 @@ struct StageArgs {
     const uint8_t *packed; const float *h; const float *q0; int N, Np, K, rows_per_group; uint16_t *WT; int nb_w;
     const uint16_t *dY; int T, Tp; uint16_t *dYT; int nb_y;
     const int8_t *Xq; uint16_t *XT; int nb_x;
+    uint32_t *zeros;          // 16 bytes to clear, or null
     int *flags; int n_flags;  // cleared by one more block (the GEMM launch behind this one raises them)
 };
 
@@ -171,6 +172,7 @@ __global__ __launch_bounds__(256) void stage_operands_kernel(const StageArgs a)
         return;
     }
     for (int i = threadIdx.x; i < a.n_flags; i += 256) a.flags[i] = 0;
+    if (a.zeros && threadIdx.x < 4) a.zeros[threadIdx.x] = 0;
 }
 
 // dYp[t][n] = dY[t][n] for n < N, 0 for N <= n < Np
@@ -253,6 +255,7 @@ struct SkProblem {
     int tiles_m, tiles_n;  // tiles along M and Nc
     int strip;     // tiles of a strip (sk_place)
     int t_rows;    // 0, or A is dY as it lies in memory (rows along the contraction, t_rows of them)
+    const void *zeros;  // sixteen bytes of zeros, for rows past them
     ClampMask mask;
 };
 constexpr int kSkMaxProblems = 2;
@@ -410,15 +413,16 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
             auto fetch = [&](int step, int stage) {
                 const uint32_t st_ = lds_base + stage * STAGE_BYTES;
                 const uint8_t *as = a_base + (size_t)step * a_step, *bs = b_base + (size_t)step * BKB;
-                if (step == tail) {  // (a contraction's last step) those re-read the last one: B holds zeros there
+                if (step == tail) {  // (a contraction's last step) rows past the end are zeros
 #pragma unroll
                     for (int i = 0; i < A_PER; ++i) {
-                        const int t = (i * NPROD + p) * 4 + (lane >> 4), over = t - (P.t_rows - 1 - (q.s0 + step) * 64);
-                        if (over > 0) a_off[i] -= (uint32_t)over * (uint32_t)(lda * 2);
+                        const bool over = (i * NPROD + p) * 4 + (lane >> 4) >= P.t_rows - (q.s0 + step) * 64;
+                        copy16_to_lds(over ? static_cast<const uint8_t *>(P.zeros) : as + a_off[i], st_ + (i * NPROD + p) * 1024);
                     }
-                }
+                } else {
 #pragma unroll
-                for (int i = 0; i < A_PER; ++i) copy16_to_lds(as + a_off[i], st_ + (i * NPROD + p) * 1024);
+                    for (int i = 0; i < A_PER; ++i) copy16_to_lds(as + a_off[i], st_ + (i * NPROD + p) * 1024);
+                }
 #pragma unroll
                 for (int i = 0; i < B_PER; ++i) copy16_to_lds(bs + b_off[i], st_ + A_BYTES + (i * NPROD + p) * 1024);
             };
@@ -831,7 +835,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
 // appends a product to a call's list: tiles of 64*TM x 96*TN, the contraction Kc a multiple of 64
 template <int TM, int TN>
 void sk_add(SkGroup &g, const uint16_t *A, const uint16_t *B, int M, int Nc, int Kc, int lda, int ldb, int out, float scale,
-            void *C, const ClampMask *mask, int t_rows)
+            void *C, const ClampMask *mask, int t_rows, const void *zeros)
 {
     if (g.n == 0) g.ustart[0] = 0;
     SkProblem &P = g.p[g.n];
@@ -840,6 +844,7 @@ void sk_add(SkGroup &g, const uint16_t *A, const uint16_t *B, int M, int Nc, int
     P.tiles_m = (M + 64 * TM - 1) / (64 * TM);
     P.strip = P.tiles_n >= 12 ? 4 : P.tiles_n;
     P.t_rows = t_rows;
+    P.zeros = zeros;
     P.mask = mask ? *mask : ClampMask{nullptr, nullptr, 0.0f, 1};
     const long long tiles = (long long)P.tiles_m * P.tiles_n;
     g.ustart[g.n + 1] = g.ustart[g.n] + tiles * P.nsteps;
@@ -872,6 +877,7 @@ struct SkProduct {
     void *C;
     const ClampMask *mask;
     int t_rows;
+    const void *zeros;
 };
 // Tiles of 128 x 192 when that leaves every CU at least kSkWideMinSteps of their steps, else 128 x 96; three stages.
 constexpr int kSkWideMinSteps = 16;
@@ -888,12 +894,12 @@ void sk_run(const SkProduct *prod, int n, float *slots, int *flags, hipStream_t 
     if (wide_units >= (long long)kSkMaxRuns * kSkWideMinSteps) {
         for (int i = 0; i < n; ++i)
             sk_add<2, 2>(g, prod[i].A, prod[i].B, prod[i].M, prod[i].Nc, prod[i].Kc, prod[i].lda, prod[i].ldb, prod[i].out,
-                         prod[i].scale, prod[i].C, prod[i].mask, prod[i].t_rows);
+                         prod[i].scale, prod[i].C, prod[i].mask, prod[i].t_rows, prod[i].zeros);
         sk_launch<3, 2, 2>(g, st);
     } else {
         for (int i = 0; i < n; ++i)
             sk_add<2, 1>(g, prod[i].A, prod[i].B, prod[i].M, prod[i].Nc, prod[i].Kc, prod[i].lda, prod[i].ldb, prod[i].out,
-                         prod[i].scale, prod[i].C, prod[i].mask, prod[i].t_rows);
+                         prod[i].scale, prod[i].C, prod[i].mask, prod[i].t_rows, prod[i].zeros);
         sk_launch<3, 2, 1>(g, st);
     }
 }
@@ -967,6 +973,7 @@ static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const
         a.WT = WT; a.nb_w = dX ? (int)(((int64_t)Np * (K / 32) + 255) / 256) : 0;
         a.dY = dY; a.T = (int)T; a.Tp = Tp; a.dYT = dYT; a.nb_y = dW && !turned ? (Tp / 64) * (int)((N + 63) / 64) : 0;
         a.Xq = Xq; a.XT = XT; a.nb_x = dW ? (Tp / 64) * (int)((K + 63) / 64) : 0;
+        a.zeros = turned ? reinterpret_cast<uint32_t *>(dYT) : nullptr;  // (the transposed copy's place is free then)
         a.flags = reinterpret_cast<int *>(ws + p.off_flags); a.n_flags = kSkMaxRuns * kSkFlagsPerRun;
         const dim3 grid((unsigned)(a.nb_w + a.nb_y + a.nb_x + 1));
         switch (bits) {
@@ -987,9 +994,9 @@ static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const
             hipLaunchKernelGGL(pad_rows_kernel, dim3((unsigned)((T * Np + 255) / 256)), dim3(256), 0, st, dY, T, (int)N, Np, dYp);
             Aop = dYp;
         }
-        prod[np++] = SkProduct{Aop, WT, (int)T, (int)K, Np, Np, Np, 0, 1.0f, dX, X ? &mx : nullptr, 0};
+        prod[np++] = SkProduct{Aop, WT, (int)T, (int)K, Np, Np, Np, 0, 1.0f, dX, X ? &mx : nullptr, 0, nullptr};
     }
-    if (dW) prod[np++] = SkProduct{turned ? dY : dYT, XT, (int)N, (int)K, Tp, turned ? (int)N : Tp, Tp, 1, clip / 255.0f, dW, W ? &mw : nullptr, turned ? (int)T : 0};
+    if (dW) prod[np++] = SkProduct{turned ? dY : dYT, XT, (int)N, (int)K, Tp, turned ? (int)N : Tp, Tp, 1, clip / 255.0f, dW, W ? &mw : nullptr, turned ? (int)T : 0, dYT};
     sk_run(prod, np, reinterpret_cast<float *>(ws + p.off_slots), reinterpret_cast<int *>(ws + p.off_flags), st);
     return launch_status();
 }

@@ -72,8 +72,13 @@ def test_one_launch_backward(qb, bits, shape):
 def test_turned_operand_gives_the_staged_operands_sums(qb, shape):
     T, N, K = shape
     dY = wl.grad_output_bf16(T, N, seed=T + N).to(DEV)
+    dY[T - 1, 3] = float("inf")  # rows past the last one are zeros, not the last one times zero
     packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N, K, seed=N + K).to(DEV), 4, 8)
     Xq, _ = qb.qb_quantize_act(wl.activation(T, K, seed=T).to(DEV), CLIP)
+    dX, dW = qb.qb_qlinear_bwd_ste(dY, Xq, CLIP, packed, h, 4, 8)
+    sX, sW = qb.qb_qlinear_bwd_ste(behind(dY, 4), Xq, CLIP, packed, h, 4, 8)
+    assert torch.equal(dX[:-1], sX[:-1]) and torch.equal(dW, sW)  # (dX's last row holds NaN)
+    dY[T - 1, 3] = 0.0
     dX, dW = qb.qb_qlinear_bwd_ste(dY, Xq, CLIP, packed, h, 4, 8)
     sX, sW = qb.qb_qlinear_bwd_ste(behind(dY, 4), Xq, CLIP, packed, h, 4, 8)
     assert torch.equal(dX, sX) and torch.equal(dW, sW)
