@@ -52,10 +52,8 @@ __device__ __forceinline__ void dequant_transpose_body(int bx, const uint8_t *__
         for (int i = 0; i < 32; ++i) dst[(size_t)i * Np] = 0;
         return;
     }
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(packed + slot_index(n, rc, K) * (size_t)(4 * BITS));
     uint32_t in[BITS], d[8];
-#pragma unroll
-    for (int i = 0; i < BITS; ++i) in[i] = src[i];
+    __builtin_memcpy(in, packed + slot_index(n, rc, K) * (size_t)(4 * BITS), 4 * BITS);  // (whatever its alignment)
     unpack_run<BITS>(in, d);
     const float hg = h[n / rows_per_group];
     constexpr int L = (1 << BITS) - 1;
@@ -77,7 +75,7 @@ __device__ __forceinline__ void dequant_transpose_body(int bx, const uint8_t *__
 
 // out[c][r] = conv(in[r][c]) for r < R, c < C; out has leading dimension ldo >= R (a multiple of 64),
 // columns r in [R, ldo) are zero filled.  MODE 0: bf16 copy, MODE 1: int8 x' -> bf16(2x'+1).
-// A block moves a 64x64 tile through LDS: rows are read with 16-byte (MODE 0) or 8-byte (MODE 1)
+// A block moves a 64x64 tile through LDS: rows are read with 16-byte (MODE 0, `in` 16-byte aligned) or 8-byte (MODE 1)
 // loads when C allows it, and every thread writes 8 consecutive r of one output row with one
 // 16-byte store.
 template <int MODE>
@@ -86,7 +84,7 @@ __device__ __forceinline__ void transpose_body(int bx, int by, uint16_t (*tile)[
 {
     const int r0 = bx * 64, c0 = by * 64;
     const int tid = threadIdx.x;
-    const bool vec = (C % 8 == 0);  // uniform: rows are then 16-byte (MODE 0) / 8-byte (MODE 1) aligned
+    const bool vec = (C % 8 == 0);  // uniform: whole pieces, and rows 16-byte aligned (MODE 0)
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
         const int i = (tid >> 3) + it * 32;  // row of the tile
@@ -102,7 +100,8 @@ __device__ __forceinline__ void transpose_body(int bx, int by, uint16_t (*tile)[
                     v[0] = q.x & 0xFFFF; v[1] = q.x >> 16; v[2] = q.y & 0xFFFF; v[3] = q.y >> 16;
                     v[4] = q.z & 0xFFFF; v[5] = q.z >> 16; v[6] = q.w & 0xFFFF; v[7] = q.w >> 16;
                 } else {
-                    const uint2 q = *reinterpret_cast<const uint2 *>(static_cast<const int8_t *>(in) + (size_t)r * C + c);
+                    uint2 q;
+                    __builtin_memcpy(&q, static_cast<const int8_t *>(in) + (size_t)r * C + c, 8);  // (whatever its alignment)
                     const uint32_t w[2] = {q.x, q.y};
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
@@ -175,7 +174,7 @@ __global__ __launch_bounds__(256) void stage_operands_kernel(const StageArgs a)
     if (a.zeros && threadIdx.x < 4) a.zeros[threadIdx.x] = 0;
 }
 
-// dYp[t][n] = dY[t][n] for n < N, 0 for N <= n < Np
+// out[t][n] = in[t][n] for n < N, 0 for N <= n < Np; `in` may lie at any address
 __global__ __launch_bounds__(256) void pad_rows_kernel(const uint16_t *__restrict__ in, int64_t T, int N, int Np,
                                                        uint16_t *__restrict__ out)
 {
@@ -951,7 +950,7 @@ static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int rpg = (int)(N / groups);
     const int teams = bwd_direct_teams(T, N, K, dX != nullptr, dW != nullptr);
-    if (teams && ((reinterpret_cast<uintptr_t>(dY) | reinterpret_cast<uintptr_t>(packed)) & 15) == 0 && (reinterpret_cast<uintptr_t>(Xq) & 1) == 0) {
+    if (teams) {
         DirectArgs d = {};
         d.dY = dY; d.Xq = Xq; d.packed = static_cast<const uint8_t *>(packed); d.h = h; d.q0 = q0; d.X = X; d.W = W; d.m = m;
         d.dX = dX; d.dW = dW; d.T = (int)T; d.N = (int)N; d.K = (int)K; d.rows_per_group = rpg; d.clip = clip; d.scale = clip / 255.0f;
@@ -962,18 +961,26 @@ static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     const int Np = (int)p.Np, Tp = (int)p.Tp;
 
-    // dW's A operand is turned on its way out of LDS where dY's rows can be copied in aligned pieces of 16 bytes, else staged
-    const bool turned = N % 8 == 0 && (reinterpret_cast<uintptr_t>(dY) & 15) == 0;
     uint16_t *WT = reinterpret_cast<uint16_t *>(ws + p.off_wt);
     uint16_t *dYT = reinterpret_cast<uint16_t *>(ws + p.off_dyt);
     uint16_t *XT = reinterpret_cast<uint16_t *>(ws + p.off_xt);
+    // dW's A operand is turned on its way out of LDS where dY's rows consist of pieces of 16 bytes, else staged
+    const bool turned = N % 8 == 0;
+    uint16_t *zeros = dYT;  // (the transposed copy's place is free then)
+    // The copies into LDS want dY's pieces aligned.  A dY that lies elsewhere is moved to the same free place first, so that
+    // the call does the same sums in the same order; the zeros stand behind it (they are read only if Tp > T).
+    if (turned && (reinterpret_cast<uintptr_t>(dY) & 15)) {
+        hipLaunchKernelGGL(pad_rows_kernel, dim3((unsigned)((T * N + 255) / 256)), dim3(256), 0, st, dY, T, (int)N, (int)N, dYT);
+        dY = dYT;
+        zeros = Tp > T ? dYT + (size_t)T * N : nullptr;
+    }
     {
         StageArgs a;
         a.packed = static_cast<const uint8_t *>(packed); a.h = h; a.q0 = q0; a.N = (int)N; a.Np = Np; a.K = (int)K; a.rows_per_group = rpg;
         a.WT = WT; a.nb_w = dX ? (int)(((int64_t)Np * (K / 32) + 255) / 256) : 0;
         a.dY = dY; a.T = (int)T; a.Tp = Tp; a.dYT = dYT; a.nb_y = dW && !turned ? (Tp / 64) * (int)((N + 63) / 64) : 0;
         a.Xq = Xq; a.XT = XT; a.nb_x = dW ? (Tp / 64) * (int)((K + 63) / 64) : 0;
-        a.zeros = turned ? reinterpret_cast<uint32_t *>(dYT) : nullptr;  // (the transposed copy's place is free then)
+        a.zeros = turned ? reinterpret_cast<uint32_t *>(zeros) : nullptr;
         a.flags = reinterpret_cast<int *>(ws + p.off_flags); a.n_flags = kSkMaxRuns * kSkFlagsPerRun;
         const dim3 grid((unsigned)(a.nb_w + a.nb_y + a.nb_x + 1));
         switch (bits) {
@@ -996,7 +1003,7 @@ static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const
         }
         prod[np++] = SkProduct{Aop, WT, (int)T, (int)K, Np, Np, Np, 0, 1.0f, dX, X ? &mx : nullptr, 0, nullptr};
     }
-    if (dW) prod[np++] = SkProduct{turned ? dY : dYT, XT, (int)N, (int)K, Tp, turned ? (int)N : Tp, Tp, 1, clip / 255.0f, dW, W ? &mw : nullptr, turned ? (int)T : 0, dYT};
+    if (dW) prod[np++] = SkProduct{turned ? dY : dYT, XT, (int)N, (int)K, Tp, turned ? (int)N : Tp, Tp, 1, clip / 255.0f, dW, W ? &mw : nullptr, turned ? (int)T : 0, zeros};
     sk_run(prod, np, reinterpret_cast<float *>(ws + p.off_slots), reinterpret_cast<int *>(ws + p.off_flags), st);
     return launch_status();
 }

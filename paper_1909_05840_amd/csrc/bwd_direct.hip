@@ -70,8 +70,14 @@ __device__ __forceinline__ gptr scalar(const P *p, size_t offset)
     asm("" : "+s"(q));
     return q;
 }
+// (no alignment is asked of p: the load unit takes any address with the same instruction, so where an input lies decides
+// neither the path of a call nor its results)
 template <typename V>
-__device__ __forceinline__ V at(gptr p) { return *(const __attribute__((address_space(1))) V *)p; }
+__device__ __forceinline__ V at(gptr p)
+{
+    struct __attribute__((packed)) Loose { V v; };
+    return ((const __attribute__((address_space(1))) Loose *)p)->v;
+}
 // dwords of packed codes a thread holds per step: half a slot (16 codes)
 template <int BITS>
 constexpr int code_words() { return BITS == 8 ? 4 : BITS == 2 ? 1 : 2; }

@@ -24,7 +24,6 @@ struct DirectArgs {
 // the faster one or the sizes do not fit.
 int bwd_direct_teams(int64_t T, int64_t N, int64_t K, bool dx, bool dw);
 
-// dY and packed 16-byte aligned, Xq 2-byte aligned
 void bwd_direct_run(DirectArgs g, int teams, int bits, hipStream_t st);
 
 }  // namespace qb

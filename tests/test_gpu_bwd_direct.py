@@ -1,11 +1,14 @@
 """The backward's one-launch kernel for small calls (N a multiple of 64) at the edges of its tiles and steps, for one, two
 and four teams per workgroup, against the oracle and against the staged kernels."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_1909_05840_amd import workloads as wl
+from paper_1909_05840_amd.binding import LIB_PATH
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -16,6 +19,13 @@ def bounds(dY, W_hat, x_hat):
     """per element: bf16 rounding of the de-quantized weights and of the result; fp32 sums of exact products"""
     a = np.abs(dY.float().numpy().astype(np.float64))
     return 2.0 ** -8 * (a @ np.abs(W_hat)), 2.0 ** -12 * (a.T @ np.abs(x_hat))
+
+
+def one_launch_teams(T, N, K, dx=True, dw=True):
+    """teams per workgroup that the library's rule gives a call, 0 for the staged path"""
+    rule = ctypes.CDLL(LIB_PATH)._ZN2qb16bwd_direct_teamsElllbb
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int64] * 3 + [ctypes.c_bool] * 2
+    return rule(T, N, K, dx, dw)
 
 
 def behind(t, elements):
@@ -42,7 +52,7 @@ def test_one_launch_backward(qb, bits, shape):
     packed, h, m, _ = qb.qb_quantize_groupwise(Wd, bits, G)
     Xq, _ = qb.qb_quantize_act(Xd, CLIP)
     dX, dW = qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G)
-    sX, sW = qb.qb_qlinear_bwd_ste(behind(dYd, 4), Xq, CLIP, packed, h, bits, G)  # (8-byte aligned: staged)
+    sX, sW = qb.qb_qlinear_bwd_ste(behind(dYd, 4), Xq, CLIP, packed, h, bits, G)  # (8-byte aligned)
     mX, mW = qb.qb_qlinear_bwd_ste_masked(dYd, Xq, CLIP, packed, h, bits, G, X=Xd, W=Wd, m=0.5 * m)
     oX = behind(torch.empty(T, K, dtype=torch.bfloat16, device=DEV), 1)
     oW = behind(torch.empty(N, K, device=DEV), 1)
@@ -55,7 +65,7 @@ def test_one_launch_backward(qb, bits, shape):
     for a, b in ((dX, dW), (sX, sW)):
         a, b = a.float().cpu().numpy().astype(np.float64), b.cpu().numpy().astype(np.float64)
         assert (np.abs(a - rX) <= 2.0 ** -8 * np.abs(rX) + tX).all() and (np.abs(b - rW) <= tW).all()
-    assert torch.equal(oX, dX) and torch.equal(oW, dW)
+    assert torch.equal(oX, dX) and torch.equal(oW, dW) and torch.equal(sX, dX) and torch.equal(sW, dW)
     out_x, out_w = Xd.abs() > CLIP, Wd.abs() > (0.5 * m).repeat_interleave(N // G)[:, None]
     assert bool(out_x[T - 1, K - 1]) and not bool(out_x[0, 0]) and bool(out_w.any())
     assert torch.equal(mX, torch.where(out_x, torch.zeros_like(dX), dX)) and torch.equal(mW, torch.where(out_w, torch.zeros_like(dW), dW))
@@ -66,24 +76,41 @@ def test_one_launch_backward(qb, bits, shape):
     assert (np.abs(a.float().cpu().numpy() - rX) <= 2.0 ** -8 * np.abs(rX) + tX).all() and (np.abs(b.cpu().numpy() - rW) <= tW).all()
 
 
-# (T, N, K): N a multiple of 8 only, T with and without rows beyond a multiple of 64, tiles of 128 x 96 and 128 x 192, columns
-# past the end of a tile
-@pytest.mark.parametrize("shape", [(65, 72, 64), (300, 136, 192), (640, 8, 128), (4099, 520, 1088), (4160, 520, 1088)])
+# (T, N, K): N a multiple of 8 or of 64, T with and without rows beyond a multiple of 64, tiles of 128 x 96 and (the last
+# three: dW alone has 256 CUs times 16 steps) 128 x 192, columns past the end of a tile.  One more column of dY makes its rows
+# no multiple of 16 bytes, so that the operand is staged; the tiles and the steps of dW stay the same.
+@pytest.mark.parametrize("shape", [(65, 72, 64), (300, 136, 192), (640, 8, 128), (4099, 520, 1088), (4160, 520, 1088),
+                                   (5500, 1000, 1088), (8200, 960, 768), (8256, 960, 768)])
 def test_turned_operand_gives_the_staged_operands_sums(qb, shape):
     T, N, K = shape
-    dY = wl.grad_output_bf16(T, N, seed=T + N).to(DEV)
-    dY[T - 1, 3] = float("inf")  # rows past the last one are zeros, not the last one times zero
-    packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N, K, seed=N + K).to(DEV), 4, 8)
+    print("bwd turned", shape, flush=True)
+    assert N % 128 != 0 and one_launch_teams(T, N, K, False, True) == 0
+    dY = wl.grad_output_bf16(T, N + 1, seed=T + N).to(DEV)
+    packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N + 1, K, seed=N + K).to(DEV), 4, 1)
     Xq, _ = qb.qb_quantize_act(wl.activation(T, K, seed=T).to(DEV), CLIP)
-    dX, dW = qb.qb_qlinear_bwd_ste(dY, Xq, CLIP, packed, h, 4, 8)
-    sX, sW = qb.qb_qlinear_bwd_ste(behind(dY, 4), Xq, CLIP, packed, h, 4, 8)
-    assert torch.equal(dX[:-1], sX[:-1]) and torch.equal(dW, sW)  # (dX's last row holds NaN)
-    dY[T - 1, 3] = 0.0
-    dX, dW = qb.qb_qlinear_bwd_ste(dY, Xq, CLIP, packed, h, 4, 8)
-    sX, sW = qb.qb_qlinear_bwd_ste(behind(dY, 4), Xq, CLIP, packed, h, 4, 8)
-    assert torch.equal(dX, sX) and torch.equal(dW, sW)
-    ref = dY.double().T @ ((2.0 * Xq.double() + 1.0) * (CLIP / 255.0))
+    for last in (float("inf"), 0.0):  # rows past the last one are zeros, not the last one times zero
+        dY[T - 1, 3] = last
+        _, dW = qb.qb_qlinear_bwd_ste(dY[:, :N].contiguous(), Xq, CLIP, packed, h, 4, 1, want_dx=False)
+        _, sW = qb.qb_qlinear_bwd_ste(dY, Xq, CLIP, packed, h, 4, 1, want_dx=False)
+        assert torch.equal(dW, sW[:N])
+    ref = dY[:, :N].double().T @ ((2.0 * Xq.double() + 1.0) * (CLIP / 255.0))
     assert (dW.double() - ref).norm() <= 1e-5 * ref.norm()  # fp32 sums of exact products
+
+
+# one launch, staged with a turned operand (T with and without rows beyond a multiple of 64, N a multiple of 64 or of 8 only),
+# staged
+@pytest.mark.parametrize("shape", [(129, 128, 192), (16, 192, 64), (300, 136, 192), (320, 136, 192), (6001, 1024, 768), (77, 50, 64)])
+@pytest.mark.parametrize("off_y,off_x,off_w", [(4, 0, 0), (1, 0, 0), (0, 1, 0), (0, 0, 4), (3, 7, 12)])
+def test_where_the_inputs_lie_does_not_change_a_bit(qb, shape, off_y, off_x, off_w):
+    T, N, K = shape
+    print("bwd alignment", shape, off_y, off_x, off_w, flush=True)
+    dY = wl.grad_output_bf16(T, N, seed=T + N).to(DEV)
+    Xq, _ = qb.qb_quantize_act(wl.activation(T, K, seed=T).to(DEV), CLIP)
+    for bits in (3, 8):
+        packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N, K, seed=N + K).to(DEV), bits, 2)
+        dX, dW = qb.qb_qlinear_bwd_ste(dY, Xq, CLIP, packed, h, bits, 2)
+        aX, aW = qb.qb_qlinear_bwd_ste(behind(dY, off_y), behind(Xq, off_x), CLIP, behind(packed, off_w), h, bits, 2)
+        assert torch.equal(aX, dX) and torch.equal(aW, dW)
 
 
 @pytest.mark.parametrize("shape", [(65, 128, 64, 2), (577, 448, 192, 64)])
