@@ -292,9 +292,17 @@ __device__ __forceinline__ SkPiece sk_piece_at(const SkGroup &g, long long u, lo
 // made the CUs of an XCD share A panels only; in strips of four they share panels in both directions, which L2 has to fetch
 // once: 12288 tokens, 768 x 3072 163.8 -> 148.9 us a call, 960 x 3840 at 6000 tokens 144 -> 134.5, 1024 x 4096 at 8000
 // 198 -> 188.5.  Rows of fewer than twelve tiles stay whole: cut into four and a narrow rest they lose (six, 1024 x 1024 at
-// 8000 tokens: 62.5 -> 68.0; eleven, 2048 x 2048 at 3000 tokens: 68.9 -> 70.2) or gain nothing (eight: 44.7, 45.0).
+// 8000 tokens: 62.5 -> 68.0; eleven, 2048 x 2048 at 3000 tokens: 68.9 -> 70.2) or gain nothing (eight: 44.7, 45.0).  So do
+// contractions of up to kSkMinUnits steps, where a run holds whole tiles and shares nothing (896 x 3584 at 6 tokens in
+// strips: 20.3 -> 23.4; 616 x 5120 at 310, dW only, five steps: 19.1 -> 17.5).  Which runs meet at a tile changes with the
+// order, so single shapes go the other way (960 x 3840 at 8067 tokens, dX only: 74.4 -> 80.4; at 9174: 101.8 -> 98.4).
 __device__ __forceinline__ void sk_place(const SkProblem &P, int t, int &tile_m, int &tile_n)
 {
+    if (P.strip == P.tiles_n) {
+        tile_m = t / P.tiles_n;
+        tile_n = t - tile_m * P.tiles_n;
+        return;
+    }
     const int per_strip = P.strip * P.tiles_m, col = t / per_strip, left = t - col * per_strip;
     const int rest = P.tiles_n - P.strip * col, width = rest < P.strip ? rest : P.strip;
     tile_m = left / width;
@@ -333,7 +341,9 @@ __device__ __forceinline__ bool sk_wait_flag(const int *f)
     return false;
 }
 
-template <int NSTAGE, bool MASK, int TM, int TN>
+// TURN: a product of the call has dY as it lies in memory for its A (calls without one pay up to 1 us, of 15 to 35, for the
+// second K-loop in the kernel)
+template <int NSTAGE, bool MASK, int TM, int TN, bool TURN>
 __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
 {
     // an MFMA wavefront owns TM x TN blocks of 32 x 32: tiles of 64*TM x 96*TN (128 x 96, or 256 x 192: half the
@@ -374,16 +384,17 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
             sk_place(P, q.tile, tile_m, tile_n);
             const int M = P.M, Nc = P.Nc, lda = P.lda, ldb = P.ldb;
             const int nsteps = q.s1 - q.s0;
+            const int t_rows = TURN ? P.t_rows : 0;
             // addresses: a wavefront-uniform base per piece and step, a 32-bit byte offset per lane and copy
             // (rows of a tile lie less than 2^32 bytes apart: at most 256 rows of at most 2^25 bytes)
-            const uint8_t *a_base = reinterpret_cast<const uint8_t *>(P.t_rows ? P.A + (size_t)q.s0 * 64 * lda : P.A + (size_t)tile_m * BM * lda + q.s0 * 64);
+            const uint8_t *a_base = reinterpret_cast<const uint8_t *>(t_rows ? P.A + (size_t)q.s0 * 64 * lda : P.A + (size_t)tile_m * BM * lda + q.s0 * 64);
             const uint8_t *b_base = reinterpret_cast<const uint8_t *>(P.B + (size_t)tile_n * BN * ldb + q.s0 * 64);
             const int a_last = M - 1 - tile_m * BM, b_last = Nc - 1 - tile_n * BN;
             uint32_t a_off[A_PER], b_off[B_PER];
 #pragma unroll
             for (int i = 0; i < A_PER; ++i) {
                 const int blk = i * NPROD + p;
-                if (P.t_rows) {
+                if (t_rows) {
                     // four rows of dY (256 bytes of the tile's columns each), their 64-byte quarters swizzled with the row
                     const int t = blk * 4 + (lane >> 4);
                     int col = tile_m * BM + ((((lane >> 2) & 3) ^ (t & 3)) << 5) + (lane & 3) * 8;
@@ -407,15 +418,15 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
                 row = row < b_last ? row : b_last;
                 b_off[i] = (uint32_t)row * (uint32_t)(ldb * 2) + (((lane & 7) ^ kx) * 16);
             }
-            const size_t a_step = P.t_rows ? (size_t)lda * 128 : (size_t)BKB;
-            const int tail = P.t_rows ? P.t_rows / 64 - q.s0 : nsteps;  // the step with rows past the end, if it has any
+            const size_t a_step = t_rows ? (size_t)lda * 128 : (size_t)BKB;
+            const int tail = t_rows ? t_rows / 64 - q.s0 : nsteps;  // the step with rows past the end, if it has any
             auto fetch = [&](int step, int stage) {
                 const uint32_t st_ = lds_base + stage * STAGE_BYTES;
                 const uint8_t *as = a_base + (size_t)step * a_step, *bs = b_base + (size_t)step * BKB;
-                if (step == tail) {  // (a contraction's last step) rows past the end are zeros
+                if (TURN && step == tail) {  // (a contraction's last step) rows past the end are zeros
 #pragma unroll
                     for (int i = 0; i < A_PER; ++i) {
-                        const bool over = (i * NPROD + p) * 4 + (lane >> 4) >= P.t_rows - (q.s0 + step) * 64;
+                        const bool over = (i * NPROD + p) * 4 + (lane >> 4) >= t_rows - (q.s0 + step) * 64;
                         copy16_to_lds(over ? static_cast<const uint8_t *>(P.zeros) : as + a_off[i], st_ + (i * NPROD + p) * 1024);
                     }
                 } else {
@@ -625,7 +636,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
             asm volatile("" ::: "memory");
         }
         };
-        if (P.t_rows) k_loop(std::true_type{});
+        if (TURN && P.t_rows) k_loop(std::true_type{});
         else k_loop(std::false_type{});
         if (!writes_tile) {
             // partial sums of the tile's leading or middle steps: to this run's slot, then the wavefront's flag
@@ -831,6 +842,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
     if (first_last) mma_piece(first);
 }
 
+constexpr int kSkMinUnits = 4;
 // appends a product to a call's list: tiles of 64*TM x 96*TN, the contraction Kc a multiple of 64
 template <int TM, int TN>
 void sk_add(SkGroup &g, const uint16_t *A, const uint16_t *B, int M, int Nc, int Kc, int lda, int ldb, int out, float scale,
@@ -841,7 +853,7 @@ void sk_add(SkGroup &g, const uint16_t *A, const uint16_t *B, int M, int Nc, int
     P.A = A; P.B = B; P.M = M; P.Nc = Nc; P.lda = lda; P.ldb = ldb; P.nsteps = Kc / 64; P.out = out; P.scale = scale; P.C = C;
     P.tiles_n = (Nc + 96 * TN - 1) / (96 * TN);
     P.tiles_m = (M + 64 * TM - 1) / (64 * TM);
-    P.strip = P.tiles_n >= 12 ? 4 : P.tiles_n;
+    P.strip = P.tiles_n >= 12 && P.nsteps > kSkMinUnits ? 4 : P.tiles_n;
     P.t_rows = t_rows;
     P.zeros = zeros;
     P.mask = mask ? *mask : ClampMask{nullptr, nullptr, 0.0f, 1};
@@ -851,7 +863,6 @@ void sk_add(SkGroup &g, const uint16_t *A, const uint16_t *B, int M, int Nc, int
 }
 
 // One launch for the list: one workgroup per CU, every workgroup at least kSkMinUnits steps.
-constexpr int kSkMinUnits = 4;
 template <int NSTAGE, int TM, int TN>
 void sk_launch(const SkGroup &g, hipStream_t st)
 {
@@ -860,12 +871,14 @@ void sk_launch(const SkGroup &g, hipStream_t st)
     if (grid > kSkMaxRuns) grid = kSkMaxRuns;
     if (grid < 1) grid = 1;
     if (grid >= 8) grid &= ~7ll;
-    bool any_mask = false;
-    for (int i = 0; i < g.n; ++i) any_mask = any_mask || g.p[i].mask.src != nullptr;
-    if (any_mask)
-        hipLaunchKernelGGL((gemm_bf16_sk_kernel<NSTAGE, true, TM, TN>), dim3((unsigned)grid), dim3(512), 0, st, g);
-    else
-        hipLaunchKernelGGL((gemm_bf16_sk_kernel<NSTAGE, false, TM, TN>), dim3((unsigned)grid), dim3(512), 0, st, g);
+    bool any_mask = false, any_turned = false;
+    for (int i = 0; i < g.n; ++i) {
+        any_mask = any_mask || g.p[i].mask.src != nullptr;
+        any_turned = any_turned || g.p[i].t_rows != 0;
+    }
+    auto *kernel = any_mask ? (any_turned ? gemm_bf16_sk_kernel<NSTAGE, true, TM, TN, true> : gemm_bf16_sk_kernel<NSTAGE, true, TM, TN, false>)
+                            : (any_turned ? gemm_bf16_sk_kernel<NSTAGE, false, TM, TN, true> : gemm_bf16_sk_kernel<NSTAGE, false, TM, TN, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(512), 0, st, g);
 }
 
 // One product of a call, as the host sees it
@@ -936,6 +949,14 @@ extern "C" size_t qb_bwd_workspace_nbytes(int64_t T, int64_t N, int64_t K)
     return make_plan(T, N, K).total;
 }
 
+// Whether dW's A operand is turned on its way out of LDS or staged transposed.  Turned it needs rows of whole 16-byte pieces,
+// and saves the staging launch a pass over dY; but the GEMM's copies then come from dY's own memory, of which few rows give
+// little for each of them, and short contractions end in a step with rows to clear.  us a call, staged -> turned:
+// 768 x 768, dW only, at 4 tokens 15.2 -> 18.3; 1024 x 1024 at 455 17.7 -> 18.2; 3072 x 768 at 272 23.1 -> 23.5, at 533
+// 25.1 -> 23.4; 2304 x 768, dW only, at 871 18.7 -> 16.8.  Below 512 tokens 2 to 4 % are lost on average, from 640 on 3 to 10
+// gained.
+namespace qb { bool bwd_turned(int64_t T, int64_t N) { return N % 8 == 0 && T >= 640; } }
+
 static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const void *packed, const float *h, int bits,
                          int groups, int64_t T, int64_t N, int64_t K, const float *X, const float *W, const float *m,
                          uint16_t *dX, float *dW, void *workspace, void *stream, const float *q0 = nullptr)
@@ -964,12 +985,13 @@ static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const
     uint16_t *WT = reinterpret_cast<uint16_t *>(ws + p.off_wt);
     uint16_t *dYT = reinterpret_cast<uint16_t *>(ws + p.off_dyt);
     uint16_t *XT = reinterpret_cast<uint16_t *>(ws + p.off_xt);
-    // dW's A operand is turned on its way out of LDS where dY's rows consist of pieces of 16 bytes, else staged
-    const bool turned = N % 8 == 0;
+    // The copies into LDS want dY's pieces of 16 bytes aligned.  A dY that lies elsewhere is moved to the place of the
+    // transposed copy first, so that the call does the same sums in the same order; the zeros stand behind it (they are read
+    // only if Tp > T).
+    const bool moved = N % 8 == 0 && (reinterpret_cast<uintptr_t>(dY) & 15);
+    const bool turned = moved || bwd_turned(T, N);
     uint16_t *zeros = dYT;  // (the transposed copy's place is free then)
-    // The copies into LDS want dY's pieces aligned.  A dY that lies elsewhere is moved to the same free place first, so that
-    // the call does the same sums in the same order; the zeros stand behind it (they are read only if Tp > T).
-    if (turned && (reinterpret_cast<uintptr_t>(dY) & 15)) {
+    if (moved) {
         hipLaunchKernelGGL(pad_rows_kernel, dim3((unsigned)((T * N + 255) / 256)), dim3(256), 0, st, dY, T, (int)N, (int)N, dYT);
         dY = dYT;
         zeros = Tp > T ? dYT + (size_t)T * N : nullptr;

@@ -78,7 +78,8 @@ def test_one_launch_backward(qb, bits, shape):
 
 # (T, N, K): N a multiple of 8 or of 64, T with and without rows beyond a multiple of 64, tiles of 128 x 96 and (the last
 # three: dW alone has 256 CUs times 16 steps) 128 x 192, columns past the end of a tile.  One more column of dY makes its rows
-# no multiple of 16 bytes, so that the operand is staged; the tiles and the steps of dW stay the same.
+# no multiple of 16 bytes, so that the operand is staged; the tiles and the steps of dW stay the same.  Of a dY that is not
+# 16-byte aligned the operand is turned at any T.
 @pytest.mark.parametrize("shape", [(65, 72, 64), (300, 136, 192), (640, 8, 128), (4099, 520, 1088), (4160, 520, 1088),
                                    (5500, 1000, 1088), (8200, 960, 768), (8256, 960, 768)])
 def test_turned_operand_gives_the_staged_operands_sums(qb, shape):
@@ -92,13 +93,13 @@ def test_turned_operand_gives_the_staged_operands_sums(qb, shape):
         dY[T - 1, 3] = last
         _, dW = qb.qb_qlinear_bwd_ste(dY[:, :N].contiguous(), Xq, CLIP, packed, h, 4, 1, want_dx=False)
         _, sW = qb.qb_qlinear_bwd_ste(dY, Xq, CLIP, packed, h, 4, 1, want_dx=False)
-        assert torch.equal(dW, sW[:N])
+        _, mW = qb.qb_qlinear_bwd_ste(behind(dY[:, :N].contiguous(), 4), Xq, CLIP, packed, h, 4, 1, want_dx=False)
+        assert torch.equal(dW, sW[:N]) and torch.equal(mW, sW[:N])
     ref = dY[:, :N].double().T @ ((2.0 * Xq.double() + 1.0) * (CLIP / 255.0))
     assert (dW.double() - ref).norm() <= 1e-5 * ref.norm()  # fp32 sums of exact products
 
 
-# one launch, staged with a turned operand (T with and without rows beyond a multiple of 64, N a multiple of 64 or of 8 only),
-# staged
+# one launch, staged (turned where dY is not aligned), turned, neither
 @pytest.mark.parametrize("shape", [(129, 128, 192), (16, 192, 64), (300, 136, 192), (320, 136, 192), (6001, 1024, 768), (77, 50, 64)])
 @pytest.mark.parametrize("off_y,off_x,off_w", [(4, 0, 0), (1, 0, 0), (0, 1, 0), (0, 0, 4), (3, 7, 12)])
 def test_where_the_inputs_lie_does_not_change_a_bit(qb, shape, off_y, off_x, off_w):
