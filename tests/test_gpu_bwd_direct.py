@@ -1,5 +1,5 @@
 """The backward's one-launch kernel for small calls (N a multiple of 64) at the edges of its tiles and steps, for one, two
-and four teams per workgroup, against the oracle and against the staged kernels."""
+and four teams per workgroup, and the staged path's turned operand and strips of tiles, against the oracle and plain fp64."""
 import ctypes
 
 import numpy as np
@@ -28,6 +28,18 @@ def one_launch_teams(T, N, K, dx=True, dw=True):
     return rule(T, N, K, dx, dw)
 
 
+def check(dY, W_hat, Xq, dX, dW):
+    """every element of dX and dW against plain fp64 within bounds() (sums on the GPU, for the host takes long)"""
+    y, w = dY.to(DEV).double(), torch.as_tensor(W_hat).to(DEV).double()
+    x = (2.0 * Xq.double() + 1.0) * (CLIP / 255.0)
+    if dX is not None:
+        ref = y @ w
+        assert bool(((dX.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -8 * (y.abs() @ w.abs())).all())
+    if dW is not None:
+        ref = y.T @ x
+        assert bool(((dW.double() - ref).abs() <= 2.0 ** -12 * (y.abs().T @ x.abs())).all())
+
+
 def behind(t, elements):
     """the same values in memory that starts `elements` elements behind an allocation's start"""
     buf = torch.empty(t.numel() + elements, dtype=t.dtype, device=DEV)
@@ -37,7 +49,8 @@ def behind(t, elements):
 
 
 # (T, N, K, groups): one step and one tile; one row beyond a step or tile, one short of it; contractions of 1..9 steps in
-# one direction and up to 36 in the other, so that teams end with and without a last step; rows per group 1, 3, 6, N
+# one direction and up to 36 in the other, so that teams end with and without a last step (two and four teams; one team for
+# the first shape); rows per group 1, 3, 6, N
 @pytest.mark.parametrize("bits", [2, 3, 4, 8])
 @pytest.mark.parametrize("shape", [(64, 64, 64, 64), (65, 128, 64, 1), (127, 192, 128, 64), (193, 64, 320, 8), (130, 2304, 64, 384),
                                    (577, 448, 192, 64), (1001, 448, 448, 64), (600, 768, 768, 128), (2111, 64, 128, 1)])
@@ -74,6 +87,44 @@ def test_one_launch_backward(qb, bits, shape):
     none2, b = qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, want_dx=False)
     assert none is None and none2 is None
     assert (np.abs(a.float().cpu().numpy() - rX) <= 2.0 ** -8 * np.abs(rX) + tX).all() and (np.abs(b.cpu().numpy() - rW) <= tW).all()
+
+
+# (T, N, K, groups, one output only): one team, contractions of 4 to 36 steps, odd and even, with and without rows beyond a
+# multiple of 64
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("shape", [(1001, 448, 1792, 64, None), (1001, 2304, 768, 128, None), (448, 320, 2560, 64, None), (300, 512, 2048, 1, None),
+                                   (1500, 256, 1024, 4, "dX"), (1001, 2304, 768, 384, "dW")])
+@pytest.mark.parametrize("asym", [False, True])
+def test_one_team(qb, bits, shape, asym):
+    T, N, K, G, only = shape
+    print("bwd one team", shape, bits, asym, flush=True)
+    assert one_launch_teams(T, N, K, only != "dW", only != "dX") == 1
+    W, dY = wl.weight(N, K, seed=N + K + bits), wl.grad_output_bf16(T, N, seed=T + N)
+    Xq, _ = qb.qb_quantize_act(wl.activation(T, K, seed=T + bits).to(DEV), CLIP)
+    want = {"want_dx": only != "dW", "want_dw": only != "dX"}
+    if asym:
+        packed, delta, q0, _ = qb.qb_quantize_groupwise_asym((W + 0.05).to(DEV), bits, G)
+        dX, dW = qb.qb_qlinear_bwd_ste_asym(dY.to(DEV), Xq, CLIP, packed, delta, q0, bits, G, **want)
+        W_hat = oracle.dequantize_groupwise_asym(qb.qb_unpack_codes(packed, N, K, bits).cpu().numpy(), delta.cpu().numpy(), q0.cpu().numpy())
+    else:
+        packed, h, _, _ = qb.qb_quantize_groupwise(W.to(DEV), bits, G)
+        dX, dW = qb.qb_qlinear_bwd_ste(dY.to(DEV), Xq, CLIP, packed, h, bits, G, **want)
+        W_hat = oracle.dequantize_groupwise(qb.qb_unpack_codes(packed, N, K, bits).cpu().numpy(), h.cpu().numpy(), bits)
+    check(dY, W_hat, Xq, dX, dW)
+
+
+# (T, N, K): rows of 22 tiles of 128 x 192 (strips of four and a last one of two) and of 13 of 128 x 96 (a last one of one), both
+# products in strips; 13 with dX (four steps) in whole rows
+@pytest.mark.parametrize("shape", [(6100, 200, 4096), (700, 264, 1216), (700, 200, 1216)])
+def test_last_strip_of_tiles_is_narrower(qb, shape):
+    T, N, K = shape
+    print("bwd strips", shape, flush=True)
+    assert one_launch_teams(T, N, K) == 0
+    dY = wl.grad_output_bf16(T, N, seed=T + N)
+    packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N, K, seed=N + K).to(DEV), 4, 8)
+    Xq, _ = qb.qb_quantize_act(wl.activation(T, K, seed=T).to(DEV), CLIP)
+    dX, dW = qb.qb_qlinear_bwd_ste(dY.to(DEV), Xq, CLIP, packed, h, 4, 8)
+    check(dY, oracle.dequantize_groupwise(qb.qb_unpack_codes(packed, N, K, 4).cpu().numpy(), h.cpu().numpy(), 4), Xq, dX, dW)
 
 
 # (T, N, K): N a multiple of 8 or of 64, T with and without rows beyond a multiple of 64, tiles of 128 x 96 and (the last
