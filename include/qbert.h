@@ -250,13 +250,18 @@ qb_status qb_quantize_act_dyn_tensor(const float *X, int64_t T, int64_t K,
  *   dW   out  [N,K] fp32 or NULL; overwritten, not accumulated into
  *   workspace  qb_bwd_workspace_nbytes(T,N,K) bytes, 256-byte aligned; contents undefined
  *              before and after the call
- * Two launches on `stream` (operand staging, then one launch that computes both products, its workgroups sharing
- * the contraction steps evenly and adding the partial sums of a shared tile in a fixed order): the same call gives
- * the same bits every time.  Which of dX and dW a call computes decides how the steps are shared, so dX of a
- * dX-only call may differ from dX of a call that also computes dW in the last bf16 bit (order of the fp32
- * additions).  Inside the launch a workgroup may wait for partial sums of workgroups dispatched before it; the
- * wait is bounded (about two seconds), after which the tile concerned is written as NaN.  Calls that share a
- * workspace must not overlap in time.
+ * One to four launches on `stream`, by a rule on T, N, K and on which outputs are asked for:
+ *   - small calls with N a multiple of 64 take one launch that computes both products from the operands as they lie in
+ *     memory; the workspace must be passed all the same, but is not touched;
+ *   - all others stage operands in the workspace and compute both products in one more launch, whose workgroups share
+ *     the contraction steps evenly and add the partial sums of a shared tile in a fixed order.  One more launch each
+ *     pads the rows of dY for dX where N is not a multiple of 64, and moves a dY that is not 16-byte aligned where N is a
+ *     multiple of 8.  A workgroup may wait for partial sums of workgroups dispatched before it; the wait is bounded
+ *     (about two seconds), after which the tile concerned is written as NaN.
+ * The same call gives the same bits every time, wherever its operands lie.  Which of dX and dW a call computes decides
+ * the path and how the steps are shared, so dX of a dX-only call may differ from dX of a call that also computes dW in
+ * the last bf16 bit, and dW in the last bits (order of the fp32 additions).  Calls that share a workspace must not
+ * overlap in time.
  */
 qb_status qb_qlinear_bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip,
                              const void *packed, const float *h, int bits, int groups,
@@ -265,7 +270,7 @@ qb_status qb_qlinear_bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip,
 
 /*
  * qb_qlinear_bwd_ste for callers that cannot allocate device memory or carry a workspace around (code under
- * HIP graph capture, tight serving or training loops, harnesses that forbid hipMalloc): the same kernels and
+ * HIP graph capture, tight serving or training loops, harnesses that forbid hipMalloc): the same rule, kernels and
  * results, with the staging area taken from a fixed array inside the library instead of a `workspace`
  * argument.  The call allocates and frees nothing.  The array has QB_BWD_STATIC_BYTES bytes on every GPU the
  * library runs on, for as long as the process lives; shapes that need more (qb_bwd_workspace_nbytes(T,N,K) >

@@ -8,8 +8,8 @@
 // contiguous along the contraction) by staging operands in the caller's workspace:
 //   WT  [K, Np]   bf16(What) transposed, Np = N rounded up to 64, zero padded
 //   dYp [T, Np]   dY zero padded along n (only when N is not a multiple of 64)
-//   dYT [N, Tp]   dY transposed, Tp = T rounded up to 64, zero padded (only where dY's rows cannot be copied in aligned
-//                 pieces of 16 bytes: else dW's A operand goes into LDS as it lies and is turned by the fragment reads)
+//   dYT [N, Tp]   dY transposed, Tp = T rounded up to 64, zero padded (only for short contractions and rows that are not
+//                 whole pieces of 16 bytes: else dW's A operand goes into LDS as it lies and is turned by the fragment reads)
 //   XT  [K, Tp]   (2x'+1) transposed; |2x'+1| <= 255 is exact in bf16, h_x goes to the epilogue
 // Both products of a call run in one launch whose workgroups share the contraction steps evenly; a tile that two
 // or more workgroups worked on has its partial sums added in a fixed order, so results do not change from run
@@ -346,8 +346,8 @@ __device__ __forceinline__ bool sk_wait_flag(const int *f)
 template <int NSTAGE, bool MASK, int TM, int TN, bool TURN>
 __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
 {
-    // an MFMA wavefront owns TM x TN blocks of 32 x 32: tiles of 64*TM x 96*TN (128 x 96, or 256 x 192: half the
-    // operand bytes per multiply-add out of L2 and LDS)
+    // an MFMA wavefront owns TM x TN blocks of 32 x 32: tiles of 64*TM x 96*TN (128 x 96, or 128 x 192: five sevenths of
+    // the operand bytes per multiply-add out of L2 and LDS)
     constexpr int WN = 3, NPROD = 2;
     constexpr int BM = 64 * TM, BN = 96 * TN, BKB = 128;  // 64 bf16 per step
     constexpr int A_TOTAL = BM / 8, B_TOTAL = BN / 8;
@@ -357,6 +357,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
     constexpr int SLOT_FLOATS = BM * BN;
     constexpr int NB = TM * TN;  // blocks per wavefront
     static_assert((D - 1) * PERP < 64, "vmcnt has six bits");
+    static_assert(!TURN || BM == 128, "a row of the turned operand is 256 bytes");
     static_assert(TN <= 2 && (NB == 2 || NB % 4 == 0) && NB <= 8, "partial sums are read four blocks at a time; mask bits of a wavefront's blocks: 16 per block in two 64-bit words");
     __shared__ __align__(1024) uint8_t lds[NSTAGE * STAGE_BYTES];
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
