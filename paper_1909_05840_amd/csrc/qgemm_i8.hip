@@ -1027,8 +1027,9 @@ __device__ __forceinline__ void quant_block_lds(const v16i &acc, const uint8_t *
     }
     // With GELU.  The exact steps are erff, the true division and a rounding; the quick ones gelu_near and the reciprocal,
     // for all sixteen values without a branch.  They give the same code unless the quick product lies closer to a rounding
-    // boundary than the two routes can differ: 4.6e-5 for the division (derived at Quantizer), 1.6e-5 for the rounding of
-    // v + c, and 2e-6 in v for GELU (8e-7 of gelu_near, 7e-7 of the binary32 steps around erff).  The few such values
+    // boundary than the two routes can differ: 4.6e-5 for the division (derived at Quantizer), 255 * 2^-23 = 3.1e-5 for the
+    // two roundings of v + c, and 2e-6 in v for GELU (8e-7 of gelu_near, 7e-7 of the binary32 steps around erff; evaluated
+    // over the binary32 arguments of both signs the two differ by 9.6e-7 at most).  The few such values
     // (GELU's flat tail below -4.7 among them, where the code hangs on the last bits of erff) are gathered over the block
     // and done exactly, 64 at a time.  A block with many of them, as a look at a quarter of its values tells before the
     // quick steps, or a range too extreme for the reciprocal, goes through the exact steps.
@@ -1047,7 +1048,7 @@ __device__ __forceinline__ void quant_block_lds(const v16i &acc, const uint8_t *
         for (int r = 0; r < 16; r += 4) total += 4 * __popcll(__ballot(y[r] < -4.7f));
         if (qo.fast && total <= 64) {
             uint64_t near[16];
-            const float lim = 0.49993f - 2.0e-6f * qo.rinv;
+            const float lim = 0.49992f - 2.0e-6f * qo.rinv;
             total = 0;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
