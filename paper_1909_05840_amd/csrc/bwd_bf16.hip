@@ -294,8 +294,9 @@ __device__ __forceinline__ SkPiece sk_piece_at(const SkGroup &g, long long u, lo
 // 198 -> 188.5.  Rows of fewer than twelve tiles stay whole: cut into four and a narrow rest they lose (six, 1024 x 1024 at
 // 8000 tokens: 62.5 -> 68.0; eleven, 2048 x 2048 at 3000 tokens: 68.9 -> 70.2) or gain nothing (eight: 44.7, 45.0).  So do
 // contractions of up to kSkMinUnits steps, where a run holds whole tiles and shares nothing (896 x 3584 at 6 tokens in
-// strips: 20.3 -> 23.4; 616 x 5120 at 310, dW only, five steps: 19.1 -> 17.5).  Which runs meet at a tile changes with the
-// order, so single shapes go the other way (960 x 3840 at 8067 tokens, dX only: 74.4 -> 80.4; at 9174: 101.8 -> 98.4).
+// strips: 20.3 -> 23.4; 616 x 5120 at 310, dW only, five steps: 19.1 -> 17.5).  Nor does dX alone on tiles of 128 x 192 gain
+// (45 calls at 3000 to 12000 tokens: 0.8 % slower on average, up to 11, as other runs meet at a tile then: 960 x 3840 at 8067
+// 74.4 -> 80.4, at 9174 101.8 -> 98.4); with dW beside it dX's strips give 2 %.
 __device__ __forceinline__ void sk_place(const SkProblem &P, int t, int &tile_m, int &tile_n)
 {
     if (P.strip == P.tiles_n) {
@@ -908,6 +909,7 @@ void sk_run(const SkProduct *prod, int n, float *slots, int *flags, hipStream_t 
         for (int i = 0; i < n; ++i)
             sk_add<2, 2>(g, prod[i].A, prod[i].B, prod[i].M, prod[i].Nc, prod[i].Kc, prod[i].lda, prod[i].ldb, prod[i].out,
                          prod[i].scale, prod[i].C, prod[i].mask, prod[i].t_rows, prod[i].zeros);
+        if (n == 1 && prod[0].out == 0) g.p[0].strip = g.p[0].tiles_n;  // (dX alone: sk_place)
         sk_launch<3, 2, 2>(g, st);
     } else {
         for (int i = 0; i < n; ++i)

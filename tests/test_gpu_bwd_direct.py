@@ -114,8 +114,8 @@ def test_one_team(qb, bits, shape, asym):
 
 
 # (T, N, K): rows of 22 tiles of 128 x 192 (strips of four and a last one of two) and of 13 of 128 x 96 (a last one of one), both
-# products in strips; 13 with dX (four steps) in whole rows
-@pytest.mark.parametrize("shape", [(6100, 200, 4096), (700, 264, 1216), (700, 200, 1216)])
+# products in strips; 13 with dX (four steps) in whole rows; wide tiles with one output (dX alone in whole rows)
+@pytest.mark.parametrize("shape", [(6100, 200, 4096), (8300, 200, 4096), (700, 264, 1216), (700, 200, 1216)])
 def test_last_strip_of_tiles_is_narrower(qb, shape):
     T, N, K = shape
     print("bwd strips", shape, flush=True)
@@ -124,7 +124,10 @@ def test_last_strip_of_tiles_is_narrower(qb, shape):
     packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N, K, seed=N + K).to(DEV), 4, 8)
     Xq, _ = qb.qb_quantize_act(wl.activation(T, K, seed=T).to(DEV), CLIP)
     dX, dW = qb.qb_qlinear_bwd_ste(dY.to(DEV), Xq, CLIP, packed, h, 4, 8)
-    check(dY, oracle.dequantize_groupwise(qb.qb_unpack_codes(packed, N, K, 4).cpu().numpy(), h.cpu().numpy(), 4), Xq, dX, dW)
+    W_hat = oracle.dequantize_groupwise(qb.qb_unpack_codes(packed, N, K, 4).cpu().numpy(), h.cpu().numpy(), 4)
+    check(dY, W_hat, Xq, dX, dW)
+    check(dY, W_hat, Xq, qb.qb_qlinear_bwd_ste(dY.to(DEV), Xq, CLIP, packed, h, 4, 8, want_dw=False)[0], None)
+    check(dY, W_hat, Xq, None, qb.qb_qlinear_bwd_ste(dY.to(DEV), Xq, CLIP, packed, h, 4, 8, want_dx=False)[1])
 
 
 # (T, N, K): N a multiple of 8 or of 64, T with and without rows beyond a multiple of 64, tiles of 128 x 96 and (the last
