@@ -16,6 +16,7 @@
 // to run.
 #include "qb_common.hpp"
 #include "bwd_direct.hpp"
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -844,6 +845,409 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
     if (first_last) mma_piece(first);
 }
 
+// The same division of the work for calls with enough steps: tiles of 128 x 192 by workgroups of four wavefronts (64 x 96
+// results each, v_mfma_f32_16x16x32_bf16), two workgroups per CU that share no barrier.  All four SIMDs multiply, a step reads
+// 80 KB of fragments out of LDS for what takes the kernel above 98, and a workgroup's start, exchange of partial sums and
+// write-out run under the other one's MFMAs.
+struct DuoShare {      // a product's share of the workgroups
+    int tiles, runs;   // its tiles; the workgroups of an XCD that work on it
+    int p, rot;        // pieces of a tile's contraction; by how much the order of the tiles turns from piece to piece
+};
+struct DuoGroup {
+    SkGroup g;         // (ustart is not used)
+    DuoShare w, x;     // dW, then dX among the workgroups of an XCD
+};
+constexpr int kDuoRuns = 2 * kSkMaxRuns;
+constexpr int kDuoPerXcd = kDuoRuns / 8;
+constexpr int kDuoFlagsPerRun = 4;
+
+// global -> LDS copy with a wavefront-uniform base and a 32-bit byte offset per lane (the base is moved into registers of the
+// block's own: a VALU instruction may have written it right in front, which a vector memory instruction may read five wait
+// states later only)
+__device__ __forceinline__ void copy16_to_lds(const void *base, uint32_t off, uint32_t lds_addr)
+{
+    const void *own;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %1\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(own) : "s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
+}
+// the same address in scalar registers (64-bit divisions in its arithmetic run on the vector unit)
+__device__ __forceinline__ const uint8_t *scalar_address(const void *p)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return reinterpret_cast<const uint8_t *>((uint64_t)hi << 32 | lo);
+}
+// twenty-four float4 of a slot, 1024 bytes apart, all under way at once, past the caches of this XCD (sc1)
+__device__ __forceinline__ void sk_load24(const float4 *p, v4f (&t)[24])
+{
+    const float4 *a = p + 256, *b = p + 768, *c = p + 1280;
+    asm volatile("global_load_dwordx4 %0, %24, off offset:-4096 sc1\n\t" "global_load_dwordx4 %1, %24, off offset:-3072 sc1\n\t"
+                 "global_load_dwordx4 %2, %24, off offset:-2048 sc1\n\t" "global_load_dwordx4 %3, %24, off offset:-1024 sc1\n\t"
+                 "global_load_dwordx4 %4, %24, off sc1\n\t" "global_load_dwordx4 %5, %24, off offset:1024 sc1\n\t"
+                 "global_load_dwordx4 %6, %24, off offset:2048 sc1\n\t" "global_load_dwordx4 %7, %24, off offset:3072 sc1\n\t"
+                 "global_load_dwordx4 %8, %25, off offset:-4096 sc1\n\t" "global_load_dwordx4 %9, %25, off offset:-3072 sc1\n\t"
+                 "global_load_dwordx4 %10, %25, off offset:-2048 sc1\n\t" "global_load_dwordx4 %11, %25, off offset:-1024 sc1\n\t"
+                 "global_load_dwordx4 %12, %25, off sc1\n\t" "global_load_dwordx4 %13, %25, off offset:1024 sc1\n\t"
+                 "global_load_dwordx4 %14, %25, off offset:2048 sc1\n\t" "global_load_dwordx4 %15, %25, off offset:3072 sc1\n\t"
+                 "global_load_dwordx4 %16, %26, off offset:-4096 sc1\n\t" "global_load_dwordx4 %17, %26, off offset:-3072 sc1\n\t"
+                 "global_load_dwordx4 %18, %26, off offset:-2048 sc1\n\t" "global_load_dwordx4 %19, %26, off offset:-1024 sc1\n\t"
+                 "global_load_dwordx4 %20, %26, off sc1\n\t" "global_load_dwordx4 %21, %26, off offset:1024 sc1\n\t"
+                 "global_load_dwordx4 %22, %26, off offset:2048 sc1\n\t" "global_load_dwordx4 %23, %26, off offset:3072 sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]), "=&v"(t[6]), "=&v"(t[7]), "=&v"(t[8]), "=&v"(t[9]), "=&v"(t[10]), "=&v"(t[11]), "=&v"(t[12]), "=&v"(t[13]), "=&v"(t[14]), "=&v"(t[15]), "=&v"(t[16]), "=&v"(t[17]), "=&v"(t[18]), "=&v"(t[19]), "=&v"(t[20]), "=&v"(t[21]), "=&v"(t[22]), "=&v"(t[23])
+                 : "v"(a), "v"(b), "v"(c) : "memory");
+}
+
+template <bool MASK, bool TURN>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_duo_kernel(const DuoGroup dg)
+{
+    constexpr int TM = 4, TN = 6;  // blocks of 16 x 16 of a wavefront
+    constexpr int BM = 128, BN = 192, BKB = 128;  // 64 bf16 per step
+    constexpr int A_BYTES = BM * BKB, STAGE = (BM + BN) * BKB;
+    constexpr int NA = BM / 32, NB = BN / 32;  // copies per wavefront and step, each fills 1 KB
+    constexpr int SLOT_FLOATS = BM * BN;
+    static_assert(2 * STAGE <= 81920, "two workgroups per CU");
+    __shared__ __align__(1024) uint8_t lds[2 * STAGE];
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
+    const SkGroup &g = dg.g;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int q16 = lane & 15, hq = lane >> 4;
+    const int xcd = (int)blockIdx.x & 7, idx = (int)blockIdx.x >> 3;
+    const bool does_w = idx < dg.w.runs;
+    const DuoShare &S = does_w ? dg.w : dg.x;
+    const int tiles = S.tiles, runs = S.runs, pieces = S.p, first_idx = does_w ? 0 : dg.w.runs;
+    const SkProblem &P = g.p[does_w ? g.n - 1 : 0];
+    // the workgroup of piece c of tile t
+    auto block_of = [&](int c, int t) {
+        int k = t - c * S.rot % tiles;
+        k = c * tiles + (k < 0 ? k + tiles : k);
+        return 8 * (first_idx + k % runs) + k / runs;
+    };
+    int tile = 0, tile_end = 0, piece = 0, owner = 0;
+    if (pieces == 1) {
+        tile = tiles * xcd / 8 + idx - first_idx;
+        tile_end = tiles * (xcd + 1) / 8;
+        if (tile >= tile_end) return;
+    } else {
+        const int k = xcd * runs + idx - first_idx;
+        if (k >= tiles * pieces) return;
+        piece = k / tiles;
+        tile = (k + piece * S.rot) % tiles;
+        for (int c = 1; c < pieces; ++c)
+            if (block_of(c, tile) > block_of(owner, tile)) owner = c;
+    }
+    const int s0 = P.nsteps * piece / pieces, n = P.nsteps * (piece + 1) / pieces - s0;
+    const bool writes_tile = piece == owner;
+
+    // fragment reads: row l%16 of a 16-row block, logical chunk 4*kk + l/16, physical chunk ^ (row/2)%8
+    int a_fr[2], b_fr[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+        const int at = q16 * BKB + (((4 * kk + hq) ^ ((q16 >> 1) & 7)) << 4);
+        a_fr[kk] = wm * 64 * BKB + at;
+        b_fr[kk] = A_BYTES + wn * 96 * BKB + at;
+    }
+    // A as rows of dY (64 rows of 256 bytes, their 64-byte quarters swizzled with the row, the halves of a quarter with row/8):
+    // the transposing read hands lane j of a block of sixteen lanes four rows of column j; lane i points at row i/4 and at
+    // columns 4*(i%4).. of them
+    int a_turn[2];
+    {
+        const int at = (8 * hq + (q16 >> 2)) * 256 + (q16 & 3) * 8;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) a_turn[half] = at + ((half ^ (hq & 1)) << 5);
+    }
+    auto a_quarter = [&](int i) { return ((2 * wm + (i >> 1)) ^ (q16 >> 2)) << 6; };
+
+    // ---- copies
+    const uint8_t *a_ptr = nullptr, *b_ptr = nullptr;  // of the next step
+    size_t a_step = 0;
+    uint32_t a_off[NA], b_off[NB];
+    int tail = -1, over_row = 0;  // (TURN) steps until the one with rows past the end, and the first of them
+    const uint8_t *zeros = nullptr;
+    auto start_tile = [&](int tile) {
+        int tile_m, tile_n;
+        sk_place(P, tile, tile_m, tile_n);
+        const int M = P.M, Nc = P.Nc, lda = P.lda, ldb = P.ldb;
+        const int t_rows = TURN ? P.t_rows : 0;
+        // (rows of a tile lie less than 2^32 bytes apart: at most 192 rows of at most 2^25 bytes)
+        a_ptr = scalar_address(t_rows ? P.A + (size_t)s0 * 64 * lda : P.A + (size_t)tile_m * BM * lda + s0 * 64);
+        b_ptr = scalar_address(P.B + (size_t)tile_n * BN * ldb + s0 * 64);
+        a_step = t_rows ? (size_t)lda * 128 : (size_t)BKB;
+        const int a_last = M - 1 - tile_m * BM, b_last = Nc - 1 - tile_n * BN;
+#pragma unroll
+        for (int e = 0; e < NA; ++e) {
+            const int blk = wave * NA + e;
+            if (TURN && t_rows) {
+                const int t = blk * 4 + (lane >> 4);
+                int col = tile_m * BM + ((((lane >> 2) & 3) ^ (t & 3)) << 5) + ((((lane >> 1) & 1) ^ ((t >> 3) & 1)) << 4) + (lane & 1) * 8;
+                col = col < M ? col : M - 8;  // (M is a multiple of 8) columns past the end: outputs masked
+                a_off[e] = (uint32_t)t * (uint32_t)(lda * 2) + (uint32_t)col * 2;
+                continue;
+            }
+            int row = blk * 8 + (lane >> 3);
+            const int key = (row >> 1) & 7;
+            row = row < a_last ? row : a_last;  // rows past the end re-read the last one; outputs masked
+            a_off[e] = (uint32_t)row * (uint32_t)(lda * 2) + (((lane & 7) ^ key) << 4);
+        }
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            int row = (wave * NB + e) * 8 + (lane >> 3);
+            const int key = (row >> 1) & 7;
+            // LDS row 32*p + 16*b + l holds row 32*p + 2*l + b of the tile: a lane's blocks 2*p, 2*p + 1 are neighbouring columns
+            row = (row & ~31) + 2 * (row & 15) + ((row >> 4) & 1);
+            row = row < b_last ? row : b_last;
+            b_off[e] = (uint32_t)row * (uint32_t)(ldb * 2) + (((lane & 7) ^ key) << 4);
+        }
+        if constexpr (TURN) {
+            tail = t_rows && (t_rows & 63) ? t_rows / 64 - s0 : -1;
+            over_row = t_rows & 63;
+            zeros = static_cast<const uint8_t *>(P.zeros);
+        }
+    };
+    auto copy_step = [&](uint32_t stage) {
+        const uint32_t dst = lds_base + stage + wave * NA * 1024, dst_b = lds_base + stage + A_BYTES + wave * NB * 1024;
+        if (TURN && tail == 0) {  // (a contraction's last step) rows past the end are zeros
+#pragma unroll
+            for (int e = 0; e < NA; ++e) {
+                const bool over = (wave * NA + e) * 4 + (lane >> 4) >= over_row;
+                copy16_to_lds(over ? zeros : a_ptr + a_off[e], dst + e * 1024);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < NA; ++e) copy16_to_lds(a_ptr, a_off[e], dst + e * 1024);
+        }
+#pragma unroll
+        for (int e = 0; e < NB; ++e) copy16_to_lds(b_ptr, b_off[e], dst_b + e * 1024);
+        a_ptr += a_step;
+        b_ptr += BKB;
+        --tail;
+    };
+    // this wavefront's copies have landed (waited for before) and its LDS reads have returned; then the barrier
+    auto fence = [&]() {
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+    };
+    // slots: the pieces that do not write their tile, dW's tiles, then dX's
+    auto slot_of = [&](int c) -> float4 * {
+        const int k = (does_w ? 0 : dg.w.tiles * (dg.w.p - 1)) + tile * (pieces - 1) + c - (c > owner);
+        return reinterpret_cast<float4 *>(g.slots + (size_t)k * SLOT_FLOATS) + wave * TM * TN * 64 + lane;
+    };
+
+    start_tile(tile);
+    copy_step(0);
+    wait_vmcnt<0>();
+    uint32_t rd = 0;
+    while (true) {
+        int tile_m, tile_n;
+        sk_place(P, tile, tile_m, tile_n);
+        const int M = P.M, Nc = P.Nc;
+        const int row0 = tile_m * BM + wm * 64 + 4 * hq, col0 = tile_n * BN + wn * 96 + 2 * q16;  // + 16*i + r, + 32*p + b
+
+        // The clamp mask of this wavefront's results, one bit each, formed before the K-loop so that the write-out depends on
+        // no load: bit 2*(4*i + r) + b of word p.  Rows and columns past the end re-read valid elements.
+        uint32_t outside[TN / 2] = {0, 0, 0};
+        bool masked = false;
+        if constexpr (MASK) {
+            masked = writes_tile && P.mask.src != nullptr;
+            if (masked) {
+                const bool pair_ok = (reinterpret_cast<uintptr_t>(P.mask.src) & 7) == 0;  // (Nc is even)
+#pragma unroll
+                for (int p = 0; p < TN / 2; ++p) {
+                    int cc = col0 + 32 * p;
+                    cc = cc < Nc ? cc : Nc - 2;
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            int row = row0 + 16 * i + r;
+                            row = row < M ? row : M - 1;
+                            const float *src = P.mask.src + (size_t)row * Nc + cc;
+                            float2 mv;
+                            if (pair_ok) mv = *reinterpret_cast<const float2 *>(src);
+                            else mv = make_float2(src[0], src[1]);
+                            const float lim = P.mask.lim ? P.mask.lim[row / P.mask.rows_per_lim] : P.mask.lim_all;
+                            outside[p] |= (fabsf(mv.x) > lim ? 1u : 0u) << (2 * (4 * i + r));
+                            outside[p] |= (fabsf(mv.y) > lim ? 2u : 0u) << (2 * (4 * i + r));
+                        }
+                }
+            }
+        }
+
+        v4f acc[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        const bool more = tile + runs < tile_end;
+        auto k_loop = [&](auto turned_const) {
+            constexpr bool TURNED = decltype(turned_const)::value;
+            auto read_a = [&](const uint8_t *st, int kk, int i) {
+                if constexpr (TURNED) {
+                    typedef __attribute__((address_space(3))) v4bf *lds4;
+                    const uint8_t *at = st + a_turn[i & 1] + a_quarter(i) + kk * 8192;
+                    const v4bf x = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4)(at)), y = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4)(at + 1024));
+                    return __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
+                } else {
+                    return *reinterpret_cast<const v8bf *>(st + a_fr[kk] + i * 16 * BKB);
+                }
+            };
+            for (int s = 0; s < n; ++s) {
+                fence();
+                // over the stage that was read in the step before; in the last step the next tile's first operands, so that
+                // the address arithmetic and the latency lie under the MFMAs
+                if (s + 1 < n) copy_step(rd ^ STAGE);
+                else if (!TURNED && more) {  // (of dW a workgroup does one piece)
+                    start_tile(tile + runs);
+                    copy_step(rd ^ STAGE);
+                }
+                const uint8_t *st = lds + rd;
+                rd ^= STAGE;
+                v8bf a[2][TM], b[2][TN];
+                auto read_half = [&](int kk) {
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) b[kk][j] = *reinterpret_cast<const v8bf *>(st + b_fr[kk] + j * 16 * BKB);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) a[kk][i] = read_a(st, kk, i);
+                };
+                read_half(0);
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) {
+                    if (kk == 0) read_half(1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // one MFMA after the other shares an operand with it
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int x = 0; x < TN; ++x) {
+                            const int j = i & 1 ? TN - 1 - x : x;
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk][i], b[kk][j], acc[i][j], 0, 0, 0);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                }
+                if (s + 1 < n) wait_vmcnt<0>();  // the next step's copies
+            }
+        };
+        if (TURN && P.t_rows) k_loop(std::true_type{});
+        else k_loop(std::false_type{});
+
+        if (!writes_tile) {
+            // partial sums of the tile's leading or middle steps: to this run's slot, then the wavefront's flag
+            float4 *slot = slot_of(piece);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) sk_store4(slot + (i * TN + j) * 64, acc[i][j]);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every lane's stores have completed
+            if (lane == 0)
+                __hip_atomic_store(g.flags + (int)blockIdx.x * kDuoFlagsPerRun + wave, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wait_vmcnt<0>();
+        } else {
+            // the tile's other pieces in ascending order
+            bool ok = true;
+            for (int c = 0; c < pieces; ++c) {
+                if (c == piece) continue;
+                ok = sk_wait_flag(g.flags + block_of(c, tile) * kDuoFlagsPerRun + wave) && ok;
+                asm volatile("" ::: "memory");
+                const float4 *slot = slot_of(c);
+                v4f t[TM * TN];
+                sk_load24(slot, t);
+#pragma unroll
+                for (int e = 0; e < TM * TN; ++e) acc[e / TN][e % TN] += t[e];
+            }
+            if (!ok) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[i][j][r] = __builtin_nanf("");
+            }
+            if constexpr (MASK) {
+                if (masked) {  // (as selects before the stores: see the kernel above)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) acc[i][j][r] = ((outside[j >> 1] >> (2 * (4 * i + r) + (j & 1))) & 1u) ? 0.0f : acc[i][j][r];
+                }
+            }
+            const bool fast = (tile_m + 1) * BM <= M && (tile_n + 1) * BN <= Nc && (Nc & 7) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0;
+            const float scale = P.scale;
+            void *__restrict__ Cout = P.C;
+            const bool as_bf16 = P.out == 0;
+            if (fast && as_bf16) {
+                // a lane's two columns make one 32-bit word per row; four neighbouring lanes exchange words (two butterfly
+                // steps inside the quad) so that each holds one row of eight columns and writes 16 bytes
+                const int lq = lane & 3, odd = lane & 1, hi2 = (lane >> 1) & 1;
+                uint16_t *out0 = static_cast<uint16_t *>(Cout) + (size_t)(row0 + lq) * Nc + (col0 - 2 * lq);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int p = 0; p < TN / 2; ++p) {
+                        uint32_t d[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            d[r] = (uint32_t)f32_to_bf16_rne(acc[i][2 * p][r]) | ((uint32_t)f32_to_bf16_rne(acc[i][2 * p + 1][r]) << 16);
+                        const uint32_t rx0 = quad_xor1(odd ? d[0] : d[1]), rx1 = quad_xor1(odd ? d[2] : d[3]);
+                        const uint32_t e_lo = odd ? rx0 : d[0], e_hi = odd ? d[1] : rx0;  // row odd: this lane pair's words
+                        const uint32_t f_lo = odd ? rx1 : d[2], f_hi = odd ? d[3] : rx1;  // row 2 + odd
+                        const uint32_t s_lo = quad_xor2(hi2 ? e_lo : f_lo), s_hi = quad_xor2(hi2 ? e_hi : f_hi);
+                        v4u o;
+                        o[0] = hi2 ? s_lo : e_lo;
+                        o[1] = hi2 ? s_hi : e_hi;
+                        o[2] = hi2 ? f_lo : s_lo;
+                        o[3] = hi2 ? f_hi : s_hi;
+                        __builtin_nontemporal_store(o, reinterpret_cast<v4u *>(out0 + (size_t)(16 * i) * Nc + 32 * p));
+                    }
+                wait_vmcnt<TM * TN / 2>();  // the stores behind them may be under way: the next tile's copies have landed
+            } else if (fast) {
+                // fp32: 8 bytes per lane and row, whole 128-byte lines per instruction
+                float *out0 = static_cast<float *>(Cout) + (size_t)row0 * Nc + col0;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int p = 0; p < TN / 2; ++p) {
+                            v2f o;
+                            o[0] = acc[i][2 * p][r] * scale;
+                            o[1] = acc[i][2 * p + 1][r] * scale;
+                            __builtin_nontemporal_store(o, reinterpret_cast<v2f *>(out0 + (size_t)(16 * i + r) * Nc + 32 * p));
+                        }
+                wait_vmcnt<TM * TN * 2>();
+            } else {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = row0 + 16 * i + r;
+                        if (row < M) {
+#pragma unroll
+                            for (int j = 0; j < TN; ++j) {
+                                const int col = col0 + 32 * (j >> 1) + (j & 1);
+                                if (col < Nc) {
+                                    const size_t at = (size_t)row * Nc + col;
+                                    if (as_bf16) static_cast<uint16_t *>(Cout)[at] = f32_to_bf16_rne(acc[i][j][r]);
+                                    else static_cast<float *>(Cout)[at] = acc[i][j][r] * scale;
+                                }
+                            }
+                        }
+                    }
+                wait_vmcnt<0>();
+            }
+        }
+        if (!more) break;
+        tile += runs;
+    }
+}
+
 constexpr int kSkMinUnits = 4;
 // appends a product to a call's list: tiles of 64*TM x 96*TN, the contraction Kc a multiple of 64
 template <int TM, int TN>
@@ -896,12 +1300,91 @@ struct SkProduct {
 // Tiles of 128 x 192 when that leaves every CU at least kSkWideMinSteps of their steps, else 128 x 96; three stages.
 constexpr int kSkWideMinSteps = 16;
 constexpr size_t kSkSlotBytes = (size_t)128 * 192 * 4;
+// What a plan for both products takes, us, without the staging launch: the slowest CU, each of which has two workgroups (idx
+// and idx + 32 of an XCD), a step 1.33 us while both multiply and 0.70 alone; a tile written costs 7.4, partial sums written
+// 5.0, read 14.2 for all of a tile but one piece; and at least the mean of all CUs, which share the chip's power.  Fitted to
+// 316 timings (84 calls of 2000 to 17000 tokens, hidden sizes 512 to 1024, each with dW's tiles in 1 to 8 pieces).
+float duo_cost(const DuoShare &w, int w_steps, const DuoShare &x, int x_steps)
+{
+    const float kTile = 7.4f, kPiece = 5.0f, kRead = 14.2f;
+    const int x_tiles = (x.tiles + 7) / 8;  // of an XCD
+    const float w_len = (float)((w_steps + w.p - 1) / w.p), w_extra = kTile + (w.p > 1 ? kPiece + kRead * (w.p - 1) / w.p : kTile);
+    float worst = 0.0f, sum = 0.0f;
+    for (int i = 0; i < kDuoPerXcd / 2; ++i) {
+        float len[2], extra[2];
+        for (int half = 0; half < 2; ++half) {
+            const int j = i + half * kDuoPerXcd / 2 - w.runs, k = j < 0 ? 0 : x_tiles / x.runs + (j < x_tiles % x.runs);
+            len[half] = j < 0 ? w_len : (float)(k * x_steps);
+            extra[half] = j < 0 ? w_extra : k * kTile;
+        }
+        const float lo = std::min(len[0], len[1]), hi = std::max(len[0], len[1]);
+        worst = std::max(worst, 1.33f * lo + 0.70f * (hi - lo) + std::max(extra[0], extra[1]));
+        sum += 0.665f * (len[0] + len[1]) + 0.5f * (extra[0] + extra[1]);
+    }
+    return std::max(worst - 14.9f, 0.975f * sum / (kDuoPerXcd / 2));
+}
+
+// How the workgroups are shared between the products; false if the kernel above is faster.  It is below 8 steps a workgroup,
+// where its tiles are the smaller ones, and where dX's contraction is long (over 30 steps): there dY is the large operand, and
+// when it comes from memory the copies, one step ahead here, are late (10265 x 3072 x 768 1.05 of the time above, 12288 x 2304 x
+// 768 and 3072 x 768 inside a training step 1.09 and 1.05, though .98 and .94 with dY in the last-level cache).  The pieces that
+// do not write their tile have kSkMaxRuns slots.
+//   Both products: the cheapest number of pieces for dW's tiles, dX's whole tiles with the workgroups that are left, if that is
+//   7 % under the time of the kernel above (fitted to the same calls).  us a call with inputs from memory, above -> here:
+//   10557 x 768 x 3072 161 -> 126, 13497 x 640 x 2560 .71, 4635 x 1024 x 4096 120 -> 102, 10672 x 768 x 768 57.9 -> 49.7, 16686 x
+//   1920 x 640 .84, 3000 x 768 x 3072 .98.  Fewer workgroups with work than 376: 2593 x 4096 x 1024 (318) 1.06, 3129 x 3072 x 768
+//   (292) 1.29.
+//   dX alone: most of the workgroups have a tile, and the last round of tiles is not nearly empty (384 tiles .88, 506 .84, 520
+//   1.15, 682 .88, 1484 .81; 320 1.03; fewer tiles cut in two 1.04 to 1.21).
+//   dW alone: four pieces of a tile, no more than seven eighths of the workgroups (70 tiles of 211 steps .89, 72 of 133 .98; 96 of
+//   161 in three pieces 1.12, 144 of 81 in two 1.12; 72 of 97 1.06).
+constexpr int kDuoMinSteps = 8, kDuoMaxPieces = 8;
+bool duo_plan(DuoGroup &d, bool has_x, bool has_w)
+{
+    const SkGroup &g = d.g;
+    const long long units = g.ustart[g.n];
+    if (units < (long long)kDuoRuns * kDuoMinSteps) return false;
+    for (int i = 0; i < g.n; ++i)  // a tile's rows lie less than 2^32 bytes apart, and tile numbers times eight fit 32 bits
+        if (g.p[i].lda >= (1 << 23) || g.p[i].ldb >= (1 << 23) || (long long)g.p[i].tiles_m * g.p[i].tiles_n >= (1 << 26)) return false;
+    const int x_tiles = has_x ? g.p[0].tiles_m * g.p[0].tiles_n : 0, x_steps = g.p[0].nsteps;
+    const int w_tiles = has_w ? g.p[g.n - 1].tiles_m * g.p[g.n - 1].tiles_n : 0, w_steps = g.p[g.n - 1].nsteps;
+    auto share = [](int tiles, int runs, int p) { return DuoShare{tiles, runs, p, std::max(runs / p, 1)}; };
+    const int most = std::min(kDuoMaxPieces, w_steps);
+    if (has_x && x_steps > 30) return false;
+    d.w = d.x = {0, 0, 1, 0};
+    if (!has_w) {
+        d.x = share(x_tiles, kDuoPerXcd, 1);
+        return x_tiles >= 328 && (x_tiles <= kDuoRuns || x_tiles >= 656);
+    }
+    if (!has_x) {
+        const int p = 4;
+        if (w_steps < 32 * p || w_tiles < 64 || w_tiles * (p - 1) > kSkMaxRuns) return false;
+        d.w = share(w_tiles, (w_tiles * p + 7) / 8, p);
+        return true;
+    }
+    float best = 0.93f * (6.6f + 0.703f * (float)units / 256 + 9.2f * (float)x_tiles / 256);
+    bool found = false;
+    for (int p = 1; p <= most && w_tiles * p <= kDuoRuns - 8 && w_tiles * (p - 1) <= kSkMaxRuns; ++p) {
+        const DuoShare w = share(w_tiles, (w_tiles * p + 7) / 8, p), x = share(x_tiles, kDuoPerXcd - w.runs, 1);
+        if (w_tiles * p + std::min(x_tiles, 8 * x.runs) < 376) continue;
+        const float cost = duo_cost(w, w_steps, x, x_steps);
+        if (cost < best) {
+            best = cost;
+            d.w = w;
+            d.x = x;
+            found = true;
+        }
+    }
+    return found;
+}
+
 void sk_run(const SkProduct *prod, int n, float *slots, int *flags, hipStream_t st)
 {
     long long wide_units = 0;
     for (int i = 0; i < n; ++i)
         wide_units += (long long)((prod[i].M + 127) / 128) * ((prod[i].Nc + 191) / 192) * (prod[i].Kc / 64);
-    SkGroup g;
+    DuoGroup d;
+    SkGroup &g = d.g;
     g.n = 0;
     g.slots = slots;
     g.flags = flags;
@@ -910,6 +1393,17 @@ void sk_run(const SkProduct *prod, int n, float *slots, int *flags, hipStream_t 
             sk_add<2, 2>(g, prod[i].A, prod[i].B, prod[i].M, prod[i].Nc, prod[i].Kc, prod[i].lda, prod[i].ldb, prod[i].out,
                          prod[i].scale, prod[i].C, prod[i].mask, prod[i].t_rows, prod[i].zeros);
         if (n == 1 && prod[0].out == 0) g.p[0].strip = g.p[0].tiles_n;  // (dX alone: sk_place)
+        if (duo_plan(d, prod[0].out == 0, prod[n - 1].out == 1)) {
+            bool any_mask = false, any_turned = false;
+            for (int i = 0; i < n; ++i) {
+                any_mask = any_mask || g.p[i].mask.src != nullptr;
+                any_turned = any_turned || g.p[i].t_rows != 0;
+            }
+            auto *kernel = any_mask ? (any_turned ? gemm_bf16_duo_kernel<true, true> : gemm_bf16_duo_kernel<true, false>)
+                                    : (any_turned ? gemm_bf16_duo_kernel<false, true> : gemm_bf16_duo_kernel<false, false>);
+            hipLaunchKernelGGL(kernel, dim3(kDuoRuns), dim3(256), 0, st, d);
+            return;
+        }
         sk_launch<3, 2, 2>(g, st);
     } else {
         for (int i = 0; i < n; ++i)

@@ -1,5 +1,6 @@
 """The backward's one-launch kernel for small calls (N a multiple of 64) at the edges of its tiles and steps, for one, two
-and four teams per workgroup, and the staged path's turned operand and strips of tiles, against the oracle and plain fp64."""
+and four teams per workgroup, and the staged path's turned operand, strips of tiles and two workgroups per CU, against the oracle
+and plain fp64."""
 import ctypes
 
 import numpy as np
@@ -151,6 +152,36 @@ def test_turned_operand_gives_the_staged_operands_sums(qb, shape):
         assert torch.equal(dW, sW[:N]) and torch.equal(mW, sW[:N])
     ref = dY[:, :N].double().T @ ((2.0 * Xq.double() + 1.0) * (CLIP / 255.0))
     assert (dW.double() - ref).norm() <= 1e-5 * ref.norm()  # fp32 sums of exact products
+
+
+# (T, N, K) of calls with enough steps for two workgroups per CU (tiles of 128 x 192, pieces of dW's tiles with their sums
+# exchanged, dX's whole tiles): dW's tiles whole, in two and in five pieces, some workgroups with more tiles of dX than others,
+# whole tiles only, tiles with rows and columns past the end, T and N with and without a rest to a step, dY turned and staged;
+# 4160 x 1030 x 4096 and 12800 x 512 x 640 for one product alone
+@pytest.mark.parametrize("bits", [3, 8])
+@pytest.mark.parametrize("shape", [(2863, 1024, 4096), (3328, 768, 3072), (8192, 700, 704), (5505, 1016, 960), (4160, 1030, 4096), (12800, 512, 640)])
+def test_two_workgroups_per_cu(qb, shape, bits):
+    T, N, K = shape
+    print("bwd two workgroups per CU", shape, bits, flush=True)
+    W, X, dY = wl.weight(N, K, seed=N + K + bits), wl.activation(T, K, seed=T), wl.grad_output_bf16(T, N, seed=T + N)
+    G = 2
+    Wd, Xd, dYd = W.to(DEV), X.to(DEV), dY.to(DEV)
+    packed, h, m, _ = qb.qb_quantize_groupwise(Wd, bits, G)
+    Xq, _ = qb.qb_quantize_act(Xd, CLIP)
+    dX, dW = qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G)
+    W_hat = oracle.dequantize_groupwise(qb.qb_unpack_codes(packed, N, K, bits).cpu().numpy(), h.cpu().numpy(), bits)
+    check(dY, W_hat, Xq, dX, dW)
+    # the same bits again, from inputs that lie elsewhere, into outputs that ask for single stores, and behind a clamp mask
+    oX = behind(torch.empty(T, K, dtype=torch.bfloat16, device=DEV), 1)
+    oW = behind(torch.empty(N, K, device=DEV), 1)
+    qb.qb_qlinear_bwd_ste(behind(dYd, 4), Xq, CLIP, packed, h, bits, G, dX=oX, dW=oW)
+    assert torch.equal(oX, dX) and torch.equal(oW, dW)
+    mX, mW = qb.qb_qlinear_bwd_ste_masked(dYd, Xq, CLIP, packed, h, bits, G, X=2.0 * Xd, W=Wd, m=0.5 * m)
+    out_x, out_w = (2.0 * Xd).abs() > CLIP, Wd.abs() > (0.5 * m).repeat_interleave(N // G)[:, None]
+    assert bool(out_x.any()) and bool(out_w.any())
+    assert torch.equal(mX, torch.where(out_x, torch.zeros_like(dX), dX)) and torch.equal(mW, torch.where(out_w, torch.zeros_like(dW), dW))
+    check(dY, W_hat, Xq, qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, want_dw=False)[0], None)
+    check(dY, W_hat, Xq, None, qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, want_dx=False)[1])
 
 
 # one launch, staged (turned where dY is not aligned), turned, neither
