@@ -57,7 +57,8 @@ __device__ __forceinline__ float asym_value(int a4, int rh, int L, float hx, flo
 }
 
 // bid: the workgroup's number among the tiles_m * tiles_n workgroups of this problem
-template <int BITS, int TM, int TN, int WM, int WN, int KU>
+// GEN: per-token scales or asymmetric group ranges (a variant of its own, so that the plain call carries none of its code)
+template <int BITS, int TM, int TN, int WM, int WN, int KU, bool GEN>
 __device__ __forceinline__ void qgemm_i8_body(
     const int8_t *__restrict__ Xq, const int32_t *__restrict__ rs_x, const uint8_t *__restrict__ packed,
     const float *__restrict__ h, const int32_t *__restrict__ rs_w, const float *__restrict__ bias,
@@ -86,7 +87,8 @@ __device__ __forceinline__ void qgemm_i8_body(
     }
     const int tile_m = logical / tiles_n, tile_n = logical - tile_m * tiles_n;
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave - wm * WN;
     const int l32 = lane & 31, hf = lane >> 5;
 
@@ -176,8 +178,42 @@ __device__ __forceinline__ void qgemm_i8_body(
                 _Pragma("unroll") for (int i = 0; i < BITS; ++i) bcur[tn][kk][i] = bnext[tn][kk][i];      \
     }
 
+    // The epilogue's parameters.  None is loaded between stores: the load would wait for every store before it (256 x 2304 x
+    // 768 with per-token scales and asymmetric ranges 6.7 -> 4.7 us; with the plain scale ragged tiles alone did so, 1499 x 768 x
+    // 768 5.8 -> 4.6, tiles of 128 x 128, 3001 x 1344 x 448 18.7 -> 11.6).  Tiles of one block a wavefront have them on their
+    // way during the K-loop, if there are registers for them (256 x 2304 x 768 4.45 -> 4.28).
+    constexpr bool AHEAD = TM * TN == 1 && KU < 4;
+    constexpr int L = (1 << BITS) - 1;
+    constexpr int E2 = (BITS == 8) ? 2 : -2 * L;  // 2*e
+    int coln[TN], rx[16];
+    float hg[TN], zn[TN], bv[TN], hr[16];
+    auto load_columns = [&]() {
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+            const int n = tile_n * BN + (wn * TN + tn) * 32 + l32, nn = n < N ? n : N - 1;
+            coln[tn] = 2 * rs_w[nn] + K;
+            hg[tn] = h[nn / rows_per_group];
+            zn[tn] = GEN && q0 ? q0[nn / rows_per_group] : 0.0f;
+            bv[tn] = bias ? bias[nn] : 0.0f;
+        }
+    };
+    auto load_rows = [&](int tm) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            int t = tile_m * BM + (wm * TM + tm) * 32 + 4 * hf + 8 * (i >> 2) + (i & 3);
+            t = t < T ? t : T - 1;
+            const uint32_t off = (uint32_t)t * 4u;  // (T <= 2^24)
+            rx[i] = *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(rs_x) + off);
+            if constexpr (GEN) hr[i] = hx_rows ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(hx_rows) + off) : hx;
+        }
+    };
+
     const int nsteps = K / BK;
     QB_LOAD_GLOBAL(0, bcur)
+    if constexpr (AHEAD) {
+        load_columns();
+        load_rows(0);
+    }
     QB_STORE_LDS(0)
     __syncthreads();
     // steady state: fetch step s+1 while the matrix cores work on step s (no branches inside)
@@ -196,81 +232,58 @@ __device__ __forceinline__ void qgemm_i8_body(
 #undef QB_COMPUTE
 #undef QB_ROTATE_B
 
-    // ---- epilogue: exact integer corrections, then one scale per column
-    constexpr int L = (1 << BITS) - 1;
-    constexpr int E2 = (BITS == 8) ? 2 : -2 * L;  // 2*e
+    // ---- epilogue: exact integer corrections, then one scale per column (or per column and token)
     const bool interior = (tile_m + 1) * BM <= T && (tile_n + 1) * BN <= N;  // uniform over the workgroup
+    if constexpr (!AHEAD) load_columns();
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn) {
-        const int n = tile_n * BN + (wn * TN + tn) * 32 + l32;
-        const bool n_ok = n < N;
-        const int nn = n_ok ? n : N - 1;
-        const int coln = 2 * rs_w[nn] + K;
-        const float hg = h[nn / rows_per_group];
-        const float scale = hx * hg;
-        const float bv = bias ? bias[nn] : 0.0f;
+    for (int tm = 0; tm < TM; ++tm) {
+        if constexpr (!AHEAD) {
+            asm volatile("" ::: "memory");  // (32 rows' parameters at a time: there are no registers for more)
+            load_rows(tm);
+        }
+        const int left = T - (tile_m * BM + (wm * TM + tm) * 32 + 4 * hf);
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-            const int t0 = tile_m * BM + (wm * TM + tm) * 32 + 4 * hf;
-            if (q0) {
-                const float zn = q0[nn / rows_per_group];
+        for (int tn = 0; tn < TN; ++tn) {
+            const bool n_ok = tile_n * BN + (wn * TN + tn) * 32 + l32 < N;
+            // a wavefront-uniform row address and the lane's 32-bit byte offset
+            const size_t block = (size_t)(tile_m * BM + (wm * TM + tm) * 32) * N + tile_n * BN + (wn * TN + tn) * 32;
+            const uint32_t lane_off = (uint32_t)(4 * hf * N + l32) * 4u;
+            auto a4_of = [&](int i) { return qb_a4(acc[tm][tn][i], qb_mad24(E2, rx[i], coln[tn])); };  // |rs_x| <= 128*K < 2^23
+            auto asym = [&](int i, int a4) { return asym_value(a4, rx[i] + (K >> 1), L, hr[i], hg[tn], zn[tn]) + bv[tn]; };
+            auto plain = [&](int i, int a4) { return ((GEN ? hr[i] : hx) * hg[tn]) * (float)a4 + bv[tn]; };
+            auto row_of = [](int i) { return 8 * (i >> 2) + (i & 3); };
+            auto put = [&](int i, float y) { *reinterpret_cast<float *>(reinterpret_cast<char *>(Y + block + (size_t)row_of(i) * N) + lane_off) = y; };
+            // (straight-line code where it can be: a check per value costs 0.8 us of 4.4)
+            if (interior && A4out == nullptr) {
+                if (GEN && q0) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int t = t0 + 8 * (i >> 2) + (i & 3);
-                    if (t < T && n_ok) {
-                        const int a4 = qb_a4(acc[tm][tn][i], E2 * rs_x[t] + coln);
-                        const size_t at = (size_t)t * N + n;
-                        Y[at] = asym_value(a4, rs_x[t] + (K >> 1), L, hx_rows ? hx_rows[t] : hx, hg, zn) + bv;
-                        if (A4out) A4out[at] = a4;
+                    for (int i = 0; i < 16; ++i) put(i, asym(i, a4_of(i)));
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) put(i, plain(i, a4_of(i)));
+                }
+            } else if (n_ok) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (row_of(i) < left) {
+                        const int a4 = a4_of(i);
+                        put(i, GEN && q0 ? asym(i, a4) : plain(i, a4));
+                        if (A4out) *reinterpret_cast<int32_t *>(reinterpret_cast<char *>(A4out + block + (size_t)row_of(i) * N) + lane_off) = a4;
                     }
-                }
-            } else if (hx_rows) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int t = t0 + 8 * (i >> 2) + (i & 3);
-                    if (t < T && n_ok) {
-                        const int a4 = qb_a4(acc[tm][tn][i], E2 * rs_x[t] + coln);
-                        const size_t at = (size_t)t * N + n;
-                        Y[at] = (hx_rows[t] * hg) * (float)a4 + bv;
-                        if (A4out) A4out[at] = a4;
-                    }
-                }
-            } else if (interior) {
-                int rx[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) rx[i] = rs_x[t0 + 8 * (i >> 2) + (i & 3)];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int t = t0 + 8 * (i >> 2) + (i & 3);
-                    const int a4 = qb_a4(acc[tm][tn][i], qb_mad24(E2, rx[i], coln));
-                    const size_t at = (size_t)t * N + n;
-                    Y[at] = scale * (float)a4 + bv;
-                    if (A4out) A4out[at] = a4;
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int t = t0 + 8 * (i >> 2) + (i & 3);
-                    if (t < T && n_ok) {
-                        const int a4 = qb_a4(acc[tm][tn][i], E2 * rs_x[t] + coln);
-                        const size_t at = (size_t)t * N + n;
-                        Y[at] = scale * (float)a4 + bv;
-                        if (A4out) A4out[at] = a4;
-                    }
-                }
             }
         }
     }
 }
 
-template <int BITS, int TM, int TN, int WM, int WN, int KU>
-__global__ __launch_bounds__(64 * WM * WN) void qgemm_i8_kernel(
+// (at least four wavefronts a SIMD, or three: the accumulators then lie in ordinary registers, 1 to 4 % of a small call)
+template <int BITS, int TM, int TN, int WM, int WN, int KU, bool GEN>
+__global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 ? 3 : KU == 4 ? 1 : 4) void qgemm_i8_kernel(
     const int8_t *__restrict__ Xq, const int32_t *__restrict__ rs_x, const uint8_t *__restrict__ packed,
     const float *__restrict__ h, const int32_t *__restrict__ rs_w, const float *__restrict__ bias,
     float *__restrict__ Y, int32_t *__restrict__ A4out, int T, int N, int K, int rows_per_group, float hx,
     int tiles_m, int tiles_n, const float *__restrict__ hx_rows, const float *__restrict__ q0)
 {
-    qgemm_i8_body<BITS, TM, TN, WM, WN, KU>(Xq, rs_x, packed, h, rs_w, bias, Y, A4out, T, N, K, rows_per_group, hx, tiles_m,
+    qgemm_i8_body<BITS, TM, TN, WM, WN, KU, GEN>(Xq, rs_x, packed, h, rs_w, bias, Y, A4out, T, N, K, rows_per_group, hx, tiles_m,
                                             tiles_n, hx_rows, q0, blockIdx.x);
 }
 
@@ -447,14 +460,14 @@ struct SmallGroup {
     SmallProblem p[QB_MAX_BATCH];
 };
 template <int BITS, int KU>
-__global__ __launch_bounds__(128) void qgemm_i8_small_group_kernel(const SmallGroup g)
+__global__ __launch_bounds__(128, 4) void qgemm_i8_small_group_kernel(const SmallGroup g)
 {
     int j = 0;
     while (j + 1 < g.n && (int)blockIdx.x >= g.first_wg[j + 1]) ++j;
     const SmallProblem &p = g.p[j];
     const int local = blockIdx.x - g.first_wg[j];
     if (local >= p.tiles_m * p.tiles_n) return;  // (uniform over the workgroup)
-    qgemm_i8_body<BITS, 1, 1, 1, 2, KU>(p.Xq, p.rs_x, p.packed, p.h, p.rs_w, p.bias, p.Y, nullptr, p.T, p.N, p.K,
+    qgemm_i8_body<BITS, 1, 1, 1, 2, KU, false>(p.Xq, p.rs_x, p.packed, p.h, p.rs_w, p.bias, p.Y, nullptr, p.T, p.N, p.K,
                                         p.rows_per_group, p.hx, p.tiles_m, p.tiles_n, nullptr, nullptr, local);
 }
 
@@ -769,6 +782,12 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_i8_dma_kernel(
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             const int t0 = tile_m * BM + (wm * TM + tm) * 32 + 4 * hf;
+            int rx[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int t = t0 + 8 * (i >> 2) + (i & 3);
+                rx[i] = rs_x[t < T ? t : T - 1];
+            }
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
                 const int n = tile_n * BN + (wn * TN + tn) * 32 + l32;
@@ -776,7 +795,7 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_i8_dma_kernel(
                 for (int i = 0; i < 16; ++i) {
                     const int t = t0 + 8 * (i >> 2) + (i & 3);
                     if (t < T && n_ok[tn]) {
-                        const int a4 = qb_a4(acc[tm][tn][i], E2 * rs_x[t] + coln[tn]);
+                        const int a4 = qb_a4(acc[tm][tn][i], E2 * rx[i] + coln[tn]);
                         const size_t at = (size_t)t * N + n;
                         Y[at] = scale[tn] * (float)a4 + bv[tn];
                         if (A4out) A4out[at] = a4;
@@ -1814,8 +1833,8 @@ void launch_cfg(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, co
 {
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
     const int tiles_m = (T + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    hipLaunchKernelGGL((qgemm_i8_kernel<BITS, TM, TN, WM, WN, KU>), dim3(tiles_m * tiles_n), dim3(64 * WM * WN), 0, st,
-                       Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, tiles_m, tiles_n, hx_rows, q0);
+    auto *kernel = hx_rows || q0 ? qgemm_i8_kernel<BITS, TM, TN, WM, WN, KU, true> : qgemm_i8_kernel<BITS, TM, TN, WM, WN, KU, false>;
+    hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(64 * WM * WN), 0, st, Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, tiles_m, tiles_n, hx_rows, q0);
 }
 
 // grid_cap: upper bound of workgroups (a multiple of 8); 0 = one workgroup per tile
