@@ -654,6 +654,63 @@ __global__ __launch_bounds__(256) void quantize_act_dyn_kernel(const float *__re
     }
 }
 
+// ---- activations, a workgroup per row (few rows, or long ones: rule at act_row_shape), with the call's range or (DYN) the row's
+// own.  What bounds small calls is latency: a wavefront that walks a row of 3072 in chunks, or holds all of it, has the loads' latency
+// and then 48 values' arithmetic per lane one after the other, on a chip that is mostly idle.  Four wavefronts share the row, all
+// loads under way at once (390 x 3072 4.55 -> 2.82 us, with a range per token 5.16 -> 3.46).  (Rows of more than 4096 values: the rest is loaded again, from L2.)
+template <bool DYN>
+__global__ __launch_bounds__(256) void quantize_act_row_kernel(const float *__restrict__ X, int K, float clip, int8_t *__restrict__ Xq,
+                                                               int32_t *__restrict__ rs_x, float *__restrict__ hx)
+{
+    constexpr int V = 4;
+    __shared__ float part_max[4];
+    __shared__ int part_sum[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = blockIdx.x;
+    const int k4 = K >> 2;
+    const float4 *src = reinterpret_cast<const float4 *>(X + (size_t)row * K);
+    float4 v[V];
+    float mx = 0.0f;
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+        const int idx = u * 256 + tid;
+        if (idx < k4) v[u] = src[idx];
+    }
+    if constexpr (DYN) {
+#pragma unroll
+        for (int u = 0; u < V; ++u)
+            if (u * 256 + tid < k4) mx = absmax4(v[u], mx);
+        for (int idx = V * 256 + tid; idx < k4; idx += 256) mx = absmax4(src[idx], mx);
+        mx = wave_max(mx);
+        if (lane == 0) part_max[wave] = mx;
+        __syncthreads();
+        clip = fmaxf(fmaxf(part_max[0], part_max[1]), fmaxf(part_max[2], part_max[3]));
+    }
+    Quantizer qz;
+    qz.set(clip, 255.0f);
+    if (DYN && tid == 0) hx[row] = qz.half_step();
+    uint32_t *dst = reinterpret_cast<uint32_t *>(Xq + (size_t)row * K);
+    uint32_t sum = 0;
+    auto quantize = [&](int idx, float4 x) {
+        if constexpr (!DYN) {
+            x.x = __builtin_amdgcn_fmed3f(x.x, -clip, clip);
+            x.y = __builtin_amdgcn_fmed3f(x.y, -clip, clip);
+            x.z = __builtin_amdgcn_fmed3f(x.z, -clip, clip);
+            x.w = __builtin_amdgcn_fmed3f(x.w, -clip, clip);
+        }
+        const uint32_t q = qz.code4(x);
+        sum = __builtin_amdgcn_sad_u8(q, 0u, sum);
+        dst[idx] = q ^ 0x80808080u;  // u - 128 as int8
+    };
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+        if (u * 256 + tid < k4) quantize(u * 256 + tid, v[u]);
+    for (int idx = V * 256 + tid; idx < k4; idx += 256) quantize(idx, src[idx]);
+    const int total = wave_sum((int)sum);
+    if (lane == 0) part_sum[wave] = total;
+    __syncthreads();
+    if (tid == 0) rs_x[row] = part_sum[0] + part_sum[1] + part_sum[2] + part_sum[3] - 128 * K;
+}
+
 // ---- test hook: slots -> row-major codes -----------------------------------------------------------
 template <int BITS>
 __global__ __launch_bounds__(256) void unpack_codes_kernel(const uint8_t *__restrict__ packed, int N, int K,
@@ -1165,12 +1222,28 @@ extern "C" qb_status qb_quantize_groupwise_batched(const qb_quant_job *jobs, int
     return launch_status();
 }
 
+// Which activation tensors have a workgroup per row instead of a wavefront.  Time / time with a wavefront, fixed range and range per
+// token:  K 1024 to 8192, up to 64 tokens .92 to .40;  768 and 1024, 512 tokens .95 and .90, 700 .99 and .94, 1001 1.03 and 1.0, 4096
+// 1.4;  448 and 256 .95 to 1.1 at any size;  1344, 1001 .87, 2048 .98, 4096 1.09;  1792, 2048 .97, 3000 1.04, 12288 .91;  2048 and
+// more .82 to .98 at 2000 to 32768 tokens (3072, 12288: 29.5 -> 27.7 and 33.0 -> 28.6 us; 4096, 32768: 133 -> 120, 136 -> 118), where
+// long runs of one row are easier on the memory than many rows at a time.
+static bool act_row_shape(int64_t T, int64_t K)
+{
+    if (K >= 2048) return T <= (1 << 22);  // (a grid has less than 2^32 threads)
+    return T <= (K > 1024 ? 2048 : K > 512 ? 640 : 0);
+}
+
 extern "C" qb_status qb_quantize_act(const float *X, int64_t T, int64_t K, float clip, int8_t *Xq, int32_t *rs_x,
                                      void *stream)
 {
     if (!X || !Xq || !rs_x) return QB_ERR_NULL;
     if (T <= 0 || T > (1 << 30) || !k_ok(K)) return QB_ERR_SHAPE;
     if (!(clip > 0.0f) || !(clip < 3.0e38f)) return QB_ERR_CLIP;
+    if (act_row_shape(T, K)) {
+        hipLaunchKernelGGL(quantize_act_row_kernel<false>, dim3((unsigned)T), dim3(256), 0, static_cast<hipStream_t>(stream), X, (int)K, clip, Xq, rs_x,
+                           static_cast<float *>(nullptr));
+        return launch_status();
+    }
     // at most 8 workgroups per CU; fewer rows than that: one wavefront per row
     unsigned blocks = (unsigned)((T + 3) / 4);
     if (blocks > 2048) blocks = 2048;
@@ -1234,9 +1307,13 @@ extern "C" qb_status qb_quantize_act_dyn(const float *X, int64_t T, int64_t K, i
 {
     if (!X || !Xq || !rs_x || !hx_rows) return QB_ERR_NULL;
     if (T <= 0 || T > (1 << 30) || !k_ok(K)) return QB_ERR_SHAPE;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (act_row_shape(T, K)) {
+        hipLaunchKernelGGL(quantize_act_row_kernel<true>, dim3((unsigned)T), dim3(256), 0, st, X, (int)K, 0.0f, Xq, rs_x, hx_rows);
+        return launch_status();
+    }
     unsigned blocks = (unsigned)((T + 3) / 4);
     if (blocks > 2048) blocks = 2048;
-    hipStream_t st = static_cast<hipStream_t>(stream);
     if (K <= 1024) hipLaunchKernelGGL(quantize_act_dyn_kernel<4>, dim3(blocks), dim3(256), 0, st, X, (int)T, (int)K, Xq, rs_x, hx_rows);
     else hipLaunchKernelGGL(quantize_act_dyn_kernel<16>, dim3(blocks), dim3(256), 0, st, X, (int)T, (int)K, Xq, rs_x, hx_rows);
     return launch_status();
