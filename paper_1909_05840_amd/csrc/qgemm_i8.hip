@@ -23,7 +23,7 @@
 //                       one's write-out runs under the other's K-loop), an 8-bit output, per-token scales,
 //                       asymmetric group ranges.
 //   qgemm_i8_split_kernel the smallest problems: the contraction sliced inside the workgroup, no LDS in the loop.
-//   qgemm_i8_duo_kernel the largest problems at 2, 3 and 4 bits: 128x256 tiles on the 16x16x64 MFMA, two independent
+//   qgemm_i8_duo_kernel the largest problems: 128x256 tiles on the 16x16x64 MFMA, two independent
 //                       workgroups per CU that multiply and write out in turn.
 // In all of them but the split kernel, whose operands go straight to registers, the token tile sits in LDS as dense
 // 128-byte rows whose 16-byte chunks are XOR-swizzled by the row number, so that the MFMA fragment reads are free of bank
@@ -1497,9 +1497,9 @@ __global__ __launch_bounds__(64 * (WM * WN + NPROD), (SIMD3 && OUT != 2 && NSTAG
 // workgroup per CU, two groups of wavefronts half a phase apart) have the same K-loop, but a tile's write-out then runs
 // next to nothing: 188 and 118 us.  A second barrier per step that frees the stage earlier (copies two steps ahead) and
 // lines touched ahead of the copies were slower (188 and 120; 188 and 124).
-// That is the 2-bit build.  At 3 and 4 bits one vector register does not fit, and its reload in front of the write-out waits
-// for the next tile's copies before the first store goes out: 4096 x 1024 165 and 155 us, 1024 x 4096 129 and 116, to 148 and 110 at
-// 2 bits (with the tokens in the last-level cache).
+// That is the 2-bit build; at 3 and 4 bits 4096 x 1024 takes 165 and 155 us, 1024 x 4096 129 and 116, to 148 and 110 at 2 bits (with the
+// tokens in the last-level cache).  8 bits: 32768 x 4096 x 1024 with its activation quantizer 243 -> 198 us (two plain 128x128 workgroups
+// per CU before), 32768 x 1024 x 4096 293 -> 246, 12288 x 3072 x 768 63 -> 58.
 struct DuoArgs {
     const int8_t *Xq;
     const int32_t *rs_x;
@@ -1521,13 +1521,16 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
 {
     constexpr int BM = 128, BN = 256, BK = 128;
     constexpr int SLOT = 4 * BITS, CH = (BITS == 3) ? 12 : 16, LSLOT = (BITS == 3) ? 16 : SLOT;
-    constexpr int PAIR = 128 * SLOT, LPAIR = 128 * LSLOT;  // a 32-neuron block of one step, in memory and in LDS
+    // A step's weights are read in one phase; at 8 bits in two of 64 features, whose stages take turns (two of 128 features
+    // for each of two workgroups would not fit the LDS).  The tokens' rows of 128 bytes are whole lines at every width.
+    constexpr int PHASES = BITS == 8 ? 2 : 1, PHF = BK / PHASES;
+    constexpr int PAIR = PHF * SLOT, LPAIR = PHF * LSLOT;  // a 32-neuron block of one phase, in memory and in LDS
     constexpr int PARTS = LPAIR / 1024;                    // copies of one such block
-    constexpr int NB = 2 * PARTS;                          // weight copies per wavefront and step
+    constexpr int NB = 2 * PARTS;                          // weight copies per wavefront and phase
     constexpr int A_BYTES = BM * BK, STAGE = A_BYTES + 8 * LPAIR;
     constexpr int PARAM = (128 + 3 * 256) * 4;             // rs_x, rs_w, h of the neuron's group, bias
-    constexpr int E2 = -2 * ((1 << BITS) - 1);             // 2*e
-    static_assert(BITS < 8, "two workgroups' stages fit the LDS up to 4 bits");
+    constexpr int E2 = (BITS == 8) ? 2 : -2 * ((1 << BITS) - 1);  // 2*e
+    static_assert(2 * (2 * STAGE + 2 * PARAM) <= 163840, "two workgroups per CU");
     __shared__ __align__(1024) uint8_t lds[2 * STAGE + 2 * PARAM];
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
 
@@ -1537,14 +1540,26 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
 
     // fragment reads: token row l%16 of a 16-row block, logical chunk 2*(l/16) + kk (the 32 features of a slot)
     const int fkey = (q16 >> 1) & 7;
-    const int a_fr[2] = {q16 * BK + (((2 * hq) ^ fkey) << 4), q16 * BK + (((2 * hq + 1) ^ fkey) << 4)};
+    // (at 8 bits chunk 4*phase + l/16: the lane's sixteen features of the phase)
+    const int a_fr[2] = {q16 * BK + (((BITS == 8 ? hq : 2 * hq) ^ fkey) << 4), q16 * BK + (((BITS == 8 ? hq + 4 : 2 * hq + 1) ^ fkey) << 4)};
     // codes: slot 2*(l%16) + b of quarter l/16 of the block; b toggles bit 4 of the address (at 2 bits one read gives both).
     // A lane's two neurons of a block are neighbours, so that its stores are 8 bytes and every store instruction covers
     // whole 128-byte lines; the copies swap neighbouring slots in every other run of sixteen against the bank conflicts
     // of that order.
+    // At 8 bits a slot is two chunks of sixteen codes and lane l reads chunk (l/16)%2 of slot 2*(l%16) + b of half l/32; the
+    // copies permute the chunks within runs of four.
     const int b_fr = A_BYTES + 2 * wave * LPAIR +
-                     (BITS == 2 ? hq * 256 + q16 * 16 : hq * 512 + (((2 * q16) ^ (q16 >> 3)) << 4));
-    const int cchunk = (lane & 7) ^ (lane >> 4);  // rows +8: ^ 4
+                     (BITS == 8 ? (hq >> 1) * 1024 + ((4 * q16 + ((hq & 1) ^ (q16 >> 2))) << 4)
+                                : BITS == 2 ? hq * 256 + q16 * 16 : hq * 512 + (((2 * q16) ^ (q16 >> 3)) << 4));
+    constexpr int B_NEXT = BITS == 8 ? 32 : 16;  // toggles b
+
+    // The lane's number formed anew where a tile needs it: kept over the K-loop it takes a register that 4 bits do not have (the
+    // spilled one cost no time that could be measured).
+    auto lane_again = []() {
+        int all = -1;
+        asm volatile("" : "+s"(all));
+        return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
+    };
 
     // The arguments are loaded where a tile needs them: known to be constant they would all be held in scalar registers
     // from the start, more than there are.
@@ -1557,16 +1572,21 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
 
     const uint8_t *a_base = nullptr, *b_base = nullptr;
     uint32_t a_off[4], b_off[NB];
-    auto copy_step = [&](int s, int par) {
-        const uint8_t *as = a_base + (size_t)s * BK, *bs = b_base + (size_t)s * PAIR;
-        const uint32_t dst = lds_base + (uint32_t)par * STAGE;
+    auto copy_weights = [&](int phase, int par) {
+        const uint8_t *bs = b_base + (size_t)phase * PAIR;
+        const uint32_t dst = lds_base + (uint32_t)par * STAGE + A_BYTES;
 #pragma unroll
-        for (int e = 0; e < NB; ++e) copy_to_lds<CH>(bs, b_off[e], dst + A_BYTES + (wave * NB + e) * 1024);
+        for (int e = 0; e < NB; ++e) copy_to_lds<CH>(bs, b_off[e], dst + (wave * NB + e) * 1024);
+    };
+    auto copy_tokens = [&](int s, int par) {
+        const uint8_t *as = a_base + (size_t)s * BK;
+        const uint32_t dst = lds_base + (uint32_t)par * STAGE;
 #pragma unroll
         for (int e = 0; e < 4; ++e) copy_to_lds<16>(as, a_off[e], dst + (wave * 4 + e) * 1024);
     };
     // addresses of a tile's operands, its epilogue parameters and the copies of its first step
     auto start_tile = [&](int tm, int tn, int pb, int par) {
+        const int lane = lane_again();
         const DuoArgs &P = args();
         const int T = P.T, N = P.N, K = P.K, kunits = K >> 6, ncb = (N + 31) >> 5;
         a_base = reinterpret_cast<const uint8_t *>(P.Xq) + (size_t)tm * BM * K;
@@ -1576,9 +1596,9 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
         for (int e = 0; e < 4; ++e) {
             int row = (wave * 4 + e) * 8 + (lane >> 3);
             row = row < a_last ? row : a_last;  // rows past the end re-read the last one; results not stored
-            a_off[e] = (uint32_t)row * (uint32_t)K + ((cchunk ^ (4 * (e & 1))) << 4);
+            a_off[e] = (uint32_t)row * (uint32_t)K + (((lane & 7) ^ (lane >> 4) ^ (4 * (e & 1))) << 4);
         }
-        const int sl = BITS == 2 ? lane : lane ^ ((lane >> 4) & 1);
+        const int sl = BITS == 2 ? lane : lane ^ ((lane >> 4) & (BITS == 8 ? 3 : 1));
 #pragma unroll
         for (int e = 0; e < NB; ++e) {
             const int x = wave * NB + e;
@@ -1599,7 +1619,8 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
             else if (x < 10) copy_to_lds<4>(P.h, (uint32_t)(nn / P.rows_per_group) * 4, dst + e * 256);
             else if (x < 14 && P.bias) copy_to_lds<4>(P.bias, (uint32_t)nn * 4, dst + e * 256);
         }
-        copy_step(0, par);
+        copy_weights(0, PHASES == 2 ? 0 : par);
+        copy_tokens(0, par);
     };
     // every wavefront's copies have landed and its LDS reads have returned; then the barrier
     auto fence = [&]() {
@@ -1635,13 +1656,60 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
             ntn = lt - ntm * tiles_n;
         }
         for (int s = 0; s < steps; ++s) {
+            if constexpr (BITS == 8) {
+                const uint8_t *sa = lds + par * STAGE;
+                par ^= 1;
+#pragma unroll
+                for (int ph = 0; ph < 2; ++ph) {
+                    fence();
+                    // over the weights of the phase before; in the first phase the next step's tokens too, over those of the
+                    // step before; in the last phase the next tile's first operands and its parameters
+                    if (ph == 0) {
+                        copy_weights(2 * s + 1, 1);
+                        if (s + 1 < steps) copy_tokens(s + 1, par);
+                    } else if (s + 1 < steps) copy_weights(2 * s + 2, 0);
+                    else if (nwork < nwg) start_tile(ntm, ntn, pb ^ 1, par);
+                    v4i a[2][4], b[2][2];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int nb = 0; nb < 2; ++nb) b[j][nb] = *reinterpret_cast<const v4i *>(lds + ph * STAGE + j * LPAIR + (b_fr ^ (nb * B_NEXT)));
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int mb = 0; mb < 4; ++mb) a[i][mb] = *reinterpret_cast<const v4i *>(sa + a_fr[ph] + (i * 4 + mb) * 16 * BK);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) b[j][nb][e] ^= (int)0x80808080u;  // u - 128 as int8
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+#pragma unroll
+                            for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                                for (int nb = 0; nb < 2; ++nb)
+                                    acc[i][j][mb][nb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i][mb], b[j][nb], acc[i][j][mb][nb], 0, 0, 0);
+                    if (ph == 0) {
+                        if (s + 1 < steps) wait_vmcnt<4>();  // the weights; the tokens behind them have another phase
+                        else wait_vmcnt<0>();
+                    } else if (s + 1 < steps) wait_vmcnt<0>();
+                }
+                continue;
+            }
             fence();
             const uint8_t *st_ = lds + par * STAGE;
             par ^= 1;
             // over the stage that was read in the step before; in the last step the next tile's first operands and its
             // parameters, so that the address arithmetic and the latency lie under the MFMAs
-            if (s + 1 < steps) copy_step(s + 1, par);
-            else if (nwork < nwg) start_tile(ntm, ntn, pb ^ 1, par);
+            if (s + 1 < steps) {
+                copy_weights(s + 1, par);
+                copy_tokens(s + 1, par);
+            } else if (nwork < nwg) start_tile(ntm, ntn, pb ^ 1, par);
             v4i a[2][4][2], b[2][2][2];
             uint32_t raw[2][2][BITS];
 #pragma unroll
@@ -1696,6 +1764,7 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
         const uint8_t *pp = lds + 2 * STAGE + pb * PARAM;
         pb ^= 1;
 
+        const int wl = lane_again(), q16 = wl & 15, hq = wl >> 4;
         const int *p_rx = reinterpret_cast<const int *>(pp) + 4 * hq;
         const int nl = wave * 64 + 2 * q16;  // + 32*j + b
         int coln[2][2];
@@ -1868,9 +1937,9 @@ inline bool split_shape(long tiles, int T, int K) { return tiles <= 256 && slice
 
 // Which problems go to the 128 x 256 kernel with two independent workgroups per CU.  Its tiles are the largest, so it
 // needs two full rounds of the 512 resident workgroups (1024 tiles); with long contractions, whose tiles are started and
-// written out more rarely, three quarters of one.  At most an eighth of the columns may be padding.  At 8 bits two workgroups'
-// stages do not fit the LDS (one: 12288 x 3072 x 768 62 / 50 us).  Time / time with the kernels of the rules below, behind the
-// activation quantizer, lowest to highest of 2 to 4 bits; n2 and n1: the most tiles of 128 x 256 and of 128 x 128 on a CU:
+// written out more rarely, and at 8 bits three quarters of one.  At most an eighth of the columns may be padding.  Time / time with the
+// kernels of the rules below, behind the activation quantizer, lowest to highest of 2 to 4 bits; n2 and n1: the most tiles of 128 x 256 and
+// of 128 x 128 on a CU:
 //   K = 512 to 1024   (n1, n2) = (8,4) .86-.95, (9,5) .81-1.08, (10,5) .81-.97, (11,6) .85-1.06, (12,6) .87-.97, (15,8) .95-1.05, above .78-1.04
 //   K < 512           (8,4) .96-.99, (9,5) .92-1.08, (10,5) .95-.97, (11,6) 1.04-1.09, (12,6) .95-1.0: with so short a contraction
 //                     tiles are mostly start and write-out, and the odd one of a CU has nothing beside it
@@ -1879,15 +1948,25 @@ inline bool split_shape(long tiles, int T, int K) { return tiles <= 256 && slice
 //   N = 1152, 1920, 2688 (the last column of tiles half empty and written element by element; the 128 x 128 tiles fill theirs)
 //                     1.03-1.05, 1.14-1.34, .89-1.16
 //   N = 998 to 3520, no multiple of 128, K <= 1024 .35-1.04;  no multiple of 4 (no 16-byte rows), K >= 2048 .63-1.0
+// 8 bits, where the other kernels read the most from LDS:
+//   K = 512 to 1280   (3,2) .98-1.10, (4,2) .75-.98, (5,3) .89-1.12, (6,3) .86-.98, (7,4) .78-.98, (8,4) .90, (9,5) .76-.94, above .75-.91
+//   K < 512           (4,2) .82-1.16, (5,3) .93-1.05, (6,3) .99-1.02, (7,4) .96-1.14, (10,5) .82
+//   K >= 2048         (3,2), 384 tiles .93-.97, fewer .93-1.02, (4,2) .84-.90, (5,3) .92-1.03, (6,3) .90-.96, (8,4) .83-.88, one tile a CU .94-1.16
+//   N = 1152, 1920, 2688 1.00-1.09;  no multiple of 4, 384 to 923 tiles .64-.87
 template <int BITS>
 bool duo_shape(int T, int N, int K)
 {
     const long tiles_m = (T + 127) / 128, tiles_n = (N + 255) / 256, tiles = tiles_m * tiles_n;
     const bool long_k = K >= 2048;
-    if (BITS == 8 || K % 128 != 0 || tiles < (long_k ? 384 : 1024) || (tiles_n * 256 - N) * 8 > N) return false;
-    if (N % 4 != 0 || (N % 128 != 0 && !long_k)) return true;
+    if (K % 128 != 0 || tiles < (long_k || (BITS == 8 && K >= 512) ? 384 : 1024) || (tiles_n * 256 - N) * 8 > N) return false;
     const long n1 = (tiles_m * ((N + 127) / 128) + 255) / 256, n2 = (tiles + 255) / 256;
-    if (long_k) return 100 * n2 + 40 * (n2 & 1) < 67 * n1;
+    const long rounds = 100 * n2 + 40 * (n2 & 1);
+    if constexpr (BITS == 8) {
+        if (N % 4 != 0) return true;
+        return (N % 256 == 0 || N % 128 != 0) && (K >= 512 || n1 >= 2 * n2) && rounds < (long_k ? 67 : 62) * n1;
+    }
+    if (N % 4 != 0 || (N % 128 != 0 && !long_k)) return true;
+    if (long_k) return rounds < 67 * n1;
     return N % 256 == 0 && (K >= 512 || n1 >= 2 * n2);
 }
 
@@ -1895,11 +1974,9 @@ template <int BITS>
 void launch_duo(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, const float *h, const int32_t *rs_w,
                 const float *bias, float *Y, int32_t *A4, int T, int N, int K, int rpg, float hx, hipStream_t st)
 {
-    if constexpr (BITS < 8) {
-        const DuoJob j{{{Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, (T + 127) / 128, (N + 255) / 256}}};
-        const int tiles = j.p[0].tiles_m * j.p[0].tiles_n;
-        hipLaunchKernelGGL((qgemm_i8_duo_kernel<BITS>), dim3(tiles < 512 ? tiles : 512), dim3(256), 0, st, j);
-    }
+    const DuoJob j{{{Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, (T + 127) / 128, (N + 255) / 256}}};
+    const int tiles = j.p[0].tiles_m * j.p[0].tiles_n;
+    hipLaunchKernelGGL((qgemm_i8_duo_kernel<BITS>), dim3(tiles < 512 ? tiles : 512), dim3(256), 0, st, j);
 }
 
 template <int BITS>
@@ -2104,7 +2181,9 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
             ++sg.n;
             continue;
         }
-        if (j.K % 128 != 0 || !(use96 || use128) || duo_shape<BITS>((int)j.T, (int)j.N, (int)j.K)) {
+        // (at 8 bits the shared launch keeps what has fewer than 1024 tiles of 128 x 256: the rule is of single calls)
+        const bool alone = duo_shape<BITS>((int)j.T, (int)j.N, (int)j.K) && (BITS < 8 || (j.T + 127) / 128 * ((j.N + 255) / 256) >= 1024);
+        if (j.K % 128 != 0 || !(use96 || use128) || alone) {
             launch_job<BITS>(j, st);
             continue;
         }

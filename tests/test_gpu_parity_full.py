@@ -575,6 +575,14 @@ def test_forward_whole_output_large_tiles(qb, bits, shape):
     assert (np.abs(Y.cpu().numpy().astype(np.float64) - (Yo + b)) <= 1e-6 * np.abs(Yo) + 2.0 ** -23 * np.abs(Yo + b)).all()
 
 
+# (T, N, K) at 8 bits, where a step of the 128 x 256 tiles is two phases of 64 features: one, three, four and five steps, the fewest
+# tiles that are taken, ends inside a tile of tokens and of neurons, odd neuron counts, a long contraction, three tiles on a CU; the last
+# is left to the 128 x 128 tiles
+@pytest.mark.parametrize("shape", [(16300, 2020, 128), (16257, 1999, 384), (5000, 3001, 512), (4100, 3072, 640), (6200, 2048, 2048), (6100, 2046, 2048), (10900, 2048, 768), (5800, 3072, 640)])
+def test_forward_whole_output_large_tiles_8_bits(qb, shape):
+    test_forward_whole_output_large_tiles(qb, 8, shape)
+
+
 # K of three units of 64 features (five of the eight slices empty) up to uneven eighths; one token, one more than a tile of
 # 32; neuron counts around the tile of 64; beside them the shortest contractions, which the stepped kernel takes
 @pytest.mark.parametrize("bits", BITS)
