@@ -122,15 +122,82 @@ __device__ __forceinline__ void qgemm_i8_body(
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[tm][tn][i] = 0;
 
-    v4u areg[A_PER_THREAD];
-    uint32_t bnext[TN][KU][BITS], bcur[TN][KU][BITS];
     const int a_frag_base = (wm * TM * 32 + l32) * LDA + hf * 32;
+    // Steps of one unit of 64 features (K no multiple of 128): what bounds them is the way from a step's loads over LDS to its two
+    // MFMAs, so a step's tokens are staged right in front of the barrier that its MFMAs follow, the codes are expanded before it and
+    // D steps are on their way.  us of the GEMM behind its quantizer, before -> now, 4 bits: 2300 x 448 x 448 5.3 -> 4.8, 1001 x 1344 x 448
+    // 5.1 -> 4.6; as 128 x 128 tiles 12000 x 1344 x 448 23.5 -> 22.0.  D = 2 / 1: 4.7 / 5.2, at 3 bits 5.8 / 5.2; four blocks a wavefront
+    // fill a step with one (22.0 / 22.3).  Wider steps are better off in the loop further below: in this one 256 features take 2 to 5 %
+    // more, 128 features 4 % less at K = 768 and 2 % more up to K = 640, where the longer code counts.
+    constexpr bool AHEAD_STEPS = KU == 1;
+    constexpr int D = TM * TN == 1 && BITS != 3 ? 2 : 1;
+    v4u areg[D][A_PER_THREAD];
+    uint32_t breg[D][TN][KU][BITS];
+    // global -> registers for K-step `step`: the token tile (to be staged in LDS) and this lane's slots
+    auto load_step = [&](int step, v4u (&ar)[A_PER_THREAD], uint32_t (&br)[TN][KU][BITS]) {
+#pragma unroll
+        for (int i = 0; i < A_PER_THREAD; ++i) ar[i] = *reinterpret_cast<const v4u *>(a_src[i] + (size_t)step * BK);
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int kk = 0; kk < KU; ++kk) {
+                const uint32_t *p = reinterpret_cast<const uint32_t *>(b_src[tn] + (size_t)(step * KU + kk) * 64 * SLOT);
+#pragma unroll
+                for (int i = 0; i < BITS; ++i) br[tn][kk][i] = p[i];
+            }
+    };
+    // one K-step: the token tile to LDS, this lane's codes expanded to int8; then the loads of step `next` into the registers
+    // that are free now (fetch), and the MFMAs with the token fragments from LDS
+    auto do_step = [&](int buf, v4u (&ar)[A_PER_THREAD], uint32_t (&br)[TN][KU][BITS], bool fetch, int next) {
+        uint8_t *abuf = lds[buf];
+#pragma unroll
+        for (int i = 0; i < A_PER_THREAD; ++i) *reinterpret_cast<v4u *>(abuf + a_dst[i]) = ar[i];
+        uint32_t d[TN][KU][8];
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int kk = 0; kk < KU; ++kk) {
+                unpack_run<BITS>(br[tn][kk], d[tn][kk]);
+                if constexpr (BITS == 8) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) d[tn][kk][i] ^= 0x80808080u;
+                }
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        if (fetch) load_step(next, ar, br);
+        // the tile is in LDS (loads stay on their way over the barrier)
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < KU; ++kk)
+#pragma unroll
+            for (int sub = 0; sub < 2; ++sub) {
+                v4i a[TM], b[TN];
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm) a[tm] = *reinterpret_cast<const v4i *>(abuf + a_frag_base + tm * 32 * LDA + kk * 64 + sub * 16);
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) b[tn][i] = (int)d[tn][kk][4 * sub + i];
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                    for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
+            }
+    };
+
+    v4u astage[A_PER_THREAD];
+    uint32_t bnext[TN][KU][BITS], bcur[TN][KU][BITS];
 
 // global -> registers for K-step `step`: the token tile (to be staged in LDS) and this lane's slots
 #define QB_LOAD_GLOBAL(step, BDST)                                                                        \
     {                                                                                                     \
         _Pragma("unroll") for (int i = 0; i < A_PER_THREAD; ++i)                                          \
-            areg[i] = *reinterpret_cast<const v4u *>(a_src[i] + (size_t)(step) * BK);                    \
+            astage[i] = *reinterpret_cast<const v4u *>(a_src[i] + (size_t)(step) * BK);                  \
         _Pragma("unroll") for (int tn = 0; tn < TN; ++tn)                                                 \
             _Pragma("unroll") for (int kk = 0; kk < KU; ++kk) {                                           \
                 const uint32_t *p_ =                                                                      \
@@ -141,7 +208,7 @@ __device__ __forceinline__ void qgemm_i8_body(
 #define QB_STORE_LDS(buf)                                                                                 \
     {                                                                                                     \
         _Pragma("unroll") for (int i = 0; i < A_PER_THREAD; ++i)                                          \
-            *reinterpret_cast<v4u *>(&lds[buf][a_dst[i]]) = areg[i];                                      \
+            *reinterpret_cast<v4u *>(&lds[buf][a_dst[i]]) = astage[i];                                    \
     }
 // all MFMAs of one K-step: expand this lane's codes to int8 in registers, A fragments from LDS
 #define QB_COMPUTE(buf)                                                                                   \
@@ -209,24 +276,48 @@ __device__ __forceinline__ void qgemm_i8_body(
     };
 
     const int nsteps = K / BK;
-    QB_LOAD_GLOBAL(0, bcur)
-    if constexpr (AHEAD) {
-        load_columns();
-        load_rows(0);
-    }
-    QB_STORE_LDS(0)
-    __syncthreads();
-    // steady state: fetch step s+1 while the matrix cores work on step s (no branches inside)
-    for (int s = 0; s < nsteps - 1; ++s) {
-        QB_LOAD_GLOBAL(s + 1, bnext)
-        __builtin_amdgcn_sched_barrier(0);  // keep the fetches ahead of the MFMAs: their latency hides under them
-        QB_COMPUTE(s & 1)
-        __builtin_amdgcn_sched_barrier(0);
-        QB_STORE_LDS((s + 1) & 1)
-        QB_ROTATE_B()
+    if constexpr (AHEAD_STEPS) {
+        load_step(0, areg[0], breg[0]);
+        if constexpr (AHEAD) {
+            load_columns();
+            load_rows(0);
+        }
+#pragma unroll
+        for (int i = 1; i < D; ++i) load_step(i < nsteps ? i : 0, areg[i], breg[i]);
+        int s = 0;
+        if constexpr (D % 2 == 0) {
+            for (; s + 2 * D <= nsteps; s += D)  // (no branches inside)
+#pragma unroll
+                for (int i = 0; i < D; ++i) do_step(i & 1, areg[i], breg[i], true, s + i + D);
+        } else {
+            for (; s + 3 * D <= nsteps; s += 2 * D)
+#pragma unroll
+                for (int i = 0; i < 2 * D; ++i) do_step(i & 1, areg[i % D], breg[i % D], true, s + i + D);
+        }
+        // the last steps, less than 2*D or 3*D
+#pragma unroll
+        for (int i = 0; i < (D % 2 == 0 ? 2 * D : 3 * D) - 1; ++i)
+            if (s + i < nsteps) do_step(i & 1, areg[i % D], breg[i % D], s + i + D < nsteps, s + i + D);
+    } else {
+        QB_LOAD_GLOBAL(0, bcur)
+        if constexpr (AHEAD) {
+            load_columns();
+            load_rows(0);
+        }
+        QB_STORE_LDS(0)
         __syncthreads();
+        // steady state: fetch step s+1 while the matrix cores work on step s (no branches inside)
+        for (int s = 0; s < nsteps - 1; ++s) {
+            QB_LOAD_GLOBAL(s + 1, bnext)
+            __builtin_amdgcn_sched_barrier(0);  // keep the fetches ahead of the MFMAs: their latency hides under them
+            QB_COMPUTE(s & 1)
+            __builtin_amdgcn_sched_barrier(0);
+            QB_STORE_LDS((s + 1) & 1)
+            QB_ROTATE_B()
+            __syncthreads();
+        }
+        QB_COMPUTE((nsteps - 1) & 1)
     }
-    QB_COMPUTE((nsteps - 1) & 1)
 #undef QB_LOAD_GLOBAL
 #undef QB_STORE_LDS
 #undef QB_COMPUTE

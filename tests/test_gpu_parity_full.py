@@ -583,6 +583,14 @@ def test_forward_whole_output_large_tiles_8_bits(qb, shape):
     test_forward_whole_output_large_tiles(qb, 8, shape)
 
 
+# K of 1, 3, 5, 7 and 15 units of 64 features, with more tiles than CUs, so that the stepped kernels take them: tiles of 32 x 64 and
+# of 128 x 128, both ending inside a tile
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("shape", [(1100, 1000, 64), (1100, 1000, 192), (1100, 1000, 320), (1100, 1000, 448), (1100, 1000, 960), (2500, 1990, 64), (2500, 1990, 192), (2500, 1990, 320), (2500, 1990, 448)])
+def test_forward_whole_output_steps_of_one_unit(qb, bits, shape):
+    test_forward_whole_output_large_tiles(qb, bits, shape)
+
+
 # K of three units of 64 features (five of the eight slices empty) up to uneven eighths; one token, one more than a tile of
 # 32; neuron counts around the tile of 64; beside them the shortest contractions, which the stepped kernel takes
 @pytest.mark.parametrize("bits", BITS)
