@@ -2026,6 +2026,25 @@ inline int stepped_steps(int K) { return K / (64 * stepped_units(K)); }
 inline bool sliced_pays(int T, int K) { return stepped_steps(K) > 3 || (T < 32 && K >= 192); }
 inline bool split_shape(long tiles, int T, int K) { return tiles <= 256 && sliced_pays(T, K); }
 
+// Which problems take tiles of 32 x 64, sliced (split_shape) or of the register-staged kernel, instead of the larger ones: few tiles
+// (small token counts, the inference regime), where the persistent kernels leave most CUs idle and pay 6.5 us at least (1024 x 768 x
+// 768 4.4-5 us against 8; equal at about 190 tiles of 128 x 128).  Up to one such tile a CU they are ahead too where 128 x 96 tiles would
+// need a second round for a few of them.  Time / time with the larger tiles, behind the activation quantizer:
+//   second round of 128 x 96 tiles, K = 256 to 512 .86-.98 (4 bits), .88-.94 (3), .91-1.0 (8);  768 .93-.99, .93-1.0, .91-1.01;  1024 .92-1.0,
+//   .95-1.05, .94-1.08;  with a range per token K up to 1024 .93-1.0, .87-1.01, .85-1.0;  K >= 2048 1.01-1.39;  N = 640
+//   1.04
+//   first round (162 to 190 tiles) .91-1.11;  289 to 384 tiles of 128 x 128 .85-1.15
+// K no multiple of 128, where the larger tiles are register-staged ones of 128 x 128, 4, 3 and 8 bits:
+//   161 to 200 tiles .70-.84, 257 to 300 .83-.94;  346 to 360, K <= 704 .87-.99, 960 .97-1.06;  414 to 420 .92-1.01, 1.0-1.14
+template <int BITS>
+bool small_tiles_shape(int T, int N, int K, bool gen)
+{
+    const long tiles_m = (T + 127) / 128, tiles128 = tiles_m * ((N + 127) / 128), tiles96 = tiles_m * ((N + 95) / 96);
+    if (tiles128 <= 160) return true;
+    if (K % 128 != 0) return K <= 1024 && tiles128 <= (K <= 704 ? 384 : 320);
+    return tiles128 <= 256 && tiles96 > 256 && N >= 768 && K <= (gen || BITS == 2 || BITS == 4 ? 1024 : 768);
+}
+
 // Which problems go to the 128 x 256 kernel with two independent workgroups per CU.  Its tiles are the largest, so it
 // needs two full rounds of the 512 resident workgroups (1024 tiles); with long contractions, whose tiles are started and
 // written out more rarely, and at 8 bits three quarters of one.  At most an eighth of the columns may be padding.  Time / time with the
@@ -2076,11 +2095,7 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
                  const float *hx_rows = nullptr, const float *q0 = nullptr)
 {
     const long tiles128 = (long)((T + 127) / 128) * ((N + 127) / 128);
-    if (tiles128 <= 160) {
-        // Few tiles (small token counts, the inference regime): the persistent kernels below leave most CUs idle
-        // and pay ~6.5 us at least; 32x64 tiles, sliced (split_shape) or of the register-staged kernel, spread the work over the chip
-        // (measured 4.4-5 us against 8 at T <= 1024, N = 768; 6.8 against 8.4 at 1024 x 2304 x 768; equal
-        // at about 190 tiles).  Long contractions take 256 features per step.
+    if (small_tiles_shape<BITS>(T, N, K, hx_rows || q0)) {  // (long contractions take 256 features per step)
         const SplitCall sc{A4, hx_rows, q0, {Xq, rs_x, packed, h, rs_w, bias, Y, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64}};
         const int tiles = sc.p.tiles_m * sc.p.tiles_n;
         if (split_shape(tiles, T, K)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sc);

@@ -586,8 +586,16 @@ def test_forward_whole_output_large_tiles_8_bits(qb, shape):
 # K of 1, 3, 5, 7 and 15 units of 64 features, with more tiles than CUs, so that the stepped kernels take them: tiles of 32 x 64 and
 # of 128 x 128, both ending inside a tile
 @pytest.mark.parametrize("bits", BITS)
-@pytest.mark.parametrize("shape", [(1100, 1000, 64), (1100, 1000, 192), (1100, 1000, 320), (1100, 1000, 448), (1100, 1000, 960), (2500, 1990, 64), (2500, 1990, 192), (2500, 1990, 320), (2500, 1990, 448)])
+@pytest.mark.parametrize("shape", [(1100, 1000, 64), (1100, 1000, 192), (1100, 1000, 320), (1100, 1000, 448), (1100, 1000, 960), (3300, 1990, 64), (3300, 1990, 192), (3300, 1990, 320), (3300, 1990, 448)])
 def test_forward_whole_output_steps_of_one_unit(qb, bits, shape):
+    test_forward_whole_output_large_tiles(qb, bits, shape)
+
+
+# both sides of the lines up to which calls of more than 160 tiles of 128 x 128 take tiles of 32 x 64: 256 of them that make a second
+# round of 128 x 96 tiles, and 272; 384 and 400 with K = 576, 320 and 336 with K = 832
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("shape", [(2015, 2048, 256), (2049, 2010, 256), (1990, 2040, 768), (3050, 2044, 576), (3073, 2044, 576), (2500, 2044, 832), (2600, 2044, 832)])
+def test_forward_whole_output_around_the_small_tiles(qb, bits, shape):
     test_forward_whole_output_large_tiles(qb, bits, shape)
 
 
