@@ -1333,7 +1333,7 @@ float duo_cost(const DuoShare &w, int w_steps, const DuoShare &x, int x_steps)
 //   7 % under the time of the kernel above (fitted to the same calls).  us a call with inputs from memory, above -> here:
 //   10557 x 768 x 3072 161 -> 126, 13497 x 640 x 2560 .71, 4635 x 1024 x 4096 120 -> 102, 10672 x 768 x 768 57.9 -> 49.7, 16686 x
 //   1920 x 640 .84, 3000 x 768 x 3072 .98.  Fewer workgroups with work than 376: 2593 x 4096 x 1024 (318) 1.06, 3129 x 3072 x 768
-//   (292) 1.29.
+//   (292) 1.29.  Several dX tiles to a workgroup and fewer than 32 steps: 4096 x 768 x 3072 inside a training step 50.8 -> 52.6.
 //   dX alone: most of the workgroups have a tile, and the last round of tiles is not nearly empty (384 tiles .88, 506 .84, 520
 //   1.15, 682 .88, 1484 .81; 320 1.03; fewer tiles cut in two 1.04 to 1.21).
 //   dW alone: four pieces of a tile, no more than seven eighths of the workgroups (70 tiles of 211 steps .89, 72 of 133 .98; 96 of
@@ -1367,6 +1367,7 @@ bool duo_plan(DuoGroup &d, bool has_x, bool has_w)
     for (int p = 1; p <= most && w_tiles * p <= kDuoRuns - 8 && w_tiles * (p - 1) <= kSkMaxRuns; ++p) {
         const DuoShare w = share(w_tiles, (w_tiles * p + 7) / 8, p), x = share(x_tiles, kDuoPerXcd - w.runs, 1);
         if (w_tiles * p + std::min(x_tiles, 8 * x.runs) < 376) continue;
+        if (x_tiles > 8 * x.runs && units < (long long)kDuoRuns * 32) continue;
         const float cost = duo_cost(w, w_steps, x, x_steps);
         if (cost < best) {
             best = cost;

@@ -159,7 +159,7 @@ def test_turned_operand_gives_the_staged_operands_sums(qb, shape):
 # whole tiles only, tiles with rows and columns past the end, T and N with and without a rest to a step, dY turned and staged;
 # 4160 x 1030 x 4096 and 12800 x 512 x 640 for one product alone
 @pytest.mark.parametrize("bits", [3, 8])
-@pytest.mark.parametrize("shape", [(2863, 1024, 4096), (3328, 768, 3072), (8192, 700, 704), (5505, 1016, 960), (4160, 1030, 4096), (12800, 512, 640)])
+@pytest.mark.parametrize("shape", [(2863, 1024, 4096), (5505, 768, 3072), (8192, 700, 704), (5505, 1016, 960), (4160, 1030, 4096), (12800, 512, 640)])
 def test_two_workgroups_per_cu(qb, shape, bits):
     T, N, K = shape
     print("bwd two workgroups per CU", shape, bits, flush=True)
