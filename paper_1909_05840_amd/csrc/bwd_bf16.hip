@@ -1300,86 +1300,97 @@ struct SkProduct {
 // Tiles of 128 x 192 when that leaves every CU at least kSkWideMinSteps of their steps, else 128 x 96; three stages.
 constexpr int kSkWideMinSteps = 16;
 constexpr size_t kSkSlotBytes = (size_t)128 * 192 * 4;
-// What a plan for both products takes, us, without the staging launch: the slowest CU, each of which has two workgroups (idx
-// and idx + 32 of an XCD), a step 1.33 us while both multiply and 0.70 alone; a tile written costs 7.4, partial sums written
-// 5.0, read 14.2 for all of a tile but one piece; and at least the mean of all CUs, which share the chip's power.  Fitted to
-// 316 timings (84 calls of 2000 to 17000 tokens, hidden sizes 512 to 1024, each with dW's tiles in 1 to 8 pieces).
+// What a plan for both products takes, us: the slowest CU, each of which has two workgroups (idx and idx + 32 of an XCD).  A step counts
+// 0.67 while both multiply and 0.47 alone, a tile or a piece written 4.0.
 float duo_cost(const DuoShare &w, int w_steps, const DuoShare &x, int x_steps)
 {
-    const float kTile = 7.4f, kPiece = 5.0f, kRead = 14.2f;
+    const float kTile = 4.0f;
     const int x_tiles = (x.tiles + 7) / 8;  // of an XCD
-    const float w_len = (float)((w_steps + w.p - 1) / w.p), w_extra = kTile + (w.p > 1 ? kPiece + kRead * (w.p - 1) / w.p : kTile);
-    float worst = 0.0f, sum = 0.0f;
+    const float w_len = (float)((w_steps + w.p - 1) / w.p);
+    float worst = 0.0f;
     for (int i = 0; i < kDuoPerXcd / 2; ++i) {
         float len[2], extra[2];
         for (int half = 0; half < 2; ++half) {
             const int j = i + half * kDuoPerXcd / 2 - w.runs, k = j < 0 ? 0 : x_tiles / x.runs + (j < x_tiles % x.runs);
             len[half] = j < 0 ? w_len : (float)(k * x_steps);
-            extra[half] = j < 0 ? w_extra : k * kTile;
+            extra[half] = j < 0 ? kTile : k * kTile;
         }
         const float lo = std::min(len[0], len[1]), hi = std::max(len[0], len[1]);
-        worst = std::max(worst, 1.33f * lo + 0.70f * (hi - lo) + std::max(extra[0], extra[1]));
-        sum += 0.665f * (len[0] + len[1]) + 0.5f * (extra[0] + extra[1]);
+        worst = std::max(worst, 0.67f * lo + 0.47f * (hi - lo) + std::max(extra[0], extra[1]));
     }
-    return std::max(worst - 14.9f, 0.975f * sum / (kDuoPerXcd / 2));
+    return worst;
+}
+// The same for the kernel above.  Where its runs end on tiles' ends of dX it exchanges less and all CUs walk the contraction in step:
+// 0.7 us for each column of tiles (4096 x 768 x 3072 61.6 us, staging launch included, between 60.9 at 3584 tokens and 75.6 at 4608).
+float equal_runs_cost(int64_t units, int x_tiles, int x_steps, int columns)
+{
+    const bool whole = units % kSkMaxRuns == 0 && units / kSkMaxRuns % x_steps == 0;
+    return 0.3f + 0.45f * (float)units / kSkMaxRuns + 7.7f * (float)x_tiles / kSkMaxRuns - (whole ? 0.7f * columns : 0.0f);
 }
 
-// How the workgroups are shared between the products; false if the kernel above is faster.  It is below 8 steps a workgroup,
-// where its tiles are the smaller ones, and where dX's contraction is long (over 30 steps): there dY is the large operand, and
-// when it comes from memory the copies, one step ahead here, are late (10265 x 3072 x 768 1.05 of the time above, 12288 x 2304 x
+// How the workgroups are shared between the products of a call; false if the kernel above is faster.  It is below 8 steps a
+// workgroup, where its tiles are the smaller ones, and where dX's contraction is long (over 30 steps): there dY is the large operand,
+// and when it comes from memory the copies, one step ahead here, are late (10265 x 3072 x 768 1.05 of the time above, 12288 x 2304 x
 // 768 and 3072 x 768 inside a training step 1.09 and 1.05, though .98 and .94 with dY in the last-level cache).  The pieces that
 // do not write their tile have kSkMaxRuns slots.
 //   Both products: the cheapest number of pieces for dW's tiles, dX's whole tiles with the workgroups that are left, if that is
-//   7 % under the time of the kernel above (fitted to the same calls).  us a call with inputs from memory, above -> here:
-//   10557 x 768 x 3072 161 -> 126, 13497 x 640 x 2560 .71, 4635 x 1024 x 4096 120 -> 102, 10672 x 768 x 768 57.9 -> 49.7, 16686 x
-//   1920 x 640 .84, 3000 x 768 x 3072 .98.  Fewer workgroups with work than 376: 2593 x 4096 x 1024 (318) 1.06, 3129 x 3072 x 768
-//   (292) 1.29.  Several dX tiles to a workgroup and fewer than 32 steps: 4096 x 768 x 3072 inside a training step 50.8 -> 52.6.
+//   3.5 us under the kernel above.  Both estimates are fitted to the change that a plan makes to a whole training step (760 calls of 740 to
+//   12288 tokens, hidden sizes 448 to 1024, steps of 24 in a row; to 2361 plans), so what both kernels have in common is in neither.  The rule
+//   takes 6111 us off those steps, the faster side of each call would take 6700; at 2.5 and 4.5 us 6226 and 5910.  Five calls make their
+//   step longer by over 1 us, the most 5569 x 832 x 832 by 2.7 of 450; of 216 others that it took, measured afterwards, 9, the most 3076 x
+//   768 x 3072 by 3.7 of 235, and all of them together made 1865 us.  us a step, kernel above -> here: 12288 x 768 x 768 -11, x 3072 -9,
+//   10361 x 768 x 3072 -27, 4169 x 768 x 3072 -5.5, 8192 x 640 x 2560 -16, 4096 x 1024 x 4096 -17;  left to the kernel above: 4096 x 768 x
+//   3072 2.2, 3072 2.3 and 6144 tokens 3.0.
+//     Of a tile in pieces no more than one workgroup of a CU (32 of an XCD): past that they meet their like (a call, staging launch
+//     included, over the kernel above: 3584 x 896 x 3584 in two pieces 1.08, in one .90, 2560 x 1024 x 4096 1.17 and .92).  Not seven pieces:
+//     a tile's are then all at the same place of their XCDs, and the last two XCDs write everything (5040 x 832 x 832 1.20, in six 1.08;
+//     12288 x 448 x 1792 in seven .95, in six .74).
 //   dX alone: most of the workgroups have a tile, and the last round of tiles is not nearly empty (384 tiles .88, 506 .84, 520
 //   1.15, 682 .88, 1484 .81; 320 1.03; fewer tiles cut in two 1.04 to 1.21).
 //   dW alone: four pieces of a tile, no more than seven eighths of the workgroups (70 tiles of 211 steps .89, 72 of 133 .98; 96 of
 //   161 in three pieces 1.12, 144 of 81 in two 1.12; 72 of 97 1.06).
 constexpr int kDuoMinSteps = 8, kDuoMaxPieces = 8;
-bool duo_plan(DuoGroup &d, bool has_x, bool has_w)
+bool duo_plan(DuoShare &w, DuoShare &x, int64_t T, int64_t N, int64_t K, bool has_x, bool has_w)
 {
-    const SkGroup &g = d.g;
-    const long long units = g.ustart[g.n];
-    if (units < (long long)kDuoRuns * kDuoMinSteps) return false;
-    for (int i = 0; i < g.n; ++i)  // a tile's rows lie less than 2^32 bytes apart, and tile numbers times eight fit 32 bits
-        if (g.p[i].lda >= (1 << 23) || g.p[i].ldb >= (1 << 23) || (long long)g.p[i].tiles_m * g.p[i].tiles_n >= (1 << 26)) return false;
-    const int x_tiles = has_x ? g.p[0].tiles_m * g.p[0].tiles_n : 0, x_steps = g.p[0].nsteps;
-    const int w_tiles = has_w ? g.p[g.n - 1].tiles_m * g.p[g.n - 1].tiles_n : 0, w_steps = g.p[g.n - 1].nsteps;
+    const int64_t cols = (K + 191) / 192, x_all = has_x ? (T + 127) / 128 * cols : 0, w_all = has_w ? (N + 127) / 128 * cols : 0;
+    const int x_steps = (int)((N + 63) / 64), w_steps = (int)((T + 63) / 64);
+    const int64_t units = x_all * x_steps + w_all * w_steps;
+    if (units < (int64_t)kDuoRuns * kDuoMinSteps) return false;
+    // (a tile's rows lie less than 2^32 bytes apart, 192 rows of less than 2^24 bytes, and tile numbers times eight fit 32 bits)
+    if (N > (1 << 23) - 64 || (has_w && T > (1 << 23) - 64) || x_all >= (1 << 26) || w_all >= (1 << 26)) return false;
+    const int x_tiles = (int)x_all, w_tiles = (int)w_all;
     auto share = [](int tiles, int runs, int p) { return DuoShare{tiles, runs, p, std::max(runs / p, 1)}; };
     const int most = std::min(kDuoMaxPieces, w_steps);
     if (has_x && x_steps > 30) return false;
-    d.w = d.x = {0, 0, 1, 0};
+    w = x = {0, 0, 1, 0};
     if (!has_w) {
-        d.x = share(x_tiles, kDuoPerXcd, 1);
+        x = share(x_tiles, kDuoPerXcd, 1);
         return x_tiles >= 328 && (x_tiles <= kDuoRuns || x_tiles >= 656);
     }
     if (!has_x) {
         const int p = 4;
         if (w_steps < 32 * p || w_tiles < 64 || w_tiles * (p - 1) > kSkMaxRuns) return false;
-        d.w = share(w_tiles, (w_tiles * p + 7) / 8, p);
+        w = share(w_tiles, (w_tiles * p + 7) / 8, p);
         return true;
     }
-    float best = 0.93f * (6.6f + 0.703f * (float)units / 256 + 9.2f * (float)x_tiles / 256);
+    float best = equal_runs_cost(units, x_tiles, x_steps, (int)cols) - 3.5f;
     bool found = false;
-    for (int p = 1; p <= most && w_tiles * p <= kDuoRuns - 8 && w_tiles * (p - 1) <= kSkMaxRuns; ++p) {
-        const DuoShare w = share(w_tiles, (w_tiles * p + 7) / 8, p), x = share(x_tiles, kDuoPerXcd - w.runs, 1);
-        if (w_tiles * p + std::min(x_tiles, 8 * x.runs) < 376) continue;
-        if (x_tiles > 8 * x.runs && units < (long long)kDuoRuns * 32) continue;
-        const float cost = duo_cost(w, w_steps, x, x_steps);
+    for (int p = 1; p <= most && w_tiles * p <= (p == 1 ? kDuoRuns - 8 : kDuoRuns / 2); ++p) {
+        if (p == 7) continue;
+        const DuoShare ws = share(w_tiles, (w_tiles * p + 7) / 8, p), xs = share(x_tiles, kDuoPerXcd - ws.runs, 1);
+        const float cost = duo_cost(ws, w_steps, xs, x_steps);
         if (cost < best) {
             best = cost;
-            d.w = w;
-            d.x = x;
+            w = ws;
+            x = xs;
             found = true;
         }
     }
     return found;
 }
 
-void sk_run(const SkProduct *prod, int n, float *slots, int *flags, hipStream_t st)
+// T, N, K: of the call
+void sk_run(const SkProduct *prod, int n, int64_t T, int64_t N, int64_t K, float *slots, int *flags, hipStream_t st)
 {
     long long wide_units = 0;
     for (int i = 0; i < n; ++i)
@@ -1394,7 +1405,7 @@ void sk_run(const SkProduct *prod, int n, float *slots, int *flags, hipStream_t 
             sk_add<2, 2>(g, prod[i].A, prod[i].B, prod[i].M, prod[i].Nc, prod[i].Kc, prod[i].lda, prod[i].ldb, prod[i].out,
                          prod[i].scale, prod[i].C, prod[i].mask, prod[i].t_rows, prod[i].zeros);
         if (n == 1 && prod[0].out == 0) g.p[0].strip = g.p[0].tiles_n;  // (dX alone: sk_place)
-        if (duo_plan(d, prod[0].out == 0, prod[n - 1].out == 1)) {
+        if (duo_plan(d.w, d.x, T, N, K, prod[0].out == 0, prod[n - 1].out == 1)) {
             bool any_mask = false, any_turned = false;
             for (int i = 0; i < n; ++i) {
                 any_mask = any_mask || g.p[i].mask.src != nullptr;
@@ -1454,6 +1465,15 @@ extern "C" size_t qb_bwd_workspace_nbytes(int64_t T, int64_t N, int64_t K)
 // 25.1 -> 23.4; 2304 x 768, dW only, at 871 18.7 -> 16.8.  Below 512 tokens 2 to 4 % are lost on average, from 640 on 3 to 10
 // gained.
 namespace qb { bool bwd_turned(int64_t T, int64_t N) { return N % 8 == 0 && T >= 640; } }
+
+// The number of pieces of dW's tiles (1 if there are none) of a call that takes two workgroups per CU, 0 for another kernel
+namespace qb {
+int bwd_duo_pieces(int64_t T, int64_t N, int64_t K, bool dx, bool dw)
+{
+    DuoShare w, x;
+    return !bwd_direct_teams(T, N, K, dx, dw) && duo_plan(w, x, T, N, K, dx, dw) ? w.p : 0;
+}
+}
 
 static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const void *packed, const float *h, int bits,
                          int groups, int64_t T, int64_t N, int64_t K, const float *X, const float *W, const float *m,
@@ -1524,7 +1544,7 @@ static qb_status bwd_ste(const uint16_t *dY, const int8_t *Xq, float clip, const
         prod[np++] = SkProduct{Aop, WT, (int)T, (int)K, Np, Np, Np, 0, 1.0f, dX, X ? &mx : nullptr, 0, nullptr};
     }
     if (dW) prod[np++] = SkProduct{turned ? dY : dYT, XT, (int)N, (int)K, Tp, turned ? (int)N : Tp, Tp, 1, clip / 255.0f, dW, W ? &mw : nullptr, turned ? (int)T : 0, zeros};
-    sk_run(prod, np, reinterpret_cast<float *>(ws + p.off_slots), reinterpret_cast<int *>(ws + p.off_flags), st);
+    sk_run(prod, np, T, N, K, reinterpret_cast<float *>(ws + p.off_slots), reinterpret_cast<int *>(ws + p.off_flags), st);
     return launch_status();
 }
 
