@@ -389,7 +389,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
             const int nsteps = q.s1 - q.s0;
             const int t_rows = TURN ? P.t_rows : 0;
             // addresses: a wavefront-uniform base per piece and step, a 32-bit byte offset per lane and copy
-            // (rows of a tile lie less than 2^32 bytes apart: at most 256 rows of at most 2^25 bytes)
+            // (rows of a tile lie less than 2^32 bytes apart: 127 rows of A of at most 2^25 bytes; B: sk_run)
             const uint8_t *a_base = reinterpret_cast<const uint8_t *>(t_rows ? P.A + (size_t)q.s0 * 64 * lda : P.A + (size_t)tile_m * BM * lda + q.s0 * 64);
             const uint8_t *b_base = reinterpret_cast<const uint8_t *>(P.B + (size_t)tile_n * BN * ldb + q.s0 * 64);
             const int a_last = M - 1 - tile_m * BM, b_last = Nc - 1 - tile_n * BN;
@@ -1393,14 +1393,17 @@ bool duo_plan(DuoShare &w, DuoShare &x, int64_t T, int64_t N, int64_t K, bool ha
 void sk_run(const SkProduct *prod, int n, int64_t T, int64_t N, int64_t K, float *slots, int *flags, hipStream_t st)
 {
     long long wide_units = 0;
-    for (int i = 0; i < n; ++i)
+    bool near = true;  // 191 rows of B, the last one to its end, lie less than 2^32 bytes apart
+    for (int i = 0; i < n; ++i) {
         wide_units += (long long)((prod[i].M + 127) / 128) * ((prod[i].Nc + 191) / 192) * (prod[i].Kc / 64);
+        near = near && (long long)prod[i].ldb * 2 * 192 <= 1ll << 32;
+    }
     DuoGroup d;
     SkGroup &g = d.g;
     g.n = 0;
     g.slots = slots;
     g.flags = flags;
-    if (wide_units >= (long long)kSkMaxRuns * kSkWideMinSteps) {
+    if (near && wide_units >= (long long)kSkMaxRuns * kSkWideMinSteps) {
         for (int i = 0; i < n; ++i)
             sk_add<2, 2>(g, prod[i].A, prod[i].B, prod[i].M, prod[i].Nc, prod[i].Kc, prod[i].lda, prod[i].ldb, prod[i].out,
                          prod[i].scale, prod[i].C, prod[i].mask, prod[i].t_rows, prod[i].zeros);

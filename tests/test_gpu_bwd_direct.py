@@ -184,6 +184,24 @@ def test_two_workgroups_per_cu(qb, shape, bits):
     check(dY, W_hat, Xq, None, qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, want_dx=False)[1])
 
 
+# 192 rows of a wide tile's second operand span more than 2^32 bytes: the tile's last columns come out as the others do
+def test_rows_far_apart(qb):
+    T, N, K = 12000000, 8, 192
+    print("bwd rows far apart", T, N, K, flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    Xq = torch.randint(-128, 128, (T, K), generator=g, device=DEV, dtype=torch.int8)
+    dY = torch.randn(T, N, generator=g, device=DEV).to(torch.bfloat16)
+    packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N, K, seed=1).to(DEV), 4, 1)
+    _, dW = qb.qb_qlinear_bwd_ste(dY, Xq, CLIP, packed, h, 4, 1, want_dx=False)
+    ref = torch.zeros(N, K, dtype=torch.float64, device=DEV)
+    for t in range(0, T, 1000000):
+        ref += dY[t:t + 1000000].double().T @ ((2.0 * Xq[t:t + 1000000].double() + 1.0) * (CLIP / 255.0))
+    # fp32 sums of exact products in 256 runs of up to 733 steps of 64: rounding errors add up like a random walk, 2^-24 * sqrt(733) of
+    # partial sums as large as the result and smaller
+    assert ((dW.double() - ref).norm(dim=0) <= 1e-5 * ref.norm(dim=0)).all()
+
+
 # one launch, staged (turned where dY is not aligned), turned, neither
 @pytest.mark.parametrize("shape", [(129, 128, 192), (16, 192, 64), (300, 136, 192), (320, 136, 192), (6001, 1024, 768), (77, 50, 64)])
 @pytest.mark.parametrize("off_y,off_x,off_w", [(4, 0, 0), (1, 0, 0), (0, 1, 0), (0, 0, 4), (3, 7, 12)])
