@@ -2,6 +2,7 @@
 and four teams per workgroup, and the staged path's turned operand, strips of tiles and two workgroups per CU, against the oracle
 and plain fp64."""
 import ctypes
+import functools
 
 import numpy as np
 import pytest
@@ -25,6 +26,13 @@ def bounds(dY, W_hat, x_hat):
 def one_launch_teams(T, N, K, dx=True, dw=True):
     """teams per workgroup that the library's rule gives a call, 0 for the staged path"""
     rule = ctypes.CDLL(LIB_PATH)._ZN2qb16bwd_direct_teamsElllbb
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int64] * 3 + [ctypes.c_bool] * 2
+    return rule(T, N, K, dx, dw)
+
+
+def duo_pieces(T, N, K, dx=True, dw=True):
+    """pieces of dW's tiles that the library's rule for two workgroups per CU gives a call, 0 for another kernel"""
+    rule = ctypes.CDLL(LIB_PATH)._ZN2qb14bwd_duo_piecesElllbb
     rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int64] * 3 + [ctypes.c_bool] * 2
     return rule(T, N, K, dx, dw)
 
@@ -154,15 +162,18 @@ def test_turned_operand_gives_the_staged_operands_sums(qb, shape):
     assert (dW.double() - ref).norm() <= 1e-5 * ref.norm()  # fp32 sums of exact products
 
 
-# (T, N, K) of calls with enough steps for two workgroups per CU (tiles of 128 x 192, pieces of dW's tiles with their sums
-# exchanged, dX's whole tiles): dW's tiles whole, in two and in five pieces, some workgroups with more tiles of dX than others,
-# whole tiles only, tiles with rows and columns past the end, T and N with and without a rest to a step, dY turned and staged;
-# 4160 x 1030 x 4096 and 12800 x 512 x 640 for one product alone
+# (T, N, K) and what calls for both products, dX alone and dW alone get: pieces of dW's tiles with two workgroups per CU (tiles of
+# 128 x 192, sums of pieces exchanged, dX's whole tiles, some workgroups with more of them than others), 0 for the kernel of equal
+# runs.  dW's tiles whole and in two to eight pieces; whole tiles only (8192 x 1024 x 1536), tiles with rows and columns past the end, T and N
+# with and without a rest to a step; dY turned with N a multiple of 8 and not of 128, and staged, for both products and for dW alone
 @pytest.mark.parametrize("bits", [3, 8])
-@pytest.mark.parametrize("shape", [(2863, 1024, 4096), (5505, 768, 3072), (8192, 700, 704), (5505, 1016, 960), (4160, 1030, 4096), (12800, 512, 640)])
+@pytest.mark.parametrize("shape", [(2863, 1024, 4096, (1, 1, 0)), (5505, 768, 3072, (2, 1, 0)), (8192, 700, 704, (8, 0, 0)), (5505, 1016, 960, (6, 0, 0)),
+                                   (4160, 1030, 4096, (1, 1, 0)), (12800, 512, 640, (8, 0, 0)), (8192, 1024, 1536, (4, 1, 4)), (8200, 1336, 1216, (3, 1, 4)),
+                                   (8250, 1012, 1472, (3, 0, 4)), (9001, 504, 1728, (5, 0, 0))])
 def test_two_workgroups_per_cu(qb, shape, bits):
-    T, N, K = shape
+    T, N, K, pieces = shape
     print("bwd two workgroups per CU", shape, bits, flush=True)
+    assert (duo_pieces(T, N, K), duo_pieces(T, N, K, dw=False), duo_pieces(T, N, K, dx=False)) == pieces
     W, X, dY = wl.weight(N, K, seed=N + K + bits), wl.activation(T, K, seed=T), wl.grad_output_bf16(T, N, seed=T + N)
     G = 2
     Wd, Xd, dYd = W.to(DEV), X.to(DEV), dY.to(DEV)
@@ -181,7 +192,42 @@ def test_two_workgroups_per_cu(qb, shape, bits):
     assert bool(out_x.any()) and bool(out_w.any())
     assert torch.equal(mX, torch.where(out_x, torch.zeros_like(dX), dX)) and torch.equal(mW, torch.where(out_w, torch.zeros_like(dW), dW))
     check(dY, W_hat, Xq, qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, want_dw=False)[0], None)
-    check(dY, W_hat, Xq, None, qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, want_dx=False)[1])
+    dW = qb.qb_qlinear_bwd_ste(dYd, Xq, CLIP, packed, h, bits, G, want_dx=False)[1]
+    check(dY, W_hat, Xq, None, dW)
+    qb.qb_qlinear_bwd_ste(behind(dYd, 4), Xq, CLIP, packed, h, bits, G, dW=oW, want_dx=False)
+    mW = qb.qb_qlinear_bwd_ste_masked(dYd, Xq, CLIP, packed, h, bits, G, X=2.0 * Xd, W=Wd, m=0.5 * m, want_dx=False)[1]
+    assert torch.equal(oW, dW) and torch.equal(mW, torch.where(out_w, torch.zeros_like(dW), dW))
+
+
+def test_two_workgroups_per_cu_on_three_streams(qb):
+    """Calls whose workgroups wait for each other's sums and fill a CU's LDS, on three streams at once: each result is, bit for
+    bit, that of the same call alone."""
+    calls = []
+    for T, N, K, dx, pieces in [(5505, 768, 3072, True, 2), (9001, 504, 1728, True, 5), (8200, 1336, 1216, False, 4)]:
+        assert duo_pieces(T, N, K, dx) == pieces
+        print("bwd two workgroups per CU, streams", T, N, K, flush=True)
+        packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N, K, seed=N).to(DEV), 4, 2)
+        Xq, _ = qb.qb_quantize_act(wl.activation(T, K, seed=T).to(DEV), CLIP)
+        out = {"dW": torch.empty(N, K, device=DEV)}
+        if dx:
+            out["dX"] = torch.empty(T, K, dtype=torch.bfloat16, device=DEV)
+        args = dict(workspace=torch.empty(qb.qb_bwd_workspace_nbytes(T, N, K), dtype=torch.uint8, device=DEV), want_dx=dx, **out)
+        call = functools.partial(qb.qb_qlinear_bwd_ste, wl.grad_output_bf16(T, N, seed=T + N).to(DEV), Xq, CLIP, packed, h, 4, 2, **args)
+        call()
+        calls.append((call, out, {n: o.clone() for n, o in out.items()}))
+    streams = [torch.cuda.Stream() for _ in calls]  # default priority
+    for _ in range(5):
+        for _, out, _ in calls:
+            for o in out.values():
+                o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for (call, _, _), st in zip(calls, streams):
+            with torch.cuda.stream(st):
+                for _ in range(3):
+                    call()
+        torch.cuda.synchronize()
+        for _, out, alone in calls:
+            assert all(torch.equal(out[n], alone[n]) for n in out)
 
 
 # 192 rows of a wide tile's second operand span more than 2^32 bytes: the tile's last columns come out as the others do
