@@ -2089,29 +2089,17 @@ void launch_duo(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, co
     hipLaunchKernelGGL((qgemm_i8_duo_kernel<BITS>), dim3(tiles < 512 ? tiles : 512), dim3(256), 0, st, j);
 }
 
+// The kernel of a call: tiles of 32 x 64, sliced or stepped; of 128 x 128 staged through registers (K no multiple of 128); of 128 x 256; role-split
+// ones of 128 x 96, two workgroups per CU or one, and of 128 x 128; plain ones of 128 x 128, two workgroups per CU
+enum FwdPath { kSliced, kStepped, kStaged128, kDuo256, kRoles96Two, kRoles96One, kRoles128, kPlain128 };
 template <int BITS>
-void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, const float *h, const int32_t *rs_w,
-                 const float *bias, float *Y, int32_t *A4, int T, int N, int K, int rpg, float hx, hipStream_t st,
-                 const float *hx_rows = nullptr, const float *q0 = nullptr)
+FwdPath fwd_path_of(int T, int N, int K, bool per_token, bool asym)
 {
     const long tiles128 = (long)((T + 127) / 128) * ((N + 127) / 128);
-    if (small_tiles_shape<BITS>(T, N, K, hx_rows || q0)) {  // (long contractions take 256 features per step)
-        const SplitCall sc{A4, hx_rows, q0, {Xq, rs_x, packed, h, rs_w, bias, Y, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64}};
-        const int tiles = sc.p.tiles_m * sc.p.tiles_n;
-        if (split_shape(tiles, T, K)) hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(tiles), dim3(512), 0, st, sc);
-        else if (stepped_units(K) == 4) launch_cfg<BITS, 1, 1, 1, 2, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
-        else if (stepped_units(K) == 2) launch_cfg<BITS, 1, 1, 1, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
-        else launch_cfg<BITS, 1, 1, 1, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
-        return;
-    }
-    if (K % 128 != 0) {  // odd number of 64-feature units: register-staged kernel, one unit per step
-        launch_cfg<BITS, 2, 2, 2, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
-        return;
-    }
-    if (!hx_rows && !q0 && duo_shape<BITS>(T, N, K)) {  // (its epilogue has neither per-token scales nor asymmetric ranges)
-        launch_duo<BITS>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st);
-        return;
-    }
+    if (small_tiles_shape<BITS>(T, N, K, per_token || asym)) return split_shape((long)((T + 31) / 32) * ((N + 63) / 64), T, K) ? kSliced : kStepped;
+    if (K % 128 != 0) return kStaged128;
+    // (the 128 x 256 tiles' epilogue has neither per-token scales nor asymmetric ranges)
+    if (!per_token && !asym && duo_shape<BITS>(T, N, K)) return kDuo256;
     // Tile choice (measured on BERT-base and BERT-large shapes).  Copies issued on a SIMD that is busy
     // with 32x32 MFMAs run at about half their stand-alone rate, so where the tile count allows it the MFMAs
     // go to three SIMDs and the copies to the fourth:
@@ -2128,17 +2116,38 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
     // (also where 128x128 tiles would need fewer rounds, for up to five rounds of 128x96 tiles: as two workgroups per CU
     // they are 3 % ahead of the plain two-workgroup kernel on BERT-base's FFN-up)
     if (86 * rounds96 < 100 * rounds128 || (N % 96 == 0 && tiles96 > 256 && tiles96 <= 1280))
-    {
         // more tiles than CUs: two workgroups per CU, one's write-out under the other's K-loop (LDS and registers allow it
         // at 2, 3 and 4 bits; at 8 bits with two stages, for the plain fp32 output)
-        if (tiles96 > 256 && BITS < 8) launch_ws<BITS, 2, 1, 2, 3, 3, 2, true>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 512, hx_rows, q0);
-        else if (tiles96 > 256 && !q0) launch_ws<BITS, 2, 1, 2, 3, 2, 2, true>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 512, hx_rows, q0);
-        else launch_ws<BITS, 2, 1, 2, 3, 3, 2, true>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 256, hx_rows, q0);
+        return tiles96 > 256 && (BITS < 8 || !asym) ? kRoles96Two : kRoles96One;
+    // (per-token scales, asymmetric ranges: role-split kernels only)
+    return per_token || asym || tiles128 <= 640 || (K >= 2048 && tiles128 <= 1024) ? kRoles128 : kPlain128;
+}
+
+template <int BITS>
+void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, const float *h, const int32_t *rs_w,
+                 const float *bias, float *Y, int32_t *A4, int T, int N, int K, int rpg, float hx, hipStream_t st,
+                 const float *hx_rows = nullptr, const float *q0 = nullptr)
+{
+    switch (fwd_path_of<BITS>(T, N, K, hx_rows != nullptr, q0 != nullptr)) {
+        case kSliced: {
+            const SplitCall sc{A4, hx_rows, q0, {Xq, rs_x, packed, h, rs_w, bias, Y, T, N, K, rpg, hx, (T + 31) / 32, (N + 63) / 64}};
+            hipLaunchKernelGGL((qgemm_i8_split_kernel<BITS>), dim3(sc.p.tiles_m * sc.p.tiles_n), dim3(512), 0, st, sc);
+            return;
+        }
+        case kStepped:  // (long contractions take 256 features per step)
+            if (stepped_units(K) == 4) launch_cfg<BITS, 1, 1, 1, 2, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
+            else if (stepped_units(K) == 2) launch_cfg<BITS, 1, 1, 1, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
+            else launch_cfg<BITS, 1, 1, 1, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
+            return;
+        case kStaged128:  // odd number of 64-feature units: one unit per step
+            launch_cfg<BITS, 2, 2, 2, 2, 1>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0);
+            return;
+        case kDuo256: launch_duo<BITS>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st); return;
+        case kRoles96Two: launch_ws<BITS, 2, 1, 2, 3, BITS < 8 ? 3 : 2, 2, true>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 512, hx_rows, q0); return;
+        case kRoles96One: launch_ws<BITS, 2, 1, 2, 3, 3, 2, true>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 256, hx_rows, q0); return;
+        case kRoles128: launch_ws<BITS, 2, 2, 2, 2, 3, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 256, hx_rows, q0); return;
+        case kPlain128: launch_dma<BITS, 2, 2, 2, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 512); return;
     }
-    else if (hx_rows || q0 || tiles128 <= 640 || (K >= 2048 && tiles128 <= 1024))  // (per-token scales, asymmetric ranges: role-split kernels only)
-        launch_ws<BITS, 2, 2, 2, 2, 3, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 256, hx_rows, q0);
-    else
-        launch_dma<BITS, 2, 2, 2, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 512);
 }
 
 // 8-bit output: the role-split kernels only (128x96 tiles on three SIMDs where they need fewer rounds, else 128x128)
@@ -2165,6 +2174,13 @@ __global__ void fill_zero_i32_kernel(int32_t *p, int n)
 }
 
 }  // namespace
+
+int fwd_path(int bits, int T, int N, int K, bool per_token, bool asym)
+{
+    return bits == 2 ? fwd_path_of<2>(T, N, K, per_token, asym) : bits == 3 ? fwd_path_of<3>(T, N, K, per_token, asym)
+         : bits == 4 ? fwd_path_of<4>(T, N, K, per_token, asym) : fwd_path_of<8>(T, N, K, per_token, asym);
+}
+
 }  // namespace qb
 
 using namespace qb;

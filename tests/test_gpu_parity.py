@@ -489,8 +489,8 @@ def test_quantize_act_dynamic(qb, shape):
                                    (2048, 1024, 128, 128), (2304, 1536, 128, 128), (4096, 768, 128, 128),
                                    (4096, 768, 192, 128)])
 def test_forward_dynamic_scales(qb, bits, shape):
-    """Per-token scales through every kernel that takes them (32x64 register-staged tiles, sliced contractions, the 128x128
-    one for K not a multiple of 128, both role-split layouts), ragged T and N, with and without bias."""
+    """Per-token scales through tiles of 32x64, stepped and sliced, and a role-split kernel (the kernels of many tiles:
+    test_forward_scales_and_ranges_through_the_large_tiles), ragged T and N, with and without bias."""
     T, N, K, G = shape
     say("fwd dynamic", shape, "bits", bits)
     W = wl.weight_uniform(N, K, seed=17 * N + K + bits, lo=-0.1, hi=0.1)
@@ -810,8 +810,7 @@ def test_quantize_asymmetric_ranges(qb, bits, shape):
                                    (2048, 1024, 128, 128), (2304, 1536, 128, 128), (4096, 768, 256, 128), (100, 96, 2048, 96)])
 def test_forward_asymmetric_ranges(qb, bits, shape):
     """Y against the oracle within 1e-6 of h_x*(Delta*|S| + |q0|*|R|) (the two products that are added), A4 bit for
-    bit; through the register-staged kernel (few tiles, K not a multiple of 128), the sliced one and both role-split layouts; ragged
-    T and N; with bias."""
+    bit; through tiles of 32x64, stepped and sliced, and a role-split kernel; ragged T and N; with bias."""
     T, N, K, G = shape
     say("fwd asym", shape, "bits", bits)
     W = shifted_weight(N, K, G, seed=3 * N + K + bits)

@@ -2,12 +2,15 @@
 configuration 4 (12-layer stack at 32 x 384 tokens with per-layer bits) forward and backward, and per-element
 bounds for the STE backward at configuration-3 size.  Everything goes through the C ABI; the reference is the
 CPU oracle (its OpenMP build, the same source)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_1909_05840_amd import workloads as wl
+from paper_1909_05840_amd.binding import LIB_PATH
 
 pytestmark = pytest.mark.gpu
 BITS = (2, 3, 4, 8)
@@ -468,7 +471,7 @@ def _shifted_weight(N, K, G, seed):
                                    (2048, 1024, 128, 128), (2304, 1536, 128, 128), (4096, 768, 256, 128)])
 def test_forward_asymmetric_ranges_with_per_token_scales(qb, bits, shape):
     """qb_qlinear_fwd_asym_dyn: asymmetric group ranges and one activation scale per token, through the few-tile kernels (the
-    stepped and the sliced one) and both role-split layouts, ragged T and N, with and without bias; rows of very different magnitude and an
+    stepped and the sliced one) and a role-split one, ragged T and N, with and without bias; rows of very different magnitude and an
     all-zero row.  Y against the oracle within 1e-6 of h_x[t]*(Delta*|S| + |q0|*|R|), A4 bit for bit; a constant scale
     vector gives the fixed-clip call's bits."""
     T, N, K, G = shape
@@ -597,6 +600,56 @@ def test_forward_whole_output_steps_of_one_unit(qb, bits, shape):
 @pytest.mark.parametrize("shape", [(2015, 2048, 256), (2049, 2010, 256), (1990, 2040, 768), (3050, 2044, 576), (3073, 2044, 576), (2500, 2044, 832), (2600, 2044, 832)])
 def test_forward_whole_output_around_the_small_tiles(qb, bits, shape):
     test_forward_whole_output_large_tiles(qb, bits, shape)
+
+
+def fwd_path(bits, T, N, K, per_token, asym):
+    """the kernel that the library's rule gives a forward call: 0 sliced, 1 stepped, 2 register-staged 128 x 128, 3 128 x 256, role-split 4 128 x 96
+    with two workgroups per CU, 5 with one, 6 128 x 128; 7 plain 128 x 128"""
+    rule = ctypes.CDLL(LIB_PATH)._ZN2qb8fwd_pathEiiiibb
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_bool] * 2
+    return rule(bits, T, N, K, per_token, asym)
+
+
+# (T, N, K, path): K of one and of odd numbers of units in register-staged tiles of 128 x 128, on both sides of K = 704 and over 1024; role-split
+# tiles of 128 x 96 as two workgroups per CU (at 8 bits with asymmetric ranges as one) and as one, of 128 x 128 in one round and two; all
+# end inside a tile of tokens and of neurons, the neuron counts even and odd
+@pytest.mark.parametrize("per_token,asym", [(True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("shape", [(3100, 2034, 64, 2), (3100, 2035, 576, 2), (2700, 2034, 832, 2), (1700, 1430, 1088, 2), (3100, 1430, 128, 4), (3099, 1431, 384, 4),
+                                   (2500, 1130, 256, 5), (5300, 700, 128, 6), (6300, 1001, 384, 6)])
+def test_forward_scales_and_ranges_through_the_large_tiles(qb, bits, shape, per_token, asym):
+    """Per-token scales, asymmetric ranges and both through each kernel for calls of many tiles: A4 (asymmetric: 2*S - L*R) exact, Y against
+    fp64 within 1e-6 of the products that are added, calls with and without the debug output with the same bits."""
+    T, N, K, path = shape
+    say("fwd scales and ranges", shape, "bits", bits, per_token, asym)
+    assert fwd_path(bits, T, N, K, per_token, asym) == (5 if bits == 8 and asym and path == 4 else path)
+    groups = 2 if N % 2 == 0 else 1
+    W = (wl.weight(N, K, seed=3 * N + K + bits) + (0.03 if asym else 0.0)).to(DEV)
+    X = wl.activation(T, K, seed=T + K + bits).to(DEV)
+    X[T // 3] *= 11.0
+    X[3] = 0.0
+    bias = (0.3 * wl.activation(1, N, seed=13)[0]).to(DEV)
+    packed, step, q0, rs_w = qb.qb_quantize_groupwise_asym(W, bits, groups) if asym else qb.qb_quantize_groupwise(W, bits, groups)
+    Xq, rs_x, hx = qb.qb_quantize_act_dyn(X) if per_token else (*qb.qb_quantize_act(X, CLIP), None)
+    scale = hx if per_token else CLIP
+    call = {(True, False): qb.qb_qlinear_fwd_dyn, (False, True): qb.qb_qlinear_fwd_asym, (True, True): qb.qb_qlinear_fwd_asym_dyn}[per_token, asym]
+    args = (Xq, rs_x, scale, packed, step) + ((q0,) if asym else ()) + (rs_w, bits, groups, N)
+    Y, A4 = call(*args, bias=bias, want_a4=True)
+    assert torch.equal(call(*args, bias=bias), Y)
+    # whole numbers below 2^53 in fp64 are exact
+    L = 2 ** bits - 1
+    xi = 2.0 * Xq.double() + 1.0
+    S, R = xi @ qb.qb_unpack_codes(packed, N, K, bits).double().T, xi.sum(dim=1)[:, None]
+    assert torch.equal(A4.double(), 2.0 * S - L * R)
+    hx64 = hx.double()[:, None] if per_token else CLIP / 255.0
+    steps, zeros = step.double().repeat_interleave(N // groups), q0.double().repeat_interleave(N // groups)
+    if asym:
+        ref, size = hx64 * (steps * S + zeros * R), hx64 * (steps * S.abs() + zeros.abs() * R.abs())
+    else:
+        ref = hx64 * steps * A4.double()
+        size = ref.abs()
+    # roundings of the products (bound as for the small shapes) and the one of the sum with the bias
+    assert bool(((Y.double() - (ref + bias.double())).abs() <= 1e-6 * size + 2.0 ** -23 * (ref + bias.double()).abs()).all())
 
 
 # K of three units of 64 features (five of the eight slices empty) up to uneven eighths; one token, one more than a tile of
