@@ -256,8 +256,9 @@ qb_status qb_quantize_act_dyn_tensor(const float *X, int64_t T, int64_t K,
  *   - all others stage operands in the workspace and compute both products in one more launch, whose workgroups share
  *     the contraction steps evenly and add the partial sums of a shared tile in a fixed order.  One more launch each
  *     pads the rows of dY for dX where N is not a multiple of 64, and moves a dY that is not 16-byte aligned where N is a
- *     multiple of 8.  A workgroup may wait for partial sums of workgroups dispatched before it; the wait is bounded
- *     (about two seconds), after which the tile concerned is written as NaN.
+ *     multiple of 8.  A workgroup may wait for partial sums of others of its launch.  Those run next to it, also while
+ *     other streams' kernels share the GPU, two further calls of this kind among them; the wait is bounded (about two
+ *     seconds), after which the tile concerned is written as NaN.
  * The same call gives the same bits every time, wherever its operands lie.  Which of dX and dW a call computes decides
  * the path and how the steps are shared, so dX of a dX-only call may differ from dX of a call that also computes dW in
  * the last bf16 bit, and dW in the last bits (order of the fp32 additions).  Calls that share a workspace must not

@@ -233,9 +233,10 @@ __device__ __forceinline__ void wait_vmcnt()
 //     wavefront waits for the flags of the same wavefront of the runs v' < v that hold the tile's earlier steps,
 //     adds their partial sums to its own in ascending order of v' (a fixed order: results do not change from run
 //     to run) and writes the tile out.
-// A workgroup thus waits only for runs below its own, which finish their pieces when it finishes its own; the
-// flags are cleared by the staging launch that precedes every GEMM launch.  The wait is bounded: if a flag has
-// not been raised after some seconds the tile is written as NaN, so that every wavefront ends.
+// A workgroup thus waits only for runs below its own, which finish their pieces when it finishes its own.  Runs are numbered
+// XCD by XCD and an XCD starts its workgroups in order, so the lowest unfinished run of an XCD waits for lower XCDs only,
+// whatever other streams' kernels hold its CUs meanwhile.  The flags are cleared by the staging launch that precedes every GEMM launch.
+// The wait is bounded: if a flag has not been raised after some seconds the tile is written as NaN, so that every wavefront ends.
 // The clamp's derivative (mask of a problem, src != null): element (r, n) of the result is set to zero where
 // |src[r, n]| exceeds its range: lim[r / rows_per_lim] for dW (weights: one range per group of rows), lim_all for dX.
 struct ClampMask {
@@ -849,9 +850,19 @@ __global__ __launch_bounds__(512) void gemm_bf16_sk_kernel(const SkGroup g)
 // results each, v_mfma_f32_16x16x32_bf16), two workgroups per CU that share no barrier.  All four SIMDs multiply, a step reads
 // 80 KB of fragments out of LDS for what takes the kernel above 98, and a workgroup's start, exchange of partial sums and
 // write-out run under the other one's MFMAs.
+// Pieces of a tile lie on several XCDs.  The one of the last workgroup in the order of the grid owns the tile and waits for the others; no
+// other workgroup waits.  Alone on the GPU all 512 are resident.  Next to other streams' kernels the XCDs start them at their own pace, so
+// what keeps a call going there is that its owners hold at most 20 of an XCD's 64 places (bwd_duo_waiting): three such calls at once
+// leave places on every XCD for the workgroups that are waited for.  With more of them only the bound of the wait would remain.
 struct DuoShare {      // a product's share of the workgroups
     int tiles, runs;   // its tiles; the workgroups of an XCD that work on it
     int p, rot;        // pieces of a tile's contraction; by how much the order of the tiles turns from piece to piece
+    // the number, XCD by XCD, of the workgroup that does piece c of tile t
+    __host__ __device__ __forceinline__ int run_of(int c, int t) const
+    {
+        const int k = t - c * rot % tiles;
+        return c * tiles + (k < 0 ? k + tiles : k);
+    }
 };
 struct DuoGroup {
     SkGroup g;         // (ustart is not used)
@@ -921,8 +932,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_duo_kernel(const DuoGroup dg
     const SkProblem &P = g.p[does_w ? g.n - 1 : 0];
     // the workgroup of piece c of tile t
     auto block_of = [&](int c, int t) {
-        int k = t - c * S.rot % tiles;
-        k = c * tiles + (k < 0 ? k + tiles : k);
+        const int k = S.run_of(c, t);
         return 8 * (first_idx + k % runs) + k / runs;
     };
     int tile = 0, tile_end = 0, piece = 0, owner = 0;
@@ -971,7 +981,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_duo_kernel(const DuoGroup dg
         sk_place(P, tile, tile_m, tile_n);
         const int M = P.M, Nc = P.Nc, lda = P.lda, ldb = P.ldb;
         const int t_rows = TURN ? P.t_rows : 0;
-        // (rows of a tile lie less than 2^32 bytes apart: at most 192 rows of at most 2^25 bytes)
+        // (rows of a tile lie less than 2^32 bytes apart: at most 192 rows of less than 2^24 bytes, see duo_plan)
         a_ptr = scalar_address(t_rows ? P.A + (size_t)s0 * 64 * lda : P.A + (size_t)tile_m * BM * lda + s0 * 64);
         b_ptr = scalar_address(P.B + (size_t)tile_n * BN * ldb + s0 * 64);
         a_step = t_rows ? (size_t)lda * 128 : (size_t)BKB;
@@ -1033,9 +1043,9 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_duo_kernel(const DuoGroup dg
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
     };
-    // slots: the pieces that do not write their tile, dW's tiles, then dX's
+    // slots: the pieces that do not write their tile (of dW; dX's are whole)
     auto slot_of = [&](int c) -> float4 * {
-        const int k = (does_w ? 0 : dg.w.tiles * (dg.w.p - 1)) + tile * (pieces - 1) + c - (c > owner);
+        const int k = tile * (pieces - 1) + c - (c > owner);
         return reinterpret_cast<float4 *>(g.slots + (size_t)k * SLOT_FLOATS) + wave * TM * TN * 64 + lane;
     };
 
@@ -1475,6 +1485,22 @@ int bwd_duo_pieces(int64_t T, int64_t N, int64_t K, bool dx, bool dw)
 {
     DuoShare w, x;
     return !bwd_direct_teams(T, N, K, dx, dw) && duo_plan(w, x, T, N, K, dx, dw) ? w.p : 0;
+}
+// The most workgroups of such a call that wait for others on one XCD
+int bwd_duo_waiting(int64_t T, int64_t N, int64_t K, bool dx, bool dw)
+{
+    DuoShare w, x;
+    int on[8] = {}, most = 0;
+    if (!duo_plan(w, x, T, N, K, dx, dw) || w.p == 1) return 0;
+    for (int t = 0; t < w.tiles; ++t) {
+        int last = 0;  // in the order of the grid, as in the kernel
+        for (int c = 0; c < w.p; ++c) {
+            const int k = w.run_of(c, t);
+            last = std::max(last, 8 * (k % w.runs) + k / w.runs);
+        }
+        most = std::max(most, ++on[last & 7]);
+    }
+    return most;
 }
 }
 

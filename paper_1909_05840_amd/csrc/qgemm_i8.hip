@@ -245,7 +245,7 @@ __device__ __forceinline__ void qgemm_i8_body(
                 _Pragma("unroll") for (int i = 0; i < BITS; ++i) bcur[tn][kk][i] = bnext[tn][kk][i];      \
     }
 
-    // The epilogue's parameters.  None is loaded between stores: the load would wait for every store before it (256 x 2304 x
+    // The epilogue's parameters.  None is loaded between the stores of 32 rows: the load would wait for every store before it (256 x 2304 x
     // 768 with per-token scales and asymmetric ranges 6.7 -> 4.7 us; with the plain scale ragged tiles alone did so, 1499 x 768 x
     // 768 5.8 -> 4.6, tiles of 128 x 128, 3001 x 1344 x 448 18.7 -> 11.6).  Tiles of one block a wavefront have them on their
     // way during the K-loop, if there are registers for them (256 x 2304 x 768 4.45 -> 4.28).
@@ -329,7 +329,7 @@ __device__ __forceinline__ void qgemm_i8_body(
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
         if constexpr (!AHEAD) {
-            asm volatile("" ::: "memory");  // (32 rows' parameters at a time: there are no registers for more)
+            asm volatile("" ::: "memory");  // (32 rows' parameters at a time, behind the stores of the 32 before: there are no registers for more)
             load_rows(tm);
         }
         const int left = T - (tile_m * BM + (wm * TM + tm) * 32 + 4 * hf);
@@ -1644,8 +1644,8 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_duo_kernel(const DuoJob job)
                                 : BITS == 2 ? hq * 256 + q16 * 16 : hq * 512 + (((2 * q16) ^ (q16 >> 3)) << 4));
     constexpr int B_NEXT = BITS == 8 ? 32 : 16;  // toggles b
 
-    // The lane's number formed anew where a tile needs it: kept over the K-loop it takes a register that 4 bits do not have (the
-    // spilled one cost no time that could be measured).
+    // The lane's number formed anew where a tile needs it: kept over the K-loop, it and what is formed from it take two registers that
+    // 4 bits do not have (spilling them cost no time that could be measured).
     auto lane_again = []() {
         int all = -1;
         asm volatile("" : "+s"(all));

@@ -42,3 +42,15 @@ def test_calls_take_one_launch_where_it_is_the_faster_path(T, N, K, dx, dw, team
                                                 (8512, 2304, 768, False, True, 4), (6208, 2304, 768, False, True, 0)])
 def test_large_calls_take_two_workgroups_per_cu_where_they_are_faster(T, N, K, dx, dw, pieces):
     assert _rule("_ZN2qb14bwd_duo_piecesElllbb", [ctypes.c_int64] * 3 + [ctypes.c_bool] * 2)(T, N, K, dx, dw) == pieces
+
+
+# Workgroups that wait hold at most 20 of an XCD's 64 places, so that three calls at once leave some on every XCD
+def test_workgroups_that_wait_leave_places_on_every_xcd():
+    waiting = _rule("_ZN2qb15bwd_duo_waitingElllbb", [ctypes.c_int64] * 3 + [ctypes.c_bool] * 2)
+    seen = set()
+    for N in range(128, 3072, 64):
+        for K in range(192, 6144, 192):
+            for T in (1000, 1700, 3000, 5000, 8200, 12288, 20000):
+                for dx in (True, False):
+                    seen.add(waiting(T, N, K, dx, True))
+    assert max(seen) <= 20 and len(seen) > 8
