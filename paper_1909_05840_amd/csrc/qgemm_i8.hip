@@ -2031,8 +2031,9 @@ inline bool split_shape(long tiles, int T, int K) { return tiles <= 256 && slice
 // 768 4.4-5 us against 8; equal at about 190 tiles of 128 x 128).  Up to one such tile a CU they are ahead too where 128 x 96 tiles would
 // need a second round for a few of them.  Time / time with the larger tiles, behind the activation quantizer:
 //   second round of 128 x 96 tiles, K = 256 to 512 .86-.98 (4 bits), .88-.94 (3), .91-1.0 (8);  768 .93-.99, .93-1.0, .91-1.01;  1024 .92-1.0,
-//   .95-1.05, .94-1.08;  with a range per token K up to 1024 .93-1.0, .87-1.01, .85-1.0;  K >= 2048 1.01-1.39;  N = 640
-//   1.04
+//   .95-1.05, .94-1.08;  with a range per token K up to 1024 .93-1.0, .87-1.01, .85-1.0;  K >= 2048 1.01-1.39
+//   N = 128 to 704, 161 to 256 tiles of 128 x 128 (lowest to highest of all widths, with one range and with one per token):  K = 128
+//   .74-.93, .77-.98;  256 .80-.97, .79-1.02;  512 .86-.98, .89-1.01;  640 .87-1.01, .90-1.02;  768 .88-1.04, .91-1.06
 //   first round (162 to 190 tiles) .91-1.11;  289 to 384 tiles of 128 x 128 .85-1.15
 // K no multiple of 128, where the larger tiles are register-staged ones of 128 x 128, 4, 3 and 8 bits:
 //   161 to 200 tiles .70-.84, 257 to 300 .83-.94;  346 to 360, K <= 704 .87-.99, 960 .97-1.06;  414 to 420 .92-1.01, 1.0-1.14
@@ -2042,7 +2043,7 @@ bool small_tiles_shape(int T, int N, int K, bool gen)
     const long tiles_m = (T + 127) / 128, tiles128 = tiles_m * ((N + 127) / 128), tiles96 = tiles_m * ((N + 95) / 96);
     if (tiles128 <= 160) return true;
     if (K % 128 != 0) return K <= 1024 && tiles128 <= (K <= 704 ? 384 : 320);
-    return tiles128 <= 256 && tiles96 > 256 && N >= 768 && K <= (gen || BITS == 2 || BITS == 4 ? 1024 : 768);
+    return tiles128 <= 256 && tiles96 > 256 && K <= (N < 768 ? 640 : gen || BITS == 2 || BITS == 4 ? 1024 : 768);
 }
 
 // Which problems go to the 128 x 256 kernel with two independent workgroups per CU.  Its tiles are the largest, so it

@@ -595,9 +595,9 @@ def test_forward_whole_output_steps_of_one_unit(qb, bits, shape):
 
 
 # both sides of the lines up to which calls of more than 160 tiles of 128 x 128 take tiles of 32 x 64: 256 of them that make a second
-# round of 128 x 96 tiles, and 272; 384 and 400 with K = 576, 320 and 336 with K = 832
+# round of 128 x 96 tiles, and 272; 384 and 400 with K = 576, 320 and 336 with K = 832; 252 of them, 700 neurons, K = 640 and 768
 @pytest.mark.parametrize("bits", BITS)
-@pytest.mark.parametrize("shape", [(2015, 2048, 256), (2049, 2010, 256), (1990, 2040, 768), (3050, 2044, 576), (3073, 2044, 576), (2500, 2044, 832), (2600, 2044, 832)])
+@pytest.mark.parametrize("shape", [(2015, 2048, 256), (2049, 2010, 256), (1990, 2040, 768), (3050, 2044, 576), (3073, 2044, 576), (2500, 2044, 832), (2600, 2044, 832), (5300, 700, 640), (5300, 701, 768)])
 def test_forward_whole_output_around_the_small_tiles(qb, bits, shape):
     test_forward_whole_output_large_tiles(qb, bits, shape)
 
@@ -616,7 +616,7 @@ def fwd_path(bits, T, N, K, per_token, asym):
 @pytest.mark.parametrize("per_token,asym", [(True, False), (False, True), (True, True)])
 @pytest.mark.parametrize("bits", BITS)
 @pytest.mark.parametrize("shape", [(3100, 2034, 64, 2), (3100, 2035, 576, 2), (2700, 2034, 832, 2), (1700, 1430, 1088, 2), (3100, 1430, 128, 4), (3099, 1431, 384, 4),
-                                   (2500, 1130, 256, 5), (5300, 700, 128, 6), (6300, 1001, 384, 6)])
+                                   (2500, 1130, 256, 5), (5300, 700, 1152, 6), (6300, 1001, 384, 6)])
 def test_forward_scales_and_ranges_through_the_large_tiles(qb, bits, shape, per_token, asym):
     """Per-token scales, asymmetric ranges and both through each kernel for calls of many tiles: A4 (asymmetric: 2*S - L*R) exact, Y against
     fp64 within 1e-6 of the products that are added, calls with and without the debug output with the same bits."""
