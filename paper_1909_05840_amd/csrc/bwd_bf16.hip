@@ -1310,32 +1310,33 @@ struct SkProduct {
 // Tiles of 128 x 192 when that leaves every CU at least kSkWideMinSteps of their steps, else 128 x 96; three stages.
 constexpr int kSkWideMinSteps = 16;
 constexpr size_t kSkSlotBytes = (size_t)128 * 192 * 4;
-// What a plan for both products takes, us: the slowest CU, each of which has two workgroups (idx and idx + 32 of an XCD).  A step counts
-// 0.67 while both multiply and 0.47 alone, a tile or a piece written 4.0.
+// What a plan for both products takes, us, less what it has in common with the kernel above: the slowest CU, each of which has two
+// workgroups (idx and idx + 32 of an XCD).  A step counts 0.73 while both multiply and 0.40 alone, a tile written 4.1, the pieces of a tile
+// 1.9 and 0.45 for each after the first; a step of dX's contraction over 16, where dY is the large operand and its copies come late, 0.8.
 float duo_cost(const DuoShare &w, int w_steps, const DuoShare &x, int x_steps)
 {
-    const float kTile = 4.0f;
+    const float kTile = 4.1f;
     const int x_tiles = (x.tiles + 7) / 8;  // of an XCD
-    const float w_len = (float)((w_steps + w.p - 1) / w.p);
+    const float w_len = (float)((w_steps + w.p - 1) / w.p), w_extra = w.p > 1 ? kTile + 1.9f + 0.45f * (w.p - 1) : kTile;
     float worst = 0.0f;
     for (int i = 0; i < kDuoPerXcd / 2; ++i) {
         float len[2], extra[2];
         for (int half = 0; half < 2; ++half) {
             const int j = i + half * kDuoPerXcd / 2 - w.runs, k = j < 0 ? 0 : x_tiles / x.runs + (j < x_tiles % x.runs);
             len[half] = j < 0 ? w_len : (float)(k * x_steps);
-            extra[half] = j < 0 ? kTile : k * kTile;
+            extra[half] = j < 0 ? w_extra : k * kTile;
         }
         const float lo = std::min(len[0], len[1]), hi = std::max(len[0], len[1]);
-        worst = std::max(worst, 0.67f * lo + 0.47f * (hi - lo) + std::max(extra[0], extra[1]));
+        worst = std::max(worst, 0.73f * lo + 0.40f * (hi - lo) + std::max(extra[0], extra[1]));
     }
-    return worst;
+    return worst + 0.8f * (float)std::max(0, x_steps - 16);
 }
-// The same for the kernel above.  Where its runs end on tiles' ends of dX it exchanges less and all CUs walk the contraction in step:
-// 0.7 us for each column of tiles (4096 x 768 x 3072 61.6 us, staging launch included, between 60.9 at 3584 tokens and 75.6 at 4608).
+// The same for the kernel above.  Where its runs end on tiles' ends of dX and the tiles are walked in strips it exchanges less and all CUs
+// walk the contraction in step: 4096 x 768 x 3072 61.6 us, staging launch included, between 60.9 at 3584 tokens and 75.6 at 4608.
 float equal_runs_cost(int64_t units, int x_tiles, int x_steps, int columns)
 {
-    const bool whole = units % kSkMaxRuns == 0 && units / kSkMaxRuns % x_steps == 0;
-    return 0.3f + 0.45f * (float)units / kSkMaxRuns + 7.7f * (float)x_tiles / kSkMaxRuns - (whole ? 0.7f * columns : 0.0f);
+    const bool whole = columns >= 12 && units % kSkMaxRuns == 0 && units / kSkMaxRuns % x_steps == 0;
+    return -1.9f + 0.6f * (float)units / kSkMaxRuns + 9.2f * (float)x_tiles / kSkMaxRuns - (whole ? 16.5f : 0.0f);
 }
 
 // How the workgroups are shared between the products of a call; false if the kernel above is faster.  It is below 8 steps a
@@ -1343,14 +1344,14 @@ float equal_runs_cost(int64_t units, int x_tiles, int x_steps, int columns)
 // and when it comes from memory the copies, one step ahead here, are late (10265 x 3072 x 768 1.05 of the time above, 12288 x 2304 x
 // 768 and 3072 x 768 inside a training step 1.09 and 1.05, though .98 and .94 with dY in the last-level cache).  The pieces that
 // do not write their tile have kSkMaxRuns slots.
-//   Both products: the cheapest number of pieces for dW's tiles, dX's whole tiles with the workgroups that are left, if that is
-//   3.5 us under the kernel above.  Both estimates are fitted to the change that a plan makes to a whole training step (760 calls of 740 to
-//   12288 tokens, hidden sizes 448 to 1024, steps of 24 in a row; to 2361 plans), so what both kernels have in common is in neither.  The rule
-//   takes 6111 us off those steps, the faster side of each call would take 6700; at 2.5 and 4.5 us 6226 and 5910.  Five calls make their
-//   step longer by over 1 us, the most 5569 x 832 x 832 by 2.7 of 450; of 216 others that it took, measured afterwards, 9, the most 3076 x
-//   768 x 3072 by 3.7 of 235, and all of them together made 1865 us.  us a step, kernel above -> here: 12288 x 768 x 768 -11, x 3072 -9,
-//   10361 x 768 x 3072 -27, 4169 x 768 x 3072 -5.5, 8192 x 640 x 2560 -16, 4096 x 1024 x 4096 -17;  left to the kernel above: 4096 x 768 x
-//   3072 2.2, 3072 2.3 and 6144 tokens 3.0.
+//   Both products: the cheapest number of pieces for dW's tiles, dX's whole tiles with the workgroups that are left, if it is cheaper than the
+//   kernel above.  The numbers are those, of many tried, that choose best among what plans were measured to do to whole training steps, 24 in a
+//   row (995 calls of 740 to 12288 tokens, hidden sizes 448 to 1024, all four linears, up to three plans of each): together they take 6672 us off
+//   those steps, the faster side of each call would take 7197.  Ten calls make their step longer by over 1.5 us, the most 6144 x 768 x 3072 by 3.0
+//   of 360; 433 other calls that the rule took, measured afterwards, made 3839 us, eleven of them longer by over 1, the most 2501 x 1024 x 4096 by
+//   3.2 of 314.  us a step, kernel above -> here: 12288 x 768 x 768 -8, x 3072 -9, 10361 x 768 x 3072 -27, 4169 x 768 x 3072 -5.5, 8192 x 640 x
+//   2560 -16, 4096 x 1024 x 4096 -17;  left to the kernel above: 4096 x 768 x 3072 2.2, 3072 tokens 2.3.  (The time of the call itself
+//   is no measure: of 4096 x 768 x 3072 inside the step it is 61.8 there and 61.3 here.)
 //     Of a tile in pieces no more than one workgroup of a CU (32 of an XCD): past that they meet their like (a call, staging launch
 //     included, over the kernel above: 3584 x 896 x 3584 in two pieces 1.08, in one .90, 2560 x 1024 x 4096 1.17 and .92).  Not seven pieces:
 //     a tile's are then all at the same place of their XCDs, and the last two XCDs write everything (5040 x 832 x 832 1.20, in six 1.08;
@@ -1383,7 +1384,7 @@ bool duo_plan(DuoShare &w, DuoShare &x, int64_t T, int64_t N, int64_t K, bool ha
         w = share(w_tiles, (w_tiles * p + 7) / 8, p);
         return true;
     }
-    float best = equal_runs_cost(units, x_tiles, x_steps, (int)cols) - 3.5f;
+    float best = equal_runs_cost(units, x_tiles, x_steps, (int)cols);
     bool found = false;
     for (int p = 1; p <= most && w_tiles * p <= (p == 1 ? kDuoRuns - 8 : kDuoRuns / 2); ++p) {
         if (p == 7) continue;

@@ -29,15 +29,17 @@ def test_calls_take_one_launch_where_it_is_the_faster_path(T, N, K, dx, dw, team
     assert _rule("_ZN2qb16bwd_direct_teamsElllbb", [ctypes.c_int64] * 3 + [ctypes.c_bool] * 2)(T, N, K, dx, dw) == teams
 
 
-# What dW's tiles in that many pieces (two workgroups per CU) take off a training step, us: 11, 9, 5.5, 20, 23, 16, 19, 11, 16; what they would
-# add to it where the older kernel keeps the call: 2.2, 2.3, 3.0, 1.1, 3.5, 3.2, 2.4, 1.8.  12288 x 3072 x 768: dY is the large operand.  One output only, over
-# the older kernel: 384 tiles of dX .88 of the time, 320 1.03, 520 1.15; 72 tiles of dW of 133 steps .98, of 97 1.06
-@pytest.mark.parametrize("T,N,K,dx,dw,pieces", [(12288, 768, 768, True, True, 6), (12288, 768, 3072, True, True, 2), (4169, 768, 3072, True, True, 2),
-                                                (9333, 448, 1792, True, True, 6), (4325, 1024, 4096, True, True, 1), (8192, 640, 2560, True, True, 3),
+# What dW's tiles in that many pieces (two workgroups per CU) take off a training step, us: 8, 9, 5.5, 17, 23, 16, 19, 11, 16, 15, 5; what they would
+# add to it where the older kernel keeps the call: 2.2, 2.3, 0.6, 3.5, 3.2, 2.4, 1.8, 2.2, 3.3.  12288 x 3072 x 768: dY is the large operand.  One output only,
+# over the older kernel: 384 tiles of dX .88 of the time, 320 1.03, 520 1.15; 72 tiles of dW of 133 steps .98, of 97 1.06
+@pytest.mark.parametrize("T,N,K,dx,dw,pieces", [(12288, 768, 768, True, True, 8), (12288, 768, 3072, True, True, 2), (4169, 768, 3072, True, True, 2),
+                                                (9333, 448, 1792, True, True, 4), (4325, 1024, 4096, True, True, 1), (8192, 640, 2560, True, True, 3),
                                                 (10752, 512, 2048, True, True, 4), (10240, 640, 640, True, True, 8), (7680, 768, 3072, True, True, 2),
-                                                (4096, 768, 3072, True, True, 0), (3072, 768, 3072, True, True, 0), (6144, 768, 3072, True, True, 0),
-                                                (5313, 832, 832, True, True, 0), (4608, 832, 832, True, True, 0), (743, 1024, 4096, True, True, 0),
-                                                (6307, 704, 704, True, True, 0), (9728, 576, 576, True, True, 0), (12288, 3072, 768, True, True, 0),
+                                                (12288, 1536, 512, True, True, 6), (1916, 832, 3328, True, True, 1),
+                                                (4096, 768, 3072, True, True, 0), (3072, 768, 3072, True, True, 0), (2048, 768, 3072, True, True, 0),
+                                                (4608, 832, 832, True, True, 0), (743, 1024, 4096, True, True, 0), (6307, 704, 704, True, True, 0),
+                                                (9728, 576, 576, True, True, 0), (9333, 1792, 448, True, True, 0), (6022, 1920, 640, True, True, 0),
+                                                (12288, 3072, 768, True, True, 0),
                                                 (4096, 1024, 2304, True, False, 1), (2560, 1024, 3072, True, False, 0), (8320, 1024, 1536, True, False, 0),
                                                 (8512, 2304, 768, False, True, 4), (6208, 2304, 768, False, True, 0)])
 def test_large_calls_take_two_workgroups_per_cu_where_they_are_faster(T, N, K, dx, dw, pieces):
