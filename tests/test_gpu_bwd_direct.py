@@ -122,13 +122,14 @@ def test_one_team(qb, bits, shape, asym):
     check(dY, W_hat, Xq, dX, dW)
 
 
-# (T, N, K): rows of 22 tiles of 128 x 192 (strips of four and a last one of two) and of 13 of 128 x 96 (a last one of one), both
-# products in strips; 13 with dX (four steps) in whole rows; wide tiles with one output (dX alone in whole rows)
-@pytest.mark.parametrize("shape", [(6100, 200, 4096), (8300, 200, 4096), (700, 264, 1216), (700, 200, 1216)])
+# (T, N, K) and the pieces of two workgroups per CU: rows of 22 tiles of 128 x 192 (strips of four and a last one of two), with two
+# workgroups per CU and, dW alone, equal runs; rows of 13, equal runs with both products, dX alone in whole rows; of 13 of 128 x 96 (a last
+# one of one), both products in strips, and with dX (four steps) in whole rows
+@pytest.mark.parametrize("shape", [(6100, 200, 4096, 4), (8300, 200, 4096, 5), (700, 264, 1216, 0), (700, 200, 1216, 0), (2500, 2000, 2496, 0)])
 def test_last_strip_of_tiles_is_narrower(qb, shape):
-    T, N, K = shape
+    T, N, K, pieces = shape
     print("bwd strips", shape, flush=True)
-    assert one_launch_teams(T, N, K) == 0
+    assert one_launch_teams(T, N, K) == 0 and duo_pieces(T, N, K) == pieces and duo_pieces(T, N, K, dx=False) == 0
     dY = wl.grad_output_bf16(T, N, seed=T + N)
     packed, h, _, _ = qb.qb_quantize_groupwise(wl.weight(N, K, seed=N + K).to(DEV), 4, 8)
     Xq, _ = qb.qb_quantize_act(wl.activation(T, K, seed=T).to(DEV), CLIP)
