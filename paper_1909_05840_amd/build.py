@@ -9,13 +9,13 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqbert.so")
 CALLS = os.path.join(HERE, "_calls.so")
-SOURCES = ("api.hip", "quantize.hip", "qgemm_i8.hip", "bwd_bf16.hip", "bwd_direct.hip", "hessian.hip")
+SOURCES = ("api.hip", "quantize.hip", "qgemm_i8.hip", "qgemm_i8_list.hip", "bwd_bf16.hip", "bwd_direct.hip", "hessian.hip")
 # packed-fp32 instructions are switched off for every device translation unit
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wno-inline-asm",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # the quantizers (also the one in the GEMM's 8-bit-output epilogue) need one rounding per operation: no fused
 # multiply-add contraction there.  (__fmul_rn/__fadd_rn are plain operators to the compiler and would be fused.)
-PER_FILE = {"quantize.hip": ["-ffp-contract=off"], "qgemm_i8.hip": ["-ffp-contract=off"]}
+PER_FILE = {"quantize.hip": ["-ffp-contract=off"], "qgemm_i8.hip": ["-ffp-contract=off"], "qgemm_i8_list.hip": ["-ffp-contract=off"]}
 
 
 def compile_calls(verbose=False):

@@ -30,31 +30,13 @@
 // conflicts; and in all of them the k-bit codes are expanded to int8 with a few byte-parallel shifts and masks in registers,
 // right in front of the MFMA that consumes them.
 // Workgroups are renumbered so that the ones sharing a token panel run on the same XCD (same L2).
-#include "qb_common.hpp"
-#include <type_traits>
+#include "qgemm_i8.hpp"
 
 namespace qb {
 namespace {
 
-// a*b + c for |a|, |b| < 2^23 (full-rate 24-bit multiplier instead of the quarter-rate 32-bit one)
-__device__ __forceinline__ int qb_mad24(int a, int b, int c) { return __mul24(a, b) + c; }
-
-// A4 = 4*acc + corr.  The result fits int32 for every K the library accepts, but 4*acc alone can reach 2^31 at
-// K = 32768 with end-of-range operands: the sum is formed modulo 2^32 in unsigned arithmetic.
-__device__ __forceinline__ int qb_a4(int acc, int corr) { return (int)(4u * (uint32_t)acc + (uint32_t)corr); }
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-
-// Asymmetric group ranges (weights Delta*u + q0, u = 0..L): with R = sum_j (2x'+1) = 2*rs_x + K and
-// S = sum_j (2x'+1)*u = (A4 + L*R)/2 the output is h_x*(Delta*S + q0*R).  A4 and R are even (K is), and
-// S = A4/2 + L*(R/2) stays inside int32 for every K the library accepts.  rh = R/2 = rs_x + K/2.
-__device__ __forceinline__ float asym_value(int a4, int rh, int L, float hx, float delta, float q0)
-{
-    const int S = (a4 >> 1) + L * rh;
-    return hx * (delta * (float)S + q0 * (float)(2 * rh));
-}
+// bytes of one of the two token tiles of the body below
+constexpr int stepped_lds(int BM, int KU) { return BM * (64 * KU + 16); }
 
 // bid: the workgroup's number among the tiles_m * tiles_n workgroups of this problem
 // GEN: per-token scales or asymmetric group ranges (a variant of its own, so that the plain call carries none of its code)
@@ -63,8 +45,9 @@ __device__ __forceinline__ void qgemm_i8_body(
     const int8_t *__restrict__ Xq, const int32_t *__restrict__ rs_x, const uint8_t *__restrict__ packed,
     const float *__restrict__ h, const int32_t *__restrict__ rs_w, const float *__restrict__ bias,
     float *__restrict__ Y, int32_t *__restrict__ A4out, int T, int N, int K, int rows_per_group, float hx,
-    int tiles_m, int tiles_n, const float *__restrict__ hx_rows, const float *__restrict__ q0, const int bid)
+    int tiles_m, int tiles_n, const float *__restrict__ hx_rows, const float *__restrict__ q0, const int bid, uint8_t *lds)
 {
+    // lds: 2 * stepped_lds(BM, KU) bytes
     // hx_rows: one activation scale per token (dynamic range) instead of hx, or null
     // q0: asymmetric group ranges: h holds Delta and q0 the lower end of every group, or null
     constexpr int THREADS = 64 * WM * WN;
@@ -73,8 +56,6 @@ __device__ __forceinline__ void qgemm_i8_body(
     constexpr int A_PER_THREAD = BM * CHUNKS_PER_ROW / THREADS;
     static_assert(BM * CHUNKS_PER_ROW % THREADS == 0, "A tile must split evenly over the threads");
     constexpr int SLOT = 4 * BITS;  // bytes per slot
-
-    __shared__ __align__(16) uint8_t lds[2][BM * LDA];
 
     // ---- which tile: blocks are dealt round-robin to the 8 XCDs; give each XCD a contiguous
     // range of tiles (n fastest) so that a token panel is fetched into one L2 only
@@ -149,7 +130,7 @@ __device__ __forceinline__ void qgemm_i8_body(
     // one K-step: the token tile to LDS, this lane's codes expanded to int8; then the loads of step `next` into the registers
     // that are free now (fetch), and the MFMAs with the token fragments from LDS
     auto do_step = [&](int buf, v4u (&ar)[A_PER_THREAD], uint32_t (&br)[TN][KU][BITS], bool fetch, int next) {
-        uint8_t *abuf = lds[buf];
+        uint8_t *abuf = lds + buf * (BM * LDA);
 #pragma unroll
         for (int i = 0; i < A_PER_THREAD; ++i) *reinterpret_cast<v4u *>(abuf + a_dst[i]) = ar[i];
         uint32_t d[TN][KU][8];
@@ -208,12 +189,12 @@ __device__ __forceinline__ void qgemm_i8_body(
 #define QB_STORE_LDS(buf)                                                                                 \
     {                                                                                                     \
         _Pragma("unroll") for (int i = 0; i < A_PER_THREAD; ++i)                                          \
-            *reinterpret_cast<v4u *>(&lds[buf][a_dst[i]]) = astage[i];                                    \
+            *reinterpret_cast<v4u *>(lds + (buf) * (BM * LDA) + a_dst[i]) = astage[i];                                    \
     }
 // all MFMAs of one K-step: expand this lane's codes to int8 in registers, A fragments from LDS
 #define QB_COMPUTE(buf)                                                                                   \
     {                                                                                                     \
-        const uint8_t *abuf = lds[buf];                                                                   \
+        const uint8_t *abuf = lds + (buf) * (BM * LDA);                                                   \
         _Pragma("unroll") for (int kk = 0; kk < KU; ++kk) {                                               \
             uint32_t d[TN][8];                                                                            \
             _Pragma("unroll") for (int tn = 0; tn < TN; ++tn) {                                           \
@@ -374,8 +355,9 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 ? 3 : KU == 4 ? 1 : 4) vo
     float *__restrict__ Y, int32_t *__restrict__ A4out, int T, int N, int K, int rows_per_group, float hx,
     int tiles_m, int tiles_n, const float *__restrict__ hx_rows, const float *__restrict__ q0)
 {
+    __shared__ __align__(16) uint8_t lds[2 * stepped_lds(WM * TM * 32, KU)];
     qgemm_i8_body<BITS, TM, TN, WM, WN, KU, GEN>(Xq, rs_x, packed, h, rs_w, bias, Y, A4out, T, N, K, rows_per_group, hx, tiles_m,
-                                            tiles_n, hx_rows, q0, blockIdx.x);
+                                            tiles_n, hx_rows, q0, blockIdx.x, lds);
 }
 
 // The few tiles of a small token count: 32 x 64 tiles, the contraction cut into eight slices inside the workgroup.
@@ -385,6 +367,7 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN > 1 ? 3 : KU == 4 ? 1 : 4) vo
 // sums meet in LDS; the write-out is split over the wavefronts as well.  Integer sums: the order does not matter, the
 // results are the ones of the other kernels bit for bit.  The direct loads touch 32 rows per instruction, so that with
 // more workgroups than CUs the kernel above is ahead again, as it is with contractions of a few steps (see split_shape).
+constexpr int kSlices = 8, kSlicedLds = kSlices * 2 * 4 * 64;  // int4 of LDS
 struct SmallProblem {
     const int8_t *Xq;
     const int32_t *rs_x;
@@ -396,16 +379,16 @@ struct SmallProblem {
     int T, N, K, rows_per_group;
     float hx;
     int tiles_m, tiles_n;
+    int kind;  // of a list: bits | units of 64 features per step << 8
 };
 
 // A4out: the debug output, or null; hx_rows: one activation scale per token (dynamic range) instead of hx, or null; q0: asymmetric
 // group ranges (h holds Delta and q0 the lower end of every group), or null
 template <int BITS>
 __device__ __forceinline__ void qgemm_i8_split_body(const SmallProblem &p, int32_t *__restrict__ A4out, const float *__restrict__ hx_rows,
-                                                    const float *__restrict__ q0, const int bid)
+                                                    const float *__restrict__ q0, const int bid, int4 *red)
 {
-    constexpr int KS = 8, SLOT = 4 * BITS, U = 2;  // units in flight, besides as many being multiplied
-    __shared__ __align__(16) int4 red[KS * 2 * 4 * 64];
+    constexpr int KS = kSlices, SLOT = 4 * BITS, U = 2;  // units in flight, besides as many being multiplied
     const int T = p.T, N = p.N, K = p.K;
     const int nwg = p.tiles_m * p.tiles_n;
     int logical;  // each XCD a contiguous range of tiles, n fastest
@@ -538,7 +521,8 @@ struct SplitCall {
 template <int BITS>
 __global__ __launch_bounds__(512) void qgemm_i8_split_kernel(const SplitCall c)
 {
-    qgemm_i8_split_body<BITS>(c.p, c.A4out, c.hx_rows, c.q0, blockIdx.x);
+    __shared__ __align__(16) int4 red[kSlicedLds];
+    qgemm_i8_split_body<BITS>(c.p, c.A4out, c.hx_rows, c.q0, blockIdx.x, red);
 }
 
 // Several few-tile problems (small token counts: the inference regime, where a launch costs more than its work) in one
@@ -550,88 +534,50 @@ struct SmallGroup {
     int first_wg[QB_MAX_BATCH + 1];
     SmallProblem p[QB_MAX_BATCH];
 };
-template <int BITS, int KU>
-__global__ __launch_bounds__(128, 4) void qgemm_i8_small_group_kernel(const SmallGroup g)
+__device__ __forceinline__ int job_of(const SmallGroup &g)
 {
     int j = 0;
     while (j + 1 < g.n && (int)blockIdx.x >= g.first_wg[j + 1]) ++j;
+    return j;
+}
+__global__ __launch_bounds__(128, 3) void qgemm_i8_small_list_kernel(const SmallGroup g)
+{
+    __shared__ __align__(16) uint8_t lds[2 * stepped_lds(32, 4)];
+    const int j = job_of(g);
     const SmallProblem &p = g.p[j];
     const int local = blockIdx.x - g.first_wg[j];
     if (local >= p.tiles_m * p.tiles_n) return;  // (uniform over the workgroup)
-    qgemm_i8_body<BITS, 1, 1, 1, 2, KU, false>(p.Xq, p.rs_x, p.packed, p.h, p.rs_w, p.bias, p.Y, nullptr, p.T, p.N, p.K,
-                                        p.rows_per_group, p.hx, p.tiles_m, p.tiles_n, nullptr, nullptr, local);
+    auto run = [&](auto bits, auto units) {
+        qgemm_i8_body<decltype(bits)::value, 1, 1, 1, 2, decltype(units)::value, false>(p.Xq, p.rs_x, p.packed, p.h, p.rs_w, p.bias, p.Y, nullptr, p.T, p.N, p.K,
+                                                                                        p.rows_per_group, p.hx, p.tiles_m, p.tiles_n, nullptr, nullptr, local, lds);
+    };
+    auto of_width = [&](auto units) {
+        switch (p.kind & 255) {
+            case 2: run(std::integral_constant<int, 2>(), units); break;
+            case 3: run(std::integral_constant<int, 3>(), units); break;
+            case 4: run(std::integral_constant<int, 4>(), units); break;
+            default: run(std::integral_constant<int, 8>(), units); break;
+        }
+    };
+    switch (p.kind >> 8) {
+        case 1: of_width(std::integral_constant<int, 1>()); break;
+        case 2: of_width(std::integral_constant<int, 2>()); break;
+        default: of_width(std::integral_constant<int, 4>()); break;
+    }
 }
-
-template <int BITS>
-__global__ __launch_bounds__(512) void qgemm_i8_split_group_kernel(const SmallGroup g)
+__global__ __launch_bounds__(512) void qgemm_i8_split_list_kernel(const SmallGroup g)
 {
-    int j = 0;
-    while (j + 1 < g.n && (int)blockIdx.x >= g.first_wg[j + 1]) ++j;
+    __shared__ __align__(16) int4 red[kSlicedLds];
+    const int j = job_of(g);
+    const SmallProblem &p = g.p[j];
     const int local = blockIdx.x - g.first_wg[j];
-    if (local >= g.p[j].tiles_m * g.p[j].tiles_n) return;  // (uniform over the workgroup)
-    qgemm_i8_split_body<BITS>(g.p[j], nullptr, nullptr, nullptr, local);
-}
-
-// global -> LDS copy by the load unit: the global address of a lane is a wavefront-uniform base (in SGPRs) plus
-// the lane's 32-bit byte offset, the data of lane l lands at LDS address m0 + BYTES*l (16*l also for the 12-byte form).
-// Written as inline assembly on purpose: the compiler then keeps no book on these copies, and the kernel states
-// itself, with wait_vmcnt, which of them must have landed before a barrier.  The compiler may have written the base with
-// a VALU instruction (v_readlane of a spilled value, v_readfirstlane) right in front, which a vector memory instruction may
-// read five wait states later only; it counts them for its own instructions, not into an asm block.  So the block moves the
-// base into registers of its own: a scalar instruction may read what a VALU instruction wrote at any time, the copy what a
-// scalar one wrote; and the move is the wait state that m0 asks for in front of the copy.  (The
-// kernel below at 2 bits, 16384 x 2304 x 768: 41.2 us, with five wait states in front of every copy 41.8, with one 40.6.)
-template <int BYTES>
-__device__ __forceinline__ void copy_to_lds(const void *base, uint32_t off, uint32_t lds_addr)
-{
-    static_assert(BYTES == 4 || BYTES == 12 || BYTES == 16, "");
-    const void *own;
-    if constexpr (BYTES == 16)
-        asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %1\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(own) : "s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
-    else if constexpr (BYTES == 12)
-        asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %1\n\tglobal_load_lds_dwordx3 %2, %0" : "=&s"(own) : "s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %1\n\tglobal_load_lds_dword %2, %0" : "=&s"(own) : "s"(base), "v"(off), "s"(lds_addr) : "memory", "m0");
-}
-
-template <int BITS> struct SlotRead;  // one lane's slot (32 codes) out of LDS
-template <> struct SlotRead<2> {
-    static __device__ __forceinline__ void get(const uint8_t *p, uint32_t (&o)[2])
-    {
-        const uint2 v = *reinterpret_cast<const uint2 *>(p);
-        o[0] = v.x; o[1] = v.y;
+    if (local >= p.tiles_m * p.tiles_n) return;  // (uniform over the workgroup)
+    switch (p.kind & 255) {
+        case 2: qgemm_i8_split_body<2>(p, nullptr, nullptr, nullptr, local, red); break;
+        case 3: qgemm_i8_split_body<3>(p, nullptr, nullptr, nullptr, local, red); break;
+        case 4: qgemm_i8_split_body<4>(p, nullptr, nullptr, nullptr, local, red); break;
+        default: qgemm_i8_split_body<8>(p, nullptr, nullptr, nullptr, local, red); break;
     }
-};
-template <> struct SlotRead<3> {
-    typedef unsigned int v3u __attribute__((ext_vector_type(3)));
-    static __device__ __forceinline__ void get(const uint8_t *p, uint32_t (&o)[3])
-    {
-        const v3u v = *reinterpret_cast<const v3u *>(p);
-        o[0] = v[0]; o[1] = v[1]; o[2] = v[2];
-    }
-};
-template <> struct SlotRead<4> {
-    static __device__ __forceinline__ void get(const uint8_t *p, uint32_t (&o)[4])
-    {
-        const v4u v = *reinterpret_cast<const v4u *>(p);
-        o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3];
-    }
-};
-template <> struct SlotRead<8> {
-    static __device__ __forceinline__ void get(const uint8_t *p, uint32_t (&o)[8])
-    {
-        const v4u a = *reinterpret_cast<const v4u *>(p), b = *reinterpret_cast<const v4u *>(p + 16);
-        o[0] = a[0]; o[1] = a[1]; o[2] = a[2]; o[3] = a[3];
-        o[4] = b[0]; o[5] = b[1]; o[6] = b[2]; o[7] = b[3];
-    }
-};
-
-// vmcnt(N) with the other counters left alone (gfx9 encoding of s_waitcnt's immediate)
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | 0x0070 | 0x0F00);
 }
 
 // Main kernel, K a multiple of 128.  One K-step is 128 features = two 64-code units.
@@ -1061,17 +1007,6 @@ __device__ __forceinline__ int problem_of(const Group &g, int work)
     while (pi + 1 < g.n && work >= g.tile_start[pi + 1]) ++pi;
     return pi;
 }
-// Tile `local` of a problem with nwg = tiles_m*tiles_n tiles -> its number in row-major order, or -1 for a padding
-// slot.  Workgroups are dealt to the 8 XCDs in turn; XCD x gets a contiguous range of tiles (n fastest), so that a
-// token panel is fetched into one L2 only.
-__device__ __forceinline__ int logical_tile(int local, int nwg)
-{
-    const int xcd = local & 7, idx = local >> 3;
-    const int q = nwg >> 3, r = nwg & 7;
-    if (idx >= q + (xcd < r ? 1 : 0)) return -1;
-    return xcd * q + (xcd < r ? xcd : r) + idx;
-}
-
 // GELU(y) = y/2 * (1 + erf(y/sqrt(2))) = max(y, 0) - w/2 * E, w = |y|, E = erfc(w/sqrt(2)) = 2^(w*R(w)), to within 8e-7: R
 // is a polynomial of degree 4, fitted on [0, 5.5] for the smallest largest error of w/2 * E (5.4e-7; Lawson's reweighted
 // least squares), beyond which w/2 * E is less than 1.1e-7.  (y + |y|)/2 keeps infinities and NaN as the product has them.
@@ -2090,14 +2025,29 @@ void launch_duo(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, co
     hipLaunchKernelGGL((qgemm_i8_duo_kernel<BITS>), dim3(tiles < 512 ? tiles : 512), dim3(256), 0, st, j);
 }
 
+// Which single calls go to the lists' kernel (qgemm_i8_list.hip, 128 x 256 tiles): what the kernel above does not take, with at least most of a
+// round of the 512 resident workgroups and rounds that are full enough.  Time / time with the other kernels, behind the activation
+// quantizer; f: the part of the rounds' places that is taken:
+//   per-token scales and asymmetric ranges, K = 768 to 4096, 2 to 8 bits: f = 1 .77-1.0, .94 .82-.92, .84 .92-.96, .75 (768 and 1152 tiles) .89-.97
+//   and (384 tiles) .94-1.08, .56 and less .89-1.7
+//   K no multiple of 128: K = 960, f = .94 .76-.94, .90 .78-.84, .75 .91-1.15; K = 704, f = .83 .82-.86, .69 .93-1.08; K = 448 .90-1.5;
+//   a tenth of the columns padding 1.03-1.2 below 1700 tiles
+inline bool general_shape(int T, int N, int K, bool gen)
+{
+    const long tiles_n = (N + 255) / 256, tiles = (long)((T + 127) / 128) * tiles_n, places = (tiles + 511) / 512 * 512;
+    if (K % 128 == 0) return gen && K >= 512 && tiles >= 480 && tiles * 100 >= 72 * places && (tiles_n * 256 - N) * 8 <= N;
+    return K >= 640 && tiles >= 448 && tiles * 100 >= 80 * places && (tiles_n * 256 - N) * 12 <= N;
+}
+
 // The kernel of a call: tiles of 32 x 64, sliced or stepped; of 128 x 128 staged through registers (K no multiple of 128); of 128 x 256; role-split
-// ones of 128 x 96, two workgroups per CU or one, and of 128 x 128; plain ones of 128 x 128, two workgroups per CU
-enum FwdPath { kSliced, kStepped, kStaged128, kDuo256, kRoles96Two, kRoles96One, kRoles128, kPlain128 };
+// ones of 128 x 96, two workgroups per CU or one, and of 128 x 128; plain ones of 128 x 128, two workgroups per CU; the lists' kernel
+enum FwdPath { kSliced, kStepped, kStaged128, kDuo256, kRoles96Two, kRoles96One, kRoles128, kPlain128, kGeneral256 };
 template <int BITS>
 FwdPath fwd_path_of(int T, int N, int K, bool per_token, bool asym)
 {
     const long tiles128 = (long)((T + 127) / 128) * ((N + 127) / 128);
     if (small_tiles_shape<BITS>(T, N, K, per_token || asym)) return split_shape((long)((T + 31) / 32) * ((N + 63) / 64), T, K) ? kSliced : kStepped;
+    if (general_shape(T, N, K, per_token || asym)) return kGeneral256;
     if (K % 128 != 0) return kStaged128;
     // (the 128 x 256 tiles' epilogue has neither per-token scales nor asymmetric ranges)
     if (!per_token && !asym && duo_shape<BITS>(T, N, K)) return kDuo256;
@@ -2147,6 +2097,7 @@ void launch_bits(const int8_t *Xq, const int32_t *rs_x, const uint8_t *packed, c
         case kRoles96Two: launch_ws<BITS, 2, 1, 2, 3, BITS < 8 ? 3 : 2, 2, true>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 512, hx_rows, q0); return;
         case kRoles96One: launch_ws<BITS, 2, 1, 2, 3, 3, 2, true>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 256, hx_rows, q0); return;
         case kRoles128: launch_ws<BITS, 2, 2, 2, 2, 3, 4>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 256, hx_rows, q0); return;
+        case kGeneral256: launch_fwd_general<BITS>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, hx_rows, q0); return;
         case kPlain128: launch_dma<BITS, 2, 2, 2, 2, 2>(Xq, rs_x, packed, h, rs_w, bias, Y, A4, T, N, K, rpg, hx, st, 512); return;
     }
 }
@@ -2236,84 +2187,141 @@ void launch_g96(const Group &g, hipStream_t st)
     else launch_group<BITS, 2, 1, 2, 3, 3, 2, true, 0>(g, st, 512);  // (no more than one workgroup per CU at 8 bits)
 }
 
-// the jobs of one bit-width: those that the single call would give to a role-split kernel share launches of it
+bool few_tiles(const qb_fwd_job &j) { return (long)((j.T + 127) / 128) * ((j.N + 127) / 128) <= 160; }
+
+// The few-tile jobs of a call, whatever their widths, side by side in one launch
+void launch_few_tiles(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
+{
+    long tiles = 0, wgs = 0;
+    int longest = 0;
+    bool sliced = false;
+    for (int i = 0; i < n_jobs; ++i)
+        if (few_tiles(jobs[i])) {
+            const long t = (long)((jobs[i].T + 31) / 32) * ((jobs[i].N + 63) / 64);
+            const int K = (int)jobs[i].K;
+            tiles += t;
+            wgs += (t + 7) & ~7l;
+            longest = stepped_steps(K) > longest ? stepped_steps(K) : longest;
+            sliced = sliced || sliced_pays((int)jobs[i].T, K);
+        }
+    sliced = sliced && tiles <= 256 && (wgs <= 256 || longest > 12);
+    SmallGroup g;
+    g.n = 0;
+    auto flush = [&]() {
+        if (g.n == 0) return;
+        if (sliced) hipLaunchKernelGGL(qgemm_i8_split_list_kernel, dim3(g.first_wg[g.n]), dim3(512), 0, st, g);
+        else hipLaunchKernelGGL(qgemm_i8_small_list_kernel, dim3(g.first_wg[g.n]), dim3(128), 0, st, g);
+        g.n = 0;
+    };
+    // (the longest contractions first: the launch ends when the last of them does)
+    int order[QB_MAX_BATCH], n = 0;
+    auto add = [&]() {
+        for (int i = 0; i < n; ++i) {
+            const qb_fwd_job &j = jobs[order[i]];
+            if (g.n == 0) g.first_wg[0] = 0;
+            SmallProblem &sp = g.p[g.n];
+            sp.Xq = j.Xq; sp.rs_x = j.rs_x; sp.packed = static_cast<const uint8_t *>(j.packed); sp.h = j.h; sp.rs_w = j.rs_w;
+            sp.bias = j.bias; sp.Y = j.Y; sp.T = (int)j.T; sp.N = (int)j.N; sp.K = (int)j.K;
+            sp.rows_per_group = (int)(j.N / j.groups); sp.hx = j.clip / 255.0f;
+            sp.tiles_m = (int)((j.T + 31) / 32); sp.tiles_n = (int)((j.N + 63) / 64);
+            sp.kind = j.bits | stepped_units((int)j.K) << 8;
+            g.first_wg[g.n + 1] = g.first_wg[g.n] + ((sp.tiles_m * sp.tiles_n + 7) & ~7);
+            ++g.n;
+        }
+        flush();
+        n = 0;
+    };
+    for (int i = 0; i < n_jobs; ++i)
+        if (few_tiles(jobs[i])) {
+            if (n == QB_MAX_BATCH) add();
+            int k = n++;
+            for (; k > 0 && jobs[order[k - 1]].K < jobs[i].K; --k) order[k] = order[k - 1];
+            order[k] = i;
+        }
+    add();
+}
+
+// The tile choice of the single call (launch_bits) for a job of more tiles: problems it gives to a role-split kernel share launches (one
+// per width and tile shape), the others (K not a multiple of 128, many tiles: two plain workgroups per CU) go one by one ...
+enum LargeJob { kAlone, kShared96, kShared128 };
+template <int BITS>
+LargeJob large_job(const qb_fwd_job &j)
+{
+    const long tiles128 = (long)((j.T + 127) / 128) * ((j.N + 127) / 128);
+    const long tiles96 = (long)((j.T + 127) / 128) * ((j.N + 95) / 96);
+    const long rounds128 = (tiles128 + 255) / 256, rounds96 = (tiles96 + 255) / 256;
+    const bool few128 = tiles128 <= 640 || (j.K >= 2048 && tiles128 <= 1024);
+    // ... except that a problem which alone would run as two plain workgroups per CU joins the 128x96 list when 96
+    // divides its N and it has no more than five rounds of tiles: inside a shared launch it pays no start-up of its
+    // own and its tiles fill the rounds the other problems leave ragged (BERT-base FFN-up at 4096 tokens: the
+    // step's GEMM stage 212 -> 197 us; with twelve and more rounds, at 12288 tokens or BERT-large's 32768, the two
+    // workgroups per CU stay 3-5 % ahead)
+    const bool use96 = 86 * rounds96 < 100 * rounds128 || (!few128 && j.N % 96 == 0 && tiles96 <= 1280);
+    // (at 8 bits the shared launch keeps what has fewer than 1024 tiles of 128 x 256: the rule is of single calls)
+    const bool alone = duo_shape<BITS>((int)j.T, (int)j.N, (int)j.K) && (BITS < 8 || (j.T + 127) / 128 * ((j.N + 255) / 256) >= 1024);
+    if (j.K % 128 != 0 || !(use96 || few128) || alone) return kAlone;
+    return use96 ? kShared96 : kShared128;
+}
+
+// Whether a call's jobs go through launch_fwd_list, all widths in one launch, by an estimate of both sides in us.
+// The list: the longest tile alone on its CU, 1.2 a step and 4, and the tiles of a workgroup if all had the same, 1.75 a step and 5 for each
+// tile, 12 at least, the time of its write-out where all write; the smaller of the two counts a third.  The other kernels: few-tile jobs of all
+// widths share a launch, 1.1 a GOP; then a launch per width and kind of tile, .69 a GOP (1.0 where K is no multiple of 128) or the
+// output at 3.5 TB/s, and 4 each.
+// Four linears of a layer, list / other kernels: hidden 768, widths 2, 3, 4 and 8, 512 tokens 42.8 / 35.7 us, 768 45.6 / 48.2, 1024 48.8 / 73.9, 1536
+// 59.5 / 147 (before few-tile jobs shared launches), 2048 75 / 144, 3072 108 / 207, 4096 147 / 172, 6144 214 / 273; two widths, 1024 tokens 41.4 /
+// 35.4, 2048 42.7 / 68.2, 4096 76.9 / 81.7; 4 bits alone, 1536 tokens 37.5 / 32.1, 3072 39.9 / 46.0, 4096 44.5 / 38.5, 6144 55.1 / 63.6; hidden
+// 320, four widths, 1024 tokens 26.9 / 21.0, 2048 33.0 / 65.7; hidden 448, four widths, 4096 tokens 80 / 149.
+inline bool list_pays(const qb_fwd_job *jobs, int n_jobs)
+{
+    double list = 0.0, other = 0.0, few = 0.0;
+    for (int at = 0; at < n_jobs; at += QB_MAX_BATCH) {
+        double longest = 0.0, work = 0.0;
+        for (int i = at; i < n_jobs && i < at + QB_MAX_BATCH; ++i) {
+            const double steps = (double)((jobs[i].K + 127) / 128), tiles = (double)((jobs[i].T + 127) / 128) * (double)((jobs[i].N + 255) / 256);
+            longest = 1.2 * steps + 4.0 > longest ? 1.2 * steps + 4.0 : longest;
+            work += tiles * (1.75 * steps + 5.0 > 12.0 ? 1.75 * steps + 5.0 : 12.0) / 512.0;
+        }
+        list += 5.0 + (longest > work ? longest + 0.3 * work : work + 0.3 * longest);
+    }
+    unsigned shared = 0;
+    for (int i = 0; i < n_jobs; ++i) {
+        const qb_fwd_job &j = jobs[i];
+        const double gop = 2e-9 * (double)j.T * (double)j.N * (double)j.K;
+        if (few_tiles(j)) {
+            few += (few == 0.0 ? 7.0 : 0.0) + 1.1 * gop;
+            continue;
+        }
+        const double math = (j.K % 128 ? 1.0 : 0.69) * gop, out = 4.0 / 3.5e6 * (double)j.T * (double)j.N;
+        other += math > out ? math : out;
+        const LargeJob kind = j.bits == 2 ? large_job<2>(j) : j.bits == 3 ? large_job<3>(j) : j.bits == 4 ? large_job<4>(j) : large_job<8>(j);
+        const unsigned bit = 1u << (2 * j.bits + (kind == kShared96));
+        if (kind == kAlone || !(shared & bit)) other += 4.0;
+        if (kind != kAlone) shared |= bit;
+    }
+    return list < 0.9 * (other + few);
+}
+
+// The jobs of one bit-width that have more tiles: those that the single call would give to a role-split kernel share launches of it
 // (one list per tile shape), the others go one by one
 template <int BITS>
 void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
 {
     Group g96, g128;
     g96.n = g128.n = 0;
-    SmallGroup small[4];  // few-tile problems, by features per step (64, 128, 256), and those with a sliced contraction
-    small[0].n = small[1].n = small[2].n = small[3].n = 0;
-    auto flush_small = [&](int c) {
-        SmallGroup &sg = small[c];
-        if (sg.n == 0) return;
-        const dim3 grid(sg.first_wg[sg.n]);
-        if (c == 3) hipLaunchKernelGGL((qgemm_i8_split_group_kernel<BITS>), grid, dim3(512), 0, st, sg);
-        else if (c == 0) hipLaunchKernelGGL((qgemm_i8_small_group_kernel<BITS, 1>), grid, dim3(128), 0, st, sg);
-        else if (c == 1) hipLaunchKernelGGL((qgemm_i8_small_group_kernel<BITS, 2>), grid, dim3(128), 0, st, sg);
-        else hipLaunchKernelGGL((qgemm_i8_small_group_kernel<BITS, 4>), grid, dim3(128), 0, st, sg);
-        sg.n = 0;
-    };
     const OutQ none{nullptr, nullptr, 1.0f, 0, nullptr, nullptr};
-    auto few_tiles = [](const qb_fwd_job &j) { return (long)((j.T + 127) / 128) * ((j.N + 127) / 128) <= 160; };
-    // The few-tile jobs of the width run side by side: the sliced kernel by the rule of the single call for their sum, one
-    // of them being enough (the longest decides how long the launch takes).  A few workgroups more than CUs (every job's start
-    // at a multiple of 8) cost a second round, which only long contractions are worth: 16 jobs of four widths, sliced / stepped,
-    // 252 tiles in 264 workgroups, K up to 1024 (8 steps) 24.2 / 19.5 us, K up to 1792 (28 steps) 29.5 / 54.4.
-    long small_tiles = 0, small_wgs = 0;
-    int longest = 0;
-    bool sliced = false;
-    for (int i = 0; i < n_jobs; ++i)
-        if (jobs[i].bits == BITS && few_tiles(jobs[i])) {
-            const long tiles = (long)((jobs[i].T + 31) / 32) * ((jobs[i].N + 63) / 64);
-            const int K = (int)jobs[i].K;
-            small_tiles += tiles;
-            small_wgs += (tiles + 7) & ~7l;
-            longest = stepped_steps(K) > longest ? stepped_steps(K) : longest;
-            sliced = sliced || sliced_pays((int)jobs[i].T, K);
-        }
-    sliced = sliced && small_tiles <= 256 && (small_wgs <= 256 || longest > 12);
     for (int i = 0; i < n_jobs; ++i) {
         const qb_fwd_job &j = jobs[i];
-        if (j.bits != BITS) continue;
-        // the tile choice of the single call (launch_bits): problems it gives to a role-split kernel share launches,
-        // the others (few tiles, K not a multiple of 128, many tiles: two plain workgroups per CU) go one by one
-        const long tiles128 = (long)((j.T + 127) / 128) * ((j.N + 127) / 128);
-        const long tiles96 = (long)((j.T + 127) / 128) * ((j.N + 95) / 96);
-        const long rounds128 = (tiles128 + 255) / 256, rounds96 = (tiles96 + 255) / 256;
-        const bool few128 = tiles128 <= 640 || (j.K >= 2048 && tiles128 <= 1024);
-        // ... except that a problem which alone would run as two plain workgroups per CU joins the 128x96 list when 96
-        // divides its N and it has no more than five rounds of tiles: inside a shared launch it pays no start-up of its
-        // own and its tiles fill the rounds the other problems leave ragged (BERT-base FFN-up at 4096 tokens: the
-        // step's GEMM stage 212 -> 197 us; with twelve and more rounds, at 12288 tokens or BERT-large's 32768, the two
-        // workgroups per CU stay 3-5 % ahead)
-        const bool use96 = 86 * rounds96 < 100 * rounds128 || (!few128 && j.N % 96 == 0 && tiles96 <= 1280);
-        const bool use128 = !use96 && few128;
-        if (few_tiles(j)) {  // few tiles: one launch per kernel
-            const int units = stepped_units((int)j.K), c = sliced ? 3 : units == 4 ? 2 : units == 2 ? 1 : 0;
-            SmallGroup &sg = small[c];
-            if (sg.n == QB_MAX_BATCH) flush_small(c);
-            if (sg.n == 0) sg.first_wg[0] = 0;
-            SmallProblem &sp = sg.p[sg.n];
-            sp.Xq = j.Xq; sp.rs_x = j.rs_x; sp.packed = static_cast<const uint8_t *>(j.packed); sp.h = j.h; sp.rs_w = j.rs_w;
-            sp.bias = j.bias; sp.Y = j.Y; sp.T = (int)j.T; sp.N = (int)j.N; sp.K = (int)j.K;
-            sp.rows_per_group = (int)(j.N / j.groups); sp.hx = j.clip / 255.0f;
-            sp.tiles_m = (int)((j.T + 31) / 32); sp.tiles_n = (int)((j.N + 63) / 64);
-            sg.first_wg[sg.n + 1] = sg.first_wg[sg.n] + ((sp.tiles_m * sp.tiles_n + 7) & ~7);
-            ++sg.n;
-            continue;
-        }
-        // (at 8 bits the shared launch keeps what has fewer than 1024 tiles of 128 x 256: the rule is of single calls)
-        const bool alone = duo_shape<BITS>((int)j.T, (int)j.N, (int)j.K) && (BITS < 8 || (j.T + 127) / 128 * ((j.N + 255) / 256) >= 1024);
-        if (j.K % 128 != 0 || !(use96 || use128) || alone) {
+        if (j.bits != BITS || few_tiles(j)) continue;
+        const LargeJob kind = large_job<BITS>(j);
+        if (kind == kAlone) {
             launch_job<BITS>(j, st);
             continue;
         }
         const uint8_t *p = static_cast<const uint8_t *>(j.packed);
         const int rpg = (int)(j.N / j.groups);
         const float hx = j.clip / 255.0f;
-        if (use96) {
+        if (kind == kShared96) {
             if (g96.n == kMaxGroup) {
                 launch_g96<BITS>(g96, st);
                 g96.n = 0;
@@ -2329,9 +2337,13 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
     }
     if (g96.n) launch_g96<BITS>(g96, st);
     if (g128.n) launch_group<BITS, 2, 2, 2, 2, 3, 4, false, 0>(g128, st, 256);
-    for (int c = 0; c < 4; ++c) flush_small(c);
 }
 }  // namespace
+
+namespace qb {
+bool fwd_takes_list(const qb_fwd_job *jobs, int n_jobs) { return list_pays(jobs, n_jobs); }
+
+}  // namespace qb
 
 extern "C" qb_status qb_qlinear_fwd_batched(const qb_fwd_job *jobs, int n_jobs, void *stream)
 {
@@ -2342,6 +2354,11 @@ extern "C" qb_status qb_qlinear_fwd_batched(const qb_fwd_job *jobs, int n_jobs, 
         if (s != QB_OK) return s;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (list_pays(jobs, n_jobs)) {
+        for (int i = 0; i < n_jobs; i += QB_MAX_BATCH) launch_fwd_list(jobs + i, n_jobs - i < QB_MAX_BATCH ? n_jobs - i : QB_MAX_BATCH, st);
+        return launch_status();
+    }
+    launch_few_tiles(jobs, n_jobs, st);
     launch_jobs_of_width<2>(jobs, n_jobs, st);
     launch_jobs_of_width<3>(jobs, n_jobs, st);
     launch_jobs_of_width<4>(jobs, n_jobs, st);

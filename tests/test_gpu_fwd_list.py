@@ -1,0 +1,86 @@
+"""The batched forward's launches of many linears of different widths, and the single calls that share their kernel: bit for bit the results of
+the other kernels, which the oracle tests cover (whole-number sums, then the same roundings)."""
+import ctypes
+
+import pytest
+
+torch = pytest.importorskip("torch")
+import paper_1909_05840_amd as qb
+from paper_1909_05840_amd import binding
+
+CLIP, GENERAL256 = 6.0, 8
+pytestmark = pytest.mark.gpu
+
+
+def takes_list(jobs):
+    rule = ctypes.CDLL(binding.LIB_PATH)._ZN2qb14fwd_takes_listEPK10qb_fwd_jobi
+    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.c_int]
+    arr = (binding._FwdJob * len(jobs))(*[binding._FwdJob(1, 1, CLIP, 1, 1, 1, j["bits"], j["groups"], j["Xq"].shape[0], j["N"], j["Xq"].shape[1], None, 1) for j in jobs])
+    return rule(ctypes.addressof(arr), len(jobs))
+
+
+def job(g, bits, T, N, K, groups, bias):
+    X = torch.randn(T, K, generator=g, device="cuda")
+    W = torch.randn(N, K, generator=g, device="cuda") * 0.04
+    packed, h, _, rs_w = qb.qb_quantize_groupwise(W, bits, groups)
+    Xq, rs_x = qb.qb_quantize_act(X, CLIP)
+    b = torch.randn(N, generator=g, device="cuda") if bias else None
+    return {"Xq": Xq, "rs_x": rs_x, "clip": CLIP, "packed": packed, "h": h, "rs_w": rs_w, "bits": bits, "groups": groups, "N": N, "bias": b,
+            "Y": torch.full((T, N), float("nan"), device="cuda")}
+
+
+# (T, N, K, groups) of every width: half a last step (K an odd number of units), one step, ragged last tiles in both directions, odd N (no
+# 8-byte rows), more tiles than resident workgroups; the last two stay with the tiles of 32 x 64
+@pytest.mark.parametrize("shapes,is_list", [
+    ([(4200, 1282, 448, 2), (4100, 1025, 128, 1), (4099, 1501, 192, 1), (129, 3000, 64, 4)], True),
+    ([(2500, 1344, 448, 64), (2500, 448, 1792, 64), (2500, 1792, 448, 64), (700, 257, 320, 1)], True),
+    ([(6000, 2304, 256, 128), (6000, 768, 384, 128), (5001, 1024, 512, 128), (128, 256, 2048, 128)], True),
+    ([(33, 300, 64, 4), (64, 65, 192, 1), (31, 128, 2048, 1), (1, 1, 256, 1)], False),
+    ([(200, 768, 768, 128), (129, 500, 320, 4), (65, 768, 3072, 128), (32, 64, 128, 1)], False)])
+def test_lists_of_all_widths_give_the_single_calls_results(shapes, is_list):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    order = [8, 4, 2, 3]  # (the widths of a workgroup's tiles change in both directions)
+    jobs = [job(g, b, *s, bias=(i + b) % 2 == 0) for i, s in enumerate(shapes) for b in order]
+    assert takes_list(jobs) == is_list
+    qb.qb_qlinear_fwd_batched(jobs)
+    for j in jobs:
+        want = qb.qb_qlinear_fwd(j["Xq"], j["rs_x"], CLIP, j["packed"], j["h"], j["rs_w"], j["bits"], j["groups"], j["N"], bias=j["bias"])
+        assert torch.equal(j["Y"], want), (j["bits"], j["Xq"].shape, j["N"])
+
+
+def test_a_list_of_more_jobs_than_a_launch_holds():
+    g = torch.Generator(device="cuda").manual_seed(8)
+    jobs = [job(g, (2, 3, 4, 8)[i % 4], 2700 + 37 * i, 1024, 448 + 64 * (i % 3), 64, False) for i in range(21)]
+    assert takes_list(jobs)
+    qb.qb_qlinear_fwd_batched(jobs)
+    for j in jobs:
+        assert torch.equal(j["Y"], qb.qb_qlinear_fwd(j["Xq"], j["rs_x"], CLIP, j["packed"], j["h"], j["rs_w"], j["bits"], j["groups"], j["N"]))
+
+
+# single calls whose rule names the lists' kernel, against their first tokens, which take another one
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("T,N,K,per_token,asym", [(7680, 2048, 512, True, True), (8100, 1921, 768, True, False), (7600, 2048, 640, False, True),
+                                                  (8190, 2048, 704, False, False), (7640, 2047, 832, True, True)])
+def test_single_calls_of_the_lists_kernel(bits, T, N, K, per_token, asym):
+    rule = ctypes.CDLL(binding.LIB_PATH)._ZN2qb8fwd_pathEiiiibb
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_bool] * 2
+    assert rule(bits, T, N, K, per_token, asym) == GENERAL256 and rule(bits, 700, N, K, per_token, asym) != GENERAL256
+    g = torch.Generator(device="cuda").manual_seed(bits)
+    X = torch.randn(T, K, generator=g, device="cuda")
+    W = torch.randn(N, K, generator=g, device="cuda") * 0.04 + 0.01
+    bias = torch.randn(N, generator=g, device="cuda")
+    if asym:
+        packed, d, q0, rs_w = qb.qb_quantize_groupwise_asym(W, bits, 1)
+    else:
+        packed, d, _, rs_w = qb.qb_quantize_groupwise(W, bits, 1)
+    Xq, rs_x, *hx = qb.qb_quantize_act_dyn(X) if per_token else qb.qb_quantize_act(X, CLIP)
+
+    def forward(sl):
+        args = [Xq[sl], rs_x[sl]] + ([hx[0][sl]] if per_token else [CLIP]) + [packed, d] + ([q0] if asym else []) + [rs_w, bits, 1, N]
+        call = {(True, True): qb.qb_qlinear_fwd_asym_dyn, (True, False): qb.qb_qlinear_fwd_dyn, (False, True): qb.qb_qlinear_fwd_asym, (False, False): qb.qb_qlinear_fwd}
+        return call[per_token, asym](*args, bias=bias, want_a4=True)
+
+    Y, A4 = forward(slice(0, T))
+    for at in (0, 3000, T - 700):
+        y, a4 = forward(slice(at, at + 700))
+        assert torch.equal(A4[at:at + 700], a4) and torch.equal(Y[at:at + 700], y)
