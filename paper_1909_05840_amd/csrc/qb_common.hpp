@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include "../../include/qbert.h"
 
 namespace qb {
@@ -85,17 +86,35 @@ __device__ __forceinline__ void unpack_run(const uint32_t (&in)[BITS], uint32_t 
     }
 }
 
+// Reductions over a wavefront whose 64 lanes are all active, the result in every lane: inside rows of sixteen lanes by row shifts, then over the
+// rows by broadcasts of a row's last lane, as operands of the vector instructions themselves.  (A shuffle goes through the LDS: six of them
+// one after the other are 0.3 us, in a kernel of four.)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp(int old, int v) { return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false); }
 __device__ __forceinline__ float wave_max(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+    // (a lane without a source sees its own value)
+    auto step = [&](auto ctrl, auto rows) {
+        const int b = __float_as_int(v);
+        v = fmaxf(v, __int_as_float(dpp<decltype(ctrl)::value, decltype(rows)::value>(b, b)));
+    };
+    step(std::integral_constant<int, 0x111>(), std::integral_constant<int, 0xf>());  // row_shr:1, 2, 4, 8
+    step(std::integral_constant<int, 0x112>(), std::integral_constant<int, 0xf>());
+    step(std::integral_constant<int, 0x114>(), std::integral_constant<int, 0xf>());
+    step(std::integral_constant<int, 0x118>(), std::integral_constant<int, 0xf>());
+    step(std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xa>());  // row_bcast:15, 31
+    step(std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xc>());
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 __device__ __forceinline__ int wave_sum(int v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    v += dpp<0x111, 0xf>(0, v);
+    v += dpp<0x112, 0xf>(0, v);
+    v += dpp<0x114, 0xf>(0, v);
+    v += dpp<0x118, 0xf>(0, v);
+    v += dpp<0x142, 0xa>(0, v);
+    v += dpp<0x143, 0xc>(0, v);
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 // The quantizer of one range [-m, +m] (q0 = -m): code = clamp(rint(fl((w + m) / Delta)), 0, L),
@@ -121,6 +140,17 @@ struct Quantizer {
         const float hg = (mg == 0.0f) ? 0.0f : __fdiv_rn(mg, L);
         delta = (mg == 0.0f) ? 1.0f : 2.0f * hg;  // all-zero group: w + m = 0 gives code 0 with any Delta
         rinv = __fdiv_rn(1.0f, delta);
+        fast = delta >= 1.0e-30f && delta <= 1.0e30f;
+    }
+    // set with the reciprocal instruction, which is within one unit in the last place: |t' - t| <= 255.0001 * 4.0001 * 2^-24 < 6.1e-5,
+    // which leaves 0.4999 room as well.  (For a range per row, where two divisions would be a good part of a short row's work.)
+    __device__ __forceinline__ void set_row(float mg, float L)
+    {
+        m = mg;
+        Lf = L;
+        const float hg = __fdiv_rn(mg, L);
+        delta = (mg == 0.0f) ? 1.0f : 2.0f * hg;
+        rinv = __builtin_amdgcn_rcpf(delta);
         fast = delta >= 1.0e-30f && delta <= 1.0e30f;
     }
     // a general range [lo, lo + L*d] (q0 = lo): code = rint(fl(fl(w - lo) / d)); d = 0 (a constant group) gives

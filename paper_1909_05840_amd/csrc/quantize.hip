@@ -420,6 +420,35 @@ __global__ void fill_zero_kernel(float *p, int n)
     if (i < n) p[i] = 0.0f;
 }
 
+// Four activations' codes: Quantizer::code4 of the values clamped to the range (CLAMP; otherwise they lie inside).  The quick steps need no
+// clamp: the conversion to a byte saturates, and makes 0 of a NaN as the clamp does.
+template <bool CLAMP>
+__device__ __forceinline__ uint32_t act_code4(const Quantizer &qz, float4 v)
+{
+    float t = __fmul_rn(__fadd_rn(v.x, qz.m), qz.rinv), r = rintf(t);
+    float far = qz.fast ? fabsf(t - r) : 1.0f;
+    uint32_t q = __builtin_amdgcn_cvt_pk_u8_f32(r, 0, 0u);
+    t = __fmul_rn(__fadd_rn(v.y, qz.m), qz.rinv); r = rintf(t);
+    far = fmaxf(far, fabsf(t - r));
+    q = __builtin_amdgcn_cvt_pk_u8_f32(r, 1, q);
+    t = __fmul_rn(__fadd_rn(v.z, qz.m), qz.rinv); r = rintf(t);
+    far = fmaxf(far, fabsf(t - r));
+    q = __builtin_amdgcn_cvt_pk_u8_f32(r, 2, q);
+    t = __fmul_rn(__fadd_rn(v.w, qz.m), qz.rinv); r = rintf(t);
+    far = fmaxf(far, fabsf(t - r));
+    q = __builtin_amdgcn_cvt_pk_u8_f32(r, 3, q);
+    if (__any(far > 0.4999f)) {  // (for all lanes: where it is not needed the division gives the same code)
+        if constexpr (CLAMP) {
+            v.x = __builtin_amdgcn_fmed3f(v.x, -qz.m, qz.m);
+            v.y = __builtin_amdgcn_fmed3f(v.y, -qz.m, qz.m);
+            v.z = __builtin_amdgcn_fmed3f(v.z, -qz.m, qz.m);
+            v.w = __builtin_amdgcn_fmed3f(v.w, -qz.m, qz.m);
+        }
+        q = qz.code4t<false>(v);
+    }
+    return q;
+}
+
 // ---- activations: a wavefront walks over token rows (row = wavefront id, + number of wavefronts, ...)
 // in chunks of 256 float4; the loads of the next chunk (possibly of the next row) are in flight while
 // the current one is quantized, so the memory pipe never drains between rows.
@@ -462,12 +491,7 @@ __global__ __launch_bounds__(256) void quantize_act_kernel(const float *__restri
         for (int u = 0; u < 4; ++u) {
             const int idx = (c << 8) + u * 64 + lane;
             if (idx < k4) {
-                float4 v = cur[u];
-                v.x = __builtin_amdgcn_fmed3f(v.x, -clip, clip);
-                v.y = __builtin_amdgcn_fmed3f(v.y, -clip, clip);
-                v.z = __builtin_amdgcn_fmed3f(v.z, -clip, clip);
-                v.w = __builtin_amdgcn_fmed3f(v.w, -clip, clip);
-                const uint32_t q = qz.code4(v);
+                const uint32_t q = act_code4<true>(qz, cur[u]);
                 sum = __builtin_amdgcn_sad_u8(q, 0u, sum);
                 dst[idx] = q ^ 0x80808080u;  // u - 128 as int8
             }
@@ -488,94 +512,183 @@ __global__ __launch_bounds__(256) void quantize_act_kernel(const float *__restri
     }
 }
 
-// Several activation tensors in one launch (the inputs of a layer's linears): the rows of all tensors form one
-// sequence that the wavefronts walk through as quantize_act_kernel walks through the rows of one tensor, the next
-// chunk (possibly of another tensor) in flight while the current one is quantized.
+// ---- activations, rows of at most 256*V values: a wavefront has a whole row in registers, V float4 per lane.
+// MODE 0: the call's range; 1: the range found by tensor_absmax_kernel; 2: a range per token, c_t = max_j |X[t,j]|.
+// What bounds it: the memory for many rows, for few ones the chain from the launch over the loads, some 30 instructions a float4 and the row's
+// sum.  So the loads come first, without branches, the range's two divisions behind them, the sums need no LDS and a rounding boundary costs
+// a scalar branch.  Against a wavefront that walks its rows in chunks of 1024 values, fixed range and range per token, us: 4096 x 768
+// 5.22 -> 4.42 and 5.55 -> 4.73, 12288 x 768 11.5 -> 10.2 and 11.3 -> 10.7, 32768 x 1024 33.6 -> 30.7 and 33.0 -> 30.4, 4096 x 1536
+// 8.2 -> 6.7 and 8.5 -> 7.2, 8000 x 256 4.45 -> 4.0 and 4.65 -> 4.5.
+template <int V, int MODE>
+__global__ __launch_bounds__(256) void quantize_act_short_kernel(const float *__restrict__ X, int T, int K, float clip, const float *__restrict__ clip_dev,
+                                                                 int8_t *__restrict__ Xq, int32_t *__restrict__ rs_x, float *__restrict__ hx_rows)
+{
+    const int lane = threadIdx.x & 63, nwaves = gridDim.x * 4;
+    int row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (row >= T) return;
+    const int k4 = K >> 2, rest = k4 - (V - 1) * 64;  // 1 to 64 lanes have a last float4; the others repeat the row's last
+    const bool live = lane < rest;
+    const int last = (V - 1) * 64 + (live ? lane : rest - 1);
+    float4 cur[V], nxt[V];
+    auto load = [&](float4 (&v)[V], int r) {
+        const float4 *src = reinterpret_cast<const float4 *>(X + (size_t)r * K);
+#pragma unroll
+        for (int u = 0; u + 1 < V; ++u) v[u] = src[u * 64 + lane];
+        v[V - 1] = src[last];
+    };
+    load(cur, row);
+    Quantizer qz;
+    if constexpr (MODE == 1) clip = *clip_dev;
+    if constexpr (MODE != 2) qz.set(clip, 255.0f);
+    auto quantize = [&](const float4 (&v)[V]) {
+        if constexpr (MODE == 2) {
+            float mx = 0.0f;
+#pragma unroll
+            for (int u = 0; u < V; ++u) mx = absmax4(v[u], mx);
+            qz.set_row(wave_max(mx), 255.0f);
+        }
+        uint32_t *dst = reinterpret_cast<uint32_t *>(Xq + (size_t)row * K);
+        uint32_t sum = 0;
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            const uint32_t q = act_code4<MODE != 2>(qz, v[u]);
+            if (u + 1 < V || live) {
+                sum = __builtin_amdgcn_sad_u8(q, 0u, sum);
+                dst[u * 64 + lane] = q ^ 0x80808080u;  // u - 128 as int8
+            }
+        }
+        const int total = wave_sum((int)sum);
+        if (lane == 0) {
+            rs_x[row] = total - 128 * K;
+            if constexpr (MODE != 0) hx_rows[row] = qz.half_step();
+        }
+    };
+    // (the last row stands behind the loop: with the next one's loads in a branch the compiler would wait for all loads where the paths meet)
+    for (; row + nwaves < T; row += nwaves) {
+        load(nxt, row + nwaves);
+        __builtin_amdgcn_sched_barrier(0);
+        quantize(cur);
+#pragma unroll
+        for (int u = 0; u < V; ++u) cur[u] = nxt[u];
+    }
+    quantize(cur);
+}
+template <int MODE>
+void launch_act_short(const float *X, int T, int K, float clip, const float *clip_dev, int8_t *Xq, int32_t *rs_x, float *hx_rows, hipStream_t st)
+{
+    // at most 8192 wavefronts, all of them resident, and the same number of rows for each
+    const int rows = (T + 8191) / 8192, waves = (T + rows - 1) / rows;
+    auto go = [&](auto v) {
+        hipLaunchKernelGGL((quantize_act_short_kernel<decltype(v)::value, MODE>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, X, T, K, clip, clip_dev, Xq,
+                           rs_x, hx_rows);
+    };
+    switch ((K + 255) / 256) {
+        case 1: go(std::integral_constant<int, 1>()); break;
+        case 2: go(std::integral_constant<int, 2>()); break;
+        case 3: go(std::integral_constant<int, 3>()); break;
+        case 4: go(std::integral_constant<int, 4>()); break;
+        case 5: go(std::integral_constant<int, 5>()); break;
+        case 6: go(std::integral_constant<int, 6>()); break;
+        case 7: go(std::integral_constant<int, 7>()); break;
+        default: go(std::integral_constant<int, 8>()); break;
+    }
+}
+
+// Several activation tensors in one launch (the inputs of a layer's linears): the rows of all tensors form one sequence, of which every
+// wavefront takes a run of rows with the same number of chunks of 256 float4 (to a row), the next chunk (possibly of another tensor) in
+// flight while the current one is quantized.  Four tensors of 4096 tokens, three of 768 values and one of 3072, 110 MB: dealt by the row some
+// wavefronts had two chunks and some four, 24.6 us; now all have three, 22.5.  4096 x 256 12.6 -> 10.4, 500 x 768 8.0 -> 6.5.
 struct ActBatch {
     int n;
-    int row_start[QB_MAX_BATCH + 1];  // first row of tensor i in the sequence; [n] = number of rows
+    int chunk_start[QB_MAX_BATCH + 1];  // first chunk of tensor i in the sequence; [n] = number of chunks (2^31 of them would be 8 TB, but for
+                                        // rows of one chunk, of which a call has at most 2^30)
+    int per, more;                      // a wavefront's chunks; the first `more` wavefronts have one more
     const float *X[QB_MAX_BATCH];
     int8_t *Xq[QB_MAX_BATCH];
     int32_t *rs_x[QB_MAX_BATCH];
-    int K[QB_MAX_BATCH];
+    int T[QB_MAX_BATCH], K[QB_MAX_BATCH];
     float clip[QB_MAX_BATCH];
 };
-
 __global__ __launch_bounds__(256) void quantize_act_batched_kernel(const ActBatch b)
 {
     const int lane = threadIdx.x & 63;
-    const int nwaves = gridDim.x * 4;
-    const int total = b.row_start[b.n];
-    int vrow = blockIdx.x * 4 + (threadIdx.x >> 6);  // position in the sequence of rows (uniform over the wavefront)
-    if (vrow >= total) return;
-    auto job_of = [&](int r) {
-        int j = 0;
-        while (j + 1 < b.n && r >= b.row_start[j + 1]) ++j;
-        return j;
-    };
-    int j = job_of(vrow);
+    const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int from = wave * b.per + (wave < b.more ? wave : b.more), to = from + b.per + (wave < b.more ? 1 : 0);
+    // the first row that begins at `from` or behind it
+    int j = 0;
+    while (j + 1 < b.n && from >= b.chunk_start[j + 1]) ++j;
     int K = b.K[j], k4 = K >> 2, chunks = (k4 + 255) >> 8;
-    float clip = b.clip[j];
-    Quantizer qz;
-    qz.set(clip, 255.0f);
-
+    int row = from - b.chunk_start[j], c = 0;
+    if (chunks > 1) row = (int)((uint32_t)(row + chunks - 1) / (uint32_t)chunks);
+    auto of_tensor = [&]() {
+        K = b.K[j];
+        k4 = K >> 2;
+        chunks = (k4 + 255) >> 8;
+    };
+    if (row == b.T[j]) {
+        if (++j == b.n) return;
+        of_tensor();
+        row = 0;
+    }
+    if (b.chunk_start[j] + row * chunks >= to) return;
     float4 cur[4], nxt[4];
-    auto load = [&](float4 (&v)[4], int jj, int r, int c) {
+    auto load = [&](float4 (&v)[4], int jj, int r, int cc) {
         const int kk4 = b.K[jj] >> 2;
-        const float4 *src = reinterpret_cast<const float4 *>(b.X[jj] + (size_t)(r - b.row_start[jj]) * b.K[jj]);
+        const float4 *src = reinterpret_cast<const float4 *>(b.X[jj] + (size_t)r * b.K[jj]);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int idx = (c << 8) + u * 64 + lane;
-            if (idx < kk4) v[u] = src[idx];
+            const int idx = (cc << 8) + u * 64 + lane;
+            v[u] = src[idx < kk4 ? idx : kk4 - 1];
         }
     };
-    load(cur, j, vrow, 0);
+    load(cur, j, row, 0);
+    Quantizer qz;
+    qz.set(b.clip[j], 255.0f);
     uint32_t sum = 0;
-    int c = 0;
-    while (true) {
-        int nrow = vrow, nc = c + 1, nj = j;
-        if (nc == chunks) {
-            nc = 0;
-            nrow = vrow + nwaves;
-            if (nrow < total) nj = job_of(nrow);
-        }
-        const bool more = nrow < total;
-        if (more) load(nxt, nj, nrow, nc);
-        const int row = vrow - b.row_start[j];
+    auto quantize = [&]() {
         uint32_t *dst = reinterpret_cast<uint32_t *>(b.Xq[j] + (size_t)row * K);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
+            if ((c << 8) + u * 64 >= k4) break;  // (uniform)
             const int idx = (c << 8) + u * 64 + lane;
+            const uint32_t q = act_code4<true>(qz, cur[u]);
             if (idx < k4) {
-                float4 v = cur[u];
-                v.x = __builtin_amdgcn_fmed3f(v.x, -clip, clip);
-                v.y = __builtin_amdgcn_fmed3f(v.y, -clip, clip);
-                v.z = __builtin_amdgcn_fmed3f(v.z, -clip, clip);
-                v.w = __builtin_amdgcn_fmed3f(v.w, -clip, clip);
-                const uint32_t q = qz.code4(v);
                 sum = __builtin_amdgcn_sad_u8(q, 0u, sum);
                 dst[idx] = q ^ 0x80808080u;  // u - 128 as int8
             }
         }
-        if (nc == 0) {  // row finished
-            const int tot = wave_sum((int)sum);
-            if (lane == 0) b.rs_x[j][row] = tot - 128 * K;
+        if (c + 1 == chunks) {  // row finished
+            const int total = wave_sum((int)sum);
+            if (lane == 0) b.rs_x[j][row] = total - 128 * K;
             sum = 0;
         }
-        if (!more) break;
+    };
+    // (the last chunk stands behind the loop: with the next one's loads in a branch the compiler would wait for all loads where the paths meet)
+    while (true) {
+        // where the next chunk is
+        int nrow = row, nc = c + 1, nj = j;
+        if (nc == chunks) {
+            nc = 0;
+            if (++nrow == b.T[j]) {
+                nrow = 0;
+                if (++nj == b.n) break;
+            }
+            if (b.chunk_start[nj] + nrow * chunks >= to) break;  // (row 0 of another tensor is its chunk 0)
+        }
+        load(nxt, nj, nrow, nc);
+        __builtin_amdgcn_sched_barrier(0);
+        quantize();
         if (nj != j) {  // the next row belongs to another tensor
             j = nj;
-            K = b.K[j];
-            k4 = K >> 2;
-            chunks = (k4 + 255) >> 8;
-            clip = b.clip[j];
-            qz.set(clip, 255.0f);
+            of_tensor();
+            qz.set(b.clip[j], 255.0f);
         }
-        vrow = nrow;
+        row = nrow;
         c = nc;
 #pragma unroll
         for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
     }
+    quantize();
 }
 
 // ---- activations with one range for the whole tensor, c = max |X|: pass 1 reduces into a device float
@@ -606,8 +719,23 @@ __global__ __launch_bounds__(1024) void tensor_absmax_kernel(const float4 *__res
     }
 }
 
-// ---- activations with a range per token: c_t = max_j |X[t,j]|.  One wavefront per row; the row's first
-// 64*V float4 stay in registers between the max and the quantization, the rest (K > 256*V) is read again.
+// ---- activations with a range per token, c_t = max_j |X[t,j]|, where quantize_act_short_kernel and quantize_act_row_kernel do not serve.
+// One wavefront per row; the row's first 64*V float4 stay in registers between the max and the quantization, the rest (K > 256*V) is
+// read again.
+// (Reductions through the LDS: many short rows are bound by the vector instructions.  32768 x 256 11.3 us, with wave_max and wave_sum 11.6, in
+// quantize_act_short_kernel 12.0.)
+__device__ __forceinline__ float shuffled_max(float v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    return v;
+}
+__device__ __forceinline__ int shuffled_sum(int v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
 template <int V>
 __global__ __launch_bounds__(256) void quantize_act_dyn_kernel(const float *__restrict__ X, int T, int K,
                                                                int8_t *__restrict__ Xq, int32_t *__restrict__ rs_x,
@@ -629,7 +757,7 @@ __global__ __launch_bounds__(256) void quantize_act_dyn_kernel(const float *__re
             }
         }
         for (int idx = V * 64 + lane; idx < k4; idx += 64) mx = absmax4(src[idx], mx);
-        const float c = wave_max(mx);
+        const float c = shuffled_max(mx);
         Quantizer qz;
         qz.set(c, 255.0f);
         if (lane == 0) hx[row] = qz.half_step();
@@ -649,7 +777,7 @@ __global__ __launch_bounds__(256) void quantize_act_dyn_kernel(const float *__re
             sum = __builtin_amdgcn_sad_u8(q, 0u, sum);
             dst[idx] = q ^ 0x80808080u;
         }
-        const int total = wave_sum((int)sum);
+        const int total = shuffled_sum((int)sum);
         if (lane == 0) rs_x[row] = total - 128 * K;
     }
 }
@@ -690,14 +818,8 @@ __global__ __launch_bounds__(256) void quantize_act_row_kernel(const float *__re
     if (DYN && tid == 0) hx[row] = qz.half_step();
     uint32_t *dst = reinterpret_cast<uint32_t *>(Xq + (size_t)row * K);
     uint32_t sum = 0;
-    auto quantize = [&](int idx, float4 x) {
-        if constexpr (!DYN) {
-            x.x = __builtin_amdgcn_fmed3f(x.x, -clip, clip);
-            x.y = __builtin_amdgcn_fmed3f(x.y, -clip, clip);
-            x.z = __builtin_amdgcn_fmed3f(x.z, -clip, clip);
-            x.w = __builtin_amdgcn_fmed3f(x.w, -clip, clip);
-        }
-        const uint32_t q = qz.code4(x);
+    auto quantize = [&](int idx, const float4 &x) {
+        const uint32_t q = act_code4<!DYN>(qz, x);
         sum = __builtin_amdgcn_sad_u8(q, 0u, sum);
         dst[idx] = q ^ 0x80808080u;  // u - 128 as int8
     };
@@ -1222,15 +1344,14 @@ extern "C" qb_status qb_quantize_groupwise_batched(const qb_quant_job *jobs, int
     return launch_status();
 }
 
-// Which activation tensors have a workgroup per row instead of a wavefront.  Time / time with a wavefront, fixed range and range per
-// token:  K 1024 to 8192, up to 64 tokens .92 to .40;  768 and 1024, 512 tokens .95 and .90, 700 .99 and .94, 1001 1.03 and 1.0, 4096
-// 1.4;  448 and 256 .95 to 1.1 at any size;  1344, 1001 .87, 2048 .98, 4096 1.09;  1792, 2048 .97, 3000 1.04, 12288 .91;  2048 and
-// more .82 to .98 at 2000 to 32768 tokens (3072, 12288: 29.5 -> 27.7 and 33.0 -> 28.6 us; 4096, 32768: 133 -> 120, 136 -> 118), where
-// long runs of one row are easier on the memory than many rows at a time.
+// Which activation tensors have a workgroup per row instead of a wavefront: rows of 2048 values and more, where the chunks of a wavefront's walk
+// come one after the other at few rows, and where long runs of one row are easier on the memory than many rows at a time.  Time / time
+// with a wavefront that walks its rows in chunks, fixed range and range per token: up to 64 tokens .92 to .40, 2000 to 32768 .82 to .98 (3072, 12288:
+// 29.5 -> 27.7 and 33.0 -> 28.6 us; 4096, 32768: 133 -> 120, 136 -> 118).  Shorter rows fit a wavefront's registers: against a
+// workgroup per row 768, 8 to 640 tokens 2.32-2.65 -> 2.07-2.36 us, 1344, 8 to 2000 tokens 2.49-4.54 -> 2.32-4.30, 1792 .97-1.07.
 static bool act_row_shape(int64_t T, int64_t K)
 {
-    if (K >= 2048) return T <= (1 << 22);  // (a grid has less than 2^32 threads)
-    return T <= (K > 1024 ? 2048 : K > 512 ? 640 : 0);
+    return K >= 2048 && T <= (1 << 22);  // (a grid has less than 2^32 threads)
 }
 
 extern "C" qb_status qb_quantize_act(const float *X, int64_t T, int64_t K, float clip, int8_t *Xq, int32_t *rs_x,
@@ -1242,6 +1363,10 @@ extern "C" qb_status qb_quantize_act(const float *X, int64_t T, int64_t K, float
     if (act_row_shape(T, K)) {
         hipLaunchKernelGGL(quantize_act_row_kernel<false>, dim3((unsigned)T), dim3(256), 0, static_cast<hipStream_t>(stream), X, (int)K, clip, Xq, rs_x,
                            static_cast<float *>(nullptr));
+        return launch_status();
+    }
+    if (K < 2048) {
+        launch_act_short<0>(X, (int)T, (int)K, clip, nullptr, Xq, rs_x, nullptr, static_cast<hipStream_t>(stream));
         return launch_status();
     }
     // at most 8 workgroups per CU; fewer rows than that: one wavefront per row
@@ -1270,14 +1395,17 @@ extern "C" qb_status qb_quantize_act_batched(const qb_act_job *jobs, int n_jobs,
     for (int i0 = 0; i0 < n_jobs; i0 += QB_MAX_BATCH) {
         ActBatch b;
         b.n = n_jobs - i0 < QB_MAX_BATCH ? n_jobs - i0 : QB_MAX_BATCH;
-        b.row_start[0] = 0;
+        b.chunk_start[0] = 0;
+        int64_t waves = 0;
         for (int k = 0; k < b.n; ++k) {
             const qb_act_job &j = jobs[i0 + k];
-            b.X[k] = j.X; b.Xq[k] = j.Xq; b.rs_x[k] = j.rs_x; b.K[k] = (int)j.K; b.clip[k] = j.clip;
-            b.row_start[k + 1] = b.row_start[k] + (int)j.T;
+            b.X[k] = j.X; b.Xq[k] = j.Xq; b.rs_x[k] = j.rs_x; b.T[k] = (int)j.T; b.K[k] = (int)j.K; b.clip[k] = j.clip;
+            b.chunk_start[k + 1] = b.chunk_start[k] + (int)(j.T * ((j.K + 1023) / 1024));
+            waves += j.T;
         }
-        unsigned blocks = (unsigned)((b.row_start[b.n] + 3) / 4);
-        if (blocks > 2048) blocks = 2048;
+        const unsigned blocks = waves < 8192 ? (unsigned)((waves + 3) / 4) : 2048;
+        b.per = b.chunk_start[b.n] / (int)(blocks * 4);
+        b.more = b.chunk_start[b.n] % (int)(blocks * 4);
         hipLaunchKernelGGL(quantize_act_batched_kernel, dim3(blocks), dim3(256), 0, st, b);
     }
     return launch_status();
@@ -1295,6 +1423,10 @@ extern "C" qb_status qb_quantize_act_dyn_tensor(const float *X, int64_t T, int64
     hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, st, c_out, 1);
     hipLaunchKernelGGL(tensor_absmax_kernel, dim3(rblocks), dim3(1024), 0, st, reinterpret_cast<const float4 *>(X), n4,
                        c_out);
+    if (K < 2048) {
+        launch_act_short<1>(X, (int)T, (int)K, 0.0f, c_out, Xq, rs_x, hx_rows, st);
+        return launch_status();
+    }
     unsigned blocks = (unsigned)((T + 3) / 4);
     if (blocks > 2048) blocks = 2048;
     hipLaunchKernelGGL(quantize_act_kernel<true>, dim3(blocks), dim3(256), 0, st, X, (int)T, (int)K, 0.0f,
@@ -1314,8 +1446,15 @@ extern "C" qb_status qb_quantize_act_dyn(const float *X, int64_t T, int64_t K, i
     }
     unsigned blocks = (unsigned)((T + 3) / 4);
     if (blocks > 2048) blocks = 2048;
-    if (K <= 1024) hipLaunchKernelGGL(quantize_act_dyn_kernel<4>, dim3(blocks), dim3(256), 0, st, X, (int)T, (int)K, Xq, rs_x, hx_rows);
-    else hipLaunchKernelGGL(quantize_act_dyn_kernel<16>, dim3(blocks), dim3(256), 0, st, X, (int)T, (int)K, Xq, rs_x, hx_rows);
+    if (K <= 256 && T > 8192) {
+        hipLaunchKernelGGL(quantize_act_dyn_kernel<4>, dim3(blocks), dim3(256), 0, st, X, (int)T, (int)K, Xq, rs_x, hx_rows);
+        return launch_status();
+    }
+    if (K < 2048) {
+        launch_act_short<2>(X, (int)T, (int)K, 0.0f, nullptr, Xq, rs_x, hx_rows, st);
+        return launch_status();
+    }
+    hipLaunchKernelGGL(quantize_act_dyn_kernel<16>, dim3(blocks), dim3(256), 0, st, X, (int)T, (int)K, Xq, rs_x, hx_rows);
     return launch_status();
 }
 
