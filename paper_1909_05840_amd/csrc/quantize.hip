@@ -853,27 +853,31 @@ __global__ __launch_bounds__(256) void unpack_codes_kernel(const uint8_t *__rest
 }
 
 // ---- embedding table: groups are column blocks --------------------------------------------------------
-// pass 1: a workgroup takes a share of the rows (at least EMB_ROWS) of up to 1024 columns; each thread owns four columns, keeps eight
-// row loads in flight, and the workgroup combines per group in LDS before it touches m (zero-filled before;
-// max-abs values are non-negative floats, which order like their bit patterns).  Every workgroup ends in one atomic per
-// group, on few lines and one at a time: the rows are shared among 256 workgroups, one per CU, and no more (30522 x 1024,
-// 128 groups: 120 rows each 20.4 us = 6.1 TB/s, 64 rows 23.2, 32 rows 28.4, 8 rows 75; the whole quantizer against 32 rows each, 8
-// bits, 30522 rows: 256 columns 22.0 / 25.1 us, 448 27.6 / 39.5, 768 40.4 / 50.6; up to 8000 rows equal).
+// pass 1: a workgroup takes a share of the rows (at least EMB_ROWS) of up to 1024 columns; each of its four teams of 256 threads takes a
+// quarter of them, a thread four columns, eight row loads in flight (the last ones too: one after the other, the rows beyond a multiple of
+// eight cost a latency each), and the workgroup combines per group in LDS before it touches m (zero-filled before; max-abs values are
+// non-negative floats, which order like their bit patterns).  Every workgroup ends in one atomic per
+// group, on few lines and one at a time: the rows are shared among 256 workgroups, one per CU, and no more (with one team, 30522 x 1024,
+// 128 groups: 120 rows each 20.4 us = 6.1 TB/s, 64 rows 23.2, 32 rows 28.4, 8 rows 75).  The whole quantizer, 8 bits, with one team and
+// rows one by one / now: 512 x 256 13.4 / 8.5, 2000 x 448 14.6 / 9.7, 8000 x 768 18.7 / 16.3, 30522 x 256 22.2 / 19.9, 30522 x 1024 50.0 / 47.9.
 constexpr int EMB_ROWS = 32;
-__global__ __launch_bounds__(256) void embedding_absmax_kernel(const float *__restrict__ E, int64_t V, int d,
+__global__ __launch_bounds__(1024) void embedding_absmax_kernel(const float *__restrict__ E, int64_t V, int d,
                                                                int cols_per_group, float *__restrict__ m, int rows_per_wg)
 {
     __shared__ unsigned int gm[1024];
     const int d4 = d >> 2;
-    const int c4 = blockIdx.x * 256 + threadIdx.x;
+    const int team = threadIdx.x >> 8, c4 = blockIdx.x * 256 + (threadIdx.x & 255);
     const int col_lo = blockIdx.x * 1024;
     const int col_hi = (col_lo + 1024 < d) ? col_lo + 1024 : d;  // exclusive
     const int g_lo = col_lo / cols_per_group, g_n = (col_hi - 1) / cols_per_group - g_lo + 1;
-    for (int i = threadIdx.x; i < g_n; i += 256) gm[i] = 0u;
+    for (int i = threadIdx.x; i < g_n; i += 1024) gm[i] = 0u;
     __syncthreads();
     if (c4 < d4) {
+        // every team takes a quarter of the workgroup's rows
         const int64_t r0 = (int64_t)blockIdx.y * rows_per_wg;
-        const int nr = (int)((V - r0 < rows_per_wg) ? V - r0 : rows_per_wg);
+        const int all = (int)((V - r0 < rows_per_wg) ? V - r0 : rows_per_wg);
+        int r = all * team / 4;
+        const int nr = all * (team + 1) / 4;
         const float4 *src = reinterpret_cast<const float4 *>(E) + r0 * d4 + c4;
         float4 mx = make_float4(0.f, 0.f, 0.f, 0.f);
         auto take = [&](const float4 v) {
@@ -882,16 +886,14 @@ __global__ __launch_bounds__(256) void embedding_absmax_kernel(const float *__re
             mx.z = fmaxf(mx.z, fabsf(v.z));
             mx.w = fmaxf(mx.w, fabsf(v.w));
         };
-        int r = 0;
-        for (; r + 8 <= nr; r += 8) {
+        for (; r < nr; r += 8) {  // (past the last row that one again: its loads are on their way with the others)
             float4 v[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = src[(int64_t)(r + i) * d4];
+            for (int i = 0; i < 8; ++i) v[i] = src[(int64_t)min(r + i, nr - 1) * d4];
 #pragma unroll
             for (int i = 0; i < 8; ++i) take(v[i]);
         }
-        for (; r < nr; ++r) take(src[(int64_t)r * d4]);
-        const int c = c4 << 2;
+        const int c = c4 << 2;  // (a team without rows has zeros)
         const int g0 = c / cols_per_group - g_lo, g3 = (c + 3) / cols_per_group - g_lo;
         if (g0 == g3) {
             atomicMax(gm + g0, __float_as_uint(fmaxf(fmaxf(mx.x, mx.y), fmaxf(mx.z, mx.w))));
@@ -904,7 +906,7 @@ __global__ __launch_bounds__(256) void embedding_absmax_kernel(const float *__re
     }
     __syncthreads();
     unsigned int *mb = reinterpret_cast<unsigned int *>(m);
-    for (int i = threadIdx.x; i < g_n; i += 256)
+    for (int i = threadIdx.x; i < g_n; i += 1024)
         if (gm[i] != 0u) atomicMax(mb + g_lo + i, gm[i]);
 }
 
@@ -915,7 +917,7 @@ template <int BITS>
 __global__ __launch_bounds__(256) void embedding_quantize_kernel(const float *__restrict__ E, int64_t V, int d,
                                                                  int cols_per_group, int groups,
                                                                  const float *__restrict__ m, float *__restrict__ h,
-                                                                 uint8_t *__restrict__ codes)
+                                                                 uint8_t *__restrict__ codes, int rows_per_wg)
 {
     constexpr float Lf = (float)((1 << BITS) - 1);
     if (blockIdx.x == 0 && blockIdx.y == 0) {
@@ -935,26 +937,41 @@ __global__ __launch_bounds__(256) void embedding_quantize_kernel(const float *__
         if (i > 0 && g == (c + i - 1) / cols_per_group) qz[i] = qz[i - 1];
         else qz[i].set(m[g], Lf);
     }
-    const int64_t r0 = (int64_t)blockIdx.y * EMB_ROWS;
-    const int nr = (int)((V - r0 < EMB_ROWS) ? V - r0 : EMB_ROWS);
+    const int64_t r0 = (int64_t)blockIdx.y * rows_per_wg;
+    const int nr = (int)((V - r0 < rows_per_wg) ? V - r0 : rows_per_wg);
     const float4 *src = reinterpret_cast<const float4 *>(E) + r0 * d4 + c4;
+    auto load8 = [&](float4 (&v)[8], int r) {  // (past the last row that one again: its loads are on their way with the others)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = src[(int64_t)min(r + i, nr - 1) * d4];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the quick steps of Quantizer::code_f for the four columns, and one look at how close any product came to a rounding boundary
+    const bool fast = qz[0].fast && qz[1].fast && qz[2].fast && qz[3].fast;
     auto code4 = [&](const float4 v) {
-        uint32_t q = __builtin_amdgcn_cvt_pk_u8_f32(qz[0].code_f(v.x), 0, 0u);
-        q = __builtin_amdgcn_cvt_pk_u8_f32(qz[1].code_f(v.y), 1, q);
-        q = __builtin_amdgcn_cvt_pk_u8_f32(qz[2].code_f(v.z), 2, q);
-        return __builtin_amdgcn_cvt_pk_u8_f32(qz[3].code_f(v.w), 3, q);
+        const float w[4] = {v.x, v.y, v.z, v.w};
+        uint32_t q = 0;
+        float far = fast ? 0.0f : 1.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float t = __fmul_rn(__fadd_rn(w[i], qz[i].m), qz[i].rinv), r = rintf(t);
+            far = fmaxf(far, fabsf(t - r));
+            q = __builtin_amdgcn_cvt_pk_u8_f32(r, i, q);
+        }
+        if (__any(far > 0.4999f)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) q = __builtin_amdgcn_cvt_pk_u8_f32(rintf(__fdiv_rn(__fadd_rn(w[i], qz[i].m), qz[i].delta)), i, q);
+        }
+        return q;
     };
     if constexpr (BITS == 8) {
         uint32_t *dst = reinterpret_cast<uint32_t *>(codes) + r0 * d4 + c4;
-        int r = 0;
-        for (; r + 8 <= nr; r += 8) {
+        for (int r = 0; r < nr; r += 8) {
             float4 v[8];
+            load8(v, r);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = src[(int64_t)(r + i) * d4];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) __builtin_nontemporal_store(code4(v[i]), dst + (int64_t)(r + i) * d4);
+            for (int i = 0; i < 8; ++i)
+                if (r + i < nr) __builtin_nontemporal_store(code4(v[i]), dst + (int64_t)(r + i) * d4);
         }
-        for (; r < nr; ++r) dst[(int64_t)r * d4] = code4(src[(int64_t)r * d4]);
     } else {
         // four codes (one per byte of q) -> two bytes: low nibbles from bytes 0 and 2, high from bytes 1 and 3
         auto nib4 = [&](const float4 v) {
@@ -962,15 +979,13 @@ __global__ __launch_bounds__(256) void embedding_quantize_kernel(const float *__
             return (uint16_t)((q & 0xFu) | ((q >> 4) & 0xF0u) | ((q >> 8) & 0xF00u) | ((q >> 12) & 0xF000u));
         };
         uint16_t *dst = reinterpret_cast<uint16_t *>(codes) + r0 * d4 + c4;
-        int r = 0;
-        for (; r + 8 <= nr; r += 8) {
+        for (int r = 0; r < nr; r += 8) {
             float4 v[8];
+            load8(v, r);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = src[(int64_t)(r + i) * d4];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) dst[(int64_t)(r + i) * d4] = nib4(v[i]);
+            for (int i = 0; i < 8; ++i)
+                if (r + i < nr) dst[(int64_t)(r + i) * d4] = nib4(v[i]);
         }
-        for (; r < nr; ++r) dst[(int64_t)r * d4] = nib4(src[(int64_t)r * d4]);
     }
 }
 
@@ -1488,11 +1503,15 @@ extern "C" qb_status qb_embedding_quantize_bits(const float *E, int64_t V, int64
     const dim3 grid((unsigned)((d / 4 + 255) / 256), (unsigned)((V + EMB_ROWS - 1) / EMB_ROWS));
     hipLaunchKernelGGL(fill_zero_kernel, dim3((groups + 255) / 256), dim3(256), 0, st, m, groups);
     const int64_t rows = (V * grid.x + 255) / 256 > EMB_ROWS ? (V * grid.x + 255) / 256 : EMB_ROWS;
-    hipLaunchKernelGGL(embedding_absmax_kernel, dim3(grid.x, (unsigned)((V + rows - 1) / rows)), dim3(256), 0, st, E, V, (int)d, cpg, m, (int)rows);
+    hipLaunchKernelGGL(embedding_absmax_kernel, dim3(grid.x, (unsigned)((V + rows - 1) / rows)), dim3(1024), 0, st, E, V, (int)d, cpg, m, (int)rows);
+    // Rows of a workgroup of the second pass: eight, one round of loads, while the table is small, us of the whole call against 32 rows: 512 x 256
+    // 8.5 / 10.8, 2000 x 1024 10.2 / 12.8, 4000 x 768 11.5 / 13.7, 6000 x 768 14.4 / 15.0, 8000 x 768 18.5 / 16.3, 8000 x 1024 20.8 / 17.8.
+    const int qrows = V * grid.x <= 6144 ? 8 : EMB_ROWS;
+    const dim3 qgrid(grid.x, (unsigned)((V + qrows - 1) / qrows));
     if (bits == 8)
-        hipLaunchKernelGGL(embedding_quantize_kernel<8>, grid, dim3(256), 0, st, E, V, (int)d, cpg, groups, m, h, codes);
+        hipLaunchKernelGGL(embedding_quantize_kernel<8>, qgrid, dim3(256), 0, st, E, V, (int)d, cpg, groups, m, h, codes, qrows);
     else
-        hipLaunchKernelGGL(embedding_quantize_kernel<4>, grid, dim3(256), 0, st, E, V, (int)d, cpg, groups, m, h, codes);
+        hipLaunchKernelGGL(embedding_quantize_kernel<4>, qgrid, dim3(256), 0, st, E, V, (int)d, cpg, groups, m, h, codes, qrows);
     return launch_status();
 }
 

@@ -1,0 +1,22 @@
+"""The embedding quantizer's shares of rows: rounds of eight rows with a remainder, teams with few rows or none, both row counts of its second
+pass, a second workgroup of columns, against the oracle bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1909_05840_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bits", (4, 8))
+@pytest.mark.parametrize("V,d,groups", [(1, 64, 8), (7, 64, 4), (8, 1024, 128), (9, 1088, 17), (31, 320, 5), (33, 1088, 272), (65, 192, 192), (3072, 1088, 68),
+                                        (3073, 1088, 17), (6144, 64, 16), (6145, 64, 16), (8192, 128, 8), (8193, 128, 8)])
+def test_shares_of_rows(qb, V, d, groups, bits):
+    E = wl.embedding_table(V, d, seed=V + d)
+    E[V - 1, d - 1], E[V // 2, 0] = -0.75, 0.0
+    codes, h, m = qb.qb_embedding_quantize_bits(E.to("cuda:0"), bits, groups)
+    oc, oh, om = oracle.embedding_quantize(E.numpy(), groups, bits=bits)
+    assert (codes.cpu().numpy() == (oracle.pack(oc, bits) if bits < 8 else oc)).all()
+    assert (h.cpu().numpy().view(np.uint32) == oh.view(np.uint32)).all() and (m.cpu().numpy().view(np.uint32) == om.view(np.uint32)).all()
