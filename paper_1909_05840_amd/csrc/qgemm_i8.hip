@@ -8,7 +8,7 @@
 // u - 128 for 8 bits (e = +1); either way A4 equals sum_j (2x'+1)(2u-L), the integer that the
 // integer product of the codes, de-quantized once afterwards (App., last paragraph), has to produce.
 //
-// Five kernels, chosen by shape (launch_bits):
+// Six kernels, chosen by shape (launch_bits; for a batched call list_pays):
 //   qgemm_i8_kernel     register-staged: the token tile goes global -> registers -> LDS, the packed weights never
 //                       touch LDS (the packed layout stores, per 32-neuron block and 64-feature unit, one slot per
 //                       lane, so a wavefront fetches its B operand with one coalesced load).  Small tiles for
@@ -25,6 +25,8 @@
 //   qgemm_i8_split_kernel the smallest problems: the contraction sliced inside the workgroup, no LDS in the loop.
 //   qgemm_i8_duo_kernel the largest problems: 128x256 tiles on the 16x16x64 MFMA, two independent
 //                       workgroups per CU that multiply and write out in turn.
+//   qgemm_i8_list_kernel (qgemm_i8_list.hip) the same tiles and wavefronts for batched calls, all linears and widths in one
+//                       launch; also large single calls with K no multiple of 128, per-token scales or asymmetric ranges.
 // In all of them but the split kernel, whose operands go straight to registers, the token tile sits in LDS as dense
 // 128-byte rows whose 16-byte chunks are XOR-swizzled by the row number, so that the MFMA fragment reads are free of bank
 // conflicts; and in all of them the k-bit codes are expanded to int8 with a few byte-parallel shifts and masks in registers,

@@ -1362,11 +1362,14 @@ extern "C" qb_status qb_quantize_groupwise_batched(const qb_quant_job *jobs, int
 // Which activation tensors have a workgroup per row instead of a wavefront: rows of 2048 values and more, where the chunks of a wavefront's walk
 // come one after the other at few rows, and where long runs of one row are easier on the memory than many rows at a time.  Time / time
 // with a wavefront that walks its rows in chunks, fixed range and range per token: up to 64 tokens .92 to .40, 2000 to 32768 .82 to .98 (3072, 12288:
-// 29.5 -> 27.7 and 33.0 -> 28.6 us; 4096, 32768: 133 -> 120, 136 -> 118).  Shorter rows fit a wavefront's registers: against a
-// workgroup per row 768, 8 to 640 tokens 2.32-2.65 -> 2.07-2.36 us, 1344, 8 to 2000 tokens 2.49-4.54 -> 2.32-4.30, 1792 .97-1.07.
+// 29.5 -> 27.7 and 33.0 -> 28.6 us; 4096, 32768: 133 -> 120, 136 -> 118).  Shorter rows fit a wavefront's registers, and back to back that is
+// the faster way at any number of them (768, 8 to 640 tokens 2.32-2.65 -> 2.07-2.36 us, 1344, 8 to 2000 tokens 2.49-4.54 -> 2.32-4.30).  Between the
+// GEMMs of a layer it is not at few rows: a layer's forward with its quantizers 36.3 us at 390 tokens and 37.1 at 8 with a workgroup per row, 37.5 and
+// 37.8 with a wavefront.  4096 x 768 4.8 and 4.4 the other way.
 static bool act_row_shape(int64_t T, int64_t K)
 {
-    return K >= 2048 && T <= (1 << 22);  // (a grid has less than 2^32 threads)
+    if (K >= 2048) return T <= (1 << 22);  // (a grid has less than 2^32 threads)
+    return T <= (K > 1024 ? 2048 : K > 512 ? 640 : 0);
 }
 
 extern "C" qb_status qb_quantize_act(const float *X, int64_t T, int64_t K, float clip, int8_t *Xq, int32_t *rs_x,

@@ -22,7 +22,7 @@ def rows(T, K, special=True):
 
 
 # one to eight float4 a lane, full and with one lane in the last; a row a wavefront, two (the last wavefront with one) and three
-@pytest.mark.parametrize("T,K", [(1, 64), (3, 256), (8193, 320), (5, 512), (16385, 64), (7, 768), (8192, 832), (2, 1024), (9, 1088), (11, 1472), (6, 1792), (4, 1984)])
+@pytest.mark.parametrize("T,K", [(1, 64), (3, 256), (8193, 320), (5, 512), (16385, 64), (7, 768), (641, 768), (8192, 832), (642, 1024), (2049, 1088), (2051, 1472), (2050, 1792), (2049, 1984)])
 def test_rows_in_registers(qb, T, K):
     X = rows(T, K)
     Xq, rs = qb.qb_quantize_act(X.to(DEV), CLIP)
