@@ -7,8 +7,8 @@ matrix, weight bit-widths {2,3,4,8}, forward only, synthetic seeded data.
 
 One step = one pass of the forward hot path over that batch for every bit-width of the sweep:
   16 x quantize/pack of fp32 master weights (16 distinct matrices, one batched launch), 4 x 8-bit activation
-  quantize (one batched launch), 16 x int8 MFMA GEMM with the scale epilogue (one batched call: per bit-width one
-  persistent launch walks the 2304 tiles of QKV, attention-out, FFN-up and FFN-down: 4 launches).
+  quantize (one batched launch), 16 x int8 MFMA GEMM with the scale epilogue (one batched call: one launch
+  whose resident workgroups walk the tiles of all linears and widths).
 All inputs are resident in HBM before the timed region.  `value` = int8 GEMM operations of the
 step (2*T*N*K summed) divided by the wall time of the whole step, in TOPS.
 
@@ -135,7 +135,7 @@ def main():
             for j in gemm_jobs:
                 qb.qb_qlinear_fwd(j["Xq"], j["rs_x"], CLIP, j["packed"], j["h"], j["rs_w"], j["bits"], GROUPS, j["N"], Y=j["Y"])
         else:
-            qb.qb_qlinear_fwd_batched(gemm_jobs)   # one persistent launch per bit-width
+            qb.qb_qlinear_fwd_batched(gemm_jobs)   # one launch walks the linears of all widths
 
     if args.calibrate_copy:
         src = torch.ones(256 << 20, dtype=torch.uint8, device=dev)
@@ -147,7 +147,7 @@ def main():
     stages = [stage_quantize, stage_act, stage_gemm]
     n_quant = 1                            # kernels per stage
     n_act = 4 if args.single_launches else 1
-    n_gemm = 16 if args.single_launches else len(BITS_SWEEP)   # one persistent launch per bit-width walks all four linears
+    n_gemm = 16 if args.single_launches else 1
     stream = torch.cuda.Stream(device=dev)   # default priority
     use_graph = not args.no_graph
 
@@ -279,9 +279,8 @@ def main():
                    "tokens": T, "groups": GROUPS, "bits": list(BITS_SWEEP), "hip_graph": use_graph,
                    "steps_per_graph": args.steps_per_graph if use_graph else 0,
                    "gemm_launches_per_step": n_gemm},
-        "roofline": {"kernel": "qgemm_i8_ws_kernel (int8 MFMA GEMM + scale epilogue; per bit-width one persistent launch "
-                               "walks the 128x96 tiles of QKV, attention-out, FFN-up and FFN-down), "
-                               "%d launches per step" % n_gemm,
+        "roofline": {"kernel": ("qgemm_i8_list_kernel (int8 MFMA GEMM + scale epilogue; one launch walks the 128x256 tiles of all linears "
+                                "and widths), " if n_gemm == 1 else "int8 MFMA GEMM + scale epilogue, ") + "launches per step: %d" % n_gemm,
                      "bound": "mfma", "achieved": round(gemm_tops, 2), "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
                      "frac": round(gemm_tops / PEAK_INT8_TOPS, 4), "traffic": measured_traffic("qgemm_i8"),
                      "avg_launch_us": round(seg_ms[2] * 1e3 / n_gemm, 3),
