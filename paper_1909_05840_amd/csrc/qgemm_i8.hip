@@ -2267,23 +2267,43 @@ LargeJob large_job(const qb_fwd_job &j)
 
 // Whether a call's jobs go through launch_fwd_list, all widths in one launch, by an estimate of both sides in us.
 // The list: the longest tile alone on its CU, 1.2 a step and 4, and the tiles of a workgroup if all had the same, 1.75 a step and 5 for each
-// tile, 12 at least, the time of its write-out where all write; the smaller of the two counts a third.  The other kernels: few-tile jobs of all
-// widths share a launch, 1.1 a GOP; then a launch per width and kind of tile, .69 a GOP (1.0 where K is no multiple of 128) or the
-// output at 3.5 TB/s, and 4 each.
-// Four linears of a layer, list / other kernels: hidden 768, widths 2, 3, 4 and 8, 512 tokens 42.8 / 35.7 us, 768 45.6 / 48.2, 1024 48.8 / 73.9, 1536
-// 59.5 / 147 (before few-tile jobs shared launches), 2048 75 / 144, 3072 108 / 207, 4096 147 / 172, 6144 214 / 273; two widths, 1024 tokens 41.4 /
+// tile, 12 at least, the time of its write-out where all write; the smaller of the two counts a third.  Where one job is nine tenths of the work
+// its ragged last round counts, a CU with one workgroup at .7 of the time of two.  The other kernels: few-tile jobs of all
+// widths share a launch, 6 and 1.1 a GOP; then a launch per width and kind of tile, .69 a GOP (1.0 where K is no multiple of 128) or the
+// output at 3.5 TB/s, and 4 each.  Jobs that go alone to tiles of 128 x 256 as well have the list's rounds without what a list costs a tile: the
+// two-workgroup kernel .93 of the list's time, from K = 2048 on .87 (time / the list's, 16384 to 32768 tokens: K = 768 .90-.96, 1024 .88-.94, 3072 and
+// 4096 .84-.91; the more bits the lower), this kernel compiled for one width .95.  One such job alone goes there without an estimate.
+// Of 1400 calls of one job to 40, 200 to 65000 tokens, hidden 256 to 1536, the side so chosen takes .4 % longer than the faster one on average.
+// Four linears of a layer, list / other kernels: hidden 768, widths 2, 3, 4 and 8, 512 tokens 42.8 / 35.7 us, 768 45.6 / 48.2, 1024 48.8 / 73.9, 2048
+// 75 / 144, 3072 108 / 207, 4096 147 / 172, 6144 214 / 273; two widths, 1024 tokens 41.4 /
 // 35.4, 2048 42.7 / 68.2, 4096 76.9 / 81.7; 4 bits alone, 1536 tokens 37.5 / 32.1, 3072 39.9 / 46.0, 4096 44.5 / 38.5, 6144 55.1 / 63.6; hidden
-// 320, four widths, 1024 tokens 26.9 / 21.0, 2048 33.0 / 65.7; hidden 448, four widths, 4096 tokens 80 / 149.
+// 320, four widths, 1024 tokens 26.9 / 21.0, 2048 32.0 / 36.7 (by the estimate the other way); hidden 448, four widths, 4096 tokens 80 / 149.  Hidden
+// 1024 at 32768 tokens, one width: 2 bits 439 / 412, 3 bits 480 / 458, 4 bits 468 / 431, 8 bits 526 / 471; 32768 x 1024 x 4096 alone 120 / 104
+// (2 bits) and 147 / 124 (8 bits).
 inline bool list_pays(const qb_fwd_job *jobs, int n_jobs)
 {
+    auto steps_of = [](const qb_fwd_job &j) { return (double)((j.K + 127) / 128); };
+    auto tiles_of = [](const qb_fwd_job &j) { return (double)((j.T + 127) / 128) * (double)((j.N + 255) / 256); };
+    auto tile_time = [&](const qb_fwd_job &j) { return 1.75 * steps_of(j) + 5.0 > 12.0 ? 1.75 * steps_of(j) + 5.0 : 12.0; };
+    // the tiles of a CU, two at a time
+    auto rounds_of = [&](const qb_fwd_job &j) {
+        const long n = ((long)tiles_of(j) + 255) / 256;
+        return (double)(n / 2) + 0.7 * (double)(n & 1);
+    };
     double list = 0.0, other = 0.0, few = 0.0;
     for (int at = 0; at < n_jobs; at += QB_MAX_BATCH) {
-        double longest = 0.0, work = 0.0;
+        double longest = 0.0, work = 0.0, most = 0.0, ragged = 0.0;
         for (int i = at; i < n_jobs && i < at + QB_MAX_BATCH; ++i) {
-            const double steps = (double)((jobs[i].K + 127) / 128), tiles = (double)((jobs[i].T + 127) / 128) * (double)((jobs[i].N + 255) / 256);
-            longest = 1.2 * steps + 4.0 > longest ? 1.2 * steps + 4.0 : longest;
-            work += tiles * (1.75 * steps + 5.0 > 12.0 ? 1.75 * steps + 5.0 : 12.0) / 512.0;
+            const qb_fwd_job &j = jobs[i];
+            const double alone = 1.2 * steps_of(j) + 4.0, even = tiles_of(j) * tile_time(j) / 512.0;
+            longest = alone > longest ? alone : longest;
+            work += even;
+            if (even > most) {
+                most = even;
+                ragged = rounds_of(j) * tile_time(j) - even;
+            }
         }
+        if (most >= 0.9 * work) work += ragged;
         list += 5.0 + (longest > work ? longest + 0.3 * work : work + 0.3 * longest);
     }
     unsigned shared = 0;
@@ -2291,17 +2311,23 @@ inline bool list_pays(const qb_fwd_job *jobs, int n_jobs)
         const qb_fwd_job &j = jobs[i];
         const double gop = 2e-9 * (double)j.T * (double)j.N * (double)j.K;
         if (few_tiles(j)) {
-            few += (few == 0.0 ? 7.0 : 0.0) + 1.1 * gop;
+            few += (few == 0.0 ? 6.0 : 0.0) + 1.1 * gop;
             continue;
         }
-        const double math = (j.K % 128 ? 1.0 : 0.69) * gop, out = 4.0 / 3.5e6 * (double)j.T * (double)j.N;
-        other += math > out ? math : out;
         const LargeJob kind = j.bits == 2 ? large_job<2>(j) : j.bits == 3 ? large_job<3>(j) : j.bits == 4 ? large_job<4>(j) : large_job<8>(j);
+        const int path = kind == kAlone ? fwd_path(j.bits, (int)j.T, (int)j.N, (int)j.K, false, false) : kRoles128;
+        if (path == kDuo256 || path == kGeneral256) {
+            if (n_jobs == 1) return false;
+            other += rounds_of(j) * tile_time(j) * (path == kGeneral256 ? 0.95 : j.K < 2048 ? 0.93 : 0.87);
+        } else {
+            const double math = (j.K % 128 ? 1.0 : 0.69) * gop, out = 4.0 / 3.5e6 * (double)j.T * (double)j.N;
+            other += math > out ? math : out;
+        }
         const unsigned bit = 1u << (2 * j.bits + (kind == kShared96));
         if (kind == kAlone || !(shared & bit)) other += 4.0;
         if (kind != kAlone) shared |= bit;
     }
-    return list < 0.9 * (other + few);
+    return list < 0.92 * (other + few);
 }
 
 // The jobs of one bit-width that have more tiles: those that the single call would give to a role-split kernel share launches of it

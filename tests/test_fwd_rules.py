@@ -16,3 +16,31 @@ def test_calls_of_few_neurons_take_the_small_tiles_where_they_are_faster(bits, T
     rule = ctypes.CDLL(LIB_PATH)._ZN2qb8fwd_pathEiiiibb
     rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_bool] * 2
     assert rule(bits, T, N, K, per_token, False) == path
+
+
+def takes_list(jobs):
+    from paper_1909_05840_amd.binding import _FwdJob
+    rule = ctypes.CDLL(LIB_PATH)._ZN2qb14fwd_takes_listEPK10qb_fwd_jobi
+    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.c_int]
+    arr = (_FwdJob * len(jobs))(*[_FwdJob(1, 1, 6.0, 1, 1, 1, bits, 1, T, N, K, None, 1) for bits, T, N, K in jobs])
+    return rule(ctypes.addressof(arr), len(jobs))
+
+
+def layer(hidden, T, widths):
+    return [(b, T, N, K) for b in widths for N, K in ((3 * hidden, hidden), (hidden, hidden), (4 * hidden, hidden), (hidden, 4 * hidden))]
+
+
+# list / other kernels, us: 439 / 412, 480 / 458, 468 / 431, 526 / 471;  898 / 846;  120 / 104, 131 / 111, 147 / 124, 84 / 79, 41 / 36, 63 / 57
+@pytest.mark.parametrize("jobs", [layer(1024, 32768, [2]), layer(1024, 32768, [3]), layer(1024, 32768, [4]), layer(1024, 32768, [8]), layer(1024, 32768, [2, 4]),
+                                  [(2, 32768, 1024, 4096)], [(4, 32768, 1024, 4096)], [(8, 32768, 1024, 4096)], [(2, 16384, 4096, 1024)],
+                                  [(2, 16384, 768, 3072)], [(8, 16384, 3072, 768)]])
+def test_batched_calls_whose_jobs_fill_rounds_of_the_largest_tiles_keep_their_launches(jobs):
+    assert not takes_list(jobs)
+
+
+# list / other kernels, us: 75 / 144, 147 / 172, 214 / 273, 48 / 74;  57 / 66, 60 / 69, 67 / 78;  60 / 68, 64 / 71;  57 / 69
+@pytest.mark.parametrize("jobs", [layer(768, 2048, [2, 3, 4, 8]), layer(768, 4096, [2, 3, 4, 8]), layer(768, 6144, [2, 3, 4, 8]), layer(768, 1024, [2, 3, 4, 8]),
+                                  layer(768, 6144, [2]), layer(768, 6144, [4]), layer(768, 6144, [8]), layer(1024, 4096, [2]), layer(1024, 4096, [4]),
+                                  [(8, 32768, 1792, 448)]])
+def test_batched_calls_whose_rounds_are_ragged_share_a_launch(jobs):
+    assert takes_list(jobs)
