@@ -542,9 +542,14 @@ __device__ __forceinline__ int job_of(const SmallGroup &g)
     while (j + 1 < g.n && (int)blockIdx.x >= g.first_wg[j + 1]) ++j;
     return j;
 }
-__global__ __launch_bounds__(128, 3) void qgemm_i8_small_list_kernel(const SmallGroup g)
+// BITS, UNITS: the width and the units of 64 features per step of all jobs, or 0 where they differ.  A kernel for everything has the registers of its
+// largest body (138: three wavefronts to a SIMD, where one width has 76 to 125) and learns late which body it takes.  Linears of 768 x 768 at 2 bits,
+// us, it / the kernel of their width and step: 3 of 64 tokens 4.2 / 4.0, 12 of 385 tokens 10.4 / 8.6, 12 of 640 tokens 12.8 / 10.9; four layers of hidden
+// 1024, 385 tokens, it / the kernel of their width 39.6 / 36.7.
+template <int BITS, int UNITS>
+__global__ __launch_bounds__(128, BITS ? 4 : 3) void qgemm_i8_small_list_kernel(const SmallGroup g)
 {
-    __shared__ __align__(16) uint8_t lds[2 * stepped_lds(32, 4)];
+    __shared__ __align__(16) uint8_t lds[2 * stepped_lds(32, UNITS ? UNITS : 4)];
     const int j = job_of(g);
     const SmallProblem &p = g.p[j];
     const int local = blockIdx.x - g.first_wg[j];
@@ -554,19 +559,23 @@ __global__ __launch_bounds__(128, 3) void qgemm_i8_small_list_kernel(const Small
                                                                                         p.rows_per_group, p.hx, p.tiles_m, p.tiles_n, nullptr, nullptr, local, lds);
     };
     auto of_width = [&](auto units) {
-        switch (p.kind & 255) {
+        if constexpr (BITS != 0) run(std::integral_constant<int, BITS>(), units);
+        else switch (p.kind & 255) {
             case 2: run(std::integral_constant<int, 2>(), units); break;
             case 3: run(std::integral_constant<int, 3>(), units); break;
             case 4: run(std::integral_constant<int, 4>(), units); break;
             default: run(std::integral_constant<int, 8>(), units); break;
         }
     };
-    switch (p.kind >> 8) {
+    if constexpr (UNITS != 0) of_width(std::integral_constant<int, UNITS>());
+    else switch (p.kind >> 8) {
         case 1: of_width(std::integral_constant<int, 1>()); break;
         case 2: of_width(std::integral_constant<int, 2>()); break;
         default: of_width(std::integral_constant<int, 4>()); break;
     }
 }
+// BITS: the width of all jobs, or 0 where they differ (three linears of 768 x 768, 64 tokens, 4.2 us with 0, 4.0 with their width)
+template <int BITS>
 __global__ __launch_bounds__(512) void qgemm_i8_split_list_kernel(const SmallGroup g)
 {
     __shared__ __align__(16) int4 red[kSlicedLds];
@@ -574,7 +583,8 @@ __global__ __launch_bounds__(512) void qgemm_i8_split_list_kernel(const SmallGro
     const SmallProblem &p = g.p[j];
     const int local = blockIdx.x - g.first_wg[j];
     if (local >= p.tiles_m * p.tiles_n) return;  // (uniform over the workgroup)
-    switch (p.kind & 255) {
+    if constexpr (BITS != 0) qgemm_i8_split_body<BITS>(p, nullptr, nullptr, nullptr, local, red);
+    else switch (p.kind & 255) {
         case 2: qgemm_i8_split_body<2>(p, nullptr, nullptr, nullptr, local, red); break;
         case 3: qgemm_i8_split_body<3>(p, nullptr, nullptr, nullptr, local, red); break;
         case 4: qgemm_i8_split_body<4>(p, nullptr, nullptr, nullptr, local, red); break;
@@ -2191,56 +2201,95 @@ void launch_g96(const Group &g, hipStream_t st)
 
 bool few_tiles(const qb_fwd_job &j) { return (long)((j.T + 127) / 128) * ((j.N + 127) / 128) <= 160; }
 
-// The few-tile jobs of a call, whatever their widths, side by side in one launch
-void launch_few_tiles(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
+// The kernel for few-tile jobs that share a launch: with the contraction sliced or stepped; the width and (stepped) the units of 64 features per
+// step that all of them have, or 0
+struct FewTilesKernel {
+    bool sliced;
+    int bits, units;
+};
+FewTilesKernel few_tiles_kernel(const qb_fwd_job *const *jobs, int n_jobs)
 {
+    FewTilesKernel k{false, -1, -1};
     long tiles = 0, wgs = 0;
     int longest = 0;
-    bool sliced = false;
-    for (int i = 0; i < n_jobs; ++i)
-        if (few_tiles(jobs[i])) {
-            const long t = (long)((jobs[i].T + 31) / 32) * ((jobs[i].N + 63) / 64);
-            const int K = (int)jobs[i].K;
-            tiles += t;
-            wgs += (t + 7) & ~7l;
-            longest = stepped_steps(K) > longest ? stepped_steps(K) : longest;
-            sliced = sliced || sliced_pays((int)jobs[i].T, K);
-        }
-    sliced = sliced && tiles <= 256 && (wgs <= 256 || longest > 12);
-    SmallGroup g;
-    g.n = 0;
-    auto flush = [&]() {
-        if (g.n == 0) return;
-        if (sliced) hipLaunchKernelGGL(qgemm_i8_split_list_kernel, dim3(g.first_wg[g.n]), dim3(512), 0, st, g);
-        else hipLaunchKernelGGL(qgemm_i8_small_list_kernel, dim3(g.first_wg[g.n]), dim3(128), 0, st, g);
-        g.n = 0;
-    };
-    // (the longest contractions first: the launch ends when the last of them does)
-    int order[QB_MAX_BATCH], n = 0;
-    auto add = [&]() {
+    auto common = [](int &all, int one) { all = all == -1 || all == one ? one : 0; };
+    for (int i = 0; i < n_jobs; ++i) {
+        const long t = (long)((jobs[i]->T + 31) / 32) * ((jobs[i]->N + 63) / 64);
+        const int K = (int)jobs[i]->K;
+        tiles += t;
+        wgs += (t + 7) & ~7l;
+        longest = stepped_steps(K) > longest ? stepped_steps(K) : longest;
+        k.sliced = k.sliced || sliced_pays((int)jobs[i]->T, K);
+        common(k.bits, jobs[i]->bits);
+        common(k.units, stepped_units(K));
+    }
+    k.sliced = k.sliced && tiles <= 256 && (wgs <= 256 || longest > 12);
+    if (k.bits == 0 || k.sliced) k.units = 0;
+    return k;
+}
+
+template <int BITS>
+void launch_small_group(const SmallGroup &g, const FewTilesKernel &k, hipStream_t st)
+{
+    const dim3 grid(g.first_wg[g.n]);
+    if (k.sliced) hipLaunchKernelGGL((qgemm_i8_split_list_kernel<BITS>), grid, dim3(512), 0, st, g);
+    else {
+        auto *kernel = qgemm_i8_small_list_kernel<BITS, 0>;
+        if constexpr (BITS != 0)
+            if (k.units) kernel = k.units == 1 ? qgemm_i8_small_list_kernel<BITS, 1> : k.units == 2 ? qgemm_i8_small_list_kernel<BITS, 2> : qgemm_i8_small_list_kernel<BITS, 4>;
+        hipLaunchKernelGGL(kernel, grid, dim3(128), 0, st, g);
+    }
+}
+
+// The few-tile jobs of a call, whatever their widths, side by side in one launch; of more jobs than a launch holds those of a width together (64
+// jobs of four widths, us, in the order of the call / by width: hidden 320, 8 tokens 21.6 / 16.0; 1024, 200 tokens 140 / 113)
+template <typename Launch>
+void each_few_tiles_launch(const qb_fwd_job *jobs, int n_jobs, Launch launch)
+{
+    int total = 0;
+    for (int i = 0; i < n_jobs; ++i) total += few_tiles(jobs[i]);
+    const qb_fwd_job *order[QB_MAX_BATCH];
+    int n = 0;
+    constexpr int widths[] = {2, 3, 4, 8};
+    for (int w = 0; w < (total > QB_MAX_BATCH ? 4 : 1); ++w)
+        for (int i = 0; i < n_jobs; ++i)
+            if (few_tiles(jobs[i]) && (total <= QB_MAX_BATCH || jobs[i].bits == widths[w])) {
+                // (the longest contractions first: the launch ends when the last of them does)
+                int k = n++;
+                for (; k > 0 && order[k - 1]->K < jobs[i].K; --k) order[k] = order[k - 1];
+                order[k] = &jobs[i];
+                if (n == QB_MAX_BATCH) {
+                    launch(order, n);
+                    n = 0;
+                }
+            }
+    if (n) launch(order, n);
+}
+void launch_few_tiles(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
+{
+    each_few_tiles_launch(jobs, n_jobs, [st](const qb_fwd_job *const *order, int n) {
+        SmallGroup g;
+        g.n = n;
+        g.first_wg[0] = 0;
         for (int i = 0; i < n; ++i) {
-            const qb_fwd_job &j = jobs[order[i]];
-            if (g.n == 0) g.first_wg[0] = 0;
-            SmallProblem &sp = g.p[g.n];
+            const qb_fwd_job &j = *order[i];
+            SmallProblem &sp = g.p[i];
             sp.Xq = j.Xq; sp.rs_x = j.rs_x; sp.packed = static_cast<const uint8_t *>(j.packed); sp.h = j.h; sp.rs_w = j.rs_w;
             sp.bias = j.bias; sp.Y = j.Y; sp.T = (int)j.T; sp.N = (int)j.N; sp.K = (int)j.K;
             sp.rows_per_group = (int)(j.N / j.groups); sp.hx = j.clip / 255.0f;
             sp.tiles_m = (int)((j.T + 31) / 32); sp.tiles_n = (int)((j.N + 63) / 64);
             sp.kind = j.bits | stepped_units((int)j.K) << 8;
-            g.first_wg[g.n + 1] = g.first_wg[g.n] + ((sp.tiles_m * sp.tiles_n + 7) & ~7);
-            ++g.n;
+            g.first_wg[i + 1] = g.first_wg[i] + ((sp.tiles_m * sp.tiles_n + 7) & ~7);
         }
-        flush();
-        n = 0;
-    };
-    for (int i = 0; i < n_jobs; ++i)
-        if (few_tiles(jobs[i])) {
-            if (n == QB_MAX_BATCH) add();
-            int k = n++;
-            for (; k > 0 && jobs[order[k - 1]].K < jobs[i].K; --k) order[k] = order[k - 1];
-            order[k] = i;
+        const FewTilesKernel kernel = few_tiles_kernel(order, n);
+        switch (kernel.bits) {
+            case 2: launch_small_group<2>(g, kernel, st); break;
+            case 3: launch_small_group<3>(g, kernel, st); break;
+            case 4: launch_small_group<4>(g, kernel, st); break;
+            case 8: launch_small_group<8>(g, kernel, st); break;
+            default: launch_small_group<0>(g, kernel, st); break;
         }
-    add();
+    });
 }
 
 // The tile choice of the single call (launch_bits) for a job of more tiles: problems it gives to a role-split kernel share launches (one
@@ -2370,7 +2419,16 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
 
 namespace qb {
 bool fwd_takes_list(const qb_fwd_job *jobs, int n_jobs) { return list_pays(jobs, n_jobs); }
-
+// the kernels of a call's few-tile jobs, a launch each: bits | units << 8 | sliced << 16; the number of launches
+int fwd_few_tiles(const qb_fwd_job *jobs, int n_jobs, int *kernels)
+{
+    int launches = 0;
+    each_few_tiles_launch(jobs, n_jobs, [&](const qb_fwd_job *const *order, int n) {
+        const FewTilesKernel k = few_tiles_kernel(order, n);
+        kernels[launches++] = k.bits | k.units << 8 | (k.sliced ? 1 : 0) << 16;
+    });
+    return launches;
+}
 }  // namespace qb
 
 extern "C" qb_status qb_qlinear_fwd_batched(const qb_fwd_job *jobs, int n_jobs, void *stream)

@@ -44,3 +44,22 @@ def test_batched_calls_whose_jobs_fill_rounds_of_the_largest_tiles_keep_their_la
                                   [(8, 32768, 1792, 448)]])
 def test_batched_calls_whose_rounds_are_ragged_share_a_launch(jobs):
     assert takes_list(jobs)
+
+
+SLICED_BIT = 1 << 16
+
+
+# the kernel compiled for what all few-tile jobs of a launch have in common, bits | units of a step << 8; of more jobs than a launch holds those of a
+# width together
+@pytest.mark.parametrize("jobs,kernels", [([(8, 64, 768, 768)] * 3, [8 | SLICED_BIT]), (layer(768, 8, [4]), [4 | SLICED_BIT]), (layer(256, 8, [4, 8]), [SLICED_BIT]),
+                                          ([(2, 385, 768, 768)] * 12, [2 | 2 << 8]), ([(3, 700, 768, 320), (3, 64, 64, 64)], [3 | 1 << 8]),
+                                          ([(4, 640, 768, 3072)] * 2, [4 | 4 << 8]), (layer(768, 385, [8]), [8]), (layer(768, 128, [2, 3, 4, 8]), [0]),
+                                          (layer(320, 8, [2, 3, 4, 8]) * 4, [2 | SLICED_BIT, 3 | SLICED_BIT, 4 | SLICED_BIT, 8 | SLICED_BIT]),
+                                          (layer(768, 385, [2, 8]) * 3, [0, 8])])
+def test_few_tile_jobs_of_one_kind_take_the_kernel_of_their_kind(jobs, kernels):
+    from paper_1909_05840_amd.binding import _FwdJob
+    rule = ctypes.CDLL(LIB_PATH)._ZN2qb13fwd_few_tilesEPK10qb_fwd_jobiPi
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    arr = (_FwdJob * len(jobs))(*[_FwdJob(1, 1, 6.0, 1, 1, 1, bits, 1, T, N, K, None, 1) for bits, T, N, K in jobs])
+    got = (ctypes.c_int * len(jobs))()
+    assert rule(ctypes.addressof(arr), len(jobs), ctypes.addressof(got)) == len(kernels) and list(got)[:len(kernels)] == kernels

@@ -84,3 +84,30 @@ def test_single_calls_of_the_lists_kernel(bits, T, N, K, per_token, asym):
     for at in (0, 3000, T - 700):
         y, a4 = forward(slice(at, at + 700))
         assert torch.equal(A4[at:at + 700], a4) and torch.equal(Y[at:at + 700], y)
+
+
+# few-tile jobs of one width, (T, N, K): sliced; one, two and four units of 64 features a step; and different ones
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("shapes,kind", [([(33, 300, 512), (31, 128, 2048), (64, 65, 320)], 1 << 16), ([(700, 768, 320), (129, 500, 192), (1, 1, 64)], 1 << 8),
+                                         ([(700, 768, 768), (65, 130, 128), (1, 33, 1024)], 2 << 8), ([(700, 768, 2048), (33, 97, 4096)], 4 << 8),
+                                         ([(700, 768, 768), (33, 97, 2048), (64, 65, 192)], 0)])
+def test_few_tile_jobs_of_one_width_give_the_single_calls_results(bits, shapes, kind):
+    g = torch.Generator(device="cuda").manual_seed(bits)
+    jobs = [job(g, bits, T, N, K, 1, bias=i % 2 == 0) for i, (T, N, K) in enumerate(shapes)]
+    rule = ctypes.CDLL(binding.LIB_PATH)._ZN2qb13fwd_few_tilesEPK10qb_fwd_jobiPi
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    arr = (binding._FwdJob * len(jobs))(*[binding._FwdJob(1, 1, CLIP, 1, 1, 1, bits, 1, T, N, K, None, 1) for T, N, K in shapes])
+    kernel = ctypes.c_int()
+    assert rule(ctypes.addressof(arr), len(jobs), ctypes.addressof(kernel)) == 1 and kernel.value == bits | kind and not takes_list(jobs)
+    qb.qb_qlinear_fwd_batched(jobs)
+    for j in jobs:
+        assert torch.equal(j["Y"], qb.qb_qlinear_fwd(j["Xq"], j["rs_x"], CLIP, j["packed"], j["h"], j["rs_w"], bits, 1, j["N"], bias=j["bias"])), (j["Xq"].shape, j["N"])
+
+
+def test_more_few_tile_jobs_than_a_launch_holds():
+    g = torch.Generator(device="cuda").manual_seed(9)
+    jobs = [job(g, (2, 3, 4, 8)[i % 4], 8 + 31 * i, 200 + i, (320, 768, 2048)[i % 3], 1, bias=i % 2 == 0) for i in range(21)]
+    assert not takes_list(jobs)
+    qb.qb_qlinear_fwd_batched(jobs)
+    for j in jobs:
+        assert torch.equal(j["Y"], qb.qb_qlinear_fwd(j["Xq"], j["rs_x"], CLIP, j["packed"], j["h"], j["rs_w"], j["bits"], 1, j["N"], bias=j["bias"])), (j["Xq"].shape, j["N"])
