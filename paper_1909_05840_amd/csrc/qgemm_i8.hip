@@ -2419,6 +2419,12 @@ void launch_jobs_of_width(const qb_fwd_job *jobs, int n_jobs, hipStream_t st)
 
 namespace qb {
 bool fwd_takes_list(const qb_fwd_job *jobs, int n_jobs) { return list_pays(jobs, n_jobs); }
+// where a job goes that is not in a list: with the few-tile ones (-1), alone (0), to the shared launch of 128 x 96 (1) or of 128 x 128 tiles (2)
+int fwd_job_kind(const qb_fwd_job *j)
+{
+    if (few_tiles(*j)) return -1;
+    return j->bits == 2 ? large_job<2>(*j) : j->bits == 3 ? large_job<3>(*j) : j->bits == 4 ? large_job<4>(*j) : large_job<8>(*j);
+}
 // the kernels of a call's few-tile jobs, a launch each: bits | units << 8 | sliced << 16; the number of launches
 int fwd_few_tiles(const qb_fwd_job *jobs, int n_jobs, int *kernels)
 {

@@ -86,6 +86,22 @@ def test_single_calls_of_the_lists_kernel(bits, T, N, K, per_token, asym):
         assert torch.equal(A4[at:at + 700], a4) and torch.equal(Y[at:at + 700], y)
 
 
+# Jobs that share launches of 128 x 96 and of 128 x 128 tiles, three problems in each, in a call that is no list: ragged last tiles in
+# both directions, odd N, one step to sixteen
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+def test_shared_launches_of_one_width_give_the_single_calls_results(bits):
+    shapes = [(4001, 767, 768, 1), (4090, 1001, 256, 2), (3500, 769, 768, 1), (3000, 1100, 256, 2), (2100, 2304, 128, 1), (3900, 770, 2048, 2)]
+    g = torch.Generator(device="cuda").manual_seed(10 + bits)
+    jobs = [job(g, bits, T, N, K, 1 if N % 2 else N // 2, bias=i % 2 == 0) for i, (T, N, K, _) in enumerate(shapes)]
+    kind = ctypes.CDLL(binding.LIB_PATH)._ZN2qb12fwd_job_kindEPK10qb_fwd_job
+    assert not takes_list(jobs)
+    assert [kind(ctypes.byref(binding._FwdJob(1, 1, CLIP, 1, 1, 1, bits, 1, T, N, K, None, 1))) for T, N, K, _ in shapes] == [s[3] for s in shapes]
+    qb.qb_qlinear_fwd_batched(jobs)
+    for j in jobs:
+        want = qb.qb_qlinear_fwd(j["Xq"], j["rs_x"], CLIP, j["packed"], j["h"], j["rs_w"], bits, j["groups"], j["N"], bias=j["bias"])
+        assert torch.equal(j["Y"], want), (j["Xq"].shape, j["N"])
+
+
 # few-tile jobs of one width, (T, N, K): sliced; one, two and four units of 64 features a step; and different ones
 @pytest.mark.parametrize("bits", [2, 3, 4, 8])
 @pytest.mark.parametrize("shapes,kind", [([(33, 300, 512), (31, 128, 2048), (64, 65, 320)], 1 << 16), ([(700, 768, 320), (129, 500, 192), (1, 1, 64)], 1 << 8),

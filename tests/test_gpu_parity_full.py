@@ -79,9 +79,10 @@ def test_forward_whole_output_of_timed_kernels(qb, bits, shape):
 
 
 def test_forward_batched_matches_single_calls(qb):
-    """The benchmark's 16 jobs (4 linears x 4 bit-widths at 4096 tokens) plus jobs that do not share launches (few
-    tiles, K not a multiple of 128, N not a multiple of 96, a very large one) in one call: every Y bit for bit the Y
-    of the single call, and one job of every bit-width element by element against the oracle."""
+    """The benchmark's 16 jobs (4 linears x 4 bit-widths at 4096 tokens) plus jobs of other sizes (few tiles, K not a
+    multiple of 128, N not a multiple of 96, a very large one) in one call, which the lists' kernel serves in two
+    launches: every Y bit for bit the Y of the single call, and one job of every bit-width element by element against
+    the oracle."""
     jobs, singles, checks = [], [], []
     shapes = [(4096, N, K) for (_, N, K) in wl.BERT_BASE_LINEARS]
     extra = [(128, 768, 3072, 4), (1000, 130, 192, 3), (2049, 1530, 256, 2), (4096, 1024, 1024, 8), (300, 96, 128, 4),
@@ -516,16 +517,15 @@ def test_forward_asymmetric_ranges_with_per_token_scales(qb, bits, shape):
 
 
 def test_forward_batched_few_token_jobs_share_launches(qb):
-    """The inference regime: few-token problems of a batched call go through shared launches (one per bit-width and
-    kernel).  At 4 bits 21 jobs with more tiles than CUs: the stepped kernel in its three step widths (K = 192, 768, 3072);
-    at the other widths the seven jobs take the sliced kernel.  Ragged T and N, with and without bias: every Y element by
-    element against the oracle, pre-filled outputs fully written.  (More jobs than a launch takes:
-    test_forward_batched_few_tile_kernels.)"""
+    """The inference regime: few-token problems of a batched call go through shared launches of 16 jobs, in the order of
+    their widths.  Here 42 jobs: a launch of different widths and one of 4 bits alone, with more tiles than CUs, take the
+    stepped kernel in its three step widths (K = 192, 768, 3072), the third, of 4 and 8 bits, the sliced kernel.  Ragged T
+    and N, with and without bias: every Y element by element against the oracle, pre-filled outputs fully written."""
     jobs, refs = [], []
     shapes = [(1, 768, 768), (8, 2304, 768), (64, 3072, 768), (128, 768, 3072), (33, 130, 192), (100, 96, 3072), (5, 64, 64)]
     case = 0
     for bits in BITS:
-        for rep in range(3 if bits == 4 else 1):        # 21 jobs and 621 tiles at 4 bits, 7 and 207 at the others
+        for rep in range(3 if bits == 4 else 1):        # 21 jobs at 4 bits, 7 at the others
             for (T, N, K) in shapes:
                 groups = G if N % G == 0 else (N // 2 if N % 2 == 0 else 1)
                 d = quantized_inputs(qb, N, K, T, bits, seed=31 * N + K + T + bits + 7 * rep, groups=groups)
