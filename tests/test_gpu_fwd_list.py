@@ -57,31 +57,39 @@ def test_a_list_of_more_jobs_than_a_launch_holds():
         assert torch.equal(j["Y"], qb.qb_qlinear_fwd(j["Xq"], j["rs_x"], CLIP, j["packed"], j["h"], j["rs_w"], j["bits"], j["groups"], j["N"]))
 
 
-# single calls whose rule names the lists' kernel, against their first tokens, which take another one
+# single calls whose rule names the lists' kernel, against slices of their tokens, which take another one.  Groups: one; of 16 neurons; of 17, 89 and 113, which
+# begin inside a wavefront's 64 neurons and end in the next one's or in the next tile
 @pytest.mark.parametrize("bits", [2, 3, 4, 8])
-@pytest.mark.parametrize("T,N,K,per_token,asym", [(7680, 2048, 512, True, True), (8100, 1921, 768, True, False), (7600, 2048, 640, False, True),
-                                                  (8190, 2048, 704, False, False), (7640, 2047, 832, True, True)])
-def test_single_calls_of_the_lists_kernel(bits, T, N, K, per_token, asym):
+@pytest.mark.parametrize("T,N,K,per_token,asym,groups", [(7680, 2048, 512, True, True, 1), (8100, 1921, 768, True, False, 1), (7600, 2048, 640, False, True, 1),
+                                                         (8190, 2048, 704, False, False, 1), (7640, 2047, 832, True, True, 1),
+                                                         (7680, 2048, 512, True, True, 128), (7600, 2048, 640, False, True, 128), (8190, 2048, 704, False, False, 128),
+                                                         (8100, 1921, 768, True, False, 113), (8100, 1921, 768, False, True, 17), (7640, 2047, 832, True, True, 23)])
+def test_single_calls_of_the_lists_kernel(bits, T, N, K, per_token, asym, groups):
     rule = ctypes.CDLL(binding.LIB_PATH)._ZN2qb8fwd_pathEiiiibb
     rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_bool] * 2
     assert rule(bits, T, N, K, per_token, asym) == GENERAL256 and rule(bits, 700, N, K, per_token, asym) != GENERAL256
     g = torch.Generator(device="cuda").manual_seed(bits)
     X = torch.randn(T, K, generator=g, device="cuda")
-    W = torch.randn(N, K, generator=g, device="cuda") * 0.04 + 0.01
+    # a level and a spread of its own for every group (37 and 11 have no factor in common with a group count above)
+    of = torch.arange(N, device="cuda") // (N // groups)
+    W = (torch.randn(N, K, generator=g, device="cuda") * 0.04 * (1 + (11 * of % groups) / groups)[:, None] + (37 * of % groups * 0.01 + 0.01)[:, None]).contiguous()
     bias = torch.randn(N, generator=g, device="cuda")
     if asym:
-        packed, d, q0, rs_w = qb.qb_quantize_groupwise_asym(W, bits, 1)
+        packed, d, q0, rs_w = qb.qb_quantize_groupwise_asym(W, bits, groups)
+        assert len(set(q0.tolist())) == groups
     else:
-        packed, d, _, rs_w = qb.qb_quantize_groupwise(W, bits, 1)
+        packed, d, _, rs_w = qb.qb_quantize_groupwise(W, bits, groups)
+    assert len(set(d.tolist())) == groups
     Xq, rs_x, *hx = qb.qb_quantize_act_dyn(X) if per_token else qb.qb_quantize_act(X, CLIP)
 
     def forward(sl):
-        args = [Xq[sl], rs_x[sl]] + ([hx[0][sl]] if per_token else [CLIP]) + [packed, d] + ([q0] if asym else []) + [rs_w, bits, 1, N]
+        args = [Xq[sl], rs_x[sl]] + ([hx[0][sl]] if per_token else [CLIP]) + [packed, d] + ([q0] if asym else []) + [rs_w, bits, groups, N]
         call = {(True, True): qb.qb_qlinear_fwd_asym_dyn, (True, False): qb.qb_qlinear_fwd_dyn, (False, True): qb.qb_qlinear_fwd_asym, (False, False): qb.qb_qlinear_fwd}
         return call[per_token, asym](*args, bias=bias, want_a4=True)
 
     Y, A4 = forward(slice(0, T))
-    for at in (0, 3000, T - 700):
+    for at in range(0, T, 700):
+        at = min(at, T - 700)
         y, a4 = forward(slice(at, at + 700))
         assert torch.equal(A4[at:at + 700], a4) and torch.equal(Y[at:at + 700], y)
 
