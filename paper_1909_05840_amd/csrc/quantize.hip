@@ -598,10 +598,19 @@ void launch_act_short(const float *X, int T, int K, float clip, const float *cli
 // wavefront takes a run of rows with the same number of chunks of 256 float4 (to a row), the next chunk (possibly of another tensor) in
 // flight while the current one is quantized.  Four tensors of 4096 tokens, three of 768 values and one of 3072, 110 MB: dealt by the row some
 // wavefronts had two chunks and some four, 24.6 us; now all have three, 22.5.  4096 x 256 12.6 -> 10.4, 500 x 768 8.0 -> 6.5.
+// Two kinds of calls have their rows dealt one by one (BY_ROWS), wavefront after wavefront, instead.
+// Long sequences, ACT_LONG values to a wavefront and more (157 MB read and written): the wavefronts then read side by side, where runs are thousands
+// of places in memory at a time, and a chunk more or less no longer shows.  Runs / rows, us: 62 to 128 MB 11.8-21.2 / 12.8-22.2, 149 to 250 MB .94-1.02 of
+// each other, 358 MB 74 / 70, 456 MB 96 / 91, 1033 MB 216 / 203.
+// Short ones, of no more rows than wavefronts, all of one chunk or less than ACT_FEW values in them: a wavefront has one row, and the longest row
+// decides, where a run may end with one.  2 x 1024 and 2 x 4096 6.8 / 5.4, three of 17 x 768 and 17 x 3072 5.2 / 4.7, 1000 x 768 four times 3.9 / 3.6; but 1000
+// x 1024 and 1000 x 4096, 26 MB, 6.5 / 7.5, where few of the rows are long ones and their wavefronts neighbours.
+constexpr int ACT_LONG = 3840, ACT_FEW = 3 << 20;
 struct ActBatch {
     int n;
     int chunk_start[QB_MAX_BATCH + 1];  // first chunk of tensor i in the sequence; [n] = number of chunks (2^31 of them would be 8 TB, but for
                                         // rows of one chunk, of which a call has at most 2^30)
+    int row_start[QB_MAX_BATCH + 1];    // first row of it
     int per, more;                      // a wavefront's chunks; the first `more` wavefronts have one more
     const float *X[QB_MAX_BATCH];
     int8_t *Xq[QB_MAX_BATCH];
@@ -609,28 +618,38 @@ struct ActBatch {
     int T[QB_MAX_BATCH], K[QB_MAX_BATCH];
     float clip[QB_MAX_BATCH];
 };
+template <bool BY_ROWS>
 __global__ __launch_bounds__(256) void quantize_act_batched_kernel(const ActBatch b)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, nwaves = gridDim.x * 4;
     const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int from = wave * b.per + (wave < b.more ? wave : b.more), to = from + b.per + (wave < b.more ? 1 : 0);
-    // the first row that begins at `from` or behind it
-    int j = 0;
-    while (j + 1 < b.n && from >= b.chunk_start[j + 1]) ++j;
-    int K = b.K[j], k4 = K >> 2, chunks = (k4 + 255) >> 8;
-    int row = from - b.chunk_start[j], c = 0;
-    if (chunks > 1) row = (int)((uint32_t)(row + chunks - 1) / (uint32_t)chunks);
+    int j = 0, row, K, k4, chunks, c = 0;
     auto of_tensor = [&]() {
         K = b.K[j];
         k4 = K >> 2;
         chunks = (k4 + 255) >> 8;
     };
-    if (row == b.T[j]) {
-        if (++j == b.n) return;
+    // runs: the chunks from `from` up to `to`; by rows: the next row's number in the sequence
+    const int from = wave * b.per + (wave < b.more ? wave : b.more), to = from + b.per + (wave < b.more ? 1 : 0);
+    int next = wave;
+    if constexpr (BY_ROWS) {
+        if (wave >= b.row_start[b.n]) return;
+        while (wave >= b.row_start[j + 1]) ++j;
+        row = wave - b.row_start[j];
         of_tensor();
-        row = 0;
+    } else {
+        // the first row that begins at `from` or behind it
+        while (j + 1 < b.n && from >= b.chunk_start[j + 1]) ++j;
+        of_tensor();
+        row = from - b.chunk_start[j];
+        if (chunks > 1) row = (int)((uint32_t)(row + chunks - 1) / (uint32_t)chunks);
+        if (row == b.T[j]) {
+            if (++j == b.n) return;
+            of_tensor();
+            row = 0;
+        }
+        if (b.chunk_start[j] + row * chunks >= to) return;
     }
-    if (b.chunk_start[j] + row * chunks >= to) return;
     float4 cur[4], nxt[4];
     auto load = [&](float4 (&v)[4], int jj, int r, int cc) {
         const int kk4 = b.K[jj] >> 2;
@@ -669,11 +688,18 @@ __global__ __launch_bounds__(256) void quantize_act_batched_kernel(const ActBatc
         int nrow = row, nc = c + 1, nj = j;
         if (nc == chunks) {
             nc = 0;
-            if (++nrow == b.T[j]) {
-                nrow = 0;
-                if (++nj == b.n) break;
+            if constexpr (BY_ROWS) {
+                next += nwaves;
+                if (next >= b.row_start[b.n]) break;
+                while (next >= b.row_start[nj + 1]) ++nj;
+                nrow = next - b.row_start[nj];
+            } else {
+                if (++nrow == b.T[j]) {
+                    nrow = 0;
+                    if (++nj == b.n) break;
+                }
+                if (b.chunk_start[nj] + nrow * chunks >= to) break;  // (row 0 of another tensor is its chunk 0)
             }
-            if (b.chunk_start[nj] + nrow * chunks >= to) break;  // (row 0 of another tensor is its chunk 0)
         }
         load(nxt, nj, nrow, nc);
         __builtin_amdgcn_sched_barrier(0);
@@ -1413,18 +1439,22 @@ extern "C" qb_status qb_quantize_act_batched(const qb_act_job *jobs, int n_jobs,
     for (int i0 = 0; i0 < n_jobs; i0 += QB_MAX_BATCH) {
         ActBatch b;
         b.n = n_jobs - i0 < QB_MAX_BATCH ? n_jobs - i0 : QB_MAX_BATCH;
-        b.chunk_start[0] = 0;
-        int64_t waves = 0;
+        b.chunk_start[0] = b.row_start[0] = 0;
+        int64_t values = 0;
         for (int k = 0; k < b.n; ++k) {
             const qb_act_job &j = jobs[i0 + k];
             b.X[k] = j.X; b.Xq[k] = j.Xq; b.rs_x[k] = j.rs_x; b.T[k] = (int)j.T; b.K[k] = (int)j.K; b.clip[k] = j.clip;
             b.chunk_start[k + 1] = b.chunk_start[k] + (int)(j.T * ((j.K + 1023) / 1024));
-            waves += j.T;
+            b.row_start[k + 1] = b.row_start[k] + (int)j.T;
+            values += j.T * j.K;
         }
-        const unsigned blocks = waves < 8192 ? (unsigned)((waves + 3) / 4) : 2048;
+        const int sum = b.row_start[b.n];
+        const unsigned blocks = sum < 8192 ? (unsigned)((sum + 3) / 4) : 2048;
         b.per = b.chunk_start[b.n] / (int)(blocks * 4);
         b.more = b.chunk_start[b.n] % (int)(blocks * 4);
-        hipLaunchKernelGGL(quantize_act_batched_kernel, dim3(blocks), dim3(256), 0, st, b);
+        const bool by_rows = values >= (int64_t)ACT_LONG * 4 * blocks || (sum <= 8192 && (b.chunk_start[b.n] == sum || values < ACT_FEW));
+        auto *kernel = by_rows ? quantize_act_batched_kernel<true> : quantize_act_batched_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, b);
     }
     return launch_status();
 }

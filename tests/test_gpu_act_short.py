@@ -49,3 +49,17 @@ def test_batched_runs_of_rows(qb, shapes):
     for i, (X, (Xq, rs)) in enumerate(zip(Xs, got)):
         oq, ors = oracle.quantize_act(X.numpy(), CLIP + i)
         assert (Xq.cpu().numpy() == oq).all() and (rs.cpu().numpy() == ors).all(), shapes[i]
+
+
+# tensors whose rows go round the wavefronts one by one: all of one chunk, one row to a wavefront; few values in short rows and long ones; more rows than
+# wavefronts and 3840 values and more to each, the last rows of a tensor and the first of the next one in the same round
+@pytest.mark.parametrize("shapes", [[(7, 768), (8000, 64), (185, 1024)], [(5, 32768), (2, 64), (1, 1088)], [(300, 64), (41, 3072), (7, 1088)],
+                                    [(13501, 1088), (1, 3072), (21001, 832), (1, 320)]])
+def test_batched_rows_in_turn(qb, shapes):
+    n, values = sum(T for T, _ in shapes), sum(T * K for T, K in shapes)
+    assert n <= 8192 and (max(K for _, K in shapes) <= 1024 or values < 3 << 20) or n > 8192 and values >= 3840 * 8192
+    Xs = [rows(T, K, special=K > 64) for T, K in shapes]
+    got = qb.qb_quantize_act_batched([{"X": X.to(DEV), "clip": CLIP + i} for i, X in enumerate(Xs)])
+    for i, (X, (Xq, rs)) in enumerate(zip(Xs, got)):
+        oq, ors = oracle.quantize_act(X.numpy(), CLIP + i)
+        assert (Xq.cpu().numpy() == oq).all() and (rs.cpu().numpy() == ors).all(), shapes[i]
