@@ -879,15 +879,18 @@ __global__ __launch_bounds__(256) void unpack_codes_kernel(const uint8_t *__rest
 }
 
 // ---- embedding table: groups are column blocks --------------------------------------------------------
-// pass 1: a workgroup takes a share of the rows (at least EMB_ROWS) of up to 1024 columns; each of its four teams of 256 threads takes a
+// pass 1: a workgroup takes a share of the rows (at least EMB_ROWS) of up to 1024 columns; each of its four teams of 256 threads (or one) takes a
 // quarter of them, a thread four columns, eight row loads in flight (the last ones too: one after the other, the rows beyond a multiple of
 // eight cost a latency each), and the workgroup combines per group in LDS before it touches m (zero-filled before; max-abs values are
 // non-negative floats, which order like their bit patterns).  Every workgroup ends in one atomic per
 // group, on few lines and one at a time: the rows are shared among 256 workgroups, one per CU, and no more (with one team, 30522 x 1024,
 // 128 groups: 120 rows each 20.4 us = 6.1 TB/s, 64 rows 23.2, 32 rows 28.4, 8 rows 75).  The whole quantizer, 8 bits, with one team and
 // rows one by one / now: 512 x 256 13.4 / 8.5, 2000 x 448 14.6 / 9.7, 8000 x 768 18.7 / 16.3, 30522 x 256 22.2 / 19.9, 30522 x 1024 50.0 / 47.9.
-constexpr int EMB_ROWS = 32;
-__global__ __launch_bounds__(1024) void embedding_absmax_kernel(const float *__restrict__ E, int64_t V, int d,
+// A table of a few rows (token types) has no work for four teams, and a workgroup of one starts and ends sooner: up to EMB_ONE_TEAM rows, one team /
+// four, 768 columns, 128 groups: 2 rows 5.9 / 6.45, 8 rows 6.4 / 7.2, 24 rows 7.0 / 7.2.
+constexpr int EMB_ROWS = 32, EMB_ONE_TEAM = 24;
+template <int TEAMS>
+__global__ __launch_bounds__(256 * TEAMS) void embedding_absmax_kernel(const float *__restrict__ E, int64_t V, int d,
                                                                int cols_per_group, float *__restrict__ m, int rows_per_wg)
 {
     __shared__ unsigned int gm[1024];
@@ -896,14 +899,14 @@ __global__ __launch_bounds__(1024) void embedding_absmax_kernel(const float *__r
     const int col_lo = blockIdx.x * 1024;
     const int col_hi = (col_lo + 1024 < d) ? col_lo + 1024 : d;  // exclusive
     const int g_lo = col_lo / cols_per_group, g_n = (col_hi - 1) / cols_per_group - g_lo + 1;
-    for (int i = threadIdx.x; i < g_n; i += 1024) gm[i] = 0u;
+    for (int i = threadIdx.x; i < g_n; i += 256 * TEAMS) gm[i] = 0u;
     __syncthreads();
     if (c4 < d4) {
-        // every team takes a quarter of the workgroup's rows
+        // every team takes its part of the workgroup's rows
         const int64_t r0 = (int64_t)blockIdx.y * rows_per_wg;
         const int all = (int)((V - r0 < rows_per_wg) ? V - r0 : rows_per_wg);
-        int r = all * team / 4;
-        const int nr = all * (team + 1) / 4;
+        int r = all * team / TEAMS;
+        const int nr = all * (team + 1) / TEAMS;
         const float4 *src = reinterpret_cast<const float4 *>(E) + r0 * d4 + c4;
         float4 mx = make_float4(0.f, 0.f, 0.f, 0.f);
         auto take = [&](const float4 v) {
@@ -932,7 +935,7 @@ __global__ __launch_bounds__(1024) void embedding_absmax_kernel(const float *__r
     }
     __syncthreads();
     unsigned int *mb = reinterpret_cast<unsigned int *>(m);
-    for (int i = threadIdx.x; i < g_n; i += 1024)
+    for (int i = threadIdx.x; i < g_n; i += 256 * TEAMS)
         if (gm[i] != 0u) atomicMax(mb + g_lo + i, gm[i]);
 }
 
@@ -1536,7 +1539,9 @@ extern "C" qb_status qb_embedding_quantize_bits(const float *E, int64_t V, int64
     const dim3 grid((unsigned)((d / 4 + 255) / 256), (unsigned)((V + EMB_ROWS - 1) / EMB_ROWS));
     hipLaunchKernelGGL(fill_zero_kernel, dim3((groups + 255) / 256), dim3(256), 0, st, m, groups);
     const int64_t rows = (V * grid.x + 255) / 256 > EMB_ROWS ? (V * grid.x + 255) / 256 : EMB_ROWS;
-    hipLaunchKernelGGL(embedding_absmax_kernel, dim3(grid.x, (unsigned)((V + rows - 1) / rows)), dim3(1024), 0, st, E, V, (int)d, cpg, m, (int)rows);
+    const dim3 agrid(grid.x, (unsigned)((V + rows - 1) / rows));
+    if (V <= EMB_ONE_TEAM) hipLaunchKernelGGL(embedding_absmax_kernel<1>, agrid, dim3(256), 0, st, E, V, (int)d, cpg, m, (int)rows);
+    else hipLaunchKernelGGL(embedding_absmax_kernel<4>, agrid, dim3(1024), 0, st, E, V, (int)d, cpg, m, (int)rows);
     // Rows of a workgroup of the second pass: eight, one round of loads, while the table is small, us of the whole call against 32 rows: 512 x 256
     // 8.5 / 10.8, 2000 x 1024 10.2 / 12.8, 4000 x 768 11.5 / 13.7, 6000 x 768 14.4 / 15.0, 8000 x 768 18.5 / 16.3, 8000 x 1024 20.8 / 17.8.
     const int qrows = V * grid.x <= 6144 ? 8 : EMB_ROWS;

@@ -20,3 +20,13 @@ def test_shares_of_rows(qb, V, d, groups, bits):
     oc, oh, om = oracle.embedding_quantize(E.numpy(), groups, bits=bits)
     assert (codes.cpu().numpy() == (oracle.pack(oc, bits) if bits < 8 else oc)).all()
     assert (h.cpu().numpy().view(np.uint32) == oh.view(np.uint32)).all() and (m.cpu().numpy().view(np.uint32) == om.view(np.uint32)).all()
+
+
+# one team up to 24 rows, four from 25 on
+@pytest.mark.parametrize("V,d,groups", [(2, 768, 128), (16, 1088, 17), (24, 1088, 272), (25, 1088, 272)])
+def test_few_rows(qb, V, d, groups):
+    E = wl.embedding_table(V, d, seed=V + d)
+    E[V - 1, d - 1] = -0.75
+    codes, h, m = qb.qb_embedding_quantize(E.to("cuda:0"), groups)
+    oc, oh, om = oracle.embedding_quantize(E.numpy(), groups, bits=8)
+    assert (codes.cpu().numpy() == oc).all() and (h.cpu().numpy().view(np.uint32) == oh.view(np.uint32)).all() and (m.cpu().numpy().view(np.uint32) == om.view(np.uint32)).all()
