@@ -34,3 +34,24 @@ def test_rows_by_whole_workgroups(qb, shape):
     oq, ors, ohx = oracle.quantize_act_dyn(X.numpy())
     assert (Xq.cpu().numpy() == oq).all() and (rs.cpu().numpy() == ors).all()
     assert (hx.cpu().numpy().view(np.uint32) == ohx.view(np.uint32)).all()
+
+
+# more rows of 2048 values than a grid of workgroups covers (34 GB): the wavefronts that walk rows, against slices of the same rows
+@pytest.mark.parametrize("per_token", [False, True])
+def test_rows_beyond_a_grid(qb, per_token):
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("needs 60 GB of device memory")
+    T, K, part = (1 << 22) + 3, 2048, 1 << 20
+    g = torch.Generator(device="cuda").manual_seed(1)
+    rows = torch.randn(part, K, generator=g, device="cuda") * 3
+    X = torch.empty(T, K, device="cuda")
+    for at in range(0, T, part):
+        X[at:at + part] = rows[:min(part, T - at)]
+    quantize = (lambda x: qb.qb_quantize_act_dyn(x)) if per_token else (lambda x: qb.qb_quantize_act(x, 6.0))
+    want, got = quantize(rows), quantize(X)
+    for at in range(0, T, part):
+        n = min(part, T - at)
+        for w, v in zip(want, got):
+            assert torch.equal(v[at:at + n], w[:n]), at
+    del X, got
+    torch.cuda.empty_cache()
