@@ -174,10 +174,11 @@ qb_status qb_qlinear_fwd(const int8_t *Xq, const int32_t *rs_x, float clip,
  * different layers or micro-batches of a model: Sec. 3.2, every layer at its own bit-width).  `jobs` is a
  * HOST array of n_jobs descriptors whose pointer fields are DEVICE pointers with the meaning of the
  * arguments of qb_qlinear_fwd (no A4_debug output); it is read during the call only.  The jobs must
- * not depend on each other: no job's Y may be another job's input or output.  Jobs of one bit-width
- * whose size makes a launch's fixed cost matter share launches (their tiles are walked as one
- * sequence by one persistent grid); the results are those of separate qb_qlinear_fwd calls, bit for
- * bit.  All jobs are validated before anything is launched.
+ * not depend on each other: no job's Y may be another job's input or output.  By an estimate of both ways
+ * all jobs, whatever their bit-widths, share a launch whose resident workgroups walk their tiles; or small
+ * jobs share one launch for all widths, middle-sized ones a launch per width, and large ones go one by
+ * one.  The results are those of separate qb_qlinear_fwd calls, bit for bit.  All jobs are validated
+ * before anything is launched.
  */
 typedef struct {
     const int8_t *Xq;

@@ -423,8 +423,9 @@ int bwd_direct_teams(int64_t T, int64_t N, int64_t K, bool dx, bool dw)
     const int64_t chain = std::max(dx ? tn : 0, dw ? tt : 0);    // steps of the longest contraction
     const double share = (double)(((dx ? 1 : 0) + (dw ? 1 : 0)) * tt * tn * tk) / 256;  // steps per CU
     // Microseconds, fitted to some six hundred calls of both paths (64..12000 tokens, N and K 256..4096, 2-8 bits, masked,
-    // asymmetric, one output), with operands turned in registers: a fixed part and the longer of the chain of one workgroup's steps and the CU's share of all
-    // steps.  A lone workgroup takes 0.40, 0.57 and 0.85 us for a step of one, two and four teams; the staged path spends two
+    // asymmetric, one output), with operands turned in registers, which took 5 to 15 % longer than the reads that turn them now (of 250 calls of 128 to 8000
+    // tokens the choice takes 2 % longer than the best one on average, just beyond the line up to 20 %: 3482 x 768 x 768 26.3 us staged, 22.3 here): a fixed
+    // part and the longer of the chain of one workgroup's steps and the CU's share of all steps.  A lone workgroup takes 0.40, 0.57 and 0.85 us for a step of one, two and four teams; the staged path spends two
     // launches, and on long contractions with few tiles a chain of partial sums.  dX alone stages only the weights, so that
     // there the GEMM's tiles (of 128 x 96) show.
     const double staged_share = dw ? 17 + 0.13 * share : 13.7 + 0.13 * share + 1.85 * (double)(((T + 127) / 128) * ((K + 95) / 96)) / 256;
@@ -436,7 +437,7 @@ int bwd_direct_teams(int64_t T, int64_t N, int64_t K, bool dx, bool dw)
     const int teams = best == one ? 1 : best == two ? 2 : 4;
     // One team: up to four workgroups share a CU from the start, dealt in the order of the launch (the longer contraction
     // first), and the CU with the most steps decides, which with few workgroups a CU has far more than its share: 3072 x 768 at
-    // 2067 tokens, dX alone, 396 workgroups of 48 steps: 31.1 us here, 23.9 staged; 2304 x 768 at 1363: 27.6 and 24.8.
+    // 2067 tokens, dX alone, 396 workgroups of 48 steps: 29.2 us here, 25.0 staged; 2304 x 768 at 1364: 25.9 and 25.9.
     const int64_t per_cu = (tiles + 255) / 256;
     if (teams == 1 && per_cu <= 4) {
         const double step[4] = {0.40, 0.28, 0.245, 0.22};  // by workgroups on the CU
@@ -445,7 +446,7 @@ int bwd_direct_teams(int64_t T, int64_t N, int64_t K, bool dx, bool dw)
         const int64_t steps = n_long * chain + (per_cu - n_long) * std::min(tt, tn);
         best = std::max(best, 4.5 + step[per_cu - 1] * (double)steps);
     }
-    // At the crossover (1024 x 1024 at 2561 tokens: 24.3 us against 28.3; 1560 x 2304 x 768 stays: 28.3 and 28.4) the vector
+    // Near the crossover (1024 x 1024 at 2561 tokens: 24.3 us against 29.5; 2099 x 2048 x 512 stays: 25.9 and 25.8) the vector
     // arithmetic that every tile repeats costs what the staging launch does once.
     return best >= 0.97 * staged ? 0 : teams;
 }

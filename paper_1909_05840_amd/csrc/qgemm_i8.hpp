@@ -33,8 +33,8 @@ __device__ __forceinline__ float asym_value(int a4, int rh, int L, float hx, flo
 // a VALU instruction (v_readlane of a spilled value, v_readfirstlane) right in front, which a vector memory instruction may
 // read five wait states later only; it counts them for its own instructions, not into an asm block.  So the block moves the
 // base into registers of its own: a scalar instruction may read what a VALU instruction wrote at any time, the copy what a
-// scalar one wrote; and the move is the wait state that m0 asks for in front of the copy.  (The
-// kernel below at 2 bits, 16384 x 2304 x 768: 41.2 us, with five wait states in front of every copy 41.8, with one 40.6.)
+// scalar one wrote; and the move is the wait state that m0 asks for in front of the copy.
+// (qgemm_i8_dma_kernel at 2 bits, 16384 x 2304 x 768: 41.2 us, with five wait states in front of every copy 41.8, with one 40.6.)
 template <int BYTES>
 __device__ __forceinline__ void copy_to_lds(const void *base, uint32_t off, uint32_t lds_addr)
 {

@@ -368,7 +368,7 @@ __global__ __launch_bounds__(256, 2) void qgemm_i8_list_kernel(const WORK job)
                 zn[j][0] = q.x; zn[j][1] = q.y;
             }
         }
-        // one result: er = 2e*rs_x of its row, rh = R/2 of it
+        // one result: rh = R/2 of its row, hr the row's scale (GEN)
         auto value = [&](int a4, int j, int nb, int rh, float hr) {
             if constexpr (!GEN) return scale[j][nb] * (float)a4 + bv[j][nb];
             if (asym) return asym_value(a4, rh, (1 << bits) - 1, hr, scale[j][nb], zn[j][nb]) + bv[j][nb];

@@ -360,7 +360,7 @@ __global__ __launch_bounds__(THREADS, MIN_WAVES) void quantize_batched_kernel(co
         const int g = (item - b.first_wg[j]) * per + team;
         const float4 *src = reinterpret_cast<const float4 *>(b.W[j]) + (size_t)g * n4;
         // All loads of the thread on their way at once (past the group's end its last float4 again): with each in a branch of its own, its maximum
-        // behind it, they came one after the other (12 layers of 768 86.2 -> 82.7 us, of 1024 149 -> 140; one layer of 768 10.2 -> 9.1).
+        // behind it, they came one after the other (the whole call, 12 layers of 768 87.9 -> 86.2 us, of 1024 151 -> 146; one layer of 768 8.6 -> 7.5).
         float4 v[V], x[PARK > 0 ? PARK : 1];
         int at = tid;
         asm volatile("" : "+v"(at));  // (the indices of the loads are not kept for the stores further below: registers)

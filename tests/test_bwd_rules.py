@@ -19,8 +19,9 @@ def test_short_contractions_stage_dy(T, N, turned):
     assert _rule("_ZN2qb10bwd_turnedEll", [ctypes.c_int64] * 2)(T, N) == turned
 
 
-# us a call with one launch and staged: 31.1 and 23.9, 25.5 and 22.5, 27.8 and 26.5, 30.8 and 28.4, 30.5 and 28.3; 24.3 and 28.3,
-# 21.9 and 24.5, 25.8 and 28.0, 8.3 and 17.3, 12.4 and 21.4
+# us a call with one launch and staged, when the line was fitted: 31.1 and 23.9, 25.5 and 22.5, 27.8 and 26.5, 30.8 and 28.4, 30.5 and 28.3; 24.3 and
+# 28.3, 21.9 and 24.5, 25.8 and 28.0, 8.3 and 17.3, 12.4 and 21.4; since the one launch turns its operands by LDS reads 26.1 and 25.0, 21.1 and 23.3 (the line
+# has not followed), 25.9 and 25.9, 25.9 and 25.8, 29.2 and 27.9; 24.3 and 29.5, 21.9 and 26.0, 25.5 and 28.1, 8.1 (7.8 with one team) and 17.0, 11.5 and 21.5
 @pytest.mark.parametrize("T,N,K,dx,dw,teams", [(2067, 3072, 768, True, False, 0), (2494, 2304, 768, True, False, 0), (1364, 2304, 768, True, True, 0),
                                                (2099, 2048, 512, True, True, 0), (2316, 768, 3072, False, True, 0),
                                                (2561, 1024, 1024, True, True, 1), (1287, 2304, 768, True, True, 1), (9214, 768, 768, True, False, 1),
