@@ -2201,8 +2201,8 @@ void launch_g96(const Group &g, hipStream_t st)
 
 bool few_tiles(const qb_fwd_job &j) { return (long)((j.T + 127) / 128) * ((j.N + 127) / 128) <= 160; }
 
-// The kernel for few-tile jobs that share a launch: with the contraction sliced or stepped; the width and (stepped) the units of 64 features per
-// step that all of them have, or 0
+// The kernel for few-tile jobs that share a launch: with the contraction sliced or stepped; compiled for the width and (stepped) the units of 64
+// features per step that all of them have, or for any (0)
 struct FewTilesKernel {
     bool sliced;
     int bits, units;
@@ -2225,6 +2225,10 @@ FewTilesKernel few_tiles_kernel(const qb_fwd_job *const *jobs, int n_jobs)
     }
     k.sliced = k.sliced && tiles <= 256 && (wgs <= 256 || longest > 12);
     if (k.bits == 0 || k.sliced) k.units = 0;
+    // Different steps at one width: 2304 workgroups of its kernel are resident (the LDS of 256 features a step) and 1536 of the one for everything.
+    // Where that takes it no fewer rounds, fewer at a time are the faster way, the longest contractions being the first.  It / the kernel for
+    // everything, a layer's linears or several, 2 to 8 bits: up to 1200 workgroups .96-1.06, 1536 .96-1.05, 2304 .81-1.03, 3072 .82-1.16, above .85-1.05.
+    if (!k.sliced && k.units == 0 && (wgs + 2303) / 2304 == (wgs + 1535) / 1536) k.bits = 0;
     return k;
 }
 

@@ -53,9 +53,10 @@ SLICED_BIT = 1 << 16
 # width together
 @pytest.mark.parametrize("jobs,kernels", [([(8, 64, 768, 768)] * 3, [8 | SLICED_BIT]), (layer(768, 8, [4]), [4 | SLICED_BIT]), (layer(256, 8, [4, 8]), [SLICED_BIT]),
                                           ([(2, 385, 768, 768)] * 12, [2 | 2 << 8]), ([(3, 700, 768, 320), (3, 64, 64, 64)], [3 | 1 << 8]),
-                                          ([(4, 640, 768, 3072)] * 2, [4 | 4 << 8]), (layer(768, 385, [8]), [8]), (layer(768, 128, [2, 3, 4, 8]), [0]),
+                                          ([(4, 640, 768, 3072)] * 2, [4 | 4 << 8]), (layer(768, 385, [8]), [0]), (layer(768, 512, [8]), [8]),
+                                          (layer(768, 704, [3]), [0]), (layer(768, 128, [2, 3, 4, 8]), [0]),
                                           (layer(320, 8, [2, 3, 4, 8]) * 4, [2 | SLICED_BIT, 3 | SLICED_BIT, 4 | SLICED_BIT, 8 | SLICED_BIT]),
-                                          (layer(768, 385, [2, 8]) * 3, [0, 8])])
+                                          (layer(768, 300, [2, 8]) * 3, [0, 8])])
 def test_few_tile_jobs_of_one_kind_take_the_kernel_of_their_kind(jobs, kernels):
     from paper_1909_05840_amd.binding import _FwdJob
     rule = ctypes.CDLL(LIB_PATH)._ZN2qb13fwd_few_tilesEPK10qb_fwd_jobiPi

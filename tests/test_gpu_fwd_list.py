@@ -110,11 +110,12 @@ def test_shared_launches_of_one_width_give_the_single_calls_results(bits):
         assert torch.equal(j["Y"], want), (j["Xq"].shape, j["N"])
 
 
-# few-tile jobs of one width, (T, N, K): sliced; one, two and four units of 64 features a step; and different ones
+# few-tile jobs of one width, (T, N, K): sliced; one, two and four units of 64 features a step; different ones, more workgroups than the kernel for
+# everything has places
 @pytest.mark.parametrize("bits", [2, 3, 4, 8])
 @pytest.mark.parametrize("shapes,kind", [([(33, 300, 512), (31, 128, 2048), (64, 65, 320)], 1 << 16), ([(700, 768, 320), (129, 500, 192), (1, 1, 64)], 1 << 8),
                                          ([(700, 768, 768), (65, 130, 128), (1, 33, 1024)], 2 << 8), ([(700, 768, 2048), (33, 97, 4096)], 4 << 8),
-                                         ([(700, 768, 768), (33, 97, 2048), (64, 65, 192)], 0)])
+                                         ([(1700, 1400, 256), (700, 768, 2048), (640, 1000, 192), (33, 97, 2048)], 0)])
 def test_few_tile_jobs_of_one_width_give_the_single_calls_results(bits, shapes, kind):
     g = torch.Generator(device="cuda").manual_seed(bits)
     jobs = [job(g, bits, T, N, K, 1, bias=i % 2 == 0) for i, (T, N, K) in enumerate(shapes)]
