@@ -136,3 +136,34 @@ def test_more_few_tile_jobs_than_a_launch_holds():
     qb.qb_qlinear_fwd_batched(jobs)
     for j in jobs:
         assert torch.equal(j["Y"], qb.qb_qlinear_fwd(j["Xq"], j["rs_x"], CLIP, j["packed"], j["h"], j["rs_w"], j["bits"], 1, j["N"], bias=j["bias"])), (j["Xq"].shape, j["N"])
+
+
+def test_a_list_next_to_another_streams_kernels():
+    """The lists' kernel while another stream's backward and quantizers share the CUs and the memory: the bits of the call run alone."""
+    g = torch.Generator(device="cuda").manual_seed(11)
+    T, G = 2048, 128
+    jobs = [job(g, b, T, N, K, G, False) for b in (2, 3, 4, 8) for N, K in ((2304, 768), (768, 768), (3072, 768), (768, 3072))]
+    assert takes_list(jobs)
+    qb.qb_qlinear_fwd_batched(jobs)
+    torch.cuda.synchronize()
+    alone = [j["Y"].clone() for j in jobs]
+    other = job(g, 3, 4096, 2304, 768, G, False)
+    W = torch.randn(2304, 768, generator=g, device="cuda")
+    dY = torch.randn(4096, 2304, generator=g, device="cuda").to(torch.bfloat16)
+    ws = torch.empty(qb.qb_bwd_workspace_nbytes(4096, 2304, 768), dtype=torch.uint8, device="cuda")
+    dX, dW = torch.empty(4096, 768, dtype=torch.bfloat16, device="cuda"), torch.empty(2304, 768, device="cuda")
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(4):
+        for j in jobs:
+            j["Y"].fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s2):
+            for _ in range(8):
+                qb.qb_qlinear_bwd_ste(dY, other["Xq"], CLIP, other["packed"], other["h"], 3, G, dX=dX, dW=dW, workspace=ws)
+                qb.qb_quantize_groupwise(W, 3, G)
+        with torch.cuda.stream(s1):
+            for _ in range(6):
+                qb.qb_qlinear_fwd_batched(jobs)
+        torch.cuda.synchronize()
+        for j, want in zip(jobs, alone):
+            assert torch.equal(j["Y"], want), (j["bits"], j["N"])
